@@ -695,11 +695,11 @@ ttc_status_t ttc_block_forward(const ttc_block_t* b, const void* x_in, void* x_o
   if (bf16) {
     ttc::GemmLnBf16Args g1{x_in, ws + L.stats_in, b->ln_in_gain, b->ln_in_offset, static_cast<const uint16_t*>(b->W_in),
                            b->b_in, nullptr, h0p, M, HD, b->C};
-    if (ttc::launch_gemm_ln_bf16(g1, true, false, st) != hipSuccess) return TTC_ERR_DEVICE;
+    if (ttc::launch_gemm_ln_bf16(g1, true, false, ttc::cu_count(), st) != hipSuccess) return TTC_ERR_DEVICE;
   } else {
     ttc::GemmLnArgs g1{static_cast<const float*>(x_in), ws + L.stats_in, b->ln_in_gain, b->ln_in_offset,
                        static_cast<const float*>(b->W_in), b->b_in, nullptr, h0p, M, HD, b->C};
-    if (ttc::launch_gemm_ln(g1, st) != hipSuccess) return TTC_ERR_DEVICE;
+    if (ttc::launch_gemm_ln(g1, ttc::cu_count(), st) != hipSuccess) return TTC_ERR_DEVICE;
   }
   // the contextualisation maps and the Q basis
   ttc::CxtMapsArgs c;
@@ -732,11 +732,11 @@ ttc_status_t ttc_block_forward(const ttc_block_t* b, const void* x_in, void* x_o
   if (bf16) {
     ttc::GemmLnBf16Args g2{op, ws + L.stats_out, b->ln_out_gain, b->ln_out_offset, static_cast<const uint16_t*>(b->W_out),
                            b->b_out, static_cast<const uint16_t*>(x_in), x_out, M, b->C, HD};
-    if (ttc::launch_gemm_ln_bf16(g2, false, true, st) != hipSuccess) return TTC_ERR_DEVICE;
+    if (ttc::launch_gemm_ln_bf16(g2, false, true, ttc::cu_count(), st) != hipSuccess) return TTC_ERR_DEVICE;
   } else {
     ttc::GemmLnArgs g2{op, ws + L.stats_out, b->ln_out_gain, b->ln_out_offset, static_cast<const float*>(b->W_out),
                        b->b_out, static_cast<const float*>(x_in), static_cast<float*>(x_out), M, b->C, HD};
-    if (ttc::launch_gemm_ln(g2, st) != hipSuccess) return TTC_ERR_DEVICE;
+    if (ttc::launch_gemm_ln(g2, ttc::cu_count(), st) != hipSuccess) return TTC_ERR_DEVICE;
   }
   return TTC_OK;
 }

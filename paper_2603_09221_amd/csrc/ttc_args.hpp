@@ -142,6 +142,20 @@ struct GemmLnBf16Args {
   int N, K;             // multiples of 8
 };
 
+// the projections of few tokens or few outputs (element types by the kernel's template arguments)
+struct GemmLnSplitArgs {
+  const void* X;        // (M, K)
+  const float* stats;   // (M, 2)
+  const float* gain;    // (K)
+  const float* offset;  // (K)
+  const void* W;        // (N, K)
+  const float* bias;    // (N) or NULL
+  const void* Res;      // (M, N) of Y's type or NULL (may be Y itself)
+  void* Y;              // (M, N)
+  long long M;
+  int N, K;             // multiples of 4 (float32 weights) or 8 (bfloat16 weights)
+};
+
 struct CxtMapsArgs {
   const float* H0;        // (M, H, 16)
   const float* W_head;    // (H, 80 + r, 16): rows sA, rinv, lgA, lgB, lgQ (16 each), sQf (r)

@@ -343,6 +343,180 @@ __global__ void __launch_bounds__(256) gemm_ln_bf16_kernel(const GemmLnBf16Args 
   }
 }
 
+// The same projections, Y = LN(X) W^T + bias (+ Res), for shapes whose 128 x 128 tiles leave most of the chip idle (few
+// tokens, or few outputs): there the tiled kernels are bound by the latency of their K loop, one slice in flight per
+// workgroup.  A workgroup owns 16 NT outputs of 16 MT tokens and its NWV wavefronts share K: wavefront v takes the
+// blocks of 32 number v, v + NWV, ...  Operands go from memory straight into matrix-core operand registers (lane
+// (i, g) holds the eight k = 8 g .. 8 g + 7 of row i of either side; the next block is requested before the current one
+// is multiplied), the partial tiles are added through LDS in wavefront order.
+template <typename TW>
+struct BlkFrag;
+template <>
+struct BlkFrag<float> {
+  blk_floatx4 v[2];
+};
+template <>
+struct BlkFrag<unsigned short> {
+  blk_u16x8 v;
+};
+
+template <typename TX, typename TW, typename TY, int NT, int MT, int NWV>
+__global__ void __launch_bounds__(64 * NWV) gemm_ln_split_kernel(const GemmLnSplitArgs p) {
+  __shared__ __attribute__((aligned(16))) blk_floatx4 red[NWV > 1 ? NWV * NT * MT * 64 : 1];
+  const TX* const X = reinterpret_cast<const TX*>(p.X);
+  const TW* const W = reinterpret_cast<const TW*>(p.W);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, i = lane & 15, g = lane >> 4;
+  const int nNt = (p.N + 16 * NT - 1) / (16 * NT);
+  const long long m0 = (long long)(blockIdx.x / nNt) * (16 * MT);
+  const int n0 = (int)(blockIdx.x % nNt) * (16 * NT);
+
+  // rows past the end are read as the last row and never written; k past the end reads the last pieces and counts as 0
+  const TX* xrow[MT];
+  const TW* wrow[NT];
+  float mean[MT], rstd[MT];
+#pragma unroll
+  for (int b = 0; b < MT; ++b) {
+    long long row = m0 + 16 * b + i;
+    row = row < p.M ? row : p.M - 1;
+    xrow[b] = X + row * p.K;
+    mean[b] = p.stats[2 * row];
+    rstd[b] = p.stats[2 * row + 1];
+  }
+#pragma unroll
+  for (int a = 0; a < NT; ++a) {
+    int o = n0 + 16 * a + i;
+    o = o < p.N ? o : p.N - 1;
+    wrow[a] = W + (long long)o * p.K;
+  }
+  struct Piece {  // one block of 32 on its way
+    BlkFrag<TW> w[NT];
+    BlkFrag<TX> x[MT];
+    blk_floatx4 gn[2], of[2];
+    bool live[2];
+  };
+  auto fetch = [&](Piece& q, int k0) {
+    const int ka = k0 + 8 * g;  // K is a multiple of 4 (float32 weights) or 8
+    q.live[0] = ka < p.K;
+    q.live[1] = ka + 4 < p.K;
+    const int k[2] = {q.live[0] ? ka : p.K - 4, q.live[1] ? ka + 4 : p.K - 4};
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      q.gn[h] = *reinterpret_cast<const blk_floatx4*>(p.gain + k[h]);
+      q.of[h] = *reinterpret_cast<const blk_floatx4*>(p.offset + k[h]);
+    }
+#pragma unroll
+    for (int b = 0; b < MT; ++b) {
+      if constexpr (sizeof(TX) == 4) {
+        q.x[b].v[0] = *reinterpret_cast<const blk_floatx4*>(xrow[b] + k[0]);
+        q.x[b].v[1] = *reinterpret_cast<const blk_floatx4*>(xrow[b] + k[1]);
+      } else {
+        q.x[b].v = *reinterpret_cast<const blk_u16x8*>(xrow[b] + (q.live[1] ? ka : p.K - 8));
+      }
+    }
+#pragma unroll
+    for (int a = 0; a < NT; ++a) {
+      if constexpr (sizeof(TW) == 4) {
+        q.w[a].v[0] = *reinterpret_cast<const blk_floatx4*>(wrow[a] + k[0]);
+        q.w[a].v[1] = *reinterpret_cast<const blk_floatx4*>(wrow[a] + k[1]);
+      } else {
+        q.w[a].v = *reinterpret_cast<const blk_u16x8*>(wrow[a] + (q.live[1] ? ka : p.K - 8));
+      }
+    }
+  };
+  blk_floatx4 acc[NT][MT];
+#pragma unroll
+  for (int a = 0; a < NT; ++a)
+#pragma unroll
+    for (int b = 0; b < MT; ++b) acc[a][b] = blk_floatx4{0.f, 0.f, 0.f, 0.f};
+  auto multiply = [&](const Piece& q) {
+    blk_floatx4 xn[MT][2];
+#pragma unroll
+    for (int b = 0; b < MT; ++b)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          float x;
+          if constexpr (sizeof(TX) == 4) x = q.x[b].v[h][e];
+          else x = bf16_to_f32(q.x[b].v[4 * h + e]);
+          const float y = (x - mean[b]) * rstd[b] * q.gn[h][e] + q.of[h][e];
+          xn[b][h][e] = q.live[h] ? y : 0.f;
+        }
+    if constexpr (sizeof(TW) == 4) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int a = 0; a < NT; ++a) {
+            const float w = q.live[h] ? q.w[a].v[h][e] : 0.f;
+#pragma unroll
+            for (int b = 0; b < MT; ++b)
+              acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(w, xn[b][h][e], acc[a][b], 0, 0, 0);
+          }
+    } else {
+      blk_u16x8 xb[MT];
+#pragma unroll
+      for (int b = 0; b < MT; ++b)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) xb[b][e] = f32_to_bf16(xn[b][e >> 2][e & 3]);
+#pragma unroll
+      for (int a = 0; a < NT; ++a) {
+        const blk_u16x8 w = q.live[1] ? q.w[a].v : blk_u16x8{0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+        for (int b = 0; b < MT; ++b)
+          acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(blk_bf16x8, w),
+                                                              __builtin_bit_cast(blk_bf16x8, xb[b]), acc[a][b], 0, 0, 0);
+      }
+    }
+  };
+  const int step = 32 * NWV;
+  if (32 * wave < p.K) {
+    Piece q[2];
+    fetch(q[0], 32 * wave);
+    int k = 32 * wave;
+    for (; k + step < p.K; k += 2 * step) {
+      fetch(q[1], k + step);
+      multiply(q[0]);
+      if (k + 2 * step < p.K) fetch(q[0], k + 2 * step);
+      multiply(q[1]);
+    }
+    if (k < p.K) multiply(q[0]);
+  }
+  if constexpr (NWV > 1) {
+#pragma unroll
+    for (int a = 0; a < NT; ++a)
+#pragma unroll
+      for (int b = 0; b < MT; ++b) red[(wave * NT * MT + a * MT + b) * 64 + lane] = acc[a][b];
+    __syncthreads();
+  }
+  // tile (a, b) of the workgroup goes to wavefront (a MT + b) % NWV
+#pragma unroll
+  for (int a = 0; a < NT; ++a)
+#pragma unroll
+    for (int b = 0; b < MT; ++b) {
+      if ((a * MT + b) % NWV != wave) continue;
+      blk_floatx4 y = acc[a][b];
+      if constexpr (NWV > 1) {
+        y = red[(a * MT + b) * 64 + lane];
+#pragma unroll
+        for (int v = 1; v < NWV; ++v) y += red[(v * NT * MT + a * MT + b) * 64 + lane];
+      }
+      // y[v] = Y[m0 + 16 b + i][n0 + 16 a + 4 g + v]
+      const int o = n0 + 16 * a + 4 * g;
+      const long long row = m0 + 16 * b + i;
+      if (o >= p.N || row >= p.M) continue;
+      if (p.bias) y += *reinterpret_cast<const blk_floatx4*>(p.bias + o);
+      if (p.Res) y += blk_ld4<TY>(reinterpret_cast<const TY*>(p.Res), row * p.N + o);
+      if constexpr (sizeof(TY) == 2) {
+        const blk_u16x4 v = {f32_to_bf16(y[0]), f32_to_bf16(y[1]), f32_to_bf16(y[2]), f32_to_bf16(y[3])};
+        *reinterpret_cast<blk_u16x4*>(reinterpret_cast<unsigned short*>(p.Y) + row * p.N + o) = v;
+      } else {
+        *reinterpret_cast<blk_floatx4*>(reinterpret_cast<float*>(p.Y) + row * p.N + o) = y;
+      }
+    }
+}
+
 __device__ __forceinline__ float softplus_f32(float z) {
   // log(1 + e^z); for large z the sum rounds to e^z and the result to z
   return z > 30.f ? z : log1pf(expf(z));

@@ -155,3 +155,31 @@ def test_bf16_block_in_place_zero_projection_and_refusals():
     xw, ww = bf16_case(4, 68, 2, 16, 3, seed=12)              # C a multiple of 4 but not of 8
     with pytest.raises(binding.TtcError):
         binding.ttc_block_forward(xw, ww, 3)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("M,C,H", [(1, 72, 1), (33, 136, 3), (517, 512, 4), (2049, 264, 8), (4097, 1032, 16)])
+def test_projections_of_every_tile_shape(M, C, H, bf16):
+    """Few tokens or outputs go to kernels that share K among the wavefronts of a workgroup, in four tile shapes chosen by
+    how many workgroups they give; ragged tokens, outputs and K (not multiples of 32).  h_0 and x_out against float64
+    torch from the inputs of each projection.  Float32: a contraction of at most 1032 terms in any order stays below
+    sqrt(K) 2^-24 = 2e-6 in norm.  Bfloat16: the reference rounds LN(x) too; an entry near a tie may round the other
+    way (2^-8 of one of K terms), and x_out is rounded once more (2^-9)."""
+    w = synth.make_block_weights(C, H, 16, 8, seed=M, device=DEV)
+    x = synth.make_block_input(M, C, seed=M, device=DEV)
+    if bf16:
+        w["W_in"], w["W_out"], x = w["W_in"].bfloat16(), w["W_out"].bfloat16(), x.bfloat16()
+    out = binding.ttc_block_forward(x, w, 1, want_h0=True, want_o=True)
+    torch.cuda.synchronize()
+    w64 = {k: v.double() for k, v in w.items()}
+
+    def norm(v, gain, offset):
+        y = (v - v.mean(-1, keepdim=True)) / torch.sqrt(v.var(-1, unbiased=False, keepdim=True) + 1e-5) * gain + offset
+        return y.float().bfloat16().double() if bf16 else y
+
+    h0 = norm(x.double(), w64["ln_in_gain"], w64["ln_in_offset"]) @ w64["W_in"].T + w64["b_in"]
+    y = x.double() + norm(out["o"].double(), w64["ln_out_gain"], w64["ln_out_offset"]) @ w64["W_out"].T + w64["b_out"]
+    for got, want, tol in ((out["h0"], h0, 2e-4 if bf16 else 2e-6), (out["x_out"], y, 4e-3 if bf16 else 2e-6)):
+        err = float((got.double() - want).norm() / want.norm())
+        print(M, C, H, bf16, "%.1e" % err)
+        assert err <= tol
