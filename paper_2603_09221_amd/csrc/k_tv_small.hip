@@ -13,7 +13,10 @@ hipError_t launch_tv_small(const TvArgs& a, bool bf16, int ppw, dim3 grid, hipSt
   }
   return hipGetLastError();
 }
-int occupancy_tv_small(bool bf16) {
+int occupancy_tv_small(bool bf16, int ppw) {
+  if (ppw == 1)
+    return bf16 ? occupancy_query(solve_tv_small_kernel<uint16_t, 1>, 64)
+                : occupancy_query(solve_tv_small_kernel<float, 1>, 64);
   return bf16 ? occupancy_query(solve_tv_small_kernel<uint16_t, 4>, 64)
               : occupancy_query(solve_tv_small_kernel<float, 4>, 64);
 }

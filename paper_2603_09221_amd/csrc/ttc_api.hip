@@ -61,7 +61,7 @@ static void* scratch_for_current_device() {
 // workgroup waits for another to finish.  The per-CU number is what the runtime reports for the kernel
 // (registers and LDS decide it); the table is the fallback when no device can be asked.
 enum Kind { KIND_SOLVE = 0, KIND_DOUBLING = 1, KIND_ROLLOUT = 2, KIND_SOLVE_QUAD = 3, KIND_SOLVE_TV = 4, KIND_TV_QUAD = 5,
-            KIND_ROLLOUT_TV = 6, KIND_CXT = 7, KIND_SCAN = 8, KIND_BACKWARD = 9, KIND_COUNT = 10 };
+            KIND_ROLLOUT_TV = 6, KIND_CXT = 7, KIND_SCAN = 8, KIND_BACKWARD = 9, KIND_TV_ONE = 10, KIND_COUNT = 11 };
 static int dindex(int d) { return d == 16 ? 0 : d == 32 ? 1 : d == 64 ? 2 : 3; }
 template <int D>
 static int occupancy_of(Kind kind, bool bf16) {
@@ -76,7 +76,8 @@ static int occupancy_of(Kind kind, bool bf16) {
     case KIND_SCAN: return occupancy_scan<D>();
     case KIND_BACKWARD: return occupancy_backward<D>(bf16);
     case KIND_SOLVE_QUAD: return occupancy_small(bf16);  // the d = 16 kernels
-    case KIND_TV_QUAD: return occupancy_tv_small(bf16);
+    case KIND_TV_QUAD: return occupancy_tv_small(bf16, 4);
+    case KIND_TV_ONE: return occupancy_tv_small(bf16, 1);
     case KIND_CXT: return occupancy_cxt(bf16);
     default: return 0;
   }
@@ -99,7 +100,7 @@ static int blocks_per_cu(Kind kind, int d, bool bf16) {
     if (nb <= 0) {
       static const int table[KIND_COUNT][4] = {{20, 8, 2, 1}, {16, 8, 2, 1}, {12, 4, 2, 1}, {8, 8, 2, 1}, {20, 8, 2, 1},
                                                {8, 8, 2, 1},  {12, 4, 2, 1}, {8, 8, 2, 1},  {16, 8, 2, 1},
-                                               {12, 4, 2, 1}};
+                                               {12, 4, 2, 1}, {16, 8, 2, 1}};
       nb = table[kind][dindex(d)];
     }
     c.value = nb > 32 ? 32 : nb;
@@ -119,9 +120,10 @@ constexpr float GROWTH_LIMIT_BF16 = 16384.f;
 
 // d = 16: large batches go four problems to a wavefront (more throughput per instruction issued), small ones
 // one problem to a wavefront (more wavefronts in flight, lower latency).  Crossover measured on MI355X, in
-// problems per compute unit: 12 for the symplectic kernel (T = 8), 24 for the Riccati kernel (T = 64).
+// problems per compute unit: 12 for the symplectic kernel (T = 8), 12 for the Riccati kernel (T = 64, one / four problems
+// per wavefront: 2048 problems 209 / 270 us, 3072: 307 / 294, 4096: 405 / 332, 6143: 601 / 529).
 constexpr long long QUAD_MIN_PER_CU_SOLVE = 12;
-constexpr long long QUAD_MIN_PER_CU_TV = 24;
+constexpr long long QUAD_MIN_PER_CU_TV = 12;
 static bool use_quad_kernel(const ttc_lqr_problem_t* q) {
   return q->d == 16 && !(q->flags & TTC_FLAG_DOUBLING) && q->n >= QUAD_MIN_PER_CU_SOLVE * cu_count();
 }
@@ -413,7 +415,8 @@ ttc_status_t ttc_lqr_solve_tv(const ttc_lqr_tv_problem_t* q, const ttc_lqr_solut
   // to a wavefront, smaller ones one problem to a wavefront
   const bool small = q->d == 16;
   const bool quad = ttc::use_quad_kernel_tv(q);
-  const long long gb = ttc::grid_blocks(small ? ttc::KIND_TV_QUAD : ttc::KIND_SOLVE_TV, q->d, bf16);
+  const long long gb =
+      ttc::grid_blocks(quad ? ttc::KIND_TV_QUAD : small ? ttc::KIND_TV_ONE : ttc::KIND_SOLVE_TV, q->d, bf16);
   const long long items = quad ? (q->n + 3) / 4 : q->n;
   const dim3 grid((unsigned)(items < gb ? items : gb));
   hipStream_t st = static_cast<hipStream_t>(hip_stream);

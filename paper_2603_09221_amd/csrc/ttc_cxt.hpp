@@ -214,7 +214,7 @@ __global__ void __launch_bounds__(64, TTC_CXT_WAVES) solve_cxt_kernel(const CxtA
       }
       wave_lds_sync();
       tm.toc(2);
-      note(invert_rows16<true, true>(Wmine, lane));  // left halves: -S^{-1}, so that the next product is the gain itself
+      note(invert_rows16<true>(Wmine, lane));  // left halves: -S^{-1}, so that the next product is the gain itself
       tm.toc(1);
       if (s == 0 && ca.dual_g) {
         // The dual problem of the backward pass starts from ut_0 = -S_0^{-1} g: y = S_0^{-1} g, refined once with the

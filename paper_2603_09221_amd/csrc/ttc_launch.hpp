@@ -34,7 +34,7 @@ template <int D> int occupancy_backward(bool bf16);
 hipError_t launch_small(const SolveArgs& a, bool bf16, int ppw, dim3 grid, hipStream_t st);
 int occupancy_small(bool bf16);
 hipError_t launch_tv_small(const TvArgs& a, bool bf16, int ppw, dim3 grid, hipStream_t st);
-int occupancy_tv_small(bool bf16);
+int occupancy_tv_small(bool bf16, int ppw);
 hipError_t launch_cxt(const CxtArgs& a, bool bf16, int ppw, dim3 grid, hipStream_t st);
 int occupancy_cxt(bool bf16);
 hipError_t launch_rollout_cxt_forward(const CxtRolloutArgs& a, bool bf16, dim3 grid, hipStream_t st);

@@ -112,16 +112,135 @@ __device__ __forceinline__ int solve_rows16(float* Wq, int lane) {
   return bad;
 }
 
-// In-place inverses of the four symmetric positive definite 16 x 16 matrices in the left halves of
-// Wm[q] (row r at Wq + r*PITCH), all at once, a lane holding one row: Gauss-Jordan without pivoting on
-// [M | I], where the column of the right part that becomes non-trivial at step j takes the place of
-// column j of M, which has just become a unit vector.  Rows are scaled by their pivots at the end.
-// The pivot row is broadcast within each row of 16 lanes by DPP.  The caller synchronises before (M
-// complete in LDS); the function ends with a barrier.  Returns, per lane, whether its problem broke
-// down (a pivot that is not positive and finite).  NEGATE leaves -M^{-1} instead (the sign rides on the final scaling);
-// ONE_WAVE: the workgroup is this wavefront alone, and the final barrier is replaced by an ordering of its LDS
-// traffic that does not wait for its global stores.
-template <bool NEGATE = false, bool ONE_WAVE = false>
+// Inverse of a symmetric positive definite 16 x 16 matrix, a row per lane (a[c] = M[r][c], r = lane & 15; the four rows
+// of 16 lanes hold four matrices, or four copies of one): Gauss-Jordan without pivoting on [M | I], where the column of
+// the right part that becomes non-trivial at step j takes the place of column j of M, which has just become a unit
+// vector.  Rows are scaled by their pivots at the end (NEGATE leaves -M^{-1}, the sign riding on that scaling).
+// The pivot row is broadcast within each row of 16 lanes as the DPP operand of the multiply-add itself.  What bounds a
+// step is the chain multiplier -> column j + 1 -> its pivot's broadcast -> reciprocal -> next multiplier, some 65 cycles,
+// beside the issue of 15 multiply-adds (4.4 cycles each): column j + 1 is updated first and its pivot's reciprocal is
+// started under the other columns' updates, so that the larger of the two counts and not their sum.
+// Returns, per lane, whether its row's pivot was not positive and finite.
+template <bool NEGATE = false>
+__device__ __forceinline__ int invert_regs16(float (&a)[16]) {
+  float mypiv = 1.f;
+  float pv = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, a[0]), 0x150, 0xF, 0xF, true));
+  float rc = __builtin_amdgcn_rcpf(pv);
+  asm volatile("s_nop 1" : "+v"(rc));  // a transcendental's result may not be read by the very next vector instruction
+  static_for<0, 16>([&](auto J) {
+    constexpr int j = decltype(J)::value;
+    float(&x)[16] = a;  // (named here, as an asm operand alone does not capture)
+    float &kept = mypiv, &piv = pv, &rec = rc;
+    const unsigned long long mine = 0x0001000100010001ull << j;  // the lanes of the pivot row
+    // nl = the row's multiplier -a[j] / pivot (0 for the pivot row itself), then a[k] += nl * (a[k] of the pivot row, lane j
+    // of this row of 16 lanes), k != j.  Written as one block so that the two wait states a DPP read needs after a vector
+    // write of the same register are in our hands: the block starts with three instructions that write none of the
+    // registers read by DPP, every multiply-add touches its own register, and the pivot of column j + 1 is read two
+    // instructions after it was written.  %[p]: the pivot, kept by its row.
+    float nl;
+#define TTC_FMAC(n) "v_fmac_f32_dpp %" #n ", %" #n ", %[nl] row_newbcast:%[j] row_mask:0xf bank_mask:0xf\n\t"
+    if constexpr (j < 15) {
+#define TTC_AK(n) x[(n) == 0 ? j + 1 : ((n) <= j ? (n) - 1 : (n) + 1)]  // a[j + 1], then the other 14, in ascending order
+      asm volatile(
+          "v_mul_f32 %[nl], %[rc], -%[aj]\n\tv_cndmask_b32 %[p], %[p], %[pv], %[m]\n\tv_cndmask_b32 %[nl], %[nl], 0, %[m]\n\t"
+          TTC_FMAC(0) TTC_FMAC(1) TTC_FMAC(2)
+          "v_mov_b32_dpp %[pv], %0 row_newbcast:%[jn] row_mask:0xf bank_mask:0xf\n\t" TTC_FMAC(3) TTC_FMAC(4)
+          "v_rcp_f32 %[rc], %[pv]\n\t" TTC_FMAC(5) TTC_FMAC(6) TTC_FMAC(7) TTC_FMAC(8) TTC_FMAC(9) TTC_FMAC(10) TTC_FMAC(11)
+              TTC_FMAC(12) TTC_FMAC(13) TTC_FMAC(14) "v_cndmask_b32 %[aj], %[nl], 1.0, %[m]"
+          : "+v"(TTC_AK(0)), "+v"(TTC_AK(1)), "+v"(TTC_AK(2)), "+v"(TTC_AK(3)), "+v"(TTC_AK(4)), "+v"(TTC_AK(5)),
+            "+v"(TTC_AK(6)), "+v"(TTC_AK(7)), "+v"(TTC_AK(8)), "+v"(TTC_AK(9)), "+v"(TTC_AK(10)), "+v"(TTC_AK(11)),
+            "+v"(TTC_AK(12)), "+v"(TTC_AK(13)), "+v"(TTC_AK(14)), [aj] "+v"(x[j]), [p] "+v"(kept), [pv] "+v"(piv),
+            [rc] "+v"(rec), [nl] "=&v"(nl)
+          : [m] "s"(mine), [j] "n"(j), [jn] "n"(j + 1));
+#undef TTC_AK
+    } else {
+      asm volatile(
+          "v_mul_f32 %[nl], %[rc], -%[aj]\n\tv_cndmask_b32 %[p], %[p], %[pv], %[m]\n\tv_cndmask_b32 %[nl], %[nl], 0, %[m]\n\t"
+          TTC_FMAC(0) TTC_FMAC(1) TTC_FMAC(2) TTC_FMAC(3) TTC_FMAC(4) TTC_FMAC(5) TTC_FMAC(6) TTC_FMAC(7) TTC_FMAC(8)
+              TTC_FMAC(9) TTC_FMAC(10) TTC_FMAC(11) TTC_FMAC(12) TTC_FMAC(13) TTC_FMAC(14)
+          "v_cndmask_b32 %[aj], %[nl], 1.0, %[m]\n\ts_nop 1"
+          : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(x[4]), "+v"(x[5]), "+v"(x[6]), "+v"(x[7]), "+v"(x[8]),
+            "+v"(x[9]), "+v"(x[10]), "+v"(x[11]), "+v"(x[12]), "+v"(x[13]), "+v"(x[14]), [aj] "+v"(x[15]), [p] "+v"(kept),
+            [pv] "+v"(piv), [rc] "+v"(rec), [nl] "=&v"(nl)
+          : [m] "s"(mine), [j] "n"(15));
+    }
+#undef TTC_FMAC
+  });
+  const float s = NEGATE ? -__builtin_amdgcn_rcpf(mypiv) : __builtin_amdgcn_rcpf(mypiv);
+#pragma unroll
+  for (int k = 0; k < 16; ++k) a[k] *= s;
+  return !(mypiv > 0.f && mypiv < __builtin_inff());
+}
+
+// x of the sixteen lanes of group J (lane / 16), in every group
+template <int J>
+__device__ __forceinline__ float broadcast_group(float x) {
+  const unsigned u = __float_as_uint(x);
+  const auto h = __builtin_amdgcn_permlane32_swap(u, u, false, false);  // both halves: groups (0, 1), or (2, 3)
+  const unsigned y = J >= 2 ? h[1] : h[0];
+  const auto q = __builtin_amdgcn_permlane16_swap(y, y, false, false);
+  return __uint_as_float((J & 1) ? q[1] : q[0]);
+}
+
+// The same inverse of one matrix by the whole wavefront: lane (i, g) holds M[i][4g .. 4g+3] (for a symmetric M its
+// accumulator layout) and ends with the same entries of the inverse, which is its A operand, so that nothing passes
+// through LDS.  Columns are taken four at a time: the four columns of a group are copied to every group first, where they
+// are kept up to date beside the lane's own four; a column then costs seven multiply-adds instead of fifteen.  Every entry
+// sees the operations of invert_regs16 in the same order.
+__device__ __forceinline__ int invert_spread16(floatx4& m, int lane) {
+  const int g = lane >> 4;
+  float a[4] = {m[0], m[1], m[2], m[3]};
+  float mypiv = 1.f;
+  static_for<0, 4>([&](auto JB) {
+    constexpr int J = decltype(JB)::value;
+    float c[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) c[k] = broadcast_group<J>(a[k]);
+    float pv = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, c[0]), 0x150 + 4 * J, 0xF, 0xF,
+                                                                  true));  // row_newbcast:4J
+    float rc = __builtin_amdgcn_rcpf(pv);
+    asm volatile("s_nop 1" : "+v"(rc));
+    static_for<0, 4>([&](auto JJ) {
+      constexpr int jj = decltype(JJ)::value, j = 4 * J + jj;
+      const unsigned long long mine = 0x0001000100010001ull << j;
+      float(&x)[4] = a, (&y)[4] = c;
+      float &kept = mypiv, &piv = pv, &rec = rc;
+      // as in invert_regs16: the next column and its pivot's reciprocal first, the other columns under them
+      float nl;
+#define TTC_FMAC(n) "v_fmac_f32_dpp %" #n ", %" #n ", %[nl] row_newbcast:%[j] row_mask:0xf bank_mask:0xf\n\t"
+      if constexpr (jj < 3) {
+        asm volatile(
+            "v_mul_f32 %[nl], %[rc], -%[cj]\n\tv_cndmask_b32 %[p], %[p], %[pv], %[m]\n\tv_cndmask_b32 %[nl], %[nl], 0, %[m]\n\t"
+            TTC_FMAC(0) TTC_FMAC(3) TTC_FMAC(4)
+            "v_mov_b32_dpp %[pv], %0 row_newbcast:%[jn] row_mask:0xf bank_mask:0xf\n\t" TTC_FMAC(5) TTC_FMAC(6)
+            "v_rcp_f32 %[rc], %[pv]\n\t" TTC_FMAC(1) TTC_FMAC(2) "v_cndmask_b32 %[cj], %[nl], 1.0, %[m]"
+            : "+v"(y[jj + 1]), "+v"(y[(jj + 2) & 3]), "+v"(y[(jj + 3) & 3]), "+v"(x[0]), "+v"(x[1]), "+v"(x[2]),
+              "+v"(x[3]), [cj] "+v"(y[jj]), [p] "+v"(kept), [pv] "+v"(piv), [rc] "+v"(rec), [nl] "=&v"(nl)
+            : [m] "s"(mine), [j] "n"(j), [jn] "n"(j + 1));
+      } else {
+        asm volatile(
+            "v_mul_f32 %[nl], %[rc], -%[cj]\n\tv_cndmask_b32 %[p], %[p], %[pv], %[m]\n\tv_cndmask_b32 %[nl], %[nl], 0, %[m]\n\t"
+            TTC_FMAC(0) TTC_FMAC(1) TTC_FMAC(2) TTC_FMAC(3) TTC_FMAC(4) TTC_FMAC(5) TTC_FMAC(6)
+            "v_cndmask_b32 %[cj], %[nl], 1.0, %[m]\n\ts_nop 1"
+            : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(y[0]), "+v"(y[1]), "+v"(y[2]), [cj] "+v"(y[3]),
+              [p] "+v"(kept), [pv] "+v"(piv), [rc] "+v"(rec), [nl] "=&v"(nl)
+            : [m] "s"(mine), [j] "n"(j));
+      }
+#undef TTC_FMAC
+    });
+    const bool own = (g == J);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) a[k] = own ? c[k] : a[k];
+  });
+  const float s = __builtin_amdgcn_rcpf(mypiv);
+  m = floatx4{a[0] * s, a[1] * s, a[2] * s, a[3] * s};
+  return !(mypiv > 0.f && mypiv < __builtin_inff());
+}
+
+// The same in place in LDS: the left halves of Wm[q] (row r at Wq + r*PITCH), by a workgroup of one wavefront.  The
+// caller has ordered its writes of M; the function ends with an ordering of the wavefront's LDS traffic, which does not
+// wait for global accesses.
+template <bool NEGATE = false>
 __device__ __forceinline__ int invert_rows16(float* Wq, int lane) {
   using C = Cfg<16>;
   const int r = lane & 15;
@@ -131,55 +250,11 @@ __device__ __forceinline__ int invert_rows16(float* Wq, int lane) {
     const floatx4 t = *reinterpret_cast<const floatx4*>(Wq + r * C::PITCH + 4 * k);
     a[4 * k + 0] = t[0]; a[4 * k + 1] = t[1]; a[4 * k + 2] = t[2]; a[4 * k + 3] = t[3];
   }
-  float mypiv = 1.f;
-  int bad = 0;
-  static_for<0, 16>([&](auto J) {
-    constexpr int j = decltype(J)::value;
-    const float pv = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, a[j]), 0x150 + j, 0xF, 0xF,
-                                                                         true));  // row_newbcast:j: the pivot
-    if (!(pv > 0.f && pv < __builtin_inff())) bad = 1;
-    const bool mine = (r == j);
-    const float nl = mine ? 0.f : -a[j] * __builtin_amdgcn_rcpf(pv);  // 0 for the pivot row itself
-    mypiv = mine ? pv : mypiv;
-    // a[k] += nl * (a[k] of the pivot row, lane j of this row of 16 lanes), k != j: the broadcast rides on the
-    // multiply-add as its DPP operand.  Written as one block so that the wait states a DPP read needs after a
-    // vector write of the same register are in our hands: within the block every instruction touches its own
-    // register, and the block starts and ends with the two idle states.
-#define TTC_AK(n) a[(n) < j ? (n) : (n) + 1]  // the 15 registers other than a[j], in ascending order
-    asm volatile(
-        "s_nop 1\n\t"
-        "v_fmac_f32_dpp %0, %0, %15 row_newbcast:%16 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %1, %1, %15 row_newbcast:%16 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %2, %2, %15 row_newbcast:%16 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %3, %3, %15 row_newbcast:%16 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %4, %4, %15 row_newbcast:%16 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %5, %5, %15 row_newbcast:%16 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %6, %6, %15 row_newbcast:%16 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %7, %7, %15 row_newbcast:%16 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %8, %8, %15 row_newbcast:%16 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %9, %9, %15 row_newbcast:%16 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %10, %10, %15 row_newbcast:%16 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %11, %11, %15 row_newbcast:%16 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %12, %12, %15 row_newbcast:%16 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %13, %13, %15 row_newbcast:%16 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %14, %14, %15 row_newbcast:%16 row_mask:0xf bank_mask:0xf\n\t"
-        "s_nop 1"
-        : "+v"(TTC_AK(0)), "+v"(TTC_AK(1)), "+v"(TTC_AK(2)), "+v"(TTC_AK(3)), "+v"(TTC_AK(4)), "+v"(TTC_AK(5)),
-          "+v"(TTC_AK(6)), "+v"(TTC_AK(7)), "+v"(TTC_AK(8)), "+v"(TTC_AK(9)), "+v"(TTC_AK(10)), "+v"(TTC_AK(11)),
-          "+v"(TTC_AK(12)), "+v"(TTC_AK(13)), "+v"(TTC_AK(14))
-        : "v"(nl), "n"(j));
-#undef TTC_AK
-    a[j] = mine ? 1.f : nl;  // column j of the right part
-  });
-  const float s = NEGATE ? -__builtin_amdgcn_rcpf(mypiv) : __builtin_amdgcn_rcpf(mypiv);
+  const int bad = invert_regs16<NEGATE>(a);
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    floatx4 t;
-    t[0] = a[4 * k + 0] * s; t[1] = a[4 * k + 1] * s; t[2] = a[4 * k + 2] * s; t[3] = a[4 * k + 3] * s;
-    *reinterpret_cast<floatx4*>(Wq + r * C::PITCH + 4 * k) = t;
-  }
-  if (ONE_WAVE) wave_lds_sync();
-  else __syncthreads();
+  for (int k = 0; k < 4; ++k)
+    *reinterpret_cast<floatx4*>(Wq + r * C::PITCH + 4 * k) = floatx4{a[4 * k], a[4 * k + 1], a[4 * k + 2], a[4 * k + 3]};
+  wave_lds_sync();
   return bad;
 }
 

@@ -242,7 +242,7 @@ __global__ void __launch_bounds__(64, PPW == 4 ? 2 : 1) solve_small_kernel(const
         PTp[q] = p.QT ? reinterpret_cast<const TIn*>(p.QT) + prob[q] * p.sQT : Qp[q];
         keep[q] = valid[q] && !info[q];
       }
-      riccati_quad<TIn, PPW>(Wm, s_red, p, prob, keep, p.T, Ap, Bp, Qp, Rp, PTp, 0, 0, 0, 0, 2, tid + opaque_zero());
+      riccati_quad<TIn, PPW>(Wm, p, prob, keep, p.T, Ap, Bp, Qp, Rp, PTp, 0, 0, 0, 0, 2, tid + opaque_zero());
 #pragma unroll
       for (int q = 0; q < PPW; ++q) {
         if (!(valid[q] && info[q])) continue;  // set-up breakdown: NaN outputs and its own code

@@ -276,27 +276,131 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR) rollout_tv_kernel(const TvRollou
   }
 }
 
-// The same at d = 16 with four problems per wavefront (see ttc_small.hpp): products of the four problems
-// interleaved on the matrix cores, their dense solves side by side with one row per lane.
-// PPW = problems per wavefront: 4 for batches that fill the chip, 1 for small ones (the four rows of 16 lanes
-// then all hold the same problem; every per-problem loop runs once).
-//
-// riccati_quad: the whole backward recursion of the wavefront's PPW problems, from their terminal value matrices
-// (PTp[q], input element type) to the outputs.  Step s of problem q reads A, B, R at Ap[q] + s*tA, ... and the
-// stage cost on the state it starts from at Qp[q] + (s-1)*tQ; zero strides give the time-invariant problem.
-// info = info_base + the index (1 = the step taken first) of the step whose solve broke down.
+// The same at d = 16 with one or four problems per wavefront (see ttc_small.hpp).  At this size the accumulator layout of
+// a matrix (lane (i, g) holds M[4g + v][i]) is at once its own B operand and the A operand of its transpose, so a step runs
+// from register to register: P A, P B, then B^T (P B), B^T (P A), A^T (P A) straight from the loaded A, B; only S passes
+// through LDS, on its way to a row per lane for the inverse.  Products of the wavefront's problems are interleaved.
+// PPW = problems per wavefront: 4 for batches that fill the chip, 1 for small ones (the four rows of 16 lanes then all
+// invert the same matrix; every per-problem loop runs once).
+
+// accumulator layout of a row-major 16 x 16 matrix in memory, and of its transpose (a lane's four values are 16 bytes)
+template <typename TIn>
+__device__ __forceinline__ floatx4 load_acc16(const TIn* M, int i, int g) {
+  floatx4 r;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) r[v] = ld1<TIn>(M, (unsigned)(64 * g + i) + 16 * v);
+  return r;
+}
+template <typename TIn>
+__device__ __forceinline__ floatx4 load_accT16(const TIn* M, int i, int g) {
+  return ld4<TIn>(M, (unsigned)(16 * i + 4 * g));
+}
+
+// acc[q] += L_q R_q for the wavefront's problems: a = the accumulator layout of L_q^T, b = that of R_q
+template <int PPW>
+__device__ __forceinline__ void mul16(floatx4 (&acc)[PPW], const floatx4 (&a)[PPW], const floatx4 (&b)[PPW]) {
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int q = 0; q < PPW; ++q) acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[q][t], b[q][t], acc[q], 0, 0, 0);
+}
+template <int PPW>
+__device__ __forceinline__ void zero16(floatx4 (&acc)[PPW]) {
+#pragma unroll
+  for (int q = 0; q < PPW; ++q) acc[q] = floatx4{0.f, 0.f, 0.f, 0.f};
+}
+// P <- (P + P^T) / 2, exactly symmetric: the transpose is formed on the matrix cores as P^T times the identity (exact)
+template <int PPW>
+__device__ __forceinline__ void symmetrise16(floatx4 (&P)[PPW], int i, int g) {
+  floatx4 eye[PPW], t[PPW];
+#pragma unroll
+  for (int q = 0; q < PPW; ++q)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) eye[q][v] = (4 * g + v == i) ? 1.f : 0.f;
+  zero16<PPW>(t);
+  mul16<PPW>(t, P, eye);
+#pragma unroll
+  for (int q = 0; q < PPW; ++q) P[q] = 0.5f * (P[q] + t[q]);
+}
+
+// One backward step of Prop. 3.1 for the wavefront's problems.  On entry P holds P_{s+1} (symmetric), A, B the step's
+// matrices and Rl(q) returns (the symmetric part of) R, asked for when it is needed; next() is called when A, B and R are
+// no longer needed; on exit Wk = S^{-1} B^T P A = -K_s and
+// pn = A^T P A - (B^T P A)^T Wk.  Wm: 16 x PITCH floats of LDS per problem.  Returns, per lane, a breakdown of the inverse.
+template <int PPW, typename RLoad, typename Next>
+__device__ __forceinline__ int riccati_step16(float (*Wm)[16 * Cfg<16>::PITCH], const floatx4 (&P)[PPW],
+                                              const floatx4 (&A)[PPW], const floatx4 (&B)[PPW], RLoad&& Rl, Next&& next,
+                                              floatx4 (&Wk)[PPW], floatx4 (&pn)[PPW], floatx4 (&S)[PPW],
+                                              floatx4 (&Si)[PPW], int lane) {
+  using C = Cfg<16>;
+  const int i = lane & 15, g = lane >> 4;
+  floatx4 PA[PPW], PB[PPW], F[PPW];
+  zero16<PPW>(PB);
+  mul16<PPW>(PB, P, B);  // P B
+  zero16<PPW>(S);
+  mul16<PPW>(S, B, PB);  // B^T P B
+  zero16<PPW>(PA);
+  mul16<PPW>(PA, P, A);  // P A
+#pragma unroll
+  for (int q = 0; q < PPW; ++q) S[q] += Rl(q);
+  // the inverse (of S^T, that is of S up to rounding), its rows as the A operand
+  int bad;
+  if constexpr (PPW == 1) {
+    zero16<PPW>(F);
+    mul16<PPW>(F, B, PA);  // F = B^T P A
+    zero16<PPW>(pn);
+    mul16<PPW>(pn, A, PA);  // A^T P A
+    next();
+    Si[0] = S[0];
+    bad = invert_spread16(Si[0], lane);
+  } else {
+#pragma unroll
+    for (int q = 0; q < PPW; ++q) *reinterpret_cast<floatx4*>(Wm[q] + i * C::PITCH + 4 * g) = S[q];  // S^T, row-major
+    wave_lds_sync();
+    zero16<PPW>(F);
+    mul16<PPW>(F, B, PA);
+    zero16<PPW>(pn);
+    mul16<PPW>(pn, A, PA);
+    next();
+    bad = invert_rows16(Wm[g & (PPW - 1)], lane);
+#pragma unroll
+    for (int q = 0; q < PPW; ++q) Si[q] = *reinterpret_cast<const floatx4*>(Wm[q] + i * C::PITCH + 4 * g);
+  }
+  zero16<PPW>(Wk);
+  mul16<PPW>(Wk, Si, F);  // W = S^{-1} F
+  // One step of refinement, W += S^{-1} (F - S W): an explicitly formed inverse leaves an error proportional to cond(S)
+  // in W, which the cancellation in A^T P A - F^T W magnifies when control is cheap; the corrected W is as good as a
+  // factor-and-solve.
+  floatx4 res[PPW], neg[PPW];
+#pragma unroll
+  for (int q = 0; q < PPW; ++q) {
+    res[q] = F[q];
+    neg[q] = -S[q];  // the A operand of -S^T, the matrix that was inverted
+  }
+  mul16<PPW>(res, neg, Wk);
+  mul16<PPW>(Wk, Si, res);
+#pragma unroll
+  for (int q = 0; q < PPW; ++q) neg[q] = -F[q];
+  mul16<PPW>(pn, neg, Wk);  // - F^T W
+  return bad;
+}
+
+// The whole backward recursion of the wavefront's PPW problems, from their terminal value matrices (PTp[q], input element
+// type) to the outputs.  Step s of problem q reads A, B, R at Ap[q] + s*tA, ... and the stage cost on the state it starts
+// from at Qp[q] + (s-1)*tQ; zero strides give the time-invariant problem.  Only problems with keep[q] are written;
+// info = info_base + the index (1 = the step taken first) of the step whose solve broke down.  Measured at T = 64, kernel
+// time, against the version that passed every operand through LDS and inverted a row per lane: 16 problems 195 -> 104 us,
+// 1024: 222 -> 127 us, 8192: 1059 -> 546 us.
 template <typename TIn, int PPW>
-__device__ __forceinline__ void riccati_quad(float (*Wm)[16 * Cfg<16>::PITCH], float* s_red, const SolveArgs& p,
-                                             const long long (&prob)[PPW], const bool (&valid)[PPW], int T,
+__device__ __forceinline__ void riccati_quad(float (*Wm)[16 * Cfg<16>::PITCH], const SolveArgs& p,
+                                             const long long (&prob)[PPW], const bool (&keep)[PPW], int T,
                                              const TIn* const (&Ap)[PPW], const TIn* const (&Bp)[PPW],
                                              const TIn* const (&Qp)[PPW], const TIn* const (&Rp)[PPW],
                                              const TIn* const (&PTp)[PPW], long long tA, long long tB, long long tQ,
                                              long long tR, int info_base, int tid) {
   constexpr int D = 16;
   using C = Cfg<D>;
-  constexpr int w = 0;
-  const int lane = tid & 63, i = lane & 15, g = lane >> 4;
-  float* const Wmine = Wm[g & (PPW - 1)];  // the problem whose rows this lane holds during the dense solves
+  const int lane = tid & 63, i = lane & 15, g = lane >> 4, gq = g & (PPW - 1);
   int info[PPW] = {};
   int nsolve = 0;
   auto note = [&](int bad) {
@@ -306,180 +410,152 @@ __device__ __forceinline__ void riccati_quad(float (*Wm)[16 * Cfg<16>::PITCH], f
     for (int q = 0; q < PPW; ++q)
       if (!info[q] && ((m >> (16 * q)) & 0xFFFFull)) info[q] = nsolve;
   };
-  // One problem per wavefront is the shape of small batches, where nothing else hides a step's reads of its matrices:
-  // there they are requested one step ahead (PF), into registers, and handed to LDS when their turn comes.
+  // One problem per wavefront is the shape of batches that do not fill the chip, where nothing else hides a step's reads:
+  // its matrices are requested two steps ahead (PF), into the registers of the step that has just used its own.  With four
+  // problems A and B are requested one step ahead, and R and Q, which a step needs late, at its start.  Every step issues
+  // the same reads (the last ones repeat what is there), so that a wait counts on exactly them.
   constexpr bool PF = PPW == 1;
-  HalfRegs<D> hA[PPW], hB[PPW], hQ[PPW];
-  floatx4 rR[PPW][C::RB][C::NT];
-  auto fetch_abr = [&](int s) {
+  constexpr int NS = PF ? 2 : 1;
+  floatx4 A[NS][PPW], B[NS][PPW], R0[NS][PPW], R1[NS][PPW], Q0[NS][PPW], Q1[NS][PPW];
+  int left = T - 1, left_r = T - 1, left_q = T - 1;  // steps before the one whose reads are issued next
+  long long oA = (T - 1) * tA, oB = (T - 1) * tB, oR = (T - 1) * tR, oQ = T >= 2 ? (T - 2) * tQ : 0;
+  auto fetch_ab = [&](int u) {
 #pragma unroll
     for (int q = 0; q < PPW; ++q) {
-      issue_half<D, TIn>(hA[q], Ap[q] + (long long)s * tA, tid);
-      issue_half<D, TIn>(hB[q], Bp[q] + (long long)s * tB, tid);
-      load_rows_input<D, TIn>(Rp[q] + (long long)s * tR, rR[q], w, i, g);
+      A[u][q] = load_acc16<TIn>(Ap[q] + oA, i, g);
+      B[u][q] = load_acc16<TIn>(Bp[q] + oB, i, g);
+    }
+    if (left > 0) {
+      --left;
+      oA -= tA;
+      oB -= tB;
     }
   };
-  auto fetch_q = [&](int s) {  // the stage cost on the state step s starts from
+  auto fetch_r = [&](int u) {
 #pragma unroll
-    for (int q = 0; q < PPW; ++q) issue_half<D, TIn>(hQ[q], Qp[q] + (long long)(s - 1) * tQ, tid);
+    for (int q = 0; q < PPW; ++q) {
+      R0[u][q] = load_acc16<TIn>(Rp[q] + oR, i, g);
+      R1[u][q] = load_accT16<TIn>(Rp[q] + oR, i, g);
+    }
+    if (left_r > 0) {
+      --left_r;
+      oR -= tR;
+    }
   };
-  if (PF) {
-    fetch_abr(T - 1);
-    if (T >= 2) fetch_q(T - 1);
-  }
+  auto fetch_q = [&](int u) {  // the stage cost on the state the step starts from
 #pragma unroll
-  for (int q = 0; q < PPW; ++q) load_half<D, TIn, false>(Wm[q] + D, PTp[q], tid);  // P_T = Q_T
-  wave_lds_sync();
-#pragma unroll
-  for (int q = 0; q < PPW; ++q) symmetrise_half<D>(Wm[q] + D, tid);
-  wave_lds_sync();
-  for (int s = T - 1; s >= 0; --s) {
-    // the step of riccati_step, for four problems at once
-    floatx4 pn[PPW][C::RB][C::NT], accF[PPW][C::RB][C::NT], accW[PPW][C::RB][C::NT];
-    {
-      float cAT[PPW][C::RB][C::KS], cBT[PPW][C::RB][C::KS];
-      {
-        floatx4 accPA[PPW][C::RB][C::NT], accPB[PPW][C::RB][C::NT];
-        {
-          float cP[PPW][C::RB][C::KS];
-#pragma unroll
-          for (int q = 0; q < PPW; ++q) {
-            load_aop_lds<D>(Wm[q] + D, cP[q], w, i, g);  // rows of P
-            if (PF) commit_half<D, false>(Wm[q], hA[q], tid);
-            else load_half<D, TIn, false>(Wm[q], Ap[q] + (long long)s * tA, tid);
-          }
-          wave_lds_sync();
-#pragma unroll
-          for (int q = 0; q < PPW; ++q) {
-            if (PF) commit_half<D, false>(Wm[q] + D, hB[q], tid);  // P is in registers now
-            else load_half<D, TIn, false>(Wm[q] + D, Bp[q] + (long long)s * tB, tid);
-            zero_acc<D>(accPA[q]);
-            zero_acc<D>(accPB[q]);
-          }
-          gemm_acc_quad<PPW>(accPA, cP, Wm, 0, i, g);  // P A
-          wave_lds_sync();
-          gemm_acc_quad<PPW>(accPB, cP, Wm, D, i, g);  // P B
-        }
-#pragma unroll
-        for (int q = 0; q < PPW; ++q) {
-          load_aopT_lds<D>(Wm[q], cAT[q], w, i, g);      // rows of A^T
-          load_aopT_lds<D>(Wm[q] + D, cBT[q], w, i, g);  // rows of B^T
-        }
-        wave_lds_sync();
-#pragma unroll
-        for (int q = 0; q < PPW; ++q) {
-          store_rows<D>(Wm[q], accPA[q], w, i, g);
-          store_rows<D>(Wm[q] + D, accPB[q], w, i, g);
-        }
-        wave_lds_sync();
-      }
-      floatx4 accS[PPW][C::RB][C::NT];
-#pragma unroll
-      for (int q = 0; q < PPW; ++q) {
-        if (PF) accS[q][0][0] = rR[q][0][0];
-        else load_rows_input<D, TIn>(Rp[q] + (long long)s * tR, accS[q], w, i, g);
-        zero_acc<D>(accF[q]);
-        zero_acc<D>(pn[q]);
-      }
-      if (PF && s >= 1) fetch_abr(s - 1);  // the next step's matrices, while this step computes
-      gemm_acc_quad<PPW>(accS, cBT, Wm, D, i, g);  // S = R + B^T P B
-      gemm_acc_quad<PPW>(accF, cBT, Wm, 0, i, g);  // F = B^T P A
-      gemm_acc_quad<PPW>(pn, cAT, Wm, 0, i, g);    // A^T P A
-      wave_lds_sync();
-#pragma unroll
-      for (int q = 0; q < PPW; ++q) store_rows<D>(Wm[q], accS[q], w, i, g);
-      wave_lds_sync();
+    for (int q = 0; q < PPW; ++q) {
+      Q0[u][q] = load_acc16<TIn>(Qp[q] + oQ, i, g);
+      Q1[u][q] = load_accT16<TIn>(Qp[q] + oQ, i, g);
     }
+    if (left_q > 1) oQ -= tQ;
+    --left_q;
+  };
+  floatx4 P[PPW], Wk[PPW];
 #pragma unroll
-    for (int q = 0; q < PPW; ++q) symmetrise_half<D>(Wm[q], tid);  // R is read as its symmetric part
-    wave_lds_sync();
-    float cS[PPW][C::RB][C::KS];
-#pragma unroll
-    for (int q = 0; q < PPW; ++q) load_aop_lds<D>(Wm[q], cS[q], w, i, g);  // rows of S, for the refinement below
-    note(invert_rows16<false, true>(Wmine, lane));  // left halves: S^{-1}
-    {
-      // At d = 16 the accumulator layout of F is both the B operand of F and the A operand of F^T.
-      float cSi[PPW][C::RB][C::KS];
-      floatx4 res[PPW];
-#pragma unroll
-      for (int q = 0; q < PPW; ++q) {
-        load_aop_lds<D>(Wm[q], cSi[q], w, i, g);  // rows of S^{-1}
-        zero_acc<D>(accW[q]);
-        res[q] = accF[q][0][0];
-      }
-#pragma unroll
-      for (int t = 0; t < 4; ++t)  // W = S^{-1} F = -K_s
-#pragma unroll
-        for (int q = 0; q < PPW; ++q)
-          accW[q][0][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(cSi[q][0][t], accF[q][0][0][t], accW[q][0][0], 0, 0, 0);
-      // One step of refinement, W += S^{-1} (F - S W): an explicitly formed inverse leaves an error proportional
-      // to cond(S) in W, which the cancellation in A^T P A - F^T W magnifies when control is cheap; the corrected
-      // W is as good as a factor-and-solve.
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int q = 0; q < PPW; ++q)
-          res[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(-cS[q][0][t], accW[q][0][0][t], res[q], 0, 0, 0);
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int q = 0; q < PPW; ++q)
-          accW[q][0][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(cSi[q][0][t], res[q][t], accW[q][0][0], 0, 0, 0);
-#pragma unroll
-      for (int t = 0; t < 4; ++t)  // - F^T W
-#pragma unroll
-        for (int q = 0; q < PPW; ++q)
-          pn[q][0][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(-accF[q][0][0][t], accW[q][0][0][t], pn[q][0][0], 0, 0, 0);
-    }
-    wave_lds_sync();
-    if (s >= 1) {
-#pragma unroll
-      for (int q = 0; q < PPW; ++q) {
-        if (PF) commit_half<D, false>(Wm[q], hQ[q], tid);
-        else load_half<D, TIn, false>(Wm[q], Qp[q] + (long long)(s - 1) * tQ, tid);
-      }
-      if (PF && s >= 2) fetch_q(s - 1);
-      wave_lds_sync();
-#pragma unroll
-      for (int q = 0; q < PPW; ++q) symmetrise_half<D>(Wm[q], tid);
-      wave_lds_sync();
-#pragma unroll
-      for (int q = 0; q < PPW; ++q) {
-        floatx4 qs[C::RB][C::NT];
-        load_rows<D>(Wm[q], qs, w, i, g);
-        pn[q][0][0] += qs[0][0];
-        store_rows<D>(Wm[q] + D, pn[q], w, i, g);  // P_s
-      }
-      wave_lds_sync();
-#pragma unroll
-      for (int q = 0; q < PPW; ++q) symmetrise_half<D>(Wm[q] + D, tid);
-      wave_lds_sync();
-    } else {
-#pragma unroll
-      for (int q = 0; q < PPW; ++q) store_rows<D>(Wm[q], pn[q], w, i, g);  // P_0 (no cost on x_0)
-      wave_lds_sync();
-#pragma unroll
-      for (int q = 0; q < PPW; ++q) symmetrise_half<D>(Wm[q], tid);
-      wave_lds_sync();
-#pragma unroll
-      for (int q = 0; q < PPW; ++q) {
-        if (!valid[q]) continue;  // uniform over the wavefront
-        const TIn* x0p = reinterpret_cast<const TIn*>(p.x0) + prob[q] * p.sx0;
-        emit_gain<D, TIn>(p, prob[q], accW[q], x0p, info[q], tid);  // rows of -K_0
-        emit_value<D, TIn>(p, prob[q], Wm[q], Qp[q], x0p, info[q] ? info_base + info[q] : 0, s_red, tid);
-      }
-      __syncthreads();
+  for (int u = 0; u < NS; ++u) {
+    fetch_ab(u);
+    if (PF) {
+      fetch_r(u);
+      fetch_q(u);
     }
   }
+#pragma unroll
+  for (int q = 0; q < PPW; ++q)  // P_T = Q_T
+    P[q] = 0.5f * (load_acc16<TIn>(PTp[q], i, g) + load_accT16<TIn>(PTp[q], i, g));
+  auto step = [&](auto U, int s) {
+    constexpr int u = decltype(U)::value;
+    if (!PF) {
+      fetch_r(u);
+      fetch_q(u);
+    }
+    floatx4 pn[PPW], S[PPW], Si[PPW];
+    note(riccati_step16<PPW>(Wm, P, A[u], B[u], [&](int q) { return 0.5f * (R0[u][q] + R1[u][q]); },
+                             [&] {
+                               fetch_ab(u);
+                               if (PF) fetch_r(u);
+                             },
+                             Wk, pn, S, Si, lane));
+#pragma unroll
+    for (int q = 0; q < PPW; ++q) {
+      P[q] = pn[q];
+      if (s >= 1) P[q] += 0.5f * (Q0[u][q] + Q1[u][q]);
+    }
+    if (PF) fetch_q(u);
+    symmetrise16<PPW>(P, i, g);
+    wave_lds_sync();
+  };
+  for (int s = T - 1; s >= 0; s -= NS) {
+    step(IntC<0>{}, s);
+    if constexpr (NS == 2) {
+      if (s == 0) break;
+      step(IntC<1>{}, s - 1);
+    }
+  }
+  // ---- outputs (no cost on x_0): lane (i, g) takes row i of its problem's K_0 and P_0 for u_0 = K_0 x_0 and
+  // value = x_0^T P_0 x_0; the matrices leave as one 16-byte piece per lane and problem
+  long long pg = prob[0];
+  int myinfo = info[0];
+  bool mykeep = keep[0];
+#pragma unroll
+  for (int q = 1; q < PPW; ++q) {
+    pg = gq == q ? prob[q] : pg;
+    myinfo = gq == q ? info[q] : myinfo;
+    mykeep = gq == q ? keep[q] : mykeep;
+  }
+  const float nanv = __builtin_nanf("");
+  const float x0_m = ld1<TIn>(reinterpret_cast<const TIn*>(p.x0), pg * p.sx0 + i);
+#pragma unroll
+  for (int q = 0; q < PPW; ++q) {
+    if (p.flags & TTC_FLAG_STAGE_COST_AT_X0)
+      P[q] += 0.5f * (load_acc16<TIn>(Qp[q], i, g) + load_accT16<TIn>(Qp[q], i, g));
+#pragma unroll
+    for (int v = 0; v < 4; ++v) Wm[q][(4 * g + v) * C::PITCH + i] = -Wk[q][v];          // K_0, row-major
+    *reinterpret_cast<floatx4*>(Wm[q] + D + i * C::PITCH + 4 * g) = P[q];                // P_0
+  }
+  if (g == gq) Wm[gq][i * C::PITCH + 2 * D] = x0_m;  // the first of the four skew columns
+  wave_lds_sync();
+  float u = 0.f, pw = 0.f;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const floatx4 kr = *reinterpret_cast<const floatx4*>(Wm[gq] + i * C::PITCH + 4 * c);
+    const floatx4 pr = *reinterpret_cast<const floatx4*>(Wm[gq] + D + i * C::PITCH + 4 * c);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const float xr = Wm[gq][(4 * c + v) * C::PITCH + 2 * D];
+      u = __builtin_fmaf(kr[v], xr, u);
+      pw = __builtin_fmaf(pr[v], xr, pw);
+    }
+  }
+  const float val = sum16(x0_m * pw);
+  if (mykeep && (PPW == 4 || g == 0)) {
+    p.u0[pg * D + i] = myinfo ? nanv : u;
+    if (i == 0) {
+      if (p.value) p.value[pg] = myinfo ? nanv : val;
+      if (p.info) p.info[pg] = myinfo ? info_base + myinfo : 0;
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < PPW; ++q) {
+    if (!keep[q]) continue;  // uniform over the wavefront
+    const floatx4 nan4 = floatx4{nanv, nanv, nanv, nanv};
+    const float* row = Wm[q] + (lane >> 2) * C::PITCH + 4 * (lane & 3);
+    if (p.K0)
+      *reinterpret_cast<floatx4*>(p.K0 + prob[q] * (long)D * D + 4 * lane) =
+          info[q] ? nan4 : *reinterpret_cast<const floatx4*>(row);
+    if (p.P0)
+      *reinterpret_cast<floatx4*>(p.P0 + prob[q] * (long)D * D + 4 * lane) =
+          info[q] ? nan4 : *reinterpret_cast<const floatx4*>(row + D);
+  }
+  wave_lds_sync();
 }
 
 template <typename TIn, int PPW>
-__global__ void __launch_bounds__(64, 2) solve_tv_small_kernel(const TvArgs ta) {
+__global__ void __launch_bounds__(64, PPW == 4 ? 2 : 4) solve_tv_small_kernel(const TvArgs ta) {
   constexpr int D = 16;
   using C = Cfg<D>;
   static_assert(PPW == 1 || PPW == 4, "one problem or four per wavefront");
   __shared__ __attribute__((aligned(16))) float Wm[PPW][D * C::PITCH];
-  __shared__ float s_red[C::NW];
   const SolveArgs& p = ta.s;
   const long long nquads = (p.n + PPW - 1) / PPW;
 
@@ -498,7 +574,7 @@ __global__ void __launch_bounds__(64, 2) solve_tv_small_kernel(const TvArgs ta) 
       Rp[q] = reinterpret_cast<const TIn*>(p.R) + prob[q] * p.sR;
       PTp[q] = Qp[q] + (long long)(p.T - 1) * ta.tQ;  // P_T = Q_T
     }
-    riccati_quad<TIn, PPW>(Wm, s_red, p, prob, valid, p.T, Ap, Bp, Qp, Rp, PTp, ta.tA, ta.tB, ta.tQ, ta.tR, 0, tid);
+    riccati_quad<TIn, PPW>(Wm, p, prob, valid, p.T, Ap, Bp, Qp, Rp, PTp, ta.tA, ta.tB, ta.tQ, ta.tR, 0, tid);
   }
 }
 
