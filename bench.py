@@ -113,6 +113,24 @@ def alg_flops_doubling(d, T):
     return (f + 8 + 8.0 / 3) * d ** 3
 
 
+def default_squares(d, T, bf16):
+    """Whether the default path of ttc_lqr_solve (Q_T = Q, rebase_every = 0) composes the equal factors by squaring: the
+    library's own rule (use_squaring in csrc/ttc_api.hip)."""
+    if d < 32 or T < 2:
+        return False
+    applications = bin(T).count("1") - 1
+    cost = 100 * (T.bit_length() - 1) + 70 * applications + (35 if applications else 0) + 10
+    return 100 * cost <= 98 * (37 if bf16 else 40) * T
+
+
+def alg_flops_default(d, T, groups, bf16, rebase_every=0):
+    """Algorithmic flops of one problem on the default path: the sequential product, or the squaring schedule, which then
+    also factors A (2/3 d^3)."""
+    if rebase_every or not default_squares(d, T, bf16):
+        return alg_flops(d, T, groups)
+    return alg_flops_doubling(d, T) + 2.0 / 3 * d ** 3
+
+
 def alg_flops_tv(d, T):
     """Algorithmic flops of one time-heterogeneous problem (ttc_lqr_solve_tv): per step the six products of the
     printed Riccati step (P A, P B, B^T P A, B^T P B, A^T P A, F^T W: 2 d^3 each) and the solve with the positive
@@ -749,14 +767,15 @@ def main():
 
     flops_pp = {"doubling": alg_flops_doubling(d, T), "tv": alg_flops_tv(d, T), "bwd": alg_flops_bwd(d, T),
                 "rollout": alg_flops_rollout(d, T)}.get(path) \
-        or alg_flops(d, T, groups)
+        or alg_flops_default(d, T, groups, cfg["dtype"] == "bf16", k)
+    squares = path == "symplectic" and not k and default_squares(d, T, cfg["dtype"] == "bf16")
     achieved = flops_pp * n / avg_kernel_s / 1e12
     steps_in = T if path == "tv" else 1          # every step has its own matrices on the tv path
     in_bytes = n * (steps_in * (2 * d * d + d * m + m * m) + d) * esize + (n * m * 4 if path == "bwd" else 0)
     out_bytes = n * out_pp
     kernel_name = {"doubling": "doubling_kernel<%d>", "tv": "solve_tv_kernel<%d>", "bwd": "backward_kernel<%d>",
                    "rollout": "rollout_kernel<%d>"}.get(
-        path, "solve_kernel<%d>") % d if d != 16 or path in ("doubling", "bwd", "rollout") else (
+        path, "squaring_kernel<%d>" if squares else "solve_kernel<%d>") % d if d != 16 or path in ("doubling", "bwd", "rollout") else (
         "solve_tv_small_kernel" if path == "tv" else "solve_small_kernel")
     res = {
         "metric": "LQR backward passes/sec (gradients of a loss of u0) at d=%d, T=%d" % (d, T) if path == "bwd" else
@@ -767,7 +786,7 @@ def main():
         "dtype": "f32", "data": "synthetic",
         "config": {"workload": args.config, "problems": n, "d": d, "m": m, "T": T, "input_dtype": cfg["dtype"],
                    "path": path, "rebase_every": None if path != "symplectic" else (k or "default"),
-                   "groups": groups if path == "symplectic" else None, "chunks": nchunks,
+                   "groups": groups if path == "symplectic" and not squares else None, "chunks": nchunks,
                    "outputs": "gA,gB,gQ,gR,gx0" if path == "bwd" else "U,X,cost" if path == "rollout" else "P0,K0,u0,value"},
         "roofline": {"bound": "mfma", "achieved": achieved, "peak": PEAK_FP32_MFMA_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / PEAK_FP32_MFMA_TFLOPS,
@@ -834,7 +853,7 @@ def main():
         other = "doubling" if path == "symplectic" else "symplectic"
         o_wall, o_ms = timed(dbl if other == "doubling" else 0, max(1, min(args.steps, 2)), 1)
         o_kernel = sum(o_ms) / len(o_ms) / 1e3
-        o_flops = alg_flops_doubling(d, T) if other == "doubling" else alg_flops(d, T, groups)
+        o_flops = alg_flops_doubling(d, T) if other == "doubling" else alg_flops_default(d, T, groups, cfg["dtype"] == "bf16")
         extra = {"path": other, "value": n / o_wall, "unit": "problems/s", "kernel_ms": o_kernel * 1e3,
                  "alg_flops_per_problem": o_flops, "achieved_TFLOPs": o_flops * n / o_kernel / 1e12,
                  "frac_of_peak": o_flops * n / o_kernel / 1e12 / PEAK_FP32_MFMA_TFLOPS}

@@ -27,6 +27,7 @@ HIPCC_FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC",
 UNITS = [("ttc_api.hip", None),
          ("k_solve.hip", (32, 64, 128)),
          ("k_doubling.hip", (16, 32, 64, 128)),
+         ("k_squaring.hip", (32, 64, 128)),
          ("k_rollout.hip", (16, 32, 64, 128)),
          ("k_tv.hip", (16, 32, 64, 128)),
          ("k_scan.hip", (16, 32, 64, 128)),
@@ -46,7 +47,8 @@ UNITS = [("ttc_api.hip", None),
 _ONE_ROW_BLOCK = "-DTTC_ROW_BLOCKS(D)=((D)==%d?1:((D)>=32?2:1))"
 UNIT_FLAGS = {("k_backward.hip", 64): [_ONE_ROW_BLOCK % 64],
               ("k_tv.hip", 128): [_ONE_ROW_BLOCK % 128],
-              ("k_doubling.hip", 128): [_ONE_ROW_BLOCK % 128]}
+              ("k_doubling.hip", 128): [_ONE_ROW_BLOCK % 128],
+              ("k_squaring.hip", 128): [_ONE_ROW_BLOCK % 128]}
 
 _NOISE = "is not a recognized feature for this target"
 

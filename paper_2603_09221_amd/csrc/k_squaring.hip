@@ -1,0 +1,17 @@
+// squaring_kernel<TTC_D> (ttc_lqr_solve, default path for longer horizons, d >= 32): one translation unit per state size.
+#include "ttc_squaring.hpp"
+#include "ttc_launch.hpp"
+
+namespace ttc {
+template <>
+hipError_t launch_squaring<TTC_D>(const DoublingArgs& a, bool bf16, dim3 grid, hipStream_t st) {
+  if (bf16) hipLaunchKernelGGL((squaring_kernel<TTC_D, uint16_t>), grid, dim3(Cfg<TTC_D>::NTHR), 0, st, a);
+  else hipLaunchKernelGGL((squaring_kernel<TTC_D, float>), grid, dim3(Cfg<TTC_D>::NTHR), 0, st, a);
+  return hipGetLastError();
+}
+template <>
+int occupancy_squaring<TTC_D>(bool bf16) {
+  return bf16 ? occupancy_query(squaring_kernel<TTC_D, uint16_t>, Cfg<TTC_D>::NTHR)
+              : occupancy_query(squaring_kernel<TTC_D, float>, Cfg<TTC_D>::NTHR);
+}
+}  // namespace ttc

@@ -61,7 +61,8 @@ static void* scratch_for_current_device() {
 // workgroup waits for another to finish.  The per-CU number is what the runtime reports for the kernel
 // (registers and LDS decide it); the table is the fallback when no device can be asked.
 enum Kind { KIND_SOLVE = 0, KIND_DOUBLING = 1, KIND_ROLLOUT = 2, KIND_SOLVE_QUAD = 3, KIND_SOLVE_TV = 4, KIND_TV_QUAD = 5,
-            KIND_ROLLOUT_TV = 6, KIND_CXT = 7, KIND_SCAN = 8, KIND_BACKWARD = 9, KIND_TV_ONE = 10, KIND_COUNT = 11 };
+            KIND_ROLLOUT_TV = 6, KIND_CXT = 7, KIND_SCAN = 8, KIND_BACKWARD = 9, KIND_TV_ONE = 10, KIND_SQUARING = 11,
+            KIND_COUNT = 12 };
 static int dindex(int d) { return d == 16 ? 0 : d == 32 ? 1 : d == 64 ? 2 : 3; }
 template <int D>
 static int occupancy_of(Kind kind, bool bf16) {
@@ -70,6 +71,9 @@ static int occupancy_of(Kind kind, bool bf16) {
       if constexpr (D >= 32) return occupancy_solve<D>(bf16);
       else return 0;  // d = 16 has its own kernel
     case KIND_DOUBLING: return occupancy_doubling<D>(bf16);
+    case KIND_SQUARING:
+      if constexpr (D >= 32) return occupancy_squaring<D>(bf16);
+      else return 0;
     case KIND_ROLLOUT: return occupancy_rollout<D>(bf16);
     case KIND_SOLVE_TV: return occupancy_tv<D>(bf16);
     case KIND_ROLLOUT_TV: return occupancy_rollout_tv<D>(bf16);
@@ -100,7 +104,7 @@ static int blocks_per_cu(Kind kind, int d, bool bf16) {
     if (nb <= 0) {
       static const int table[KIND_COUNT][4] = {{20, 8, 2, 1}, {16, 8, 2, 1}, {12, 4, 2, 1}, {8, 8, 2, 1}, {20, 8, 2, 1},
                                                {8, 8, 2, 1},  {12, 4, 2, 1}, {8, 8, 2, 1},  {16, 8, 2, 1},
-                                               {12, 4, 2, 1}, {16, 8, 2, 1}};
+                                               {12, 4, 2, 1}, {16, 8, 2, 1}, {16, 8, 2, 1}};
       nb = table[kind][dindex(d)];
     }
     c.value = nb > 32 ? 32 : nb;
@@ -126,6 +130,27 @@ constexpr long long QUAD_MIN_PER_CU_SOLVE = 12;
 constexpr long long QUAD_MIN_PER_CU_TV = 12;
 static bool use_quad_kernel(const ttc_lqr_problem_t* q) {
   return q->d == 16 && !(q->flags & TTC_FLAG_DOUBLING) && q->n >= QUAD_MIN_PER_CU_SOLVE * cu_count();
+}
+// Squaring (d >= 32): the largest max |I + G_e H_e| of a solve before the problem is handed to the Riccati recursion (see
+// ttc_squaring.hpp).
+constexpr float SQUARING_LIMIT = 16.f;
+// Q_T "is Q" when it is absent or the very same array: then P_T = Q = f(0) and a recursion may start at 0
+static bool qt_is_q(const ttc_lqr_problem_t* q) { return !q->QT || (q->QT == q->Q && q->sQT == q->sQ); }
+// Default path, d >= 32: whether the T equal factors are composed by squaring (squaring_kernel) or one after the other
+// (solve_kernel).  Costs in hundredths of a squaring, fitted to both kernels at d = 32, 64, 128 and T = 8..64: a squaring
+// 100, an application of a power to P 70, A and G of the last square 35 (not needed when P is still 0), 10 more for the
+// set-up (A is factored for its report); a factor of the sequential product 40, with bfloat16 inputs (longer groups) 37.
+// Measured, sequential / squaring, ms: d = 64, 8192 problems, T = 8 2.14 / 1.88, T = 9 2.26 / 2.34, 12 2.84 / 2.32, 15
+// 3.41 / 2.88, 16 4.44 / 2.31, 64 15.9 / 3.17; d = 128, 2048 problems, T = 8 3.70 / 3.69, 9 3.95 / 4.61, 12 4.95 / 4.61,
+// 16 7.01 / 4.52 (with its own Q_T 7.01 / 6.40), 32 11.8 / 5.35; bfloat16 inputs T = 13 4.91 / 5.22, 16 5.92 / 4.52.
+static bool use_squaring(const ttc_lqr_problem_t* q) {
+  if (q->d < 32 || (q->flags & (TTC_FLAG_DOUBLING | TTC_FLAG_PURE_SYMPLECTIC)) || q->rebase_every != 0) return false;
+  const bool from_zero = qt_is_q(q);
+  const unsigned m = (unsigned)(from_zero ? q->T : q->T - 1);
+  if (m < 2) return false;
+  const int squarings = 31 - __builtin_clz(m), applications = __builtin_popcount(m) - (from_zero ? 1 : 0);
+  const long long cost = 100 * squarings + 70 * applications + (applications ? 35 : 0) + 10;
+  return 100 * cost <= 98LL * (q->in_dtype == TTC_BF16 ? 37 : 40) * q->T;
 }
 static bool use_quad_kernel_tv(const ttc_lqr_tv_problem_t* q) {
   return q->d == 16 && q->n >= QUAD_MIN_PER_CU_TV * cu_count();
@@ -169,6 +194,14 @@ static hipError_t run_solve(const SolveArgs& a, int d, bool bf16, dim3 grid, hip
     case 32: return launch_solve<32>(a, bf16, grid, st);
     case 64: return launch_solve<64>(a, bf16, grid, st);
     case 128: return launch_solve<128>(a, bf16, grid, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+static hipError_t run_squaring(const DoublingArgs& a, int d, bool bf16, dim3 grid, hipStream_t st) {
+  switch (d) {
+    case 32: return launch_squaring<32>(a, bf16, grid, st);
+    case 64: return launch_squaring<64>(a, bf16, grid, st);
+    case 128: return launch_squaring<128>(a, bf16, grid, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -283,13 +316,21 @@ ttc_status_t ttc_lqr_solve(const ttc_lqr_problem_t* problem, const ttc_lqr_solut
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   hipError_t e;
   if (problem->flags & TTC_FLAG_DOUBLING) {
-    // Q_T "is Q" when it is absent or the very same array: then P_T = Q = f(0) and the recursion starts at 0
     ttc::DoublingArgs da;
-    const bool qt_is_q = !problem->QT || (problem->QT == problem->Q && problem->sQT == problem->sQ);
     da.s = a;
-    da.m = qt_is_q ? problem->T : problem->T - 1;
-    da.p_from_qt = qt_is_q ? 0 : 1;
+    da.m = ttc::qt_is_q(problem) ? problem->T : problem->T - 1;
+    da.p_from_qt = ttc::qt_is_q(problem) ? 0 : 1;
     e = ttc::run_doubling(da, problem->d, bf16, grid, s);
+  } else if (ttc::use_squaring(problem)) {
+    ttc::DoublingArgs da;
+    da.s = a;
+    da.s.growth_limit = ttc::SQUARING_LIMIT;
+    da.m = ttc::qt_is_q(problem) ? problem->T : problem->T - 1;
+    da.p_from_qt = ttc::qt_is_q(problem) ? 0 : 1;
+    // one workspace slot per workgroup, of which there are as many as solve_kernel's grid
+    const long long gs = ttc::grid_blocks(ttc::KIND_SQUARING, problem->d, bf16);
+    const long long blocks = gs < gb ? gs : gb;
+    e = ttc::run_squaring(da, problem->d, bf16, dim3((unsigned)(problem->n < blocks ? problem->n : blocks)), s);
   } else if (quad) {
     e = ttc::launch_small(a, bf16, 4, grid, s);
   } else if (small) {  // a batch that does not fill the chip: one problem to a wavefront

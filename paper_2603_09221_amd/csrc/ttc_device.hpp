@@ -881,8 +881,9 @@ __device__ __forceinline__ void solve_update_first(float* W, SolveScratch<D>& S,
     *reinterpret_cast<floatx4*>(rowp + 16 * (RT0 * w + r) * C::PITCH + 16 + 4 * g) = acc[r];
 }
 
-// PARTS is kept for the callers' template argument lists (always 7).
-template <int D, int PARTS = 7, bool PIVOT = true>
+// PARTS is kept for the callers' template argument lists (always 7).  RHS = false factors M alone (lds_factor): the
+// columns from D on are neither read nor written.
+template <int D, int PARTS = 7, bool PIVOT = true, bool RHS = true>
 __device__ __forceinline__ int lds_solve(float* W, SolveScratch<D>& S, int tid) {
   using C = Cfg<D>;
   constexpr int NP = D / 16;
@@ -900,7 +901,7 @@ __device__ __forceinline__ int lds_solve(float* W, SolveScratch<D>& S, int tid) 
   for (int p = 0; p < NP; ++p) {
     __syncthreads();  // panel p is in place; every update of panel p-1 is done
     const int cb = 16 * p;
-    const int nct = (2 * D - cb - 16) / 16;  // column tiles to the right of the panel
+    const int nct = ((RHS ? 2 * D : D) - cb - 16) / 16;  // column tiles to the right of the panel
     const bool more = (p + 1 < NP);
     const floatx4 la = *reinterpret_cast<const floatx4*>(S.Linv[p & 1] + (lane & 15) * 16 + 4 * (lane >> 4));
     if (more && C::NW > 1) {
@@ -918,7 +919,7 @@ __device__ __forceinline__ int lds_solve(float* W, SolveScratch<D>& S, int tid) 
       solve_update<D>(W, S, cb, lane, 0, nct, la);
       solve_panel<D, PIVOT>(W, S, cb + 16, lane, atag, bad);
       panel_linv<D>(S, cb + 16, lane);
-    } else {
+    } else if constexpr (RHS) {
       solve_update<D, true>(W, S, cb, lane, (w * nct) / C::NW, ((w + 1) * nct) / C::NW, la);
     }
   }
@@ -927,6 +928,11 @@ __device__ __forceinline__ int lds_solve(float* W, SolveScratch<D>& S, int tid) 
   const int flag = S.flag;
   __syncthreads();
   return flag;
+}
+// The breakdown flag of a pivoted elimination of the left half alone (which it overwrites).
+template <int D>
+__device__ __forceinline__ int lds_factor(float* W, SolveScratch<D>& S, int tid) {
+  return lds_solve<D, 7, true, false>(W, S, tid);
 }
 
 

@@ -14,6 +14,8 @@ template <int D> hipError_t launch_solve(const SolveArgs& a, bool bf16, dim3 gri
 template <int D> int occupancy_solve(bool bf16);
 template <int D> hipError_t launch_doubling(const DoublingArgs& a, bool bf16, dim3 grid, hipStream_t st);
 template <int D> int occupancy_doubling(bool bf16);
+template <int D> hipError_t launch_squaring(const DoublingArgs& a, bool bf16, dim3 grid, hipStream_t st);
+template <int D> int occupancy_squaring(bool bf16);
 template <int D> hipError_t launch_rollout(const RolloutArgs& a, bool bf16, dim3 grid, hipStream_t st);
 template <int D> int occupancy_rollout(bool bf16);
 template <int D> hipError_t launch_tv(const TvArgs& a, bool bf16, dim3 grid, hipStream_t st);

@@ -1,0 +1,307 @@
+// The default path of ttc_lqr_solve for longer horizons at d >= 32: time-invariant parameters make the T factors of
+// Thm 3.3 equal, so their product is formed by squaring (the algebra of ttc_doubling.hpp), with the element on chip.
+//
+// The sequential product costs four products per factor and a pivoted solve per group of three or so, whatever T; a
+// squaring costs eight products and one solve and doubles the number of factors.  Its weak side is accuracy when control
+// is cheap or the open loop grows: I + G_e H_e is then large and the composition loses digits in proportion, while on
+// ordinary problems it is several times more accurate than the grouped product (no A^{-1}, no accumulated pair).  So the
+// kernel watches max |I + G_e H_e| (and |I + P G_e|): a problem that passes the limit goes to the recursion of Prop. 3.1
+// in its printed form, as one that trips the growth guard of solve_kernel does.  Measured over R, Q scaled by 1e-2..1e2
+// and rho(A) in 0.5..1.2 at d = 32, 64, 128: ordinary problems stay below 7, with errors of 1e-6..5e-6; ratios of the
+// scales of 1e2 give 110 and more and errors of 2e-5..1e-4; between, at 16, errors are still below 1e-5.
+//
+// Where things live.  A_e, G_e, H_e and X = R^{-1} B^T are row blocks in registers (the A operand of a product), across
+// the dense solves, as solve_kernel's constants are; LDS holds the pair a product or solve works on; the one workspace
+// slot of the workgroup holds P while the bits of T still have squarings between them (never for T a power of two).
+// A^{-1} is not needed, but a singular A is reported as before (info = 2): A is factored, without right-hand sides.
+#pragma once
+#include "ttc_doubling.hpp"
+#include "ttc_tv.hpp"
+
+namespace ttc {
+
+// rows[rb][k] += the wavefront's rows of the matrix in the LDS half Wh
+template <int D>
+__device__ __forceinline__ void add_aop_lds(const float* Wh, float (&rows)[Cfg<D>::RB][Cfg<D>::KS], int w, int i, int g) {
+  using C = Cfg<D>;
+  float t[C::RB][C::KS];
+  load_aop_lds<D>(Wh, t, w, i, g);
+#pragma unroll
+  for (int rb = 0; rb < C::RB; ++rb)
+#pragma unroll
+    for (int k = 0; k < C::KS; ++k) rows[rb][k] += t[rb][k];
+}
+
+// One row block per wavefront at d = 128 (build.py: with two, 448 of the 512 registers hold matrices and the solves spill:
+// 31.9 against 4.5 ms for 2048 problems, T = 16), two at d = 64 (2.31 against 2.84 ms for 8192 problems, T = 16).
+// Measured against solve_kernel: d = 64, T = 64, 4099 problems 10.3 -> 2.2 ms; d = 128, T = 16, 8192 problems 25.5 -> 18.2 ms;
+// d = 128, T = 32, bfloat16 inputs, 4096 problems 21.3 -> 10.7 ms; errors against float64 5e-6..1.3e-5 -> 1e-6..2e-6.
+template <int D, typename TIn>
+__global__ void __launch_bounds__(Cfg<D>::NTHR, (D == 64 ? 2 : 1)) squaring_kernel(const DoublingArgs da) {
+  using C = Cfg<D>;
+  __shared__ __attribute__((aligned(16))) float W[D * C::PITCH];
+  __shared__ __attribute__((aligned(16))) SolveScratch<D> S;
+  __shared__ float s_red[C::NW];
+  __shared__ float s_max[C::NW];  // per wavefront: max |I + G H| of the solve being set up
+  const SolveArgs& p = da.s;
+  float* const WL = W;
+  float* const WR = W + D;
+  float* const wsP = p.ws + (long)blockIdx.x * D * D;  // P, rows in register layout
+
+  for (long long prob = blockIdx.x; prob < p.n; prob += gridDim.x) {
+    const int tid = threadIdx.x + opaque_zero(), lane = tid & 63, w = tid >> 6, i = lane & 15, g = lane >> 4;
+    const TIn* Ap = reinterpret_cast<const TIn*>(p.A) + prob * p.sA;
+    const TIn* Bp = reinterpret_cast<const TIn*>(p.B) + prob * p.sB;
+    const TIn* Qp = reinterpret_cast<const TIn*>(p.Q) + prob * p.sQ;
+    const TIn* Rp = reinterpret_cast<const TIn*>(p.R) + prob * p.sR;
+    const TIn* x0p = reinterpret_cast<const TIn*>(p.x0) + prob * p.sx0;
+    const TIn* QTp = da.p_from_qt ? reinterpret_cast<const TIn*>(p.QT) + prob * p.sQT : Qp;
+    int info = 0, nsolve = 0;
+    bool hard = false;
+    float rA[C::RB][C::KS], rG[C::RB][C::KS], rH[C::RB][C::KS], rX[C::RB][C::KS];
+    floatx4 acc[C::RB][C::NT];
+
+    // the wavefront's max |acc| for the guard; read by everyone after the next barrier
+    auto publish_max = [&] {
+      const float m = wave_absmax<D>(acc);
+      if (lane == 0) s_max[w] = m;
+    };
+    auto over_limit = [&] {  // uniform over the workgroup; also true for NaN
+      float m = s_max[0];
+      bool bad = !(m <= p.growth_limit);
+#pragma unroll
+      for (int ww = 1; ww < C::NW; ++ww) bad = bad || !(s_max[ww] <= p.growth_limit);
+      return bad;
+    };
+
+    // ---- set-up: X = R^{-1} B^T, G = B X, A (factored for its report), H = Q, P = Q_T when it is a matrix of its own
+    load_half<D, TIn, false>(WL, Rp, tid);
+    load_half<D, TIn, false>(WR, Bp, tid);
+    __syncthreads();
+    symmetrise_half<D>(WL, tid);
+    transpose_half<D>(WR, w, i, g);
+    ++nsolve;
+    if (lds_solve<D, 7, false>(W, S, tid) && !info) info = nsolve;  // R is positive definite: no pivot search
+    load_aop_lds<D>(WR, rX, w, i, g);
+    // G = B X into the left half, exactly symmetric (X in the right half)
+    auto form_G = [&] {
+      float c[C::RB][C::KS];
+      load_aop_global<D, TIn>(Bp, c, w, i, g);
+      zero_acc<D>(acc);
+      gemm_acc<D>(acc, c, WR, i, g);
+      store_rows<D>(WL, acc, w, i, g);
+      __syncthreads();
+      symmetrise_half<D>(WL, tid);
+      __syncthreads();
+    };
+    form_G();
+    load_aop_lds<D>(WL, rG, w, i, g);
+    __syncthreads();
+    load_half<D, TIn, false>(WL, Ap, tid);
+    load_half<D, TIn, false>(WR, Qp, tid);
+    __syncthreads();
+    load_aop_lds<D>(WL, rA, w, i, g);
+    symmetrise_half<D>(WR, tid);
+    __syncthreads();
+    load_aop_lds<D>(WR, rH, w, i, g);
+    ++nsolve;
+    if (lds_factor<D>(W, S, tid) && !info) info = nsolve;
+    bool have_p = da.p_from_qt != 0;
+    if (have_p) {
+      load_half<D, TIn, false>(WR, QTp, tid);
+      __syncthreads();
+      symmetrise_half<D>(WR, tid);
+      __syncthreads();
+      float c[C::RB][C::KS];
+      load_aop_lds<D>(WR, c, w, i, g);
+      store_aop_ws<D>(wsP, c, tid);
+      __syncthreads();
+    }
+
+    // [I + P G | P A] with P's rows in c, G and A as the halves hold them, then the solve: the right half becomes
+    // (I + P G)^{-1} P A
+    auto mobius = [&](const float(&c)[C::RB][C::KS]) {
+      eye_acc<D>(acc, w, i, g);
+      gemm_acc<D>(acc, c, WL, i, g);
+      publish_max();
+      __syncthreads();
+      if (over_limit()) return false;
+      store_rows<D>(WL, acc, w, i, g);
+      zero_acc<D>(acc);
+      gemm_acc<D>(acc, c, WR, i, g);
+      __syncthreads();
+      store_rows<D>(WR, acc, w, i, g);
+      __syncthreads();
+      ++nsolve;
+      if (lds_solve<D>(W, S, tid) && !info) info = nsolve;
+      return true;
+    };
+    // rows[rb][k] <- rH + A_e^T (the matrix in the right half), through the left half (rows may be rH itself)
+    auto apply_AT = [&](float (&rows)[C::RB][C::KS]) {
+      float c[C::RB][C::KS];
+      store_aop_lds<D>(WL, rA, w, i, g);
+      __syncthreads();
+      load_aopT_lds<D>(WL, c, w, i, g);
+      zero_acc<D>(acc);
+      gemm_acc<D>(acc, c, WR, i, g);
+      __syncthreads();
+      store_rows<D>(WL, acc, w, i, g);
+      __syncthreads();
+      load_aop_lds<D>(WL, c, w, i, g);
+#pragma unroll
+      for (int rb = 0; rb < C::RB; ++rb)
+#pragma unroll
+        for (int k = 0; k < C::KS; ++k) rows[rb][k] = rH[rb][k] + c[rb][k];
+      __syncthreads();
+    };
+
+    // ---- P_1 by binary powering of the one-step map (see ttc_doubling.hpp)
+    bool p_is_H = false;  // P_1 = H_e: the last bit met no P
+    for (int m = da.m; m && !hard;) {
+      if (m & 1) {
+        if (!have_p) {
+          have_p = true;
+          if (m == 1) p_is_H = true;  // f_e(0) = H_e, and e is not touched again
+          else store_aop_ws<D>(wsP, rH, tid);
+        } else {
+          float c[C::RB][C::KS];
+          load_aop_ws<D>(wsP, c, tid, opaque_zero());
+          store_aop_lds<D>(WL, rG, w, i, g);
+          store_aop_lds<D>(WR, rA, w, i, g);
+          __syncthreads();
+          if (!mobius(c)) {
+            hard = true;
+            break;
+          }
+          apply_AT(c);  // P <- H_e + A_e^T (I + P G_e)^{-1} P A_e
+          store_aop_ws<D>(wsP, c, tid);
+        }
+      }
+      m >>= 1;
+      if (!m) break;
+      // e <- e o e
+      store_aop_lds<D>(WR, rH, w, i, g);
+      __syncthreads();
+      eye_acc<D>(acc, w, i, g);
+      gemm_acc<D>(acc, rG, WR, i, g);  // I + G H
+      publish_max();
+      store_rows<D>(WL, acc, w, i, g);
+      __syncthreads();
+      if (over_limit()) {
+        hard = true;
+        break;
+      }
+      const bool only_H = m == 1 && !have_p;  // the last squaring, and P is still 0: A and G of the square are not needed
+      if (only_H) store_aop_lds<D>(WR, rA, w, i, g);
+      else set_half_identity<D>(WR, tid);
+      __syncthreads();
+      ++nsolve;
+      if (lds_solve<D>(W, S, tid) && !info) info = nsolve;  // right half: M = (I + G H)^{-1}, or M A
+      if (only_H) {
+        zero_acc<D>(acc);
+        gemm_acc<D>(acc, rH, WR, i, g);  // V = H M A
+        __syncthreads();
+        store_rows<D>(WR, acc, w, i, g);
+        apply_AT(rH);  // H' = H + A^T V
+      } else {
+        float rM[C::RB][C::KS];
+        load_aop_lds<D>(WR, rM, w, i, g);
+        store_aop_lds<D>(WL, rA, w, i, g);
+        __syncthreads();
+        zero_acc<D>(acc);
+        gemm_acc<D>(acc, rM, WL, i, g);  // M A
+        {
+          float rAT[C::RB][C::KS];
+          load_aopT_lds<D>(WL, rAT, w, i, g);
+          __syncthreads();
+          store_rows<D>(WL, acc, w, i, g);
+          __syncthreads();
+          zero_acc<D>(acc);
+          gemm_acc<D>(acc, rH, WL, i, g);  // V = H M A
+          store_rows<D>(WR, acc, w, i, g);
+          __syncthreads();
+          zero_acc<D>(acc);
+          gemm_acc<D>(acc, rAT, WR, i, g);  // A^T V
+        }
+        __syncthreads();
+        store_rows<D>(WR, acc, w, i, g);
+        __syncthreads();
+        add_aop_lds<D>(WR, rH, w, i, g);  // H' = H + A^T V
+        __syncthreads();
+        store_aop_lds<D>(WR, rG, w, i, g);
+        floatx4 accA[C::RB][C::NT];
+        zero_acc<D>(accA);
+        gemm_acc<D>(accA, rA, WL, i, g);  // A' = A M A
+        __syncthreads();
+        zero_acc<D>(acc);
+        gemm_acc<D>(acc, rA, WR, i, g);  // A G
+        __syncthreads();
+        store_rows_T<D>(WR, acc, w, i, g);  // G A^T
+        __syncthreads();
+        zero_acc<D>(acc);
+        gemm_acc<D>(acc, rM, WR, i, g);  // M G A^T
+        store_rows<D>(WL, acc, w, i, g);
+        __syncthreads();
+        zero_acc<D>(acc);
+        gemm_acc<D>(acc, rA, WL, i, g);  // A M G A^T
+        store_rows<D>(WR, acc, w, i, g);  // (every wavefront is past its reads of G A^T)
+        __syncthreads();
+        store_rows<D>(WL, accA, w, i, g);
+        __syncthreads();
+        load_aop_lds<D>(WL, rA, w, i, g);
+        add_aop_lds<D>(WR, rG, w, i, g);  // G' = G + A M G A^T
+        __syncthreads();
+      }
+    }
+
+    // ---- last step with the problem's own (A, G): M_1 = (I + P_1 G)^{-1} P_1 A, P_0 = A^T M_1, -K_0 = X M_1
+    if (!hard) {
+      float c[C::RB][C::KS];
+      if (p_is_H) {
+#pragma unroll
+        for (int rb = 0; rb < C::RB; ++rb)
+#pragma unroll
+          for (int k = 0; k < C::KS; ++k) c[rb][k] = rH[rb][k];
+      } else {
+        load_aop_ws<D>(wsP, c, tid, opaque_zero());
+      }
+      store_aop_lds<D>(WR, rX, w, i, g);
+      __syncthreads();
+      form_G();
+      load_half<D, TIn, false>(WR, Ap, tid);
+      __syncthreads();
+      hard = !mobius(c);
+    }
+    if (hard) {
+      __syncthreads();  // every wavefront has left the pair
+      if (info) {       // a set-up breakdown keeps its report
+        zero_acc<D>(acc);
+        emit_gain<D, TIn>(p, prob, acc, x0p, info, tid);
+        emit_value<D, TIn>(p, prob, WL, Qp, x0p, info, s_red, tid);
+      } else {
+        riccati_problem<D, TIn>(W, S, s_red, p, prob, p.T, Ap, Bp, Qp, Rp, 0, 0, 0, 0, QTp, nullptr, Qp, x0p, 2,
+                                tid + opaque_zero());
+      }
+      continue;
+    }
+    zero_acc<D>(acc);
+    gemm_acc<D>(acc, rX, WR, i, g);  // rows of -K_0
+    emit_gain<D, TIn>(p, prob, acc, x0p, info, tid);
+    {
+      float c[C::RB][C::KS];
+      load_half<D, TIn, false>(WL, Ap, tid);
+      __syncthreads();
+      load_aopT_lds<D>(WL, c, w, i, g);
+      zero_acc<D>(acc);
+      gemm_acc<D>(acc, c, WR, i, g);
+      __syncthreads();
+      store_rows<D>(WL, acc, w, i, g);
+      __syncthreads();
+      symmetrise_half<D>(WL, tid);
+      __syncthreads();
+    }
+    emit_value<D, TIn>(p, prob, WL, Qp, x0p, info, s_red, tid);
+  }
+}
+
+}  // namespace ttc

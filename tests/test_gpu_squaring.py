@@ -1,0 +1,131 @@
+"""Default path at d >= 32 where the equal factors are composed by squaring on chip: horizons around the rule's edges
+(powers of two, all bits set, a terminal cost of its own), each state size, batches below and above one grid, the guard's
+way out to the Riccati recursion, breakdown reports, and the rule itself."""
+import numpy as np
+import pytest
+import torch
+
+import bench
+from paper_2603_09221_amd import binding, synth
+from tests.parity import SOLVE_KEYS, oracle_solve, solve_errors
+
+DEV = "cuda:0"
+
+
+def solve(b, QT=None, **kw):
+    out = binding.ttc_lqr_solve(b.A, b.B, b.Q, b.R, QT, b.x0, b.T, **kw)
+    torch.cuda.synchronize()
+    return out
+
+
+def test_the_rule_takes_long_horizons_and_leaves_short_ones():
+    """Float32: every horizon from 12 on and T = 8; never below 8, where the sequential
+    product is cheaper; never at d = 16, which has its own kernel."""
+    for d in (32, 64, 128):
+        for bf16 in (False, True):
+            assert not any(bench.default_squares(d, T, bf16) for T in range(1, 8))
+            assert all(bench.default_squares(d, T, bf16) for T in range(16, 300))
+        assert bench.default_squares(d, 8, False) and not bench.default_squares(d, 9, False)
+    assert not any(bench.default_squares(16, T, False) for T in range(1, 100))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,n", [(32, 5), (32, 2100), (64, 9), (64, 1100), (128, 3), (128, 270)])
+@pytest.mark.parametrize("T", [8, 12, 15, 16, 31])
+def test_against_the_oracle(d, n, T):
+    """1e-4 is the path's tolerance; on ordinary problems the composition keeps 2e-5 per problem (measured 1e-6..5e-6)."""
+    b = synth.make_batch(n, d, d, T, seed=d + T, device=DEV)
+    out = solve(b)
+    assert int(out["info"].abs().max()) == 0
+    for k, v in solve_errors(out, oracle_solve(b)).items():
+        assert v <= 2e-5, (k, v)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("T", [16, 17, 33])
+def test_terminal_cost_stage_flag_shared_and_bf16(d, T):
+    b = synth.make_batch(11, d, d, T, seed=T, device=DEV)
+    QT = (1.5 * b.Q + 0.2 * torch.eye(d, device=DEV)).contiguous()
+    for qt, flag in ((QT, False), (QT, True), (None, True)):
+        out = solve(b, QT=qt, flags=binding.TTC_FLAG_STAGE_COST_AT_X0 if flag else 0)
+        for k, v in solve_errors(out, oracle_solve(b, QT=qt, flag=flag)).items():
+            assert v <= 2e-5, (k, v)
+    same = solve(b, QT=b.Q)  # Q_T given as the very same array is Q_T = Q
+    ref = solve(b)
+    for k in SOLVE_KEYS:
+        assert torch.equal(same[k], ref[k]), k
+    shared = synth.LqrBatch(b.A[:1].expand(11, -1, -1), b.B, b.Q[:1].expand(11, -1, -1), b.R, b.x0, T)
+    full = synth.LqrBatch(shared.A.contiguous(), b.B, shared.Q.contiguous(), b.R, b.x0, T)
+    got, want = solve(shared), solve(full)
+    for k in SOLVE_KEYS:
+        assert torch.equal(got[k], want[k]), k
+    h = synth.make_batch(7, d, d, T, seed=T + 1, device=DEV, dtype="bf16")
+    for k, v in solve_errors(solve(h), oracle_solve(h)).items():  # the oracle consumes the rounded values
+        assert v <= 2e-5, (k, v)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,n", [(32, 40), (64, 30), (128, 9)])
+def test_cheap_control_takes_the_riccati_recursion_and_growth_stays_accurate(d, n):
+    """Cost ratios of 1e2 and more make I + G H large: such problems leave for the printed recursion (mixed here with
+    ordinary ones); an unstable open loop with costly control grows it later.  1e-4 as in the guard's own sweep; at a ratio
+    of 1e4 four times what the recursion itself (ttc_lqr_solve_tv on repeated matrices) shows."""
+    T = 16
+    for qs, rs, rho in ((1.0, 1e-2, None), (1e2, 1.0, None), (1e-2, 1e2, 1.2), (1.0, 1.0, 1.2), (1e2, 1e-2, None)):
+        b = synth.make_batch(n, d, d, T, seed=d, device=DEV, q_scale=qs, r_scale=rs, rho=rho)
+        easy = synth.make_batch(n, d, d, T, seed=d, device=DEV)
+        pick = (torch.arange(n, device=DEV) % 3 == 1)[:, None, None]
+        mix = synth.LqrBatch(torch.where(pick, b.A, easy.A), easy.B, torch.where(pick, b.Q, easy.Q),
+                             torch.where(pick, b.R, easy.R), easy.x0, T)
+        for batch in (b, mix):
+            out = solve(batch)
+            assert int(out["info"].abs().max()) == 0
+            ref = oracle_solve(batch)
+            tol = 1e-4
+            if qs / rs > 1e3:
+                rep = lambda t: t.unsqueeze(1).expand(-1, T, -1, -1)
+                tv = binding.ttc_lqr_solve_tv(rep(batch.A), rep(batch.B), rep(batch.Q), rep(batch.R), batch.x0)
+                tol = max(tol, 4 * max(solve_errors(tv, ref).values()))
+            for k, v in solve_errors(out, ref).items():
+                assert v <= tol, (qs, rs, rho, k, v)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_breakdowns_are_reported_as_on_the_sequential_path(d):
+    """R not positive definite: info = 1; a singular A: info = 2, although composing needs no inverse of A; both NaN, also
+    when the problem would have left for the Riccati recursion; the others are what they are alone."""
+    n, T = 12, 16
+    b = synth.make_batch(n, d, d, T, seed=4, device=DEV)
+    A, R, Q = b.A.clone(), b.R.clone(), b.Q.clone()
+    R[3] = -R[3]
+    A[5] = 0.0
+    A[7] = 0.0
+    R[7] *= 1e-2  # cheap control beside a singular A
+    Q[9] *= 1e2   # cheap control alone
+    out = solve(synth.LqrBatch(A, b.B, Q, R, b.x0, T))
+    info = out["info"].cpu().numpy()
+    assert info[3] == 1 and info[5] == 2 and info[7] == 2 and (np.delete(info, [3, 5, 7]) == 0).all()
+    for k in SOLVE_KEYS:
+        bad = torch.isnan(out[k].reshape(n, -1)).all(1).cpu().numpy()
+        assert bad[[3, 5, 7]].all() and not np.delete(bad, [3, 5, 7]).any(), k
+    seq = solve(synth.LqrBatch(A, b.B, Q, R, b.x0, T), rebase_every=3)
+    assert (seq["info"].cpu().numpy() == info).all()
+    keep = torch.tensor([0, 1, 2, 4, 6, 8, 10, 11], device=DEV)
+    alone = solve(synth.LqrBatch(A, b.B, Q, R, b.x0, T).take(keep))
+    for k in SOLVE_KEYS:
+        assert torch.equal(out[k][keep], alone[k]), k
+
+
+@pytest.mark.gpu
+def test_noalloc_takes_the_same_path():
+    for d, T, n in ((64, 16, 1030), (128, 32, 260)):
+        b = synth.make_batch(n, d, d, T, seed=6, device=DEV)
+        f32 = dict(dtype=torch.float32, device=DEV)
+        out = {"P0": torch.empty((n, d, d), **f32), "K0": torch.empty((n, d, d), **f32), "u0": torch.empty((n, d), **f32),
+               "value": torch.empty((n,), **f32), "info": torch.empty((n,), dtype=torch.int32, device=DEV)}
+        binding.ttc_lqr_solve_noalloc(b.A, b.B, b.Q, b.R, None, b.x0, T, out)
+        ref = solve(b)
+        for k in SOLVE_KEYS:
+            assert torch.equal(out[k], ref[k]), k
