@@ -38,14 +38,16 @@ UNITS = [("ttc_api.hip", None),
          ("k_cxt_bwd.hip", None),
          ("k_block.hip", None)]
 
-# Per (source, state size) compile flags: wavefronts of one 16-row block each (twice as many per problem) instead of
-# two row blocks, where measured faster.  The dense solve inside these kernels is a third or more of their time and
-# all but one wavefront share its tiles; the default forward kernel is faster with fewer, fatter wavefronts (its
-# constant operands stay in registers; at d = 64 four problems fit a compute unit).  Measured, problems/s:
-# backward d = 64, T = 8: 1.99M against 1.79M; time-heterogeneous d = 128, T = 16: 179k against 170k; squaring path
-# d = 128, T = 16: 501k against 488k (T = 32, bf16 inputs: 421k against 404k).
+# Per (source, state size) compile flags: wavefronts of one 16-wide block each (twice as many per problem) instead of
+# two, where measured faster.  The Riccati kernels own matrices by columns: at d = 64 one column tile a wavefront leaves
+# room for three workgroups a compute unit.  The default forward kernel is faster with fewer, fatter wavefronts (its
+# constant operands stay in registers; at d = 64 four problems fit a compute unit).  Measured with one block against two:
+# squaring path d = 128, T = 16 4.5 ms against 31.9 for one
+# batch (two blocks spill, as they do in the time-heterogeneous kernel); flagged doubling d = 128, T = 16 501k problems/s
+# against 488k.
 _ONE_ROW_BLOCK = "-DTTC_ROW_BLOCKS(D)=((D)==%d?1:((D)>=32?2:1))"
 UNIT_FLAGS = {("k_backward.hip", 64): [_ONE_ROW_BLOCK % 64],
+              ("k_tv.hip", 64): [_ONE_ROW_BLOCK % 64],
               ("k_tv.hip", 128): [_ONE_ROW_BLOCK % 128],
               ("k_doubling.hip", 128): [_ONE_ROW_BLOCK % 128],
               ("k_squaring.hip", 128): [_ONE_ROW_BLOCK % 128]}

@@ -93,13 +93,12 @@ __device__ __forceinline__ void outer2_global(float* out, const float* a, const 
 }
 
 template <int D, typename TIn>
-__global__ void __launch_bounds__(Cfg<D>::NTHR) backward_kernel(const BackwardArgs ba) {
+__global__ void __launch_bounds__(Cfg<D>::NTHR, TTC_COLS_WAVES(D)) backward_kernel(const BackwardArgs ba) {
   using C = Cfg<D>;
   constexpr int TPR = C::NTHR / D;
   __shared__ __attribute__((aligned(16))) float W[D * C::PITCH];
-  __shared__ __attribute__((aligned(16))) SolveScratch<D> S;
   __shared__ float s_red[2 * TPR * D];
-  __shared__ float s_v[8][D];  // working vectors
+  __shared__ __attribute__((aligned(16))) float s_v[8][D];  // working vectors
   const RolloutArgs& p = ba.r;
   float* const WL = W;
   float* const WR = W + D;
@@ -133,21 +132,11 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR) backward_kernel(const BackwardAr
     symmetrise_half<D>(WR, tid);
     __syncthreads();
     for (int s = T - 1; s >= 1; --s) {
-      floatx4 pn[C::RB][C::NT];
-      const int flag = riccati_step<D, TIn>(W, S, Ap + (long long)s * ba.tA, Bp + (long long)s * ba.tB,
-                                            Rp + (long long)s * ba.tR, pn, tid);
+      Cols<D> wk, pn;
+      const int flag = riccati_step<D, TIn>(W, Ap + (long long)s * ba.tA, Bp + (long long)s * ba.tB,
+                                            Rp + (long long)s * ba.tR, wk, pn, tid);
       if (flag && !info) info = T - s;
-      {
-        floatx4 acc[C::RB][C::NT];
-        load_rows<D>(WR, acc, w, i, g);
-#pragma unroll
-        for (int rb = 0; rb < C::RB; ++rb) {
-#pragma unroll
-          for (int cc = 0; cc < C::NT; ++cc) acc[rb][cc] = -acc[rb][cc];
-          write_rows_global<D>(wsK + (long)(s - 1) * D * D, acc[rb], C::RB * w + rb, i, g);  // K_s
-        }
-      }
-      __syncthreads();
+      store_cols<D, -1>(wsK + (long)(s - 1) * D * D, D, wk, w, i, g);  // K_s
       next_value_matrix<D, TIn>(W, stage_cost(s - 1), pn, tid);
     }
 
@@ -186,43 +175,37 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR) backward_kernel(const BackwardAr
     }
     __syncthreads();
     {
-      float cP[C::RB][C::KS], cBT[C::RB][C::KS];
-      floatx4 acc[C::RB][C::NT];
-      load_aop_lds<D>(WR, cP, w, i, g);  // rows of P_1
-      load_half<D, TIn, false>(WL, Bp, tid);
+      // S_0 by columns as in riccati_step; the right-hand sides are columns 0 and 1 of one column tile
+      Cols<D> s0, b, pb;
+      floatx4 f[C::NT][1];
+      load_cols<D, TIn>(Bp, b, w, i, g);
+      store_cols_T<D>(WL, b, w, i, g);  // B_0^T
+      zero_cols<D>(s0);
+      add_sym_cols<D, TIn>(Rp, s0, w, i, g);
       __syncthreads();
-      zero_acc<D>(acc);
-      gemm_acc<D>(acc, cP, WL, i, g);  // P_1 B_0
-      load_aopT_lds<D>(WL, cBT, w, i, g);  // rows of B_0^T
+      zero_cols<D>(pb);
+      gemm_cols<D>(pb, WR, b, i, g);   // P_1 B_0
+      gemm_cols<D>(s0, WL, pb, i, g);  // S_0 = R_0 + B_0^T P_1 B_0
       float fx, dummy;
-      matvecT2<D>(lds1(WL), v_z, v_xt, s_red, tid, fx, dummy);  // B_0^T P_1 A_0 x_0 (contains barriers)
-      store_rows<D>(WR, acc, w, i, g);  // right half: P_1 B_0 (every wavefront holds its rows of P_1)
-      __syncthreads();
-      load_rows_input<D, TIn>(Rp, acc, w, i, g);
-      gemm_acc<D>(acc, cBT, WR, i, g);  // S_0 = R_0 + B_0^T P_1 B_0
-      __syncthreads();
-      store_rows<D>(WL, acc, w, i, g);
-      // right-hand sides: column 0 = F x_0, column 1 = g, the other columns zero
-      for (int idx = tid; idx < D * D / 4; idx += C::NTHR) {
-        const int r = idx / (D / 4), c4 = (idx % (D / 4)) * 4;
-        *reinterpret_cast<floatx4*>(WR + r * C::PITCH + c4) = floatx4{0.f, 0.f, 0.f, 0.f};
+      matvec2<D>(lds4(WL), v_z, v_xt, tid, fx, dummy);  // B_0^T P_1 A_0 x_0
+      if (lead) {
+        v_u[row] = -fx;
+        v_ut[row] = -gp[row];
       }
       __syncthreads();
-      if (tid < D) {
-        WR[tid * C::PITCH + 0] = fx;
-        WR[tid * C::PITCH + 1] = gp[tid];
+      zero_cols<D>(f);
+      if (w == 0 && i < 2) {
+#pragma unroll
+        for (int r = 0; r < C::NT; ++r) f[r][0] = *reinterpret_cast<const floatx4*>((i ? v_ut : v_u) + 16 * r + 4 * g);
       }
-      __syncthreads();
-    }
-    symmetrise_half<D>(WL, tid);  // R is read as its symmetric part
-    __syncthreads();
-    {
-      const int flag = lds_solve<D, 7, false>(W, S, tid);
+      const int flag = spd_solve_cols<D, 1>(WR, s0, f, w, lane);
       if (flag && !info) info = T;
+      if (w == 0 && i < 2) {
+#pragma unroll
+        for (int r = 0; r < C::NT; ++r) *reinterpret_cast<floatx4*>((i ? v_ut : v_u) + 16 * r + 4 * g) = f[r][0];
+      }
     }
     if (tid < D) {
-      v_u[tid] = -WR[tid * C::PITCH + 0];
-      v_ut[tid] = -WR[tid * C::PITCH + 1];
       tX[tid] = v_x[tid];
       tXt[tid] = 0.f;
     }

@@ -1,0 +1,281 @@
+// One backward step of the Riccati recursion with every matrix held by columns, and the dense solve that goes with it.
+//
+// The accumulator layout of a 16 x 16 tile (lane 16 g + i holds M[4g + v][i], v = 0..3) is at once its B operand when the
+// contraction index is visited as k = 4 g + t.  A wavefront that owns whole columns of a product therefore holds, without
+// a move, the right operand of the next one: P A, then B^T (P A) and A^T (P A), then S^{-1} (B^T P A) run from register to
+// register, and LDS holds left operands only, each read 16 bytes a lane for 4 RB matrix instructions.  (Owning rows
+// instead, every product passes through LDS and every wavefront reads every right operand.)
+//
+// Measured against steps with matrices by rows and the panel-wise lds_solve, T = 8, float32: ttc_lqr_solve_tv d = 64, 4096
+// problems 1.84 -> 1.29 ms (six products and the solve at 98 TFLOP/s of the 152 the matrix cores reach in float32), d = 32,
+// 8192 problems 0.59 -> 0.44 ms, d = 128, 1024 problems 2.99 -> 2.54 ms; ttc_lqr_backward d = 64, 8192 problems 4.15 -> 2.94
+// ms.  What is left is the inverse's serial chain, hidden as far as three workgroups a compute unit allow.
+#pragma once
+#include "ttc_common.hpp"
+#include "ttc_small.hpp"
+
+namespace ttc {
+
+// Workgroup barrier that orders LDS accesses only: global loads stay in flight across it.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Wavefronts per SIMD that the registers of a kernel built on these steps are kept small enough for: with one column tile
+// a wavefront at d = 64 three workgroups fit a compute unit (four spill), as do three wavefronts a SIMD at d <= 32.
+#ifndef TTC_COLS_WAVES
+#define TTC_COLS_WAVES(D) ((D) == 64 && Cfg<D>::RB == 1 ? 3 : (D) <= 32 ? 3 : 1)
+#endif
+
+// A d x d matrix by columns: wavefront w owns the column tiles RB w + k, tile (r, k) of it is m[r][k].
+template <int D, int CT = Cfg<D>::RB>
+using Cols = floatx4[Cfg<D>::NT][CT];
+
+template <int D, int CT>
+__device__ __forceinline__ void zero_cols(floatx4 (&m)[D / 16][CT]) {
+#pragma unroll
+  for (int r = 0; r < D / 16; ++r)
+#pragma unroll
+    for (int k = 0; k < CT; ++k) m[r][k] = floatx4{0.f, 0.f, 0.f, 0.f};
+}
+// from a row-major matrix in memory: a row of 16 lanes reads 16 consecutive elements
+template <int D, typename TIn>
+__device__ __forceinline__ void load_cols(const TIn* M, Cols<D>& m, int w, int i, int g) {
+  const unsigned o = (unsigned)(4 * g * D + 16 * Cfg<D>::RB * w + i);
+#pragma unroll
+  for (int r = 0; r < D / 16; ++r)
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+      for (int k = 0; k < Cfg<D>::RB; ++k) m[r][k][v] = ld1<TIn>(M, o + (unsigned)((16 * r + v) * D + 16 * k));
+}
+// m += the symmetric part of such a matrix (the transposed entries of a lane are four consecutive elements)
+template <int D, typename TIn>
+__device__ __forceinline__ void add_sym_cols(const TIn* M, Cols<D>& m, int w, int i, int g) {
+  Cols<D> t;
+  load_cols<D, TIn>(M, t, w, i, g);
+  const unsigned o = (unsigned)((16 * Cfg<D>::RB * w + i) * D + 4 * g);
+#pragma unroll
+  for (int r = 0; r < D / 16; ++r)
+#pragma unroll
+    for (int k = 0; k < Cfg<D>::RB; ++k) m[r][k] += 0.5f * (t[r][k] + ld4<TIn>(M, o + (unsigned)(16 * k * D + 16 * r)));
+}
+// the transpose (times SIGN) to LDS, row-major: a lane's four values are 16 bytes of one row
+template <int D, int SIGN = 1>
+__device__ __forceinline__ void store_cols_T(float* L, const Cols<D>& m, int w, int i, int g) {
+  float* const o = L + (16 * Cfg<D>::RB * w + i) * Cfg<D>::PITCH + 4 * g;
+#pragma unroll
+  for (int k = 0; k < Cfg<D>::RB; ++k)
+#pragma unroll
+    for (int r = 0; r < D / 16; ++r)
+      *reinterpret_cast<floatx4*>(o + 16 * k * Cfg<D>::PITCH + 16 * r) = SIGN > 0 ? m[r][k] : -m[r][k];
+}
+// the matrix itself to LDS (row pitch PITCH) or to memory (row pitch D), row-major
+template <int D, int SIGN = 1>
+__device__ __forceinline__ void store_cols(float* L, int pitch, const Cols<D>& m, int w, int i, int g) {
+  float* const o = L + 4 * g * pitch + 16 * Cfg<D>::RB * w + i;
+#pragma unroll
+  for (int r = 0; r < D / 16; ++r)
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+      for (int k = 0; k < Cfg<D>::RB; ++k) o[(16 * r + v) * pitch + 16 * k] = SIGN > 0 ? m[r][k][v] : -m[r][k][v];
+}
+
+// acc += L R: L row-major in LDS, R by columns.  The left operand of the next four k-steps is read while the current ones
+// run; scheduling barriers keep the compiler from hoisting more reads than that.
+template <int D, int CT>
+__device__ __forceinline__ void gemm_cols(floatx4 (&acc)[D / 16][CT], const float* L, const floatx4 (&b)[D / 16][CT], int i,
+                                          int g) {
+  using C = Cfg<D>;
+  constexpr int NT = C::NT;
+  // rows of one base register (an LDS instruction carries a 16-bit byte offset)
+  constexpr int RSEG = 65000 / (16 * C::PITCH * 4) > 0 ? 65000 / (16 * C::PITCH * 4) : 1;
+  const float* const base = L + i * C::PITCH + 4 * g;
+  const float* seg[(NT - 1) / RSEG + 1];
+  seg[0] = base;
+#pragma unroll
+  for (int s = 1; s <= (NT - 1) / RSEG; ++s) seg[s] = base + opaque_int(16 * s * RSEG * C::PITCH);
+  floatx4 a[2];
+  a[0] = *reinterpret_cast<const floatx4*>(base);
+  static_for<0, NT * NT>([&](auto X) {
+    constexpr int x = decltype(X)::value, r = x / NT, q = x % NT, cur = x & 1;
+    if constexpr (x + 1 < NT * NT) {
+      constexpr int r1 = (x + 1) / NT, q1 = (x + 1) % NT;
+      a[cur ^ 1] = *reinterpret_cast<const floatx4*>(seg[r1 / RSEG] + 16 * (r1 % RSEG) * C::PITCH + 16 * q1);
+      TTC_SCHED_BARRIER();
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int k = 0; k < CT; ++k)
+        acc[r][k] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[cur][t], b[q][k][t], acc[r][k], 0, 0, 0);
+    TTC_SCHED_BARRIER();
+  });
+}
+
+// Dense solve f <- s^{-1} f for a symmetric positive definite s, both by columns (f: FT column tiles a wavefront, also none):
+// block Gauss-Jordan with 16 x 16 pivot blocks and no pivot search.  Per block p, the wavefront that owns its columns
+// inverts s[p][p] in registers and publishes that inverse and the rest of the column, negated, as left operands (Wp: the
+// right half of the pair); every wavefront then does its own columns, U = s[p][p]^{-1} s[p][c], s[r][c] -= s[r][p] U,
+// the next block's first, so that its inverse is formed and published under the others' updates: one workgroup barrier
+// per block, no right operand through LDS, and a serial chain of some 1500 cycles per 16 columns (the pivoted panels of
+// lds_solve: about 5000).
+// With d <= 32 the explicit inverse alone loses up to a factor of three where control is cheap (the block is most of the
+// matrix); there one step of refinement, U += s[p][p]^{-1} (s[p][c] - s[p][p] U), restores a factor-and-solve's accuracy;
+// from d = 64 on it makes no difference (measured against float64, cost ratios 1 to 1e4).
+// Returns, uniformly, whether a pivot was not positive and finite.  Wp must be free to every wavefront on entry; its last
+// reads may still be under way in other wavefronts on return.
+template <int D, int FT>
+__device__ __forceinline__ int spd_solve_cols(float* Wp, Cols<D>& s, floatx4 (&f)[D / 16][FT > 0 ? FT : 1], int w, int lane) {
+  using C = Cfg<D>;
+  constexpr int NT = C::NT, CT = C::RB;
+  constexpr bool REFINE = C::NW == 1;  // d <= 32: one wavefront, which holds the pivot block's operands itself
+  const int i = lane & 15, g = lane >> 4;
+  w = uniform(w);
+  int bad = 0;
+  floatx4 di_own, d_own;  // REFINE: the A operands of the inverse and of minus the block
+  auto publish = [&](auto P) {  // by the wavefront that owns column tile p
+    constexpr int p = decltype(P)::value, k = p % CT;
+    floatx4 inv = s[p][k];
+    if constexpr (REFINE) d_own = -s[p][k];
+    bad |= invert_spread16(inv, lane);
+    if constexpr (REFINE) di_own = inv;
+    float* const o = Wp + 4 * g * C::PITCH + 16 * (p & 1) + i;
+#pragma unroll
+    for (int r = 0; r < NT; ++r) {
+      const floatx4 x = r == p ? inv : -s[r][k];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) o[(16 * r + v) * C::PITCH] = x[v];
+    }
+  };
+  auto column = [&](auto P, const floatx4 (&x)[NT], auto& m, auto K) {
+    constexpr int p = decltype(P)::value, k = decltype(K)::value;
+    floatx4 u = floatx4{0.f, 0.f, 0.f, 0.f};
+    if constexpr (REFINE) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) u = __builtin_amdgcn_mfma_f32_16x16x4f32(di_own[t], m[p][k][t], u, 0, 0, 0);
+      floatx4 res = m[p][k];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) res = __builtin_amdgcn_mfma_f32_16x16x4f32(d_own[t], u[t], res, 0, 0, 0);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) u = __builtin_amdgcn_mfma_f32_16x16x4f32(di_own[t], res[t], u, 0, 0, 0);
+    } else {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) u = __builtin_amdgcn_mfma_f32_16x16x4f32(x[p][t], m[p][k][t], u, 0, 0, 0);
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int r = 0; r < NT; ++r)
+        if (r != p) m[r][k] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[r][t], u[t], m[r][k], 0, 0, 0);
+    m[p][k] = u;
+  };
+  if (w == 0) publish(IntC<0>{});
+  static_for<0, NT>([&](auto P) {
+    constexpr int p = decltype(P)::value;
+    lds_barrier();  // block p is published; block p - 1 (the other buffer) was read before
+    floatx4 x[NT];
+#pragma unroll
+    for (int r = 0; r < NT; ++r) x[r] = *reinterpret_cast<const floatx4*>(Wp + (16 * r + i) * C::PITCH + 16 * (p & 1) + 4 * g);
+    auto rest = [&](auto SKIP) {
+      static_for<0, CT>([&](auto K) {
+        constexpr int k = decltype(K)::value;
+        if constexpr (k != decltype(SKIP)::value)
+          if (CT * w + k > p) column(P, x, s, K);
+      });
+      if constexpr (FT > 0) static_for<0, FT>([&](auto K) { column(P, x, f, K); });
+    };
+    if constexpr (p + 1 < NT) {
+      constexpr int kn = (p + 1) % CT;
+      if (w == (p + 1) / CT) {
+        column(P, x, s, IntC<kn>{});
+        if constexpr (REFINE) {  // the others still need this block's operands
+          rest(IntC<kn>{});
+          publish(IntC<p + 1>{});
+        } else {
+          publish(IntC<p + 1>{});
+          rest(IntC<kn>{});
+        }
+      } else {
+        rest(IntC<-1>{});
+      }
+    } else {
+      rest(IntC<-1>{});
+    }
+  });
+  // the wavefronts' flags meet in the skew columns of the pair, which nothing else uses
+  const int any = __any(bad) ? 1 : 0;
+  if constexpr (C::NW == 1) {
+    lds_barrier();
+    return any;
+  } else {
+    int* const flags = reinterpret_cast<int*>(Wp + D);
+    if (lane == 0) flags[w * C::PITCH] = any;
+    lds_barrier();
+    int all = 0;
+#pragma unroll
+    for (int ww = 0; ww < C::NW; ++ww) all |= flags[ww * C::PITCH];
+    return uniform(all);
+  }
+}
+
+// One backward step of Prop. 3.1 with the matrices of one step.  On entry the right half of the pair holds P_{s+1}
+// (symmetric, visible) and the left half is free; on exit, by columns, wk = S^{-1} B^T P A = -K_s, S = R + B^T P B, and
+// pn = A^T P A - (B^T P A)^T wk, which is P_s up to the stage cost.  Six products and one unpivoted solve (S is positive
+// definite).  Returns the solve's breakdown flag.  Other wavefronts may still be reading the left half on return.
+template <int D, typename TIn>
+__device__ __forceinline__ int riccati_step(float* W, const TIn* As, const TIn* Bs, const TIn* Rs, Cols<D>& wk, Cols<D>& pn,
+                                            int tid) {
+  using C = Cfg<D>;
+  tid += opaque_zero();
+  const int lane = tid & 63, w = uniform(tid >> 6), i = lane & 15, g = lane >> 4;
+  float* const WL = W;
+  float* const WR = W + D;
+  Cols<D> s, a;
+  {
+    Cols<D> b, pb;
+    load_cols<D, TIn>(Bs, b, w, i, g);
+    store_cols_T<D>(WL, b, w, i, g);  // B^T
+    load_cols<D, TIn>(As, a, w, i, g);
+    zero_cols<D>(s);
+    add_sym_cols<D, TIn>(Rs, s, w, i, g);  // R is read as its symmetric part
+    lds_barrier();
+    zero_cols<D>(pb);
+    gemm_cols<D>(pb, WR, b, i, g);  // P B
+    gemm_cols<D>(s, WL, pb, i, g);  // S = R + B^T P B
+  }
+  {
+    Cols<D> pa;
+    zero_cols<D>(pa);
+    gemm_cols<D>(pa, WR, a, i, g);  // P A
+    zero_cols<D>(wk);
+    gemm_cols<D>(wk, WL, pa, i, g);  // F = B^T P A
+    lds_barrier();                 // P and B^T are no longer read
+    store_cols_T<D>(WR, a, w, i, g);       // A^T
+    store_cols_T<D, -1>(WL, wk, w, i, g);  // -F^T
+    lds_barrier();
+    zero_cols<D>(pn);
+    gemm_cols<D>(pn, WR, pa, i, g);  // A^T P A
+  }
+  lds_barrier();
+  const int flag = spd_solve_cols<D, C::RB>(WR, s, wk, w, lane);  // W = S^{-1} F
+  gemm_cols<D>(pn, WL, wk, i, g);                                 // - F^T W
+  return flag;
+}
+
+// P_s = pn + the symmetric part of the stage cost Qs goes to the right half, exactly symmetric.  Contains the barriers it
+// needs.
+template <int D, typename TIn>
+__device__ __forceinline__ void next_value_matrix(float* W, const TIn* Qs, Cols<D>& pn, int tid) {
+  const int lane = tid & 63, w = uniform(tid >> 6), i = lane & 15, g = lane >> 4;
+  add_sym_cols<D, TIn>(Qs, pn, w, i, g);
+  store_cols_T<D>(W + D, pn, w, i, g);  // (the solve ended with a barrier: the right half is free)
+  lds_barrier();
+  symmetrise_half<D>(W + D, tid);
+  lds_barrier();
+}
+
+}  // namespace ttc

@@ -58,6 +58,10 @@ __device__ __forceinline__ int opaque_int(int x) {
   return x;
 }
 
+// A value that is the same in all lanes, as a scalar.  Branches on it become scalar branches; a branch on a lane value is
+// taken by masking lanes off, which matrix-core instructions do not heed.
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+
 template <int D>
 struct Cfg {
   static constexpr int RB = TTC_ROW_BLOCKS(D);  // 16-row blocks owned by one wavefront
@@ -889,7 +893,7 @@ __device__ __forceinline__ int lds_solve(float* W, SolveScratch<D>& S, int tid) 
   constexpr int NP = D / 16;
   constexpr int NRL = (D + 63) / 64;
   tid += opaque_zero();
-  const int lane = tid & 63, w = tid >> 6;
+  const int lane = tid & 63, w = uniform(tid >> 6);
   int atag[NRL];
 #pragma unroll
   for (int rr = 0; rr < NRL; ++rr) atag[rr] = (lane + 64 * rr) < D ? 127 - (lane + 64 * rr) : (int)0x80000000;
@@ -925,7 +929,7 @@ __device__ __forceinline__ int lds_solve(float* W, SolveScratch<D>& S, int tid) 
   }
   if (tid == 0) S.flag = bad;
   __syncthreads();
-  const int flag = S.flag;
+  const int flag = uniform(S.flag);
   __syncthreads();
   return flag;
 }

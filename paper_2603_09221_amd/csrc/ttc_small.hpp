@@ -131,7 +131,8 @@ __device__ __forceinline__ int invert_regs16(float (&a)[16]) {
     constexpr int j = decltype(J)::value;
     float(&x)[16] = a;  // (named here, as an asm operand alone does not capture)
     float &kept = mypiv, &piv = pv, &rec = rc;
-    const unsigned long long mine = 0x0001000100010001ull << j;  // the lanes of the pivot row
+    constexpr unsigned mine = 0x00010001u << j;  // the lanes of the pivot row, either half of the mask (set up in vcc inside
+                                                 // the block: as operands the masks are hoisted and spill scalar registers)
     // nl = the row's multiplier -a[j] / pivot (0 for the pivot row itself), then a[k] += nl * (a[k] of the pivot row, lane j
     // of this row of 16 lanes), k != j.  Written as one block so that the two wait states a DPP read needs after a vector
     // write of the same register are in our hands: the block starts with three instructions that write none of the
@@ -142,27 +143,29 @@ __device__ __forceinline__ int invert_regs16(float (&a)[16]) {
     if constexpr (j < 15) {
 #define TTC_AK(n) x[(n) == 0 ? j + 1 : ((n) <= j ? (n) - 1 : (n) + 1)]  // a[j + 1], then the other 14, in ascending order
       asm volatile(
-          "v_mul_f32 %[nl], %[rc], -%[aj]\n\tv_cndmask_b32 %[p], %[p], %[pv], %[m]\n\tv_cndmask_b32 %[nl], %[nl], 0, %[m]\n\t"
+          "s_mov_b32 vcc_lo, %[m]\n\ts_mov_b32 vcc_hi, %[m]\n\tv_mul_f32 %[nl], %[rc], -%[aj]\n\tv_cndmask_b32 %[p], %[p], %[pv], vcc\n\tv_cndmask_b32 %[nl], %[nl], 0, vcc\n\t"
           TTC_FMAC(0) TTC_FMAC(1) TTC_FMAC(2)
           "v_mov_b32_dpp %[pv], %0 row_newbcast:%[jn] row_mask:0xf bank_mask:0xf\n\t" TTC_FMAC(3) TTC_FMAC(4)
           "v_rcp_f32 %[rc], %[pv]\n\t" TTC_FMAC(5) TTC_FMAC(6) TTC_FMAC(7) TTC_FMAC(8) TTC_FMAC(9) TTC_FMAC(10) TTC_FMAC(11)
-              TTC_FMAC(12) TTC_FMAC(13) TTC_FMAC(14) "v_cndmask_b32 %[aj], %[nl], 1.0, %[m]"
+              TTC_FMAC(12) TTC_FMAC(13) TTC_FMAC(14) "v_cndmask_b32 %[aj], %[nl], 1.0, vcc"
           : "+v"(TTC_AK(0)), "+v"(TTC_AK(1)), "+v"(TTC_AK(2)), "+v"(TTC_AK(3)), "+v"(TTC_AK(4)), "+v"(TTC_AK(5)),
             "+v"(TTC_AK(6)), "+v"(TTC_AK(7)), "+v"(TTC_AK(8)), "+v"(TTC_AK(9)), "+v"(TTC_AK(10)), "+v"(TTC_AK(11)),
             "+v"(TTC_AK(12)), "+v"(TTC_AK(13)), "+v"(TTC_AK(14)), [aj] "+v"(x[j]), [p] "+v"(kept), [pv] "+v"(piv),
             [rc] "+v"(rec), [nl] "=&v"(nl)
-          : [m] "s"(mine), [j] "n"(j), [jn] "n"(j + 1));
+          : [m] "n"(mine), [j] "n"(j), [jn] "n"(j + 1)
+          : "vcc");
 #undef TTC_AK
     } else {
       asm volatile(
-          "v_mul_f32 %[nl], %[rc], -%[aj]\n\tv_cndmask_b32 %[p], %[p], %[pv], %[m]\n\tv_cndmask_b32 %[nl], %[nl], 0, %[m]\n\t"
+          "s_mov_b32 vcc_lo, %[m]\n\ts_mov_b32 vcc_hi, %[m]\n\tv_mul_f32 %[nl], %[rc], -%[aj]\n\tv_cndmask_b32 %[p], %[p], %[pv], vcc\n\tv_cndmask_b32 %[nl], %[nl], 0, vcc\n\t"
           TTC_FMAC(0) TTC_FMAC(1) TTC_FMAC(2) TTC_FMAC(3) TTC_FMAC(4) TTC_FMAC(5) TTC_FMAC(6) TTC_FMAC(7) TTC_FMAC(8)
               TTC_FMAC(9) TTC_FMAC(10) TTC_FMAC(11) TTC_FMAC(12) TTC_FMAC(13) TTC_FMAC(14)
-          "v_cndmask_b32 %[aj], %[nl], 1.0, %[m]\n\ts_nop 1"
+          "v_cndmask_b32 %[aj], %[nl], 1.0, vcc\n\ts_nop 1"
           : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(x[4]), "+v"(x[5]), "+v"(x[6]), "+v"(x[7]), "+v"(x[8]),
             "+v"(x[9]), "+v"(x[10]), "+v"(x[11]), "+v"(x[12]), "+v"(x[13]), "+v"(x[14]), [aj] "+v"(x[15]), [p] "+v"(kept),
             [pv] "+v"(piv), [rc] "+v"(rec), [nl] "=&v"(nl)
-          : [m] "s"(mine), [j] "n"(15));
+          : [m] "n"(mine), [j] "n"(15)
+          : "vcc");
     }
 #undef TTC_FMAC
   });
@@ -202,7 +205,7 @@ __device__ __forceinline__ int invert_spread16(floatx4& m, int lane) {
     asm volatile("s_nop 1" : "+v"(rc));
     static_for<0, 4>([&](auto JJ) {
       constexpr int jj = decltype(JJ)::value, j = 4 * J + jj;
-      const unsigned long long mine = 0x0001000100010001ull << j;
+      constexpr unsigned mine = 0x00010001u << j;
       float(&x)[4] = a, (&y)[4] = c;
       float &kept = mypiv, &piv = pv, &rec = rc;
       // as in invert_regs16: the next column and its pivot's reciprocal first, the other columns under them
@@ -210,21 +213,23 @@ __device__ __forceinline__ int invert_spread16(floatx4& m, int lane) {
 #define TTC_FMAC(n) "v_fmac_f32_dpp %" #n ", %" #n ", %[nl] row_newbcast:%[j] row_mask:0xf bank_mask:0xf\n\t"
       if constexpr (jj < 3) {
         asm volatile(
-            "v_mul_f32 %[nl], %[rc], -%[cj]\n\tv_cndmask_b32 %[p], %[p], %[pv], %[m]\n\tv_cndmask_b32 %[nl], %[nl], 0, %[m]\n\t"
+            "s_mov_b32 vcc_lo, %[m]\n\ts_mov_b32 vcc_hi, %[m]\n\tv_mul_f32 %[nl], %[rc], -%[cj]\n\tv_cndmask_b32 %[p], %[p], %[pv], vcc\n\tv_cndmask_b32 %[nl], %[nl], 0, vcc\n\t"
             TTC_FMAC(0) TTC_FMAC(3) TTC_FMAC(4)
             "v_mov_b32_dpp %[pv], %0 row_newbcast:%[jn] row_mask:0xf bank_mask:0xf\n\t" TTC_FMAC(5) TTC_FMAC(6)
-            "v_rcp_f32 %[rc], %[pv]\n\t" TTC_FMAC(1) TTC_FMAC(2) "v_cndmask_b32 %[cj], %[nl], 1.0, %[m]"
+            "v_rcp_f32 %[rc], %[pv]\n\t" TTC_FMAC(1) TTC_FMAC(2) "v_cndmask_b32 %[cj], %[nl], 1.0, vcc"
             : "+v"(y[jj + 1]), "+v"(y[(jj + 2) & 3]), "+v"(y[(jj + 3) & 3]), "+v"(x[0]), "+v"(x[1]), "+v"(x[2]),
               "+v"(x[3]), [cj] "+v"(y[jj]), [p] "+v"(kept), [pv] "+v"(piv), [rc] "+v"(rec), [nl] "=&v"(nl)
-            : [m] "s"(mine), [j] "n"(j), [jn] "n"(j + 1));
+            : [m] "n"(mine), [j] "n"(j), [jn] "n"(j + 1)
+          : "vcc");
       } else {
         asm volatile(
-            "v_mul_f32 %[nl], %[rc], -%[cj]\n\tv_cndmask_b32 %[p], %[p], %[pv], %[m]\n\tv_cndmask_b32 %[nl], %[nl], 0, %[m]\n\t"
+            "s_mov_b32 vcc_lo, %[m]\n\ts_mov_b32 vcc_hi, %[m]\n\tv_mul_f32 %[nl], %[rc], -%[cj]\n\tv_cndmask_b32 %[p], %[p], %[pv], vcc\n\tv_cndmask_b32 %[nl], %[nl], 0, vcc\n\t"
             TTC_FMAC(0) TTC_FMAC(1) TTC_FMAC(2) TTC_FMAC(3) TTC_FMAC(4) TTC_FMAC(5) TTC_FMAC(6)
-            "v_cndmask_b32 %[cj], %[nl], 1.0, %[m]\n\ts_nop 1"
+            "v_cndmask_b32 %[cj], %[nl], 1.0, vcc\n\ts_nop 1"
             : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(y[0]), "+v"(y[1]), "+v"(y[2]), [cj] "+v"(y[3]),
               [p] "+v"(kept), [pv] "+v"(piv), [rc] "+v"(rec), [nl] "=&v"(nl)
-            : [m] "s"(mine), [j] "n"(j));
+            : [m] "n"(mine), [j] "n"(j)
+            : "vcc");
       }
 #undef TTC_FMAC
     });

@@ -153,12 +153,12 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D == 64 ? TTC_D64_WAVES : 1)) s
             float gm = s_growth[0];
 #pragma unroll
             for (int ww = 1; ww < C::NW; ++ww) gm = fmaxf(gm, s_growth[ww]);
-            if (!(gm <= p.growth_limit) && !info) {  // also true for NaN; every thread reads the same values
+            if (uniform(!(gm <= p.growth_limit)) && !info) {  // also true for NaN; every thread reads the same values
               // (a problem whose set-up broke down is NaN anyway and keeps its report)
               hard = true;
               break;
             }
-            if (!last && k >= 2 && s < p.T && gm * (gm / g_prev) > p.growth_limit) {
+            if (!last && k >= 2 && s < p.T && uniform(gm * (gm / g_prev) > p.growth_limit)) {
               last = true;
               plan_base = s;
               plan_T = p.T - s;
@@ -210,7 +210,7 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D == 64 ? TTC_D64_WAVES : 1)) s
       const TIn* Bp = reinterpret_cast<const TIn*>(p.B) + prob * p.sB;
       const TIn* Rp = reinterpret_cast<const TIn*>(p.R) + prob * p.sR;
       const TIn* QTp = p.QT ? reinterpret_cast<const TIn*>(p.QT) + prob * p.sQT : Qp;
-      riccati_problem<D, TIn>(W, S, s_red, p, prob, p.T, Ap, Bp, Qp, Rp, 0, 0, 0, 0, QTp, nullptr, Qp, x0p, 2,
+      riccati_problem<D, TIn>(W, s_red, p, prob, p.T, Ap, Bp, Qp, Rp, 0, 0, 0, 0, QTp, nullptr, Qp, x0p, 2,
                               tid + opaque_zero());
       continue;
     }

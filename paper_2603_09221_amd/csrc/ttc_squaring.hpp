@@ -67,11 +67,10 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D == 64 ? 2 : 1)) squaring_kern
       if (lane == 0) s_max[w] = m;
     };
     auto over_limit = [&] {  // uniform over the workgroup; also true for NaN
-      float m = s_max[0];
-      bool bad = !(m <= p.growth_limit);
+      bool bad = false;
 #pragma unroll
-      for (int ww = 1; ww < C::NW; ++ww) bad = bad || !(s_max[ww] <= p.growth_limit);
-      return bad;
+      for (int ww = 0; ww < C::NW; ++ww) bad = bad || !(s_max[ww] <= p.growth_limit);
+      return uniform(bad) != 0;
     };
 
     // ---- set-up: X = R^{-1} B^T, G = B X, A (factored for its report), H = Q, P = Q_T when it is a matrix of its own
@@ -279,7 +278,7 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D == 64 ? 2 : 1)) squaring_kern
         emit_gain<D, TIn>(p, prob, acc, x0p, info, tid);
         emit_value<D, TIn>(p, prob, WL, Qp, x0p, info, s_red, tid);
       } else {
-        riccati_problem<D, TIn>(W, S, s_red, p, prob, p.T, Ap, Bp, Qp, Rp, 0, 0, 0, 0, QTp, nullptr, Qp, x0p, 2,
+        riccati_problem<D, TIn>(W, s_red, p, prob, p.T, Ap, Bp, Qp, Rp, 0, 0, 0, 0, QTp, nullptr, Qp, x0p, 2,
                                 tid + opaque_zero());
       }
       continue;

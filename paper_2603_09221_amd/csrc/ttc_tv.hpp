@@ -13,6 +13,7 @@
 #pragma once
 #include "ttc_common.hpp"
 #include "ttc_small.hpp"
+#include "ttc_columns.hpp"
 #include "ttc_rollout.hpp"
 
 namespace ttc {
@@ -40,97 +41,13 @@ __device__ __forceinline__ void load_rows_input(const TIn* src, floatx4 (&acc)[C
       }
 }
 
-// One backward step of Prop. 3.1 with the matrices of one step.  On entry the right half of the pair
-// holds P_{s+1} (symmetric); on exit it holds W = S^{-1} B^T P A = -K_s, S = R + B^T P B, and pn holds this
-// wavefront's rows of A^T P A - (B^T P A)^T W, which is P_s up to the stage cost.  Six products and one
-// unpivoted solve (S is positive definite).  Returns the solve's breakdown flag.
-template <int D, typename TIn>
-__device__ __forceinline__ int riccati_step(float* W, SolveScratch<D>& S, const TIn* As, const TIn* Bs, const TIn* Rs,
-                                            floatx4 (&pn)[Cfg<D>::RB][Cfg<D>::NT], int tid) {
-  using C = Cfg<D>;
-  tid += opaque_zero();
-  const int lane = tid & 63, w = tid >> 6, i = lane & 15, g = lane >> 4;
-  float* const WL = W;
-  float* const WR = W + D;
-  float cFT[C::RB][C::KS];
-  {
-    float cAT[C::RB][C::KS], cBT[C::RB][C::KS];
-    {
-      floatx4 accPA[C::RB][C::NT], accPB[C::RB][C::NT];
-      {
-        float cP[C::RB][C::KS];
-        load_aop_lds<D>(WR, cP, w, i, g);  // rows of P (symmetric)
-        load_half<D, TIn, false>(WL, As, tid);
-        __syncthreads();
-        load_half<D, TIn, false>(WR, Bs, tid);  // P is in registers now
-        zero_acc<D>(accPA);
-        gemm_acc<D>(accPA, cP, WL, i, g);  // P A
-        __syncthreads();
-        zero_acc<D>(accPB);
-        gemm_acc<D>(accPB, cP, WR, i, g);  // P B
-      }
-      load_aopT_lds<D>(WL, cAT, w, i, g);  // rows of A^T
-      load_aopT_lds<D>(WR, cBT, w, i, g);  // rows of B^T
-      __syncthreads();
-      store_rows<D>(WL, accPA, w, i, g);
-      store_rows<D>(WR, accPB, w, i, g);
-      __syncthreads();
-    }
-    floatx4 accS[C::RB][C::NT], accF[C::RB][C::NT];
-    load_rows_input<D, TIn>(Rs, accS, w, i, g);
-    gemm_acc<D>(accS, cBT, WR, i, g);  // S = R + B^T P B
-    zero_acc<D>(accF);
-    gemm_acc<D>(accF, cBT, WL, i, g);  // F = B^T P A
-    zero_acc<D>(pn);
-    gemm_acc<D>(pn, cAT, WL, i, g);    // A^T P A
-    __syncthreads();
-    store_rows<D>(WL, accS, w, i, g);
-    store_rows<D>(WR, accF, w, i, g);
-    __syncthreads();
-  }
-  symmetrise_half<D>(WL, tid);  // R is read as its symmetric part
-  load_aopT_lds<D>(WR, cFT, w, i, g);  // rows of F^T
-  __syncthreads();
-  const int flag = lds_solve<D, 7, false>(W, S, tid);  // right half: W = S^{-1} F
-#pragma unroll
-  for (int rb = 0; rb < C::RB; ++rb)
-#pragma unroll
-    for (int k = 0; k < C::KS; ++k) cFT[rb][k] = -cFT[rb][k];
-  gemm_acc<D>(pn, cFT, WR, i, g);  // - F^T W
-  return flag;
-}
-
-// pn += the symmetric part of the stage cost Qs (staged through the left half), then P_s = pn goes to the
-// right half, exactly symmetric.  Contains the barriers it needs; the right half must no longer be read.
-template <int D, typename TIn>
-__device__ __forceinline__ void next_value_matrix(float* W, const TIn* Qs, floatx4 (&pn)[Cfg<D>::RB][Cfg<D>::NT], int tid) {
-  using C = Cfg<D>;
-  const int lane = tid & 63, w = tid >> 6, i = lane & 15, g = lane >> 4;
-  float* const WL = W;
-  float* const WR = W + D;
-  load_half<D, TIn, false>(WL, Qs, tid);
-  __syncthreads();
-  symmetrise_half<D>(WL, tid);
-  __syncthreads();
-  floatx4 q[C::RB][C::NT];
-  load_rows<D>(WL, q, w, i, g);
-#pragma unroll
-  for (int rb = 0; rb < C::RB; ++rb)
-#pragma unroll
-    for (int c = 0; c < C::NT; ++c) pn[rb][c] += q[rb][c];
-  store_rows<D>(WR, pn, w, i, g);
-  __syncthreads();
-  symmetrise_half<D>(WR, tid);
-  __syncthreads();
-}
-
 // The whole backward recursion of one problem by one workgroup, from P_T to the outputs P_0, K_0, u_0, value and
 // info: T calls of riccati_step.  Step s reads A, B, R at As + s*tA, Bs + s*tB, Rs + s*tR and the stage cost on
 // the state it starts from at Qs + (s-1)*tQ (none for s = 0); zero strides give the time-invariant problem.
 // The terminal value matrix is PTf (float32) if given, else PT (input element type).  info_base is added to the
 // index (1 = the step taken first, s = T-1) of the step whose solve broke down.  All threads must call it.
 template <int D, typename TIn>
-__device__ __forceinline__ void riccati_problem(float* W, SolveScratch<D>& S, float* s_red, const SolveArgs& p,
+__device__ __forceinline__ void riccati_problem(float* W, float* s_red, const SolveArgs& p,
                                                 long long prob, int T, const TIn* As, const TIn* Bs, const TIn* Qs,
                                                 const TIn* Rs, long long tA, long long tB, long long tQ, long long tR,
                                                 const TIn* PT, const float* PTf, const TIn* Qflag, const TIn* x0p,
@@ -146,15 +63,16 @@ __device__ __forceinline__ void riccati_problem(float* W, SolveScratch<D>& S, fl
   symmetrise_half<D>(WR, tid);
   __syncthreads();
   for (int s = T - 1; s >= 0; --s) {
-    floatx4 pn[C::RB][C::NT];
-    const int flag = riccati_step<D, TIn>(W, S, As + (long long)s * tA, Bs + (long long)s * tB, Rs + (long long)s * tR,
+    Cols<D> wk, pn;
+    const int flag = riccati_step<D, TIn>(W, As + (long long)s * tA, Bs + (long long)s * tB, Rs + (long long)s * tR, wk,
                                           pn, tid);
     if (flag && !info) info = info_base + T - s;
     if (s >= 1) {
-      __syncthreads();  // every wavefront is done reading W = -K_s
       next_value_matrix<D, TIn>(W, Qs + (long long)(s - 1) * tQ, pn, tid);
     } else {
-      store_rows<D>(WL, pn, w, i, g);  // P_0 (no cost on x_0)
+      __syncthreads();  // every wavefront has left the pair
+      store_cols_T<D>(WL, pn, w, i, g);  // P_0 (no cost on x_0)
+      store_cols<D>(WR, C::PITCH, wk, w, i, g);
       __syncthreads();
       symmetrise_half<D>(WL, tid);
       __syncthreads();
@@ -167,10 +85,9 @@ __device__ __forceinline__ void riccati_problem(float* W, SolveScratch<D>& S, fl
 }
 
 template <int D, typename TIn>
-__global__ void __launch_bounds__(Cfg<D>::NTHR) solve_tv_kernel(const TvArgs ta) {
+__global__ void __launch_bounds__(Cfg<D>::NTHR, TTC_COLS_WAVES(D)) solve_tv_kernel(const TvArgs ta) {
   using C = Cfg<D>;
   __shared__ __attribute__((aligned(16))) float W[D * C::PITCH];
-  __shared__ __attribute__((aligned(16))) SolveScratch<D> S;
   __shared__ float s_red[C::NW];
   const SolveArgs& p = ta.s;
 
@@ -181,7 +98,7 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR) solve_tv_kernel(const TvArgs ta)
     const TIn* Qp = reinterpret_cast<const TIn*>(p.Q) + prob * p.sQ;
     const TIn* Rp = reinterpret_cast<const TIn*>(p.R) + prob * p.sR;
     const TIn* x0p = reinterpret_cast<const TIn*>(p.x0) + prob * p.sx0;
-    riccati_problem<D, TIn>(W, S, s_red, p, prob, p.T, Ap, Bp, Qp, Rp, ta.tA, ta.tB, ta.tQ, ta.tR,
+    riccati_problem<D, TIn>(W, s_red, p, prob, p.T, Ap, Bp, Qp, Rp, ta.tA, ta.tB, ta.tQ, ta.tR,
                             Qp + (long long)(p.T - 1) * ta.tQ, ta.PT ? ta.PT + prob * ta.sPT : nullptr, Qp, x0p, 0, tid);
   }
 }
@@ -190,10 +107,9 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR) solve_tv_kernel(const TvArgs ta)
 // keeping every gain K_s in the workspace, then the closed-loop forward sweep
 // u_s = K_s x_s, x_{s+1} = A_s x_s + B_s u_s with the cost sum_s u_s^T R_s u_s + x_{s+1}^T Q[s] x_{s+1}.
 template <int D, typename TIn>
-__global__ void __launch_bounds__(Cfg<D>::NTHR) rollout_tv_kernel(const TvRolloutArgs ta) {
+__global__ void __launch_bounds__(Cfg<D>::NTHR, TTC_COLS_WAVES(D)) rollout_tv_kernel(const TvRolloutArgs ta) {
   using C = Cfg<D>;
   __shared__ __attribute__((aligned(16))) float W[D * C::PITCH];
-  __shared__ __attribute__((aligned(16))) SolveScratch<D> S;
   __shared__ float s_red[C::NW];
   __shared__ float s_x[D], s_u[D], s_xn[D];
   const RolloutArgs& p = ta.r;
@@ -215,21 +131,11 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR) rollout_tv_kernel(const TvRollou
       __syncthreads();
       // ---- backward sweep
       for (int s = p.T - 1; s >= 0; --s) {
-        floatx4 pn[C::RB][C::NT];
-        const int flag = riccati_step<D, TIn>(W, S, Ap + (long long)s * ta.tA, Bp + (long long)s * ta.tB,
-                                              Rp + (long long)s * ta.tR, pn, tid);
+        Cols<D> wk, pn;
+        const int flag = riccati_step<D, TIn>(W, Ap + (long long)s * ta.tA, Bp + (long long)s * ta.tB,
+                                              Rp + (long long)s * ta.tR, wk, pn, tid);
         if (flag && !info) info = p.T - s;
-        {
-          floatx4 acc[C::RB][C::NT];
-          load_rows<D>(WR, acc, w, i, g);
-#pragma unroll
-          for (int rb = 0; rb < C::RB; ++rb) {
-#pragma unroll
-            for (int cc = 0; cc < C::NT; ++cc) acc[rb][cc] = -acc[rb][cc];
-            write_rows_global<D>(wsK + (long)s * D * D, acc[rb], C::RB * w + rb, i, g);  // K_s
-          }
-        }
-        __syncthreads();
+        store_cols<D, -1>(wsK + (long)s * D * D, D, wk, w, i, g);  // K_s
         if (s >= 1) next_value_matrix<D, TIn>(W, Qp + (long long)(s - 1) * ta.tQ, pn, tid);
       }
     }

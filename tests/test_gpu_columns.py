@@ -1,0 +1,67 @@
+"""The Riccati step by columns and its block-pivoted dense solve (time-heterogeneous solve and roll-out), against the float64 recursion.
+
+Tolerance of the cheap-control cases: the float32 error of P and K is proportional to cond(S), S = R + B^T P B, times the
+unit roundoff; the same recursion in float32 on the CPU stays below 1.4 of that product over these cases, and 4 are allowed."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import lqr_oracle
+from paper_2603_09221_amd import binding, synth
+from tests.parity import rel_err
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def max_cond(b):
+    A, B, Q, R, _ = b.numpy64()
+    Qs, P = 0.5 * (Q + Q.swapaxes(-1, -2)), None
+    P = Qs
+    worst = 0.0
+    for s in range(b.T - 1, -1, -1):
+        S = 0.5 * (R + R.swapaxes(-1, -2)) + B.swapaxes(-1, -2) @ P @ B
+        worst = max(worst, np.linalg.cond(S).max())
+        F = B.swapaxes(-1, -2) @ P @ A
+        P = Qs + A.swapaxes(-1, -2) @ P @ A - F.swapaxes(-1, -2) @ np.linalg.solve(S, F)
+    return worst
+
+
+@pytest.mark.parametrize("r_scale", [1.0, 1e-2, 1e-3])
+@pytest.mark.parametrize("d,T,n", [(16, 1, 3), (16, 3, 65), (32, 1, 3), (32, 3, 65), (64, 1, 3), (64, 3, 65), (128, 1, 3),
+                                   (128, 3, 17)])
+def test_cheap_control(d, T, n, r_scale):
+    b = synth.make_batch(n, d, d, T, seed=5, device=DEV, r_scale=r_scale)
+    tol = 4 * 2.0 ** -24 * max_cond(b)
+    ref = lqr_oracle.riccati_solve(*b.numpy64()[:4], None, b.numpy64()[4], T)
+    steps = [m[:, None].expand(-1, T, -1, -1) for m in (b.A, b.B, b.Q, b.R)]
+    tv = binding.ttc_lqr_solve_tv(*steps, b.x0)
+    ro = binding.ttc_lqr_rollout_tv(*steps, b.x0)
+    torch.cuda.synchronize()
+    assert not tv["info"].any() and not ro["info"].any()
+    for k in ("P0", "K0"):
+        assert rel_err(tv[k].cpu().numpy(), ref[k]).max() <= tol, k
+    # u_0 and the cost see the error of K_0 and P_0 through x_0: norm-wise no larger than |K_0| |x_0|, |P_0| |x_0|^2
+    A, B, Q, R, x0 = b.numpy64()
+    nx = np.linalg.norm(x0, axis=-1)
+    du = np.linalg.norm(ro["U"][:, 0].double().cpu().numpy() - ref["u0"], axis=-1)
+    assert (du <= tol * np.linalg.norm(ref["K0"], axis=(-1, -2)) * nx).all()
+    dc = np.abs(ro["cost"].double().cpu().numpy() - ref["value"])
+    assert (dc <= tol * np.linalg.norm(ref["P0"], axis=(-1, -2)) * nx * nx).all()
+
+
+@pytest.mark.parametrize("d", [16, 32, 64, 128])
+def test_a_breakdown_in_any_pivot_block_is_reported_for_its_own_problem(d):
+    n, T = 2 * (d // 16) + 1, 3
+    b = synth.make_tv_batch(n, d, d, T, seed=d, device=DEV)
+    good = binding.ttc_lqr_solve_tv(b.A, b.B, b.Q, b.R, b.x0)
+    R = b.R.clone()
+    for p in range(d // 16):  # step 1 is the second one taken
+        R[2 * p + 1, 1, 16 * p + 5, 16 * p + 5] = -1e4
+    for call in (binding.ttc_lqr_solve_tv, binding.ttc_lqr_rollout_tv):
+        out = call(b.A, b.B, b.Q, R, b.x0)
+        torch.cuda.synchronize()
+        assert out["info"].tolist() == [T - 1 if k % 2 else 0 for k in range(n)]
+    out = binding.ttc_lqr_solve_tv(b.A, b.B, b.Q, R, b.x0)
+    assert torch.equal(out["K0"][0::2], good["K0"][0::2]) and torch.isnan(out["K0"][1::2]).all()
+
