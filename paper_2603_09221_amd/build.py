@@ -42,7 +42,7 @@ UNITS = [("ttc_api.hip", None),
 # two, where measured faster.  The Riccati kernels own matrices by columns: at d = 64 one column tile a wavefront leaves
 # room for three workgroups a compute unit.  The default forward kernel is faster with fewer, fatter wavefronts (its
 # constant operands stay in registers; at d = 64 four problems fit a compute unit).  Measured with one block against two:
-# squaring path d = 128, T = 16 4.5 ms against 31.9 for one
+# roll-out d = 128, T = 8, 1024 problems 2.75 ms against 3.04; squaring path d = 128, T = 16 4.5 ms against 31.9 for one
 # batch (two blocks spill, as they do in the time-heterogeneous kernel); flagged doubling d = 128, T = 16 501k problems/s
 # against 488k.
 _ONE_ROW_BLOCK = "-DTTC_ROW_BLOCKS(D)=((D)==%d?1:((D)>=32?2:1))"
@@ -50,6 +50,8 @@ UNIT_FLAGS = {("k_backward.hip", 64): [_ONE_ROW_BLOCK % 64],
               ("k_tv.hip", 64): [_ONE_ROW_BLOCK % 64],
               ("k_tv.hip", 128): [_ONE_ROW_BLOCK % 128],
               ("k_doubling.hip", 128): [_ONE_ROW_BLOCK % 128],
+              ("k_rollout.hip", 64): [_ONE_ROW_BLOCK % 64],
+              ("k_rollout.hip", 128): [_ONE_ROW_BLOCK % 128],
               ("k_squaring.hip", 128): [_ONE_ROW_BLOCK % 128]}
 
 _NOISE = "is not a recognized feature for this target"

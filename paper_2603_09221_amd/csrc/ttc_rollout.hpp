@@ -1,5 +1,6 @@
 // Roll-out kernel of the time-invariant problem (Alg. 1, forward loop, r = 0).
 #pragma once
+#include "ttc_columns.hpp"
 #include "ttc_common.hpp"
 
 namespace ttc {
@@ -23,19 +24,133 @@ __device__ __forceinline__ float matvec_row(const TM* M, const float* xs, int ti
   return s;
 }
 
-// Roll-out kernel (Alg. 1 with r = 0).  Backward sweep: the value matrices P_T .. P_1 are produced
-// one step at a time in the re-based form of the reverse symplectic factor (re-base every step):
-//     M_t = (I + P_{t+1} G)^{-1} P_{t+1} A,   K_t = -(R^{-1} B^T) M_t,   P_t = Q + A^T M_t,
-// the gains go to the workspace; forward sweep: u_t = K_t x_t, x_{t+1} = A x_t + B u_t and the cost.
+// The same with M in LDS (row pitch PITCH).
+template <int D>
+__device__ __forceinline__ float matvec_row_lds(const float* M, const float* xs, int tid) {
+  constexpr int TPR = Cfg<D>::NTHR / D;
+  const int r = tid / TPR, part = tid % TPR;
+  float s = 0.f;
+#pragma unroll
+  for (int c4 = part * (D / TPR); c4 < (part + 1) * (D / TPR); c4 += 4) {
+    const floatx4 mv = *reinterpret_cast<const floatx4*>(M + r * Cfg<D>::PITCH + c4);
+    s += mv[0] * xs[c4] + mv[1] * xs[c4 + 1] + mv[2] * xs[c4 + 2] + mv[3] * xs[c4 + 3];
+  }
+#pragma unroll
+  for (int m = 1; m < TPR; m <<= 1) s += __shfl_xor(s, m, 64);
+  return s;
+}
+
+// Backward sweep of rollout_kernel for a problem whose R + B^T P B is not positive definite everywhere (a stage cost that is
+// not positive semidefinite): the value matrices P_T .. P_1 one step at a time in the re-based form of the reverse
+// symplectic factor, whose solve is pivoted and asks for nothing but a non-singular matrix,
+//     M_t = (I + P_{t+1} G)^{-1} P_{t+1} A,   K_t = -(R^{-1} B^T) M_t,   P_t = Q + A^T M_t.
+// wsC: 3 d x d of workspace; the gains go to wsK.  Returns info: 1 = R, then a step each.
 template <int D, typename TIn>
-__global__ void __launch_bounds__(Cfg<D>::NTHR) rollout_kernel(const RolloutArgs p) {
+__device__ __forceinline__ int rollout_pivoted_sweep(float* W, SolveScratch<D>& S, int T, const TIn* Ap, const TIn* Bp,
+                                                     const TIn* Qp, const TIn* Rp, const TIn* QTp, float* wsC, float* wsK,
+                                                     int tid) {
+  using C = Cfg<D>;
+  const int lane = tid & 63, w = tid >> 6, i = lane & 15, g = lane >> 4;
+  float* const WL = W;
+  float* const WR = W + D;
+  int info = 0, nsolve = 0;
+  floatx4 acc[C::RB][C::NT];
+
+  // ---- setup: X = R^{-1} B^T, G = B X; row blocks of G, X, A^T to the workspace
+  load_half<D, TIn, false>(WL, Rp, tid);
+  load_half<D, TIn, false>(WR, Bp, tid);
+  __syncthreads();
+  symmetrise_half<D>(WL, tid);
+  transpose_half<D>(WR, w, i, g);              // RHS = B^T
+  ++nsolve;
+  if (lds_solve<D, 7, false>(W, S, tid) && !info) info = nsolve;  // R is positive definite: no pivot search
+  {
+    float c[C::RB][C::KS];
+    load_aop_lds<D>(WR, c, w, i, g);
+    store_aop_ws<D>(wsC + 1 * D * D, c, tid);
+    load_aop_global<D, TIn>(Bp, c, w, i, g);
+    zero_acc<D>(acc);
+    gemm_acc<D>(acc, c, WR, i, g);
+    store_rows<D>(WL, acc, w, i, g);
+    __syncthreads();
+    symmetrise_half<D>(WL, tid);
+    __syncthreads();
+    load_aop_lds<D>(WL, c, w, i, g);
+    store_aop_ws<D>(wsC + 0 * D * D, c, tid);
+#pragma unroll
+    for (int rb = 0; rb < C::RB; ++rb)
+#pragma unroll
+      for (int k = 0; k < C::KS; ++k)
+        c[rb][k] = ld1<TIn>(Ap, (long)(16 * (k / 4) + 4 * g + (k % 4)) * D + 16 * (C::RB * w + rb) + i);
+    store_aop_ws<D>(wsC + 2 * D * D, c, tid);
+  }
+  __syncthreads();
+  load_half<D, TIn, false>(WR, QTp, tid);
+  __syncthreads();
+  symmetrise_half<D>(WR, tid);
+  __syncthreads();
+
+  // ---- backward sweep (the constant row blocks are read again for every product: held in registers, they would cost the
+  // sweep that almost every problem takes)
+  auto times = [&](int k) {  // acc += (G, X or A^T) * the right half
+    float c[C::RB][C::KS];
+    load_aop_ws<D>(wsC + k * D * D, c, tid, opaque_zero());
+    gemm_acc<D>(acc, c, WR, i, g);
+  };
+  for (int t = T - 1; t >= 0; --t) {
+    eye_acc<D>(acc, w, i, g);
+    times(0);                         // (I + P G)^T
+    store_rows_T<D>(WL, acc, w, i, g);
+    zero_acc<D>(acc);
+    times(2);                         // (P A)^T
+    __syncthreads();
+    store_rows_T<D>(WR, acc, w, i, g);
+    __syncthreads();
+    ++nsolve;
+    if (lds_solve<D>(W, S, tid) && !info) info = nsolve;
+    zero_acc<D>(acc);
+    times(1);                         // -K_t
+#pragma unroll
+    for (int rb = 0; rb < C::RB; ++rb) {
+#pragma unroll
+      for (int cc = 0; cc < C::NT; ++cc) acc[rb][cc] = -acc[rb][cc];
+      write_rows_global<D>(wsK + (long)t * D * D, acc[rb], C::RB * w + rb, i, g);
+    }
+    if (t >= 1) {
+#pragma unroll
+      for (int rb = 0; rb < C::RB; ++rb)
+#pragma unroll
+        for (int cc = 0; cc < C::NT; ++cc)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const long row = 16 * (C::RB * w + rb) + 4 * g + v, col = tile_col<D>(cc, i);
+            acc[rb][cc][v] = 0.5f * (ld1<TIn>(Qp, row * D + col) + ld1<TIn>(Qp, col * D + row));
+          }
+      times(2);                         // P_t = Q + A^T M_t
+      __syncthreads();
+      store_rows<D>(WR, acc, w, i, g);
+      __syncthreads();
+      symmetrise_half<D>(WR, tid);
+      __syncthreads();
+    }
+  }
+  return info;
+}
+
+// Roll-out kernel (Alg. 1 with r = 0).  Backward sweep: the recursion of Prop. 3.1 as ttc_lqr_solve_tv runs it, with the
+// same matrices in every step, the gains to the workspace; forward sweep: u_t = K_t x_t, x_{t+1} = A x_t + B u_t and the
+// cost, A and B read from LDS.  R is factored once for its report.
+// Against the pivoted sweep for every problem and all five matrices of a forward step from memory: d = 64, T = 8, 4096
+// problems 1.94 -> 1.38 ms; d = 32, 8192 problems 0.79 -> 0.48 ms; d = 128, 1024 problems 3.01 -> 2.75 ms.
+template <int D, typename TIn>
+__global__ void __launch_bounds__(Cfg<D>::NTHR, TTC_COLS_WAVES(D)) rollout_kernel(const RolloutArgs p) {
   using C = Cfg<D>;
   __shared__ __attribute__((aligned(16))) float W[D * C::PITCH];
   __shared__ __attribute__((aligned(16))) SolveScratch<D> S;
   __shared__ float s_red[C::NW];
   __shared__ float s_x[D], s_u[D], s_xn[D];
 
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, i = lane & 15, g = lane >> 4;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   float* const WL = W;
   float* const WR = W + D;
   float* const wsC = p.ws + (long)blockIdx.x * (p.T + 3) * D * D;  // G, X, A^T in register layout
@@ -48,85 +163,38 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR) rollout_kernel(const RolloutArgs
     const TIn* Rp = reinterpret_cast<const TIn*>(p.R) + prob * p.sR;
     const TIn* QTp = p.QT ? reinterpret_cast<const TIn*>(p.QT) + prob * p.sQT : Qp;
     const TIn* x0p = reinterpret_cast<const TIn*>(p.x0) + prob * p.sx0;
-    int info = 0, nsolve = 0;
-    floatx4 acc[C::RB][C::NT];
-
-    // ---- setup: X = R^{-1} B^T, G = B X; row blocks of G, X, A^T to the workspace
-    load_half<D, TIn, false>(WL, Rp, tid);
-    load_half<D, TIn, false>(WR, Bp, tid);
-    __syncthreads();
-    symmetrise_half<D>(WL, tid);
-    transpose_half<D>(WR, w, i, g);              // RHS = B^T
-    ++nsolve;
-    if (lds_solve<D, 7, false>(W, S, tid) && !info) info = nsolve;  // R is positive definite: no pivot search
+    int info = 0;
     {
-      float c[C::RB][C::KS];
-      load_aop_lds<D>(WR, c, w, i, g);
-      store_aop_ws<D>(wsC + 1 * D * D, c, tid);
-      load_aop_global<D, TIn>(Bp, c, w, i, g);
-      zero_acc<D>(acc);
-      gemm_acc<D>(acc, c, WR, i, g);
-      store_rows<D>(WL, acc, w, i, g);
-      __syncthreads();
-      symmetrise_half<D>(WL, tid);
-      __syncthreads();
-      load_aop_lds<D>(WL, c, w, i, g);
-      store_aop_ws<D>(wsC + 0 * D * D, c, tid);
-#pragma unroll
-      for (int rb = 0; rb < C::RB; ++rb)
-#pragma unroll
-        for (int k = 0; k < C::KS; ++k)
-          c[rb][k] = ld1<TIn>(Ap, (long)(16 * (k / 4) + 4 * g + (k % 4)) * D + 16 * (C::RB * w + rb) + i);
-      store_aop_ws<D>(wsC + 2 * D * D, c, tid);
-    }
-    __syncthreads();
-    load_half<D, TIn, false>(WR, QTp, tid);
-    __syncthreads();
-    symmetrise_half<D>(WR, tid);
-    __syncthreads();
-
-    // ---- backward sweep (the constant row blocks stay in registers)
-    float cG[C::RB][C::KS], cX[C::RB][C::KS], cAT[C::RB][C::KS];
-    load_aop_ws<D>(wsC + 0 * D * D, cG, tid, 0);
-    load_aop_ws<D>(wsC + 1 * D * D, cX, tid, 0);
-    load_aop_ws<D>(wsC + 2 * D * D, cAT, tid, 0);
-    for (int t = p.T - 1; t >= 0; --t) {
-      eye_acc<D>(acc, w, i, g);
-      gemm_acc<D>(acc, cG, WR, i, g);   // (I + P G)^T
-      store_rows_T<D>(WL, acc, w, i, g);
-      zero_acc<D>(acc);
-      gemm_acc<D>(acc, cAT, WR, i, g);  // (P A)^T
-      __syncthreads();
-      store_rows_T<D>(WR, acc, w, i, g);
-      __syncthreads();
-      ++nsolve;
-      if (lds_solve<D>(W, S, tid) && !info) info = nsolve;
-      zero_acc<D>(acc);
-      gemm_acc<D>(acc, cX, WR, i, g);    // -K_t
-#pragma unroll
-      for (int rb = 0; rb < C::RB; ++rb) {
-#pragma unroll
-        for (int cc = 0; cc < C::NT; ++cc) acc[rb][cc] = -acc[rb][cc];
-        write_rows_global<D>(wsK + (long)t * D * D, acc[rb], C::RB * w + rb, i, g);
+      const int tb = tid + opaque_zero(), lane = tb & 63, w = uniform(tb >> 6), i = lane & 15, g = lane >> 4;
+      {
+        Cols<D> r;
+        floatx4 none[C::NT][1];
+        zero_cols<D>(r);
+        add_sym_cols<D, TIn>(Rp, r, w, i, g);
+        info = spd_solve_cols<D, 0>(WR, r, none, w, lane);
       }
-      if (t >= 1) {
-#pragma unroll
-        for (int rb = 0; rb < C::RB; ++rb)
-#pragma unroll
-          for (int cc = 0; cc < C::NT; ++cc)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-              const long row = 16 * (C::RB * w + rb) + 4 * g + v, col = tile_col<D>(cc, i);
-              acc[rb][cc][v] = 0.5f * (ld1<TIn>(Qp, row * D + col) + ld1<TIn>(Qp, col * D + row));
-            }
-        gemm_acc<D>(acc, cAT, WR, i, g);  // P_t = Q + A^T M_t
+      __syncthreads();
+      if (!info) {
+        load_half<D, TIn, false>(WR, QTp, tb);  // P_T = Q_T
         __syncthreads();
-        store_rows<D>(WR, acc, w, i, g);
+        symmetrise_half<D>(WR, tb);
         __syncthreads();
-        symmetrise_half<D>(WR, tid);
-        __syncthreads();
+        int t = p.T - 1;
+        for (; t >= 0; --t) {
+          Cols<D> wk, pn;
+          if (riccati_step<D, TIn>(W, Ap, Bp, Rp, wk, pn, tb)) break;
+          store_cols<D, -1>(wsK + (long)t * D * D, D, wk, w, i, g);  // K_t
+          if (t >= 1) next_value_matrix<D, TIn>(W, Qp, pn, tb);
+        }
+        if (t >= 0) {
+          __syncthreads();
+          info = rollout_pivoted_sweep<D, TIn>(W, S, p.T, Ap, Bp, Qp, Rp, QTp, wsC, wsK, tb);
+        }
       }
     }
+    __syncthreads();
+    load_half<D, TIn, false>(WL, Ap, tid);
+    load_half<D, TIn, false>(WR, Bp, tid);
     __syncthreads();  // gains visible to the whole workgroup
 
     // ---- forward sweep
@@ -144,7 +212,7 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR) rollout_kernel(const RolloutArgs
       if (part == 0) s_u[r] = u;
       __syncthreads();
       const float ru = matvec_row<D, TIn>(Rp, s_u, tid);
-      const float xn = matvec_row<D, TIn>(Ap, s_x, tid) + matvec_row<D, TIn>(Bp, s_u, tid);
+      const float xn = matvec_row_lds<D>(WL, s_x, tid) + matvec_row_lds<D>(WR, s_u, tid);
       if (part == 0) {
         cpart += s_u[r] * ru;
         s_xn[r] = xn;

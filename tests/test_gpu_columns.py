@@ -1,4 +1,5 @@
-"""The Riccati step by columns and its block-pivoted dense solve (time-heterogeneous solve and roll-out), against the float64 recursion.
+"""The Riccati step by columns and its block-pivoted dense solve (time-heterogeneous solve and roll-out, time-invariant
+roll-out), against the float64 recursion.
 
 Tolerance of the cheap-control cases: the float32 error of P and K is proportional to cond(S), S = R + B^T P B, times the
 unit roundoff; the same recursion in float32 on the CPU stays below 1.4 of that product over these cases, and 4 are allowed."""
@@ -36,7 +37,7 @@ def test_cheap_control(d, T, n, r_scale):
     ref = lqr_oracle.riccati_solve(*b.numpy64()[:4], None, b.numpy64()[4], T)
     steps = [m[:, None].expand(-1, T, -1, -1) for m in (b.A, b.B, b.Q, b.R)]
     tv = binding.ttc_lqr_solve_tv(*steps, b.x0)
-    ro = binding.ttc_lqr_rollout_tv(*steps, b.x0)
+    ro = binding.ttc_lqr_rollout(b.A, b.B, b.Q, b.R, None, b.x0, T)
     torch.cuda.synchronize()
     assert not tv["info"].any() and not ro["info"].any()
     for k in ("P0", "K0"):
@@ -65,3 +66,34 @@ def test_a_breakdown_in_any_pivot_block_is_reported_for_its_own_problem(d):
     out = binding.ttc_lqr_solve_tv(b.A, b.B, b.Q, R, b.x0)
     assert torch.equal(out["K0"][0::2], good["K0"][0::2]) and torch.isnan(out["K0"][1::2]).all()
 
+
+@pytest.mark.parametrize("d", [16, 32, 64, 128])
+def test_rollout_of_indefinite_costs_and_broken_R(d):
+    """A stage cost that leaves R + B^T P B indefinite but regular is answered (the pivoted sweep: the stationary point);
+    an R that is not positive definite is refused as the first solve."""
+    n, T = 5, 2
+    b = synth.make_batch(n, d, d, T, seed=d, device=DEV)
+    B = 0.1 * b.B + torch.eye(d, device=DEV)
+    R = torch.eye(d, device=DEV).repeat(n, 1, 1)
+    Q = b.Q.clone()
+    Q[1] = torch.diag(torch.where(torch.arange(d, device=DEV) % 3 == 0, -6.0, 3.0))
+    R[3, d - 2, d - 2] = -1.0
+    out = binding.ttc_lqr_rollout(b.A, B, Q, R, None, b.x0, T)
+    torch.cuda.synchronize()
+    assert out["info"].tolist() == [0, 0, 0, 1, 0] and torch.isnan(out["U"][3]).all()
+    A, B, Q, R, x0 = (t.double().cpu().numpy() for t in (b.A, B, Q, R, b.x0))
+    keep = [0, 2, 4]
+    U, _, _ = lqr_oracle.riccati_rollout(A[keep], B[keep], Q[keep], R[keep], None, x0[keep], T)
+    assert rel_err(out["U"][keep].cpu().numpy(), U).max() <= 1e-4
+    # problem 1, whose S the oracle's Cholesky factorisation does not take: the same recursion with a general solve
+    A, B, Q, R, x = A[1], B[1], Q[1], R[1], x0[1]
+    P, K = Q, []
+    for _ in range(T):
+        S, F = R + B.T @ P @ B, B.T @ P @ A
+        assert np.linalg.eigvalsh(S).min() < 0 and np.linalg.cond(S) < 10
+        K.insert(0, -np.linalg.solve(S, F))
+        P = Q + A.T @ P @ A + F.T @ K[0]
+    for t in range(T):
+        u = K[t] @ x
+        assert np.linalg.norm(out["U"][1, t].double().cpu().numpy() - u) <= 1e-4 * np.linalg.norm(u)
+        x = A @ x + B @ u
