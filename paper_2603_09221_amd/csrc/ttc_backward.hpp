@@ -198,7 +198,7 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, TTC_COLS_WAVES(D)) backward_kern
 #pragma unroll
         for (int r = 0; r < C::NT; ++r) f[r][0] = *reinterpret_cast<const floatx4*>((i ? v_ut : v_u) + 16 * r + 4 * g);
       }
-      const int flag = spd_solve_cols<D, 1>(WR, s0, f, w, lane);
+      const int flag = solve_cols<D, 1>(WR, s0, f, w, lane);
       if (flag && !info) info = T;
       if (w == 0 && i < 2) {
 #pragma unroll

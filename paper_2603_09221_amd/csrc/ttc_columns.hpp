@@ -116,8 +116,8 @@ __device__ __forceinline__ void gemm_cols(floatx4 (&acc)[D / 16][CT], const floa
   });
 }
 
-// Dense solve f <- s^{-1} f for a symmetric positive definite s, both by columns (f: FT column tiles a wavefront, also none):
-// block Gauss-Jordan with 16 x 16 pivot blocks and no pivot search.  Per block p, the wavefront that owns its columns
+// Dense solve f <- s^{-1} f, both by columns (f: FT column tiles a wavefront, also none), for a symmetric positive definite s,
+// or any whose elimination in order meets pivots above piv_min only: block Gauss-Jordan with 16 x 16 pivot blocks and no pivot search.  Per block p, the wavefront that owns its columns
 // inverts s[p][p] in registers and publishes that inverse and the rest of the column, negated, as left operands (Wp: the
 // right half of the pair); every wavefront then does its own columns, U = s[p][p]^{-1} s[p][c], s[r][c] -= s[r][p] U,
 // the next block's first, so that its inverse is formed and published under the others' updates: one workgroup barrier
@@ -126,24 +126,31 @@ __device__ __forceinline__ void gemm_cols(floatx4 (&acc)[D / 16][CT], const floa
 // With d <= 32 the explicit inverse alone loses up to a factor of three where control is cheap (the block is most of the
 // matrix); there one step of refinement, U += s[p][p]^{-1} (s[p][c] - s[p][p] U), restores a factor-and-solve's accuracy;
 // from d = 64 on it makes no difference (measured against float64, cost ratios 1 to 1e4).
-// Returns, uniformly, whether a pivot was not positive and finite.  Wp must be free to every wavefront on entry; its last
+// Returns, uniformly, whether a pivot was not above piv_min and finite.  Wp must be free to every wavefront on entry; its last
 // reads may still be under way in other wavefronts on return.
 template <int D, int FT>
-__device__ __forceinline__ int spd_solve_cols(float* Wp, Cols<D>& s, floatx4 (&f)[D / 16][FT > 0 ? FT : 1], int w, int lane) {
+__device__ __forceinline__ int solve_cols(float* Wp, Cols<D>& s, floatx4 (&f)[D / 16][FT > 0 ? FT : 1], int w, int lane,
+                                          float piv_min = 0.f) {
   using C = Cfg<D>;
   constexpr int NT = C::NT, CT = C::RB;
-  constexpr bool REFINE = C::NW == 1;  // d <= 32: one wavefront, which holds the pivot block's operands itself
+  constexpr bool REFINE = D <= 32;
+  static_assert(!REFINE || C::NW == 1, "the refinement's operand stays in the wavefront that published the block");
   const int i = lane & 15, g = lane >> 4;
   w = uniform(w);
   int bad = 0;
-  floatx4 di_own, d_own;  // REFINE: the A operands of the inverse and of minus the block
+  floatx4 d_neg;  // REFINE: minus the pivot block, as a left operand
   auto publish = [&](auto P) {  // by the wavefront that owns column tile p
     constexpr int p = decltype(P)::value, k = p % CT;
-    floatx4 inv = s[p][k];
-    if constexpr (REFINE) d_own = -s[p][k];
-    bad |= invert_spread16(inv, lane);
-    if constexpr (REFINE) di_own = inv;
     float* const o = Wp + 4 * g * C::PITCH + 16 * (p & 1) + i;
+    if constexpr (REFINE) {  // through the tile the inverse goes to below (a wavefront's LDS operations run in order)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) o[(16 * p + v) * C::PITCH] = -s[p][k][v];
+      wave_lds_sync();
+      d_neg = *reinterpret_cast<const floatx4*>(Wp + (16 * p + i) * C::PITCH + 16 * (p & 1) + 4 * g);
+      wave_lds_sync();
+    }
+    floatx4 inv = s[p][k];
+    bad |= invert_spread16(inv, lane, piv_min);
 #pragma unroll
     for (int r = 0; r < NT; ++r) {
       const floatx4 x = r == p ? inv : -s[r][k];
@@ -154,17 +161,14 @@ __device__ __forceinline__ int spd_solve_cols(float* Wp, Cols<D>& s, floatx4 (&f
   auto column = [&](auto P, const floatx4 (&x)[NT], auto& m, auto K) {
     constexpr int p = decltype(P)::value, k = decltype(K)::value;
     floatx4 u = floatx4{0.f, 0.f, 0.f, 0.f};
-    if constexpr (REFINE) {
 #pragma unroll
-      for (int t = 0; t < 4; ++t) u = __builtin_amdgcn_mfma_f32_16x16x4f32(di_own[t], m[p][k][t], u, 0, 0, 0);
+    for (int t = 0; t < 4; ++t) u = __builtin_amdgcn_mfma_f32_16x16x4f32(x[p][t], m[p][k][t], u, 0, 0, 0);
+    if constexpr (REFINE) {
       floatx4 res = m[p][k];
 #pragma unroll
-      for (int t = 0; t < 4; ++t) res = __builtin_amdgcn_mfma_f32_16x16x4f32(d_own[t], u[t], res, 0, 0, 0);
+      for (int t = 0; t < 4; ++t) res = __builtin_amdgcn_mfma_f32_16x16x4f32(d_neg[t], u[t], res, 0, 0, 0);
 #pragma unroll
-      for (int t = 0; t < 4; ++t) u = __builtin_amdgcn_mfma_f32_16x16x4f32(di_own[t], res[t], u, 0, 0, 0);
-    } else {
-#pragma unroll
-      for (int t = 0; t < 4; ++t) u = __builtin_amdgcn_mfma_f32_16x16x4f32(x[p][t], m[p][k][t], u, 0, 0, 0);
+      for (int t = 0; t < 4; ++t) u = __builtin_amdgcn_mfma_f32_16x16x4f32(x[p][t], res[t], u, 0, 0, 0);
     }
 #pragma unroll
     for (int t = 0; t < 4; ++t)
@@ -222,6 +226,34 @@ __device__ __forceinline__ int spd_solve_cols(float* Wp, Cols<D>& s, floatx4 (&f
   }
 }
 
+// The same on the pair in LDS, [M | RHS] (visible): the right half becomes M^{-1} RHS, the left half is left as it was.
+// RHS = false only reports the pivots (the right half is overwritten all the same).
+template <int D, bool RHS = true>
+__device__ __forceinline__ int solve_pair_in_order(float* W, float piv_min, int tid) {
+  using C = Cfg<D>;
+  tid += opaque_zero();
+  const int lane = tid & 63, w = uniform(tid >> 6), i = lane & 15, g = lane >> 4;
+  float* const WR = W + D;
+  Cols<D> m;
+  floatx4 f[C::NT][RHS ? C::RB : 1];
+  auto read = [&](const float* L, auto& c) {
+    const float* const o = L + 4 * g * C::PITCH + 16 * C::RB * w + i;
+#pragma unroll
+    for (int r = 0; r < C::NT; ++r)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int k = 0; k < C::RB; ++k) c[r][k][v] = o[(16 * r + v) * C::PITCH + 16 * k];
+  };
+  read(W, m);
+  if constexpr (RHS) read(WR, f);
+  lds_barrier();
+  const int flag = solve_cols<D, RHS ? C::RB : 0>(WR, m, f, w, lane, piv_min);
+  if constexpr (RHS) store_cols<D>(WR, C::PITCH, f, w, i, g);
+  lds_barrier();
+  return flag;
+}
+
 // One backward step of Prop. 3.1 with the matrices of one step.  On entry the right half of the pair holds P_{s+1}
 // (symmetric, visible) and the left half is free; on exit, by columns, wk = S^{-1} B^T P A = -K_s, S = R + B^T P B, and
 // pn = A^T P A - (B^T P A)^T wk, which is P_s up to the stage cost.  Six products and one unpivoted solve (S is positive
@@ -261,7 +293,7 @@ __device__ __forceinline__ int riccati_step(float* W, const TIn* As, const TIn* 
     gemm_cols<D>(pn, WR, pa, i, g);  // A^T P A
   }
   lds_barrier();
-  const int flag = spd_solve_cols<D, C::RB>(WR, s, wk, w, lane);  // W = S^{-1} F
+  const int flag = solve_cols<D, C::RB>(WR, s, wk, w, lane);  // W = S^{-1} F
   gemm_cols<D>(pn, WL, wk, i, g);                                 // - F^T W
   return flag;
 }

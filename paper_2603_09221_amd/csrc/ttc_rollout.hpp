@@ -168,10 +168,10 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, TTC_COLS_WAVES(D)) rollout_kerne
       const int tb = tid + opaque_zero(), lane = tb & 63, w = uniform(tb >> 6), i = lane & 15, g = lane >> 4;
       {
         Cols<D> r;
-        floatx4 none[C::NT][1];
+        floatx4 none[C::NT][1];  // no right-hand sides
         zero_cols<D>(r);
         add_sym_cols<D, TIn>(Rp, r, w, i, g);
-        info = spd_solve_cols<D, 0>(WR, r, none, w, lane);
+        info = solve_cols<D, 0>(WR, r, none, w, lane);
       }
       __syncthreads();
       if (!info) {

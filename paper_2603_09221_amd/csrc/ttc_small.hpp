@@ -189,8 +189,8 @@ __device__ __forceinline__ float broadcast_group(float x) {
 // accumulator layout) and ends with the same entries of the inverse, which is its A operand, so that nothing passes
 // through LDS.  Columns are taken four at a time: the four columns of a group are copied to every group first, where they
 // are kept up to date beside the lane's own four; a column then costs seven multiply-adds instead of fifteen.  Every entry
-// sees the operations of invert_regs16 in the same order.
-__device__ __forceinline__ int invert_spread16(floatx4& m, int lane) {
+// sees the operations of invert_regs16 in the same order.  A pivot that is not above piv_min is reported.
+__device__ __forceinline__ int invert_spread16(floatx4& m, int lane, float piv_min = 0.f) {
   const int g = lane >> 4;
   float a[4] = {m[0], m[1], m[2], m[3]};
   float mypiv = 1.f;
@@ -239,7 +239,7 @@ __device__ __forceinline__ int invert_spread16(floatx4& m, int lane) {
   });
   const float s = __builtin_amdgcn_rcpf(mypiv);
   m = floatx4{a[0] * s, a[1] * s, a[2] * s, a[3] * s};
-  return !(mypiv > 0.f && mypiv < __builtin_inff());
+  return !(mypiv > piv_min && mypiv < __builtin_inff());
 }
 
 // The same in place in LDS: the left halves of Wm[q] (row r at Wq + r*PITCH), by a workgroup of one wavefront.  The

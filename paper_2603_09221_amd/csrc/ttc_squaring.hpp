@@ -14,6 +14,7 @@
 // the dense solves, as solve_kernel's constants are; LDS holds the pair a product or solve works on; the one workspace
 // slot of the workgroup holds P while the bits of T still have squarings between them (never for T a power of two).
 // A^{-1} is not needed, but a singular A is reported as before (info = 2): A is factored, without right-hand sides.
+// The dense solves eliminate in order (solve_cols) where that is safe, and search pivots where it is not.
 #pragma once
 #include "ttc_doubling.hpp"
 #include "ttc_tv.hpp"
@@ -32,10 +33,18 @@ __device__ __forceinline__ void add_aop_lds(const float* Wh, float (&rows)[Cfg<D
     for (int k = 0; k < C::KS; ++k) rows[rb][k] += t[rb][k];
 }
 
+// Both I + G_e H_e and I + P G_e have the eigenvalues of I plus a positive semidefinite matrix, so elimination in order
+// meets no small pivot on the problems the guard lets through (CPU, float64: pivots of 1.2 and more, random semidefinite
+// pairs and the benchmark's): the solve is solve_cols, without a pivot search.  A pivot below PIVOT_MIN (a stage cost that is
+// not semidefinite, say) starts the problem over with pivoted solves.  A is tried the same way; a pivot below PIVOT_MIN_A
+// leaves the report to the pivoted factorisation.
+static constexpr float PIVOT_MIN = 0.25f, PIVOT_MIN_A = 0.015625f;
+
 // One row block per wavefront at d = 128 (build.py: with two, 448 of the 512 registers hold matrices and the solves spill:
 // 31.9 against 4.5 ms for 2048 problems, T = 16), two at d = 64 (2.31 against 2.84 ms for 8192 problems, T = 16).
-// Measured against solve_kernel: d = 64, T = 64, 4099 problems 10.3 -> 2.2 ms; d = 128, T = 16, 8192 problems 25.5 -> 18.2 ms;
-// d = 128, T = 32, bfloat16 inputs, 4096 problems 21.3 -> 10.7 ms; errors against float64 5e-6..1.3e-5 -> 1e-6..2e-6.
+// Measured against solve_kernel, and with pivoted solves throughout: d = 64, T = 8, 16384 problems 4.24 -> 3.74 -> 3.32 ms;
+// T = 64, 4099 problems 10.4 -> 1.71 -> 1.56 ms; d = 128, T = 16, 8192 problems 25.5 -> 17.5 -> 16.8 ms; d = 128, T = 32,
+// bfloat16 inputs, 4096 problems 21.3 -> 10.7 -> 10.0 ms; errors against float64 5e-6..1.3e-5 -> 1e-6..2e-6.
 template <int D, typename TIn>
 __global__ void __launch_bounds__(Cfg<D>::NTHR, (D == 64 ? 2 : 1)) squaring_kernel(const DoublingArgs da) {
   using C = Cfg<D>;
@@ -48,6 +57,7 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D == 64 ? 2 : 1)) squaring_kern
   float* const WR = W + D;
   float* const wsP = p.ws + (long)blockIdx.x * D * D;  // P, rows in register layout
 
+  bool pivoted = false;  // this problem is done again, with pivoted solves
   for (long long prob = blockIdx.x; prob < p.n; prob += gridDim.x) {
     const int tid = threadIdx.x + opaque_zero(), lane = tid & 63, w = tid >> 6, i = lane & 15, g = lane >> 4;
     const TIn* Ap = reinterpret_cast<const TIn*>(p.A) + prob * p.sA;
@@ -73,6 +83,14 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D == 64 ? 2 : 1)) squaring_kern
       return uniform(bad) != 0;
     };
 
+    // the dense solve of the pair; false: a pivot below PIVOT_MIN, and the problem starts over with pivoting
+    auto dense = [&] {
+      ++nsolve;
+      if (!pivoted) return solve_pair_in_order<D>(W, PIVOT_MIN, tid) == 0;
+      if (lds_solve<D>(W, S, tid) && !info) info = nsolve;
+      return true;
+    };
+
     // ---- set-up: X = R^{-1} B^T, G = B X, A (factored for its report), H = Q, P = Q_T when it is a matrix of its own
     load_half<D, TIn, false>(WL, Rp, tid);
     load_half<D, TIn, false>(WR, Bp, tid);
@@ -80,7 +98,8 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D == 64 ? 2 : 1)) squaring_kern
     symmetrise_half<D>(WL, tid);
     transpose_half<D>(WR, w, i, g);
     ++nsolve;
-    if (lds_solve<D, 7, false>(W, S, tid) && !info) info = nsolve;  // R is positive definite: no pivot search
+    __syncthreads();
+    if (solve_pair_in_order<D>(W, 0.f, tid)) info = nsolve;  // R is positive definite
     load_aop_lds<D>(WR, rX, w, i, g);
     // G = B X into the left half, exactly symmetric (X in the right half)
     auto form_G = [&] {
@@ -104,7 +123,7 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D == 64 ? 2 : 1)) squaring_kern
     __syncthreads();
     load_aop_lds<D>(WR, rH, w, i, g);
     ++nsolve;
-    if (lds_factor<D>(W, S, tid) && !info) info = nsolve;
+    if (solve_pair_in_order<D, false>(W, PIVOT_MIN_A, tid) && lds_factor<D>(W, S, tid) && !info) info = nsolve;
     bool have_p = da.p_from_qt != 0;
     if (have_p) {
       load_half<D, TIn, false>(WR, QTp, tid);
@@ -118,7 +137,8 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D == 64 ? 2 : 1)) squaring_kern
     }
 
     // [I + P G | P A] with P's rows in c, G and A as the halves hold them, then the solve: the right half becomes
-    // (I + P G)^{-1} P A
+    // (I + P G)^{-1} P A.  False: over the limit, or (again) a small pivot
+    bool again = false;
     auto mobius = [&](const float(&c)[C::RB][C::KS]) {
       eye_acc<D>(acc, w, i, g);
       gemm_acc<D>(acc, c, WL, i, g);
@@ -131,9 +151,7 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D == 64 ? 2 : 1)) squaring_kern
       __syncthreads();
       store_rows<D>(WR, acc, w, i, g);
       __syncthreads();
-      ++nsolve;
-      if (lds_solve<D>(W, S, tid) && !info) info = nsolve;
-      return true;
+      return (again = !dense()) == false;
     };
     // rows[rb][k] <- rH + A_e^T (the matrix in the right half), through the left half (rows may be rH itself)
     auto apply_AT = [&](float (&rows)[C::RB][C::KS]) {
@@ -156,7 +174,7 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D == 64 ? 2 : 1)) squaring_kern
 
     // ---- P_1 by binary powering of the one-step map (see ttc_doubling.hpp)
     bool p_is_H = false;  // P_1 = H_e: the last bit met no P
-    for (int m = da.m; m && !hard;) {
+    for (int m = da.m; m && !hard && !again;) {
       if (m & 1) {
         if (!have_p) {
           have_p = true;
@@ -169,7 +187,7 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D == 64 ? 2 : 1)) squaring_kern
           store_aop_lds<D>(WR, rA, w, i, g);
           __syncthreads();
           if (!mobius(c)) {
-            hard = true;
+            hard = !again;
             break;
           }
           apply_AT(c);  // P <- H_e + A_e^T (I + P G_e)^{-1} P A_e
@@ -194,8 +212,10 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D == 64 ? 2 : 1)) squaring_kern
       if (only_H) store_aop_lds<D>(WR, rA, w, i, g);
       else set_half_identity<D>(WR, tid);
       __syncthreads();
-      ++nsolve;
-      if (lds_solve<D>(W, S, tid) && !info) info = nsolve;  // right half: M = (I + G H)^{-1}, or M A
+      if (!dense()) {  // right half: M = (I + G H)^{-1}, or M A
+        again = true;
+        break;
+      }
       if (only_H) {
         zero_acc<D>(acc);
         gemm_acc<D>(acc, rH, WR, i, g);  // V = H M A
@@ -254,7 +274,7 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D == 64 ? 2 : 1)) squaring_kern
     }
 
     // ---- last step with the problem's own (A, G): M_1 = (I + P_1 G)^{-1} P_1 A, P_0 = A^T M_1, -K_0 = X M_1
-    if (!hard) {
+    if (!hard && !again) {
       float c[C::RB][C::KS];
       if (p_is_H) {
 #pragma unroll
@@ -269,8 +289,15 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D == 64 ? 2 : 1)) squaring_kern
       form_G();
       load_half<D, TIn, false>(WR, Ap, tid);
       __syncthreads();
-      hard = !mobius(c);
+      hard = !mobius(c) && !again;
     }
+    if (again) {
+      pivoted = true;
+      prob -= gridDim.x;
+      __syncthreads();  // every wavefront has left the pair
+      continue;
+    }
+    pivoted = false;
     if (hard) {
       __syncthreads();  // every wavefront has left the pair
       if (info) {       // a set-up breakdown keeps its report

@@ -129,3 +129,33 @@ def test_noalloc_takes_the_same_path():
         ref = solve(b)
         for k in SOLVE_KEYS:
             assert torch.equal(out[k], ref[k]), k
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,n", [(32, 7), (64, 1100), (128, 7)])
+@pytest.mark.parametrize("T", [8, 12])
+def test_a_small_pivot_starts_the_problem_over_with_pivoting(d, n, T):
+    """A stage cost that is not semidefinite: elimination of I + G H in order meets negative pivots, although the problem
+    is well conditioned and below the guard's limit (float32 on the CPU: errors below 1e-6).  Its neighbours, also those the
+    same workgroup takes next, come out as they do alone."""
+    b = synth.make_batch(n, d, d, T, seed=d, device=DEV)
+    B = 0.1 * b.B + torch.eye(d, device=DEV)
+    R = torch.eye(d, device=DEV).repeat(n, 1, 1)
+    Q = b.Q.clone()
+    Q[1] = torch.diag(torch.where(torch.arange(d, device=DEV) % 3 == 0, -6.0, 1.0))
+    out = solve(synth.LqrBatch(b.A, B, Q, R, b.x0, T))
+    assert not out["info"].any()
+    A1, B1, Q1, R1 = (t[1].double().cpu().numpy() for t in (b.A, B, Q, R))
+    P = Q1
+    for s in range(T - 1, -1, -1):  # the printed recursion with a general solve
+        S, F = R1 + B1.T @ P @ B1, B1.T @ P @ A1
+        assert np.linalg.eigvalsh(S).min() < 0 and np.linalg.cond(S) < 10
+        K = -np.linalg.solve(S, F)
+        P = (Q1 if s else 0) + A1.T @ P @ A1 + F.T @ K
+        P = 0.5 * (P + P.T)
+    for k, want in (("P0", P), ("K0", K)):
+        assert np.linalg.norm(out[k][1].double().cpu().numpy() - want) <= 2e-5 * np.linalg.norm(want), k
+    alone = solve(synth.LqrBatch(b.A, B, b.Q, R, b.x0, T))
+    keep = torch.arange(n, device=DEV) != 1
+    for k in SOLVE_KEYS:
+        assert torch.equal(out[k][keep], alone[k][keep]), k
