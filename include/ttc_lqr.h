@@ -138,7 +138,7 @@ size_t ttc_lqr_noalloc_scratch_bytes(void);
 /* Full optimal trajectory (Alg. 1, forward loop, r = 0): U (n, T, m) controls u_0..u_{T-1},
  * X (n, T+1, d) states x_0..x_T, cost (n) = sum_t u_t^T R u_t + sum_{t=1}^{T-1} x_t^T Q x_t +
  * x_T^T Q_T x_T (+ x_0^T Q x_0 with TTC_FLAG_STAGE_COST_AT_X0), which equals `value` of
- * ttc_lqr_solve.  The gains K_t are produced by a re-based backward sweep and kept in the
+ * ttc_lqr_solve.  The gains K_t are produced by the backward recursion of Prop. 3.1 and kept in the
  * workspace.  X, cost and info may be NULL.  Same conventions and error behaviour as above. */
 ttc_status_t ttc_lqr_rollout(const ttc_lqr_problem_t *problem, float *U, float *X, float *cost,
                              int32_t *info, void *workspace, size_t workspace_bytes,
