@@ -44,9 +44,10 @@ static constexpr float PIVOT_MIN = 0.25f, PIVOT_MIN_A = 0.015625f;
 // 31.9 against 4.5 ms for 2048 problems, T = 16), two at d = 64 (2.31 against 2.84 ms for 8192 problems, T = 16).
 // Measured against solve_kernel, and with pivoted solves throughout: d = 64, T = 8, 16384 problems 4.24 -> 3.74 -> 3.32 ms;
 // T = 64, 4099 problems 10.4 -> 1.71 -> 1.56 ms; d = 128, T = 16, 8192 problems 25.5 -> 17.5 -> 16.8 ms; d = 128, T = 32,
-// bfloat16 inputs, 4096 problems 21.3 -> 10.7 -> 10.0 ms; errors against float64 5e-6..1.3e-5 -> 1e-6..2e-6.
+// bfloat16 inputs, 4096 problems 21.3 -> 10.7 -> 10.0 ms; d = 32, T = 16, 8192 problems 0.85 -> 0.38 ms with registers held
+// to two wavefronts a SIMD (0.50 with one); errors against float64 5e-6..1.3e-5 -> 1e-6..2e-6.
 template <int D, typename TIn>
-__global__ void __launch_bounds__(Cfg<D>::NTHR, (D == 64 ? 2 : 1)) squaring_kernel(const DoublingArgs da) {
+__global__ void __launch_bounds__(Cfg<D>::NTHR, (D <= 64 ? 2 : 1)) squaring_kernel(const DoublingArgs da) {
   using C = Cfg<D>;
   __shared__ __attribute__((aligned(16))) float W[D * C::PITCH];
   __shared__ __attribute__((aligned(16))) SolveScratch<D> S;
