@@ -15,7 +15,8 @@
  * ceil(T/k) groups of nearly equal length (the paper's algorithm is one group, rebase_every >= T).
  * At d >= 32, from horizons on at which it is cheaper (all T from 16 on, some from 8 on), the T equal factors are instead
  * composed by squaring (the algebra described at TTC_FLAG_DOUBLING; rebase_every must be 0): more accurate on
- * ordinary problems, and watched by a guard of its own on max |I + G_e H_e|, with the same way out as below.
+ * ordinary problems, and watched by a guard of its own on max |I + G_e H_e|.  What it cannot do is solved by a second launch
+ * behind it: by the recursion as below, or (stage costs that are not semidefinite, breakdowns) by the product.
  * A growth guard watches max |Y1| inside every group (Y1 starts a group as the identity): a group that
  * is about to pass the limit is ended early, and a problem whose pair has passed it is solved instead
  * by the recursion of Prop. 3.1 in its printed form (one positive definite solve per step, as
@@ -104,8 +105,7 @@ typedef struct {
   float *u0;     /* (n, m)    first optimal control u0 = K0 x0 (the layer's output o)               */
   float *value;  /* (n)       x0^T P0 x0 = 2x the optimal objective of Eq. "ttc"                    */
   int32_t *info; /* (n)       0 = ok; s > 0 = the s-th dense solve of that problem broke down
-                               (1: R^{-1}B^T, 2: A^{-1} (when composing by squaring: a factorisation of A), 3..: re-bases,
-                               or the solves of the squarings, in order; the last yields P0;
+                               (1: R^{-1}B^T, 2: A^{-1}, 3..: re-bases in order; the last yields P0;
                                for a problem the growth guard handed to the recursion of Prop. 3.1:
                                2 + the index of the step, counted from the end of the horizon)      */
 } ttc_lqr_solution_t;

@@ -146,7 +146,7 @@ static bool qt_is_q(const ttc_lqr_problem_t* q) { return !q->QT || (q->QT == q->
 static bool use_squaring(const ttc_lqr_problem_t* q) {
   if (q->d < 32 || (q->flags & (TTC_FLAG_DOUBLING | TTC_FLAG_PURE_SYMPLECTIC)) || q->rebase_every != 0) return false;
   const bool from_zero = qt_is_q(q);
-  const unsigned m = (unsigned)(from_zero ? q->T : q->T - 1);
+  const int m = from_zero ? q->T : q->T - 1;
   if (m < 2) return false;
   const int squarings = 31 - __builtin_clz(m), applications = __builtin_popcount(m) - (from_zero ? 1 : 0);
   const long long cost = 100 * squarings + 70 * applications + (applications ? 35 : 0) + 10;
@@ -194,6 +194,14 @@ static hipError_t run_solve(const SolveArgs& a, int d, bool bf16, dim3 grid, hip
     case 32: return launch_solve<32>(a, bf16, grid, st);
     case 64: return launch_solve<64>(a, bf16, grid, st);
     case 128: return launch_solve<128>(a, bf16, grid, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+static hipError_t run_solve_handed(const SolveArgs& a, int d, bool bf16, dim3 grid, hipStream_t st) {
+  switch (d) {
+    case 32: return launch_solve_handed<32>(a, bf16, grid, st);
+    case 64: return launch_solve_handed<64>(a, bf16, grid, st);
+    case 128: return launch_solve_handed<128>(a, bf16, grid, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -331,6 +339,7 @@ ttc_status_t ttc_lqr_solve(const ttc_lqr_problem_t* problem, const ttc_lqr_solut
     const long long gs = ttc::grid_blocks(ttc::KIND_SQUARING, problem->d, bf16);
     const long long blocks = gs < gb ? gs : gb;
     e = ttc::run_squaring(da, problem->d, bf16, dim3((unsigned)(problem->n < blocks ? problem->n : blocks)), s);
+    if (e == hipSuccess) e = ttc::run_solve_handed(a, problem->d, bf16, grid, s);  // the problems it gave up, usually none
   } else if (quad) {
     e = ttc::launch_small(a, bf16, 4, grid, s);
   } else if (small) {  // a batch that does not fill the chip: one problem to a wavefront

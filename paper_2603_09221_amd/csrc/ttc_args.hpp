@@ -5,6 +5,11 @@
 
 namespace ttc {
 
+// What squaring_kernel leaves in the first word of a problem's u_0 where it gives a problem up, for solve_handed_kernel
+// behind it to find: signalling NaNs, which no arithmetic produces.  The guard's problems go to the recursion of Prop. 3.1
+// first, the others (a small pivot, a set-up breakdown) straight to the sequential product.
+constexpr uint32_t HANDED_TO_RECURSION = 0x7FA17C0Du, HANDED_TO_PRODUCT = 0x7FA17C0Eu;
+
 struct SolveArgs {
   long long n;
   int T, flags, ngroups;  // the T factors are applied in ngroups groups, one dense solve each

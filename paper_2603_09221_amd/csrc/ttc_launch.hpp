@@ -11,6 +11,7 @@ namespace ttc {
 // launch_*: enqueue the kernel on `st` with `grid` workgroups; bf16 selects the bfloat16-input instance.
 // occupancy_*: resident workgroups per compute unit the runtime reports for that instance (0 on error).
 template <int D> hipError_t launch_solve(const SolveArgs& a, bool bf16, dim3 grid, hipStream_t st);
+template <int D> hipError_t launch_solve_handed(const SolveArgs& a, bool bf16, dim3 grid, hipStream_t st);
 template <int D> int occupancy_solve(bool bf16);
 template <int D> hipError_t launch_doubling(const DoublingArgs& a, bool bf16, dim3 grid, hipStream_t st);
 template <int D> int occupancy_doubling(bool bf16);

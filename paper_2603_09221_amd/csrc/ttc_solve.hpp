@@ -8,6 +8,20 @@
 #endif
 namespace ttc {
 
+// The number of the first thread of the workgroup with `yes`, or how many threads there are; the same in every thread.
+template <int NW>
+__device__ __forceinline__ int first_thread(bool yes, int* s_first) {
+  const unsigned long long b = __ballot(yes);
+  if ((threadIdx.x & 63) == 0) s_first[threadIdx.x >> 6] = b ? (int)__builtin_ctzll(b) : 64;
+  __syncthreads();
+  int first = 64 * NW;
+#pragma unroll
+  for (int w = NW - 1; w >= 0; --w)
+    if (s_first[w] < 64) first = 64 * w + s_first[w];
+  __syncthreads();
+  return uniform(first);
+}
+
 // Solve kernel.  Persistent workgroups: workgroup b handles problems b, b + gridDim.x, ...
 //
 // Per problem the work is a sequence of phases, each "build [M | RHS] in LDS, dense solve, consume":
@@ -21,13 +35,18 @@ namespace ttc {
 // The row blocks of G, A^T, Q and A^{-1} go from LDS straight into registers as they are produced and
 // stay there to the end of the problem; only C_K, needed once at the very end, waits in the workspace.
 // Global reads are started a phase ahead of their use where registers allow.
-template <int D, typename TIn>
-__global__ void __launch_bounds__(Cfg<D>::NTHR, (D == 64 ? TTC_D64_WAVES : 1)) solve_kernel(const SolveArgs p) {
+//
+// HANDED: only the problems that squaring_kernel has marked.  Those of its guard take the recursion first; one whose
+// R + B^T P B is not positive definite there (a stage cost that is not semidefinite) takes the symplectic iteration, whose
+// solves are pivoted and ask for nothing but non-singular matrices.
+template <int D, typename TIn, bool HANDED = false>
+__device__ __forceinline__ void solve_problems(const SolveArgs& p) {
   using C = Cfg<D>;
   __shared__ __attribute__((aligned(16))) float W[D * C::PITCH];
   __shared__ __attribute__((aligned(16))) SolveScratch<D> S;
   __shared__ float s_red[C::NW];
   __shared__ float s_growth[C::NW];  // per wavefront: max |Y1| after the step just taken
+  __shared__ int s_first[HANDED ? C::NW : 1];
 
   float* const WL = W;      // left half  (Z1 / Y1 / M of a dense solve)
   float* const WR = W + D;  // right half (Z2 / Y2 / RHS)
@@ -35,7 +54,25 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D == 64 ? TTC_D64_WAVES : 1)) s
   float* const wsC = p.ws + (long)blockIdx.x * D * D;
   const bool pure = (p.flags & TTC_FLAG_PURE_SYMPLECTIC) != 0;
 
+  bool retry = false;  // HANDED: the recursion has failed this problem
   for (long long prob = blockIdx.x; prob < p.n; prob += gridDim.x) {
+    bool hard = false;  // the growth guard tripped: this problem goes to the Riccati recursion instead
+    bool recursion = false;
+    if constexpr (HANDED) {
+      if (!retry) {  // on to the next problem that is marked, a thread looking at one each
+        const long long mine = prob + (long long)threadIdx.x * gridDim.x;
+        const uint32_t mark = mine < p.n ? reinterpret_cast<const uint32_t*>(p.u0)[mine * D] : 0u;
+        const int first = first_thread<C::NW>(mark == HANDED_TO_RECURSION || mark == HANDED_TO_PRODUCT, s_first);
+        prob += (long long)first * gridDim.x;
+        if (first == C::NTHR) {
+          prob -= gridDim.x;
+          continue;
+        }
+        recursion = uniform((int)reinterpret_cast<const uint32_t*>(p.u0)[prob * D]) == (int)HANDED_TO_RECURSION;
+        __syncthreads();  // every wavefront has read the mark
+      }
+      retry = false;
+    }
     // (the opaque zero keeps the address arithmetic of a problem from being hoisted out of this loop and spilled)
     const int tid = threadIdx.x + opaque_zero(), lane = tid & 63, w = tid >> 6, i = lane & 15, g = lane >> 4;
     const TIn* Ap = reinterpret_cast<const TIn*>(p.A) + prob * p.sA;
@@ -47,11 +84,11 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D == 64 ? TTC_D64_WAVES : 1)) s
     int s = 1;          // next reverse step (1 .. T; step s applies Sigma_{T-s+1})
     int grp = 0;        // current group of steps
     bool fresh = true;  // Z1 = I, not materialised
-    bool hard = false;  // the growth guard tripped: this problem goes to the Riccati recursion instead
     int plan_base = 0, plan_T = p.T, plan_ng = p.ngroups;  // grouping of the steps after plan_base
     // the constant row blocks, in registers from here to the end of the problem
     float cG[C::RB][C::KS], cAi[C::RB][C::KS], cAT[C::RB][C::KS], cQ[C::RB][C::KS];
 
+    if (!HANDED || !recursion) {
     // ---------------------------------------------------------------- phase R: X = R^{-1} B^T, G = B X
     load_half<D, TIn, false>(WL, reinterpret_cast<const TIn*>(p.R) + prob * p.sR, tid);
     load_half<D, TIn, false>(WR, reinterpret_cast<const TIn*>(p.B) + prob * p.sB, tid);
@@ -202,16 +239,21 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D == 64 ? TTC_D64_WAVES : 1)) s
       ++grp;
       if (s > p.T) break;
     }
+    }
 
-    if (hard) {
+    if (hard || recursion) {
       // Prop. 3.1 as printed, from P_T: one positive definite solve per step, no A^{-1}, no accumulated factors
       // (what ttc_lqr_solve_tv runs, here with the same matrices in every step).  info: 2 + index of the step.
       __syncthreads();  // every wavefront has left the pair
       const TIn* Bp = reinterpret_cast<const TIn*>(p.B) + prob * p.sB;
       const TIn* Rp = reinterpret_cast<const TIn*>(p.R) + prob * p.sR;
       const TIn* QTp = p.QT ? reinterpret_cast<const TIn*>(p.QT) + prob * p.sQT : Qp;
-      riccati_problem<D, TIn>(W, s_red, p, prob, p.T, Ap, Bp, Qp, Rp, 0, 0, 0, 0, QTp, nullptr, Qp, x0p, 2,
-                              tid + opaque_zero());
+      const int broke = riccati_problem<D, TIn>(W, s_red, p, prob, p.T, Ap, Bp, Qp, Rp, 0, 0, 0, 0, QTp, nullptr, Qp, x0p, 2,
+                                                tid + opaque_zero());
+      if (HANDED && recursion && broke) {
+        retry = true;
+        prob -= gridDim.x;
+      }
       continue;
     }
     // ---- outputs: WR holds P_0 (paper convention, Q_0 = 0)
@@ -227,6 +269,15 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D == 64 ? TTC_D64_WAVES : 1)) s
     TTC_TOC(5)
     TTC_TIMER_DUMP(p)
   }
+}
+
+template <int D, typename TIn>
+__global__ void __launch_bounds__(Cfg<D>::NTHR, (D == 64 ? TTC_D64_WAVES : 1)) solve_kernel(const SolveArgs p) {
+  solve_problems<D, TIn>(p);
+}
+template <int D, typename TIn>
+__global__ void __launch_bounds__(Cfg<D>::NTHR, (D == 64 ? TTC_D64_WAVES : 1)) solve_handed_kernel(const SolveArgs p) {
+  solve_problems<D, TIn, true>(p);
 }
 
 }  // namespace ttc

@@ -2,19 +2,22 @@
 // Thm 3.3 equal, so their product is formed by squaring (the algebra of ttc_doubling.hpp), with the element on chip.
 //
 // The sequential product costs four products per factor and a pivoted solve per group of three or so, whatever T; a
-// squaring costs eight products and one solve and doubles the number of factors.  Its weak side is accuracy when control
-// is cheap or the open loop grows: I + G_e H_e is then large and the composition loses digits in proportion, while on
-// ordinary problems it is several times more accurate than the grouped product (no A^{-1}, no accumulated pair).  So the
-// kernel watches max |I + G_e H_e| (and |I + P G_e|): a problem that passes the limit goes to the recursion of Prop. 3.1
-// in its printed form, as one that trips the growth guard of solve_kernel does.  Measured over R, Q scaled by 1e-2..1e2
+// squaring costs eight products and one solve and doubles the number of factors, and on ordinary problems it is several
+// times more accurate (no A^{-1}, no accumulated pair).  Its weak side is accuracy when control is cheap or the open loop
+// grows: I + G_e H_e is then large and the composition loses digits in proportion.  So the kernel watches
+// max |I + G_e H_e| (and |I + P G_e|) and gives up a problem that passes the limit.  Measured over R, Q scaled by 1e-2..1e2
 // and rho(A) in 0.5..1.2 at d = 32, 64, 128: ordinary problems stay below 7, with errors of 1e-6..5e-6; ratios of the
 // scales of 1e2 give 110 and more and errors of 2e-5..1e-4; between, at 16, errors are still below 1e-5.
 //
-// Where things live.  A_e, G_e, H_e and X = R^{-1} B^T are row blocks in registers (the A operand of a product), across
-// the dense solves, as solve_kernel's constants are; LDS holds the pair a product or solve works on; the one workspace
-// slot of the workgroup holds P while the bits of T still have squarings between them (never for T a power of two).
-// A^{-1} is not needed, but a singular A is reported as before (info = 2): A is factored, without right-hand sides.
-// The dense solves eliminate in order (solve_cols) where that is safe, and search pivots where it is not.
+// A problem given up is marked in its u_0 and solved by solve_handed_kernel, launched behind this one: one over the limit by
+// the recursion of Prop. 3.1 in its printed form, and by the sequential product if R + B^T P B is not positive definite there
+// (a stage cost that is not semidefinite, which squaring loses all digits on); one with a small pivot, a singular A or an R
+// that is not positive definite by the product at once, whose reports it thereby gets.
+//
+// Where things live.  A_e, G_e and H_e are row blocks in registers (the A operand of a product), across the dense solves, as
+// solve_kernel's constants are; LDS holds the pair a product or solve works on; the one workspace slot of the workgroup
+// holds P while the bits of T still have squarings between them (never for T a power of two).  The last step is the printed
+// one (riccati_step), which needs nothing but P_1 and the problem's own matrices.
 #pragma once
 #include "ttc_doubling.hpp"
 #include "ttc_tv.hpp"
@@ -34,18 +37,21 @@ __device__ __forceinline__ void add_aop_lds(const float* Wh, float (&rows)[Cfg<D
 }
 
 // Both I + G_e H_e and I + P G_e have the eigenvalues of I plus a positive semidefinite matrix, so elimination in order
-// meets no small pivot on the problems the guard lets through (CPU, float64: pivots of 1.2 and more, random semidefinite
+// meets no small pivot on the problems the guard lets through (CPU, float64: pivots of 1.1 and more, random semidefinite
 // pairs and the benchmark's): the solve is solve_cols, without a pivot search.  A pivot below PIVOT_MIN (a stage cost that is
-// not semidefinite, say) starts the problem over with pivoted solves.  A is tried the same way; a pivot below PIVOT_MIN_A
-// leaves the report to the pivoted factorisation.
+// not semidefinite, say) gives the problem up.  A is tried the same way; a pivot below PIVOT_MIN_A leaves the verdict to the
+// pivoted factorisation.
 static constexpr float PIVOT_MIN = 0.25f, PIVOT_MIN_A = 0.015625f;
 
 // One row block per wavefront at d = 128 (build.py: with two, 448 of the 512 registers hold matrices and the solves spill:
 // 31.9 against 4.5 ms for 2048 problems, T = 16), two at d = 64 (2.31 against 2.84 ms for 8192 problems, T = 16).
-// Measured against solve_kernel, and with pivoted solves throughout: d = 64, T = 8, 16384 problems 4.24 -> 3.74 -> 3.32 ms;
-// T = 64, 4099 problems 10.4 -> 1.71 -> 1.56 ms; d = 128, T = 16, 8192 problems 25.5 -> 17.5 -> 16.8 ms; d = 128, T = 32,
-// bfloat16 inputs, 4096 problems 21.3 -> 10.7 -> 10.0 ms; d = 32, T = 16, 8192 problems 0.85 -> 0.38 ms with registers held
-// to two wavefronts a SIMD (0.50 with one); errors against float64 5e-6..1.3e-5 -> 1e-6..2e-6.
+// The recursion and the solves of the problems given up are in a kernel of their own: inlined here they spilled 345 vector and
+// 107 scalar registers at d = 128 (now 271 and 78), and with R^{-1} B^T kept for a last step without R + B^T P B as well.
+// The thread index is formed anew in the loop: shared with the set-up, its address arithmetic lives across the solves
+// (4.15 against 4.52 ms below).
+// Measured, solve_kernel / with the cold paths inlined / now: d = 128, T = 16, 2048 problems 7.01 / 4.27 / 4.15 ms, T = 64
+// 35 / 5.88 / 5.74; T = 32, bfloat16 inputs 11.8 / 5.35; d = 64, 8192 problems, T = 8 2.14 / 1.70 / 1.65, T = 64
+// 15.9 / 2.87 / 2.81; d = 32, T = 16, 16384 problems 1.7 / 0.73 / 0.71.
 template <int D, typename TIn>
 __global__ void __launch_bounds__(Cfg<D>::NTHR, (D <= 64 ? 2 : 1)) squaring_kernel(const DoublingArgs da) {
   using C = Cfg<D>;
@@ -58,7 +64,6 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D <= 64 ? 2 : 1)) squaring_kern
   float* const WR = W + D;
   float* const wsP = p.ws + (long)blockIdx.x * D * D;  // P, rows in register layout
 
-  bool pivoted = false;  // this problem is done again, with pivoted solves
   for (long long prob = blockIdx.x; prob < p.n; prob += gridDim.x) {
     const int tid = threadIdx.x + opaque_zero(), lane = tid & 63, w = tid >> 6, i = lane & 15, g = lane >> 4;
     const TIn* Ap = reinterpret_cast<const TIn*>(p.A) + prob * p.sA;
@@ -67,9 +72,8 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D <= 64 ? 2 : 1)) squaring_kern
     const TIn* Rp = reinterpret_cast<const TIn*>(p.R) + prob * p.sR;
     const TIn* x0p = reinterpret_cast<const TIn*>(p.x0) + prob * p.sx0;
     const TIn* QTp = da.p_from_qt ? reinterpret_cast<const TIn*>(p.QT) + prob * p.sQT : Qp;
-    int info = 0, nsolve = 0;
-    bool hard = false;
-    float rA[C::RB][C::KS], rG[C::RB][C::KS], rH[C::RB][C::KS], rX[C::RB][C::KS];
+    uint32_t give_up = 0;   // whom the problem is handed to
+    float rA[C::RB][C::KS], rG[C::RB][C::KS], rH[C::RB][C::KS];
     floatx4 acc[C::RB][C::NT];
 
     // the wavefront's max |acc| for the guard; read by everyone after the next barrier
@@ -77,43 +81,49 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D <= 64 ? 2 : 1)) squaring_kern
       const float m = wave_absmax<D>(acc);
       if (lane == 0) s_max[w] = m;
     };
-    auto over_limit = [&] {  // uniform over the workgroup; also true for NaN
-      bool bad = false;
+    auto measure = [&] {  // its maximum over the workgroup (NaN on top)
+      uint32_t m = 0;
 #pragma unroll
-      for (int ww = 0; ww < C::NW; ++ww) bad = bad || !(s_max[ww] <= p.growth_limit);
-      return uniform(bad) != 0;
+      for (int ww = 0; ww < C::NW; ++ww) {
+        const uint32_t b = __float_as_uint(s_max[ww]);
+        m = b > m ? b : m;
+      }
+      return __uint_as_float(uniform(m));
+    };
+    // (the word's writer is the thread that writes the first of u_0 in emit_gain)
+    auto hand_over = [&](uint32_t how) {
+      if (threadIdx.x == 0) reinterpret_cast<uint32_t*>(p.u0)[prob * D] = how;
+      __syncthreads();  // every wavefront has left the pair
     };
 
-    // the dense solve of the pair; false: a pivot below PIVOT_MIN, and the problem starts over with pivoting
-    auto dense = [&] {
-      ++nsolve;
-      if (!pivoted) return solve_pair_in_order<D>(W, PIVOT_MIN, tid) == 0;
-      if (lds_solve<D>(W, S, tid) && !info) info = nsolve;
-      return true;
-    };
-
-    // ---- set-up: X = R^{-1} B^T, G = B X, A (factored for its report), H = Q, P = Q_T when it is a matrix of its own
+    // ---- a singular A is reported, although nothing here divides by A
+    load_half<D, TIn, false>(WL, Ap, tid);
+    __syncthreads();
+    if (solve_pair_in_order<D, false>(W, PIVOT_MIN_A, tid) && lds_factor<D>(W, S, tid)) {
+      hand_over(HANDED_TO_PRODUCT);
+      continue;
+    }
+    // ---- set-up: G = B R^{-1} B^T, A, H = Q; P = Q_T when it is a matrix of its own
     load_half<D, TIn, false>(WL, Rp, tid);
     load_half<D, TIn, false>(WR, Bp, tid);
     __syncthreads();
     symmetrise_half<D>(WL, tid);
     transpose_half<D>(WR, w, i, g);
-    ++nsolve;
     __syncthreads();
-    if (solve_pair_in_order<D>(W, 0.f, tid)) info = nsolve;  // R is positive definite
-    load_aop_lds<D>(WR, rX, w, i, g);
-    // G = B X into the left half, exactly symmetric (X in the right half)
-    auto form_G = [&] {
+    if (solve_pair_in_order<D>(W, 0.f, tid)) {  // R is not positive definite
+      hand_over(HANDED_TO_PRODUCT);
+      continue;
+    }
+    {
       float c[C::RB][C::KS];
       load_aop_global<D, TIn>(Bp, c, w, i, g);
       zero_acc<D>(acc);
       gemm_acc<D>(acc, c, WR, i, g);
       store_rows<D>(WL, acc, w, i, g);
       __syncthreads();
-      symmetrise_half<D>(WL, tid);
+      symmetrise_half<D>(WL, tid);  // G is symmetric up to rounding; make it exactly so
       __syncthreads();
-    };
-    form_G();
+    }
     load_aop_lds<D>(WL, rG, w, i, g);
     __syncthreads();
     load_half<D, TIn, false>(WL, Ap, tid);
@@ -123,10 +133,9 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D <= 64 ? 2 : 1)) squaring_kern
     symmetrise_half<D>(WR, tid);
     __syncthreads();
     load_aop_lds<D>(WR, rH, w, i, g);
-    ++nsolve;
-    if (solve_pair_in_order<D, false>(W, PIVOT_MIN_A, tid) && lds_factor<D>(W, S, tid) && !info) info = nsolve;
     bool have_p = da.p_from_qt != 0;
     if (have_p) {
+      __syncthreads();
       load_half<D, TIn, false>(WR, QTp, tid);
       __syncthreads();
       symmetrise_half<D>(WR, tid);
@@ -134,25 +143,28 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D <= 64 ? 2 : 1)) squaring_kern
       float c[C::RB][C::KS];
       load_aop_lds<D>(WR, c, w, i, g);
       store_aop_ws<D>(wsP, c, tid);
-      __syncthreads();
     }
+    __syncthreads();
 
     // [I + P G | P A] with P's rows in c, G and A as the halves hold them, then the solve: the right half becomes
-    // (I + P G)^{-1} P A.  False: over the limit, or (again) a small pivot
-    bool again = false;
+    // (I + P G)^{-1} P A.  False: over the limit, or no solution
     auto mobius = [&](const float(&c)[C::RB][C::KS]) {
       eye_acc<D>(acc, w, i, g);
       gemm_acc<D>(acc, c, WL, i, g);
       publish_max();
       __syncthreads();
-      if (over_limit()) return false;
+      if (!(measure() <= p.growth_limit)) {
+        give_up = HANDED_TO_RECURSION;
+        return false;
+      }
       store_rows<D>(WL, acc, w, i, g);
       zero_acc<D>(acc);
       gemm_acc<D>(acc, c, WR, i, g);
       __syncthreads();
       store_rows<D>(WR, acc, w, i, g);
       __syncthreads();
-      return (again = !dense()) == false;
+      if (solve_pair_in_order<D>(W, PIVOT_MIN, tid)) give_up = HANDED_TO_PRODUCT;
+      return give_up == 0;
     };
     // rows[rb][k] <- rH + A_e^T (the matrix in the right half), through the left half (rows may be rH itself)
     auto apply_AT = [&](float (&rows)[C::RB][C::KS]) {
@@ -175,7 +187,8 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D <= 64 ? 2 : 1)) squaring_kern
 
     // ---- P_1 by binary powering of the one-step map (see ttc_doubling.hpp)
     bool p_is_H = false;  // P_1 = H_e: the last bit met no P
-    for (int m = da.m; m && !hard && !again;) {
+    for (int m = da.m; m && !give_up;) {
+      const int tid = threadIdx.x + opaque_zero(), lane = tid & 63, w = tid >> 6, i = lane & 15, g = lane >> 4;
       if (m & 1) {
         if (!have_p) {
           have_p = true;
@@ -187,10 +200,7 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D <= 64 ? 2 : 1)) squaring_kern
           store_aop_lds<D>(WL, rG, w, i, g);
           store_aop_lds<D>(WR, rA, w, i, g);
           __syncthreads();
-          if (!mobius(c)) {
-            hard = !again;
-            break;
-          }
+          if (!mobius(c)) break;
           apply_AT(c);  // P <- H_e + A_e^T (I + P G_e)^{-1} P A_e
           store_aop_ws<D>(wsP, c, tid);
         }
@@ -205,16 +215,16 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D <= 64 ? 2 : 1)) squaring_kern
       publish_max();
       store_rows<D>(WL, acc, w, i, g);
       __syncthreads();
-      if (over_limit()) {
-        hard = true;
+      if (!(measure() <= p.growth_limit)) {
+        give_up = HANDED_TO_RECURSION;
         break;
       }
       const bool only_H = m == 1 && !have_p;  // the last squaring, and P is still 0: A and G of the square are not needed
       if (only_H) store_aop_lds<D>(WR, rA, w, i, g);
       else set_half_identity<D>(WR, tid);
       __syncthreads();
-      if (!dense()) {  // right half: M = (I + G H)^{-1}, or M A
-        again = true;
+      if (solve_pair_in_order<D>(W, PIVOT_MIN, tid)) {  // right half: M = (I + G H)^{-1}, or M A
+        give_up = HANDED_TO_PRODUCT;
         break;
       }
       if (only_H) {
@@ -224,6 +234,7 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D <= 64 ? 2 : 1)) squaring_kern
         store_rows<D>(WR, acc, w, i, g);
         apply_AT(rH);  // H' = H + A^T V
       } else {
+        const int tid = threadIdx.x + opaque_zero(), lane = tid & 63, w = tid >> 6, i = lane & 15, g = lane >> 4;
         float rM[C::RB][C::KS];
         load_aop_lds<D>(WR, rM, w, i, g);
         store_aop_lds<D>(WL, rA, w, i, g);
@@ -274,60 +285,24 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D <= 64 ? 2 : 1)) squaring_kern
       }
     }
 
-    // ---- last step with the problem's own (A, G): M_1 = (I + P_1 G)^{-1} P_1 A, P_0 = A^T M_1, -K_0 = X M_1
-    if (!hard && !again) {
-      float c[C::RB][C::KS];
+    // ---- last step, with the problem's own matrices: as printed
+    if (!give_up) {
+      const int tid = threadIdx.x + opaque_zero(), lane = tid & 63, w = tid >> 6, i = lane & 15, g = lane >> 4;
       if (p_is_H) {
-#pragma unroll
-        for (int rb = 0; rb < C::RB; ++rb)
-#pragma unroll
-          for (int k = 0; k < C::KS; ++k) c[rb][k] = rH[rb][k];
+        store_aop_lds<D>(WR, rH, w, i, g);
       } else {
+        float c[C::RB][C::KS];
         load_aop_ws<D>(wsP, c, tid, opaque_zero());
+        store_aop_lds<D>(WR, c, w, i, g);
       }
-      store_aop_lds<D>(WR, rX, w, i, g);
       __syncthreads();
-      form_G();
-      load_half<D, TIn, false>(WR, Ap, tid);
+      symmetrise_half<D>(WR, tid);
       __syncthreads();
-      hard = !mobius(c) && !again;
+      Cols<D> wk, pn;
+      if (riccati_step<D, TIn>(W, Ap, Bp, Rp, wk, pn, tid)) give_up = HANDED_TO_PRODUCT;
+      else emit_step<D, TIn>(W, s_red, p, prob, wk, pn, Qp, x0p, 0, tid);
     }
-    if (again) {
-      pivoted = true;
-      prob -= gridDim.x;
-      __syncthreads();  // every wavefront has left the pair
-      continue;
-    }
-    pivoted = false;
-    if (hard) {
-      __syncthreads();  // every wavefront has left the pair
-      if (info) {       // a set-up breakdown keeps its report
-        zero_acc<D>(acc);
-        emit_gain<D, TIn>(p, prob, acc, x0p, info, tid);
-        emit_value<D, TIn>(p, prob, WL, Qp, x0p, info, s_red, tid);
-      } else {
-        riccati_problem<D, TIn>(W, s_red, p, prob, p.T, Ap, Bp, Qp, Rp, 0, 0, 0, 0, QTp, nullptr, Qp, x0p, 2,
-                                tid + opaque_zero());
-      }
-      continue;
-    }
-    zero_acc<D>(acc);
-    gemm_acc<D>(acc, rX, WR, i, g);  // rows of -K_0
-    emit_gain<D, TIn>(p, prob, acc, x0p, info, tid);
-    {
-      float c[C::RB][C::KS];
-      load_half<D, TIn, false>(WL, Ap, tid);
-      __syncthreads();
-      load_aopT_lds<D>(WL, c, w, i, g);
-      zero_acc<D>(acc);
-      gemm_acc<D>(acc, c, WR, i, g);
-      __syncthreads();
-      store_rows<D>(WL, acc, w, i, g);
-      __syncthreads();
-      symmetrise_half<D>(WL, tid);
-      __syncthreads();
-    }
-    emit_value<D, TIn>(p, prob, WL, Qp, x0p, info, s_red, tid);
+    if (give_up) hand_over(give_up);
   }
 }
 

@@ -41,20 +41,38 @@ __device__ __forceinline__ void load_rows_input(const TIn* src, floatx4 (&acc)[C
       }
 }
 
+// The outputs from the last step taken, as riccati_step leaves it: wk = -K_0 and pn = P_0 (no cost on x_0).
+template <int D, typename TIn>
+__device__ __forceinline__ void emit_step(float* W, float* s_red, const SolveArgs& p, long long prob, const Cols<D>& wk,
+                                          const Cols<D>& pn, const TIn* Qflag, const TIn* x0p, int info, int tid) {
+  using C = Cfg<D>;
+  const int lane = tid & 63, w = tid >> 6, i = lane & 15, g = lane >> 4;
+  float* const WL = W;
+  float* const WR = W + D;
+  __syncthreads();  // every wavefront has left the pair
+  store_cols_T<D>(WL, pn, w, i, g);
+  store_cols<D>(WR, C::PITCH, wk, w, i, g);
+  __syncthreads();
+  symmetrise_half<D>(WL, tid);
+  __syncthreads();
+  floatx4 acc[C::RB][C::NT];
+  load_rows<D>(WR, acc, w, i, g);  // rows of -K_0
+  emit_gain<D, TIn>(p, prob, acc, x0p, info, tid);
+  emit_value<D, TIn>(p, prob, WL, Qflag, x0p, info, s_red, tid);
+}
+
 // The whole backward recursion of one problem by one workgroup, from P_T to the outputs P_0, K_0, u_0, value and
 // info: T calls of riccati_step.  Step s reads A, B, R at As + s*tA, Bs + s*tB, Rs + s*tR and the stage cost on
 // the state it starts from at Qs + (s-1)*tQ (none for s = 0); zero strides give the time-invariant problem.
 // The terminal value matrix is PTf (float32) if given, else PT (input element type).  info_base is added to the
-// index (1 = the step taken first, s = T-1) of the step whose solve broke down.  All threads must call it.
+// index (1 = the step taken first, s = T-1) of the step whose solve broke down; the result is what info becomes.  All
+// threads must call it.
 template <int D, typename TIn>
-__device__ __forceinline__ void riccati_problem(float* W, float* s_red, const SolveArgs& p,
+__device__ __forceinline__ int riccati_problem(float* W, float* s_red, const SolveArgs& p,
                                                 long long prob, int T, const TIn* As, const TIn* Bs, const TIn* Qs,
                                                 const TIn* Rs, long long tA, long long tB, long long tQ, long long tR,
                                                 const TIn* PT, const float* PTf, const TIn* Qflag, const TIn* x0p,
                                                 int info_base, int tid) {
-  using C = Cfg<D>;
-  const int lane = tid & 63, w = tid >> 6, i = lane & 15, g = lane >> 4;
-  float* const WL = W;
   float* const WR = W + D;
   int info = 0;
   if (PTf) load_half<D, float, false>(WR, PTf, tid);
@@ -67,21 +85,14 @@ __device__ __forceinline__ void riccati_problem(float* W, float* s_red, const So
     const int flag = riccati_step<D, TIn>(W, As + (long long)s * tA, Bs + (long long)s * tB, Rs + (long long)s * tR, wk,
                                           pn, tid);
     if (flag && !info) info = info_base + T - s;
-    if (s >= 1) {
+    if (s >= 1 && !info) {
       next_value_matrix<D, TIn>(W, Qs + (long long)(s - 1) * tQ, pn, tid);
     } else {
-      __syncthreads();  // every wavefront has left the pair
-      store_cols_T<D>(WL, pn, w, i, g);  // P_0 (no cost on x_0)
-      store_cols<D>(WR, C::PITCH, wk, w, i, g);
-      __syncthreads();
-      symmetrise_half<D>(WL, tid);
-      __syncthreads();
-      floatx4 acc[C::RB][C::NT];
-      load_rows<D>(WR, acc, w, i, g);  // rows of -K_0
-      emit_gain<D, TIn>(p, prob, acc, x0p, info, tid);
-      emit_value<D, TIn>(p, prob, WL, Qflag, x0p, info, s_red, tid);
+      emit_step<D, TIn>(W, s_red, p, prob, wk, pn, Qflag, x0p, info, tid);
+      break;
     }
   }
+  return info;
 }
 
 template <int D, typename TIn>

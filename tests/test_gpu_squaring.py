@@ -135,8 +135,9 @@ def test_noalloc_takes_the_same_path():
 @pytest.mark.parametrize("d,n", [(32, 7), (64, 1100), (128, 7)])
 @pytest.mark.parametrize("T", [8, 12])
 def test_a_small_pivot_starts_the_problem_over_with_pivoting(d, n, T):
-    """A stage cost that is not semidefinite: elimination of I + G H in order meets negative pivots, although the problem
-    is well conditioned and below the guard's limit (float32 on the CPU: errors below 1e-6).  Its neighbours, also those the
+    """A stage cost that is not semidefinite: elimination of I + G H in order meets negative pivots, and the sequential
+    product, whose solves are pivoted, takes the problem, which
+    is well conditioned (float32 on the CPU: errors below 1e-6).  Its neighbours, also those the
     same workgroup takes next, come out as they do alone."""
     b = synth.make_batch(n, d, d, T, seed=d, device=DEV)
     B = 0.1 * b.B + torch.eye(d, device=DEV)
@@ -159,3 +160,90 @@ def test_a_small_pivot_starts_the_problem_over_with_pivoting(d, n, T):
     keep = torch.arange(n, device=DEV) != 1
     for k in SOLVE_KEYS:
         assert torch.equal(out[k][keep], alone[k][keep]), k
+
+
+def recursion64(b, QT=None):
+    """P_0, K_0 of the printed recursion in float64 with general solves (R + B^T P B need not be positive definite)."""
+    A, B, Q, R, _ = b.numpy64()
+    t = lambda M: M.swapaxes(-1, -2)
+    Q, R = 0.5 * (Q + t(Q)), 0.5 * (R + t(R))
+    P = Q if QT is None else 0.5 * (QT + t(QT))
+    for s in range(b.T - 1, -1, -1):
+        F = t(B) @ P @ A
+        K = -np.linalg.solve(R + t(B) @ P @ B, F)
+        P = (Q if s else 0) + t(A) @ P @ A + t(F) @ K
+        P = 0.5 * (P + t(P))
+    return {"P0": P, "K0": K}
+
+
+def problem_errors(out, ref):
+    """The larger of the errors of P_0 and K_0, per problem (NaN where there is no answer)."""
+    rel = lambda k: np.linalg.norm(out[k].double().cpu().numpy() - ref[k], axis=(-1, -2)) / np.linalg.norm(ref[k], axis=(-1, -2))
+    return np.maximum(rel("P0"), rel("K0"))
+
+
+def indefinite(n, d, T, seed=None):
+    """Stage costs with eigenvalues of about -0.2: R + B^T P B becomes indefinite, and regular, within a few steps."""
+    b = synth.make_batch(n, d, d, T, seed=d + T if seed is None else seed, device=DEV)
+    b.Q.sub_(0.2 * torch.eye(d, device=DEV))
+    return b
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,n", [(32, 40), (64, 30), (128, 9)])
+@pytest.mark.parametrize("T", [12, 15, 32])
+def test_a_stage_cost_that_is_not_semidefinite_is_answered_as_by_the_product(d, n, T):
+    """The recursion refuses such problems and squaring loses their digits; the sequential product, whose solves are
+    pivoted, answers them.  At these horizons rebase_every = 3 is the product's own grouping.  What it answers is answered,
+    and as well: problems near a singular R + B^T P B lose digits on either path (1e-4 and more), and there the errors of
+    two float32 evaluations are independent draws, for which 10 is allowed."""
+    b = indefinite(n, d, T)
+    ref = recursion64(b)
+    out, seq = solve(b), solve(b, rebase_every=3)
+    answered = (seq["info"] == 0).cpu().numpy()
+    assert answered.mean() >= 0.5
+    assert not out["info"].cpu().numpy()[answered].any()
+    err, err_seq = problem_errors(out, ref)[answered], problem_errors(seq, ref)[answered]
+    print(d, T, "median %.1e %.1e, largest %.1e %.1e" % (np.median(err), np.median(err_seq), err.max(), err_seq.max()))
+    assert (err <= np.maximum(1e-4, 10 * err_seq)).all()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,n", [(32, 7000), (64, 2100), (128, 530)])
+def test_problems_handed_on_stay_by_themselves(d, n):
+    """Ordinary problems beside ones of each kind that is handed on, more than one pass of the grid, outputs left out and in
+    a captured graph: everything is what it is alone."""
+    T = 12
+    b = synth.make_batch(n, d, d, T, seed=3, device=DEV)
+    odd, ind = synth.make_batch(n, d, d, T, seed=3, device=DEV, r_scale=1e-3), indefinite(n, d, T, seed=3)
+    kind = torch.arange(n, device=DEV) % 7
+    b.R[kind == 2] = odd.R[kind == 2]   # over the limit
+    b.Q[kind == 4] = ind.Q[kind == 4]   # not semidefinite
+    b.A[n - 3] = 0.0                    # singular
+    b.R[n - 5].neg_()                   # not positive definite
+    out = solve(b)
+    info = out["info"].cpu().numpy()
+    assert info[n - 3] == 2 and info[n - 5] == 1
+    for which in (kind == 2, kind == 4, (kind != 2) & (kind != 4)):
+        pick = which.nonzero()[:, 0]
+        alone = solve(b.take(pick))
+        for k in SOLVE_KEYS + ("info",):
+            assert torch.equal(out[k][pick].nan_to_num(nan=1e30), alone[k].nan_to_num(nan=1e30)
+                               if alone[k].is_floating_point() else alone[k]), k
+    few = binding.ttc_lqr_solve(b.A, b.B, b.Q, b.R, None, b.x0, T, want_P0=False, want_K0=False)
+    assert torch.equal(few["u0"].nan_to_num(nan=1e30), out["u0"].nan_to_num(nan=1e30))
+    res = {k: torch.zeros_like(v) for k, v in out.items()}
+    graph = torch.cuda.CUDAGraph()
+    ws = torch.empty(binding.ttc_lqr_workspace_bytes(binding.make_problem(b.A, b.B, b.Q, b.R, None, b.x0, T)),
+                     dtype=torch.uint8, device=DEV)
+    with torch.cuda.graph(graph):
+        binding.ttc_lqr_solve(b.A, b.B, b.Q, b.R, None, b.x0, T, out=res, workspace=ws)
+    for _ in range(3):
+        for v in res.values():
+            v.zero_()
+        graph.replay()
+        solve(b.take(slice(0, 5)))
+        torch.cuda.synchronize()
+        for k in SOLVE_KEYS + ("info",):
+            got, want = (res[k].nan_to_num(nan=1e30), out[k].nan_to_num(nan=1e30)) if k != "info" else (res[k], out[k])
+            assert torch.equal(got, want), k
