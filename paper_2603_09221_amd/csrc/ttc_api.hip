@@ -131,9 +131,12 @@ constexpr long long QUAD_MIN_PER_CU_TV = 12;
 static bool use_quad_kernel(const ttc_lqr_problem_t* q) {
   return q->d == 16 && !(q->flags & TTC_FLAG_DOUBLING) && q->n >= QUAD_MIN_PER_CU_SOLVE * cu_count();
 }
-// Squaring (d >= 32): the largest max |I + G_e H_e| of a solve before the problem is handed to the Riccati recursion (see
-// ttc_squaring.hpp).
-constexpr float SQUARING_LIMIT = 16.f;
+// Squaring (d >= 32): the largest max |I + G_e H_e| of the first squaring, and the largest max |I + Q_T G_e| where a terminal cost
+// of its own is first used (ttc_squaring.hpp has what was measured).  A float32 problem over them goes to the Riccati recursion,
+// where the product's guard sent it too (from 30 Q on with Q_T, from ratios of the scales of 10 on); with bfloat16 inputs the
+// product kept such problems, at a ratio of 33 with errors of 1e-3, and squaring does too.
+constexpr float SQUARING_LIMIT_F32 = 16.f, SQUARING_LIMIT_BF16 = 64.f;
+constexpr float SQUARING_QT_LIMIT_F32 = 64.f, SQUARING_QT_LIMIT_BF16 = 4096.f;
 // Q_T "is Q" when it is absent or the very same array: then P_T = Q = f(0) and a recursion may start at 0
 static bool qt_is_q(const ttc_lqr_problem_t* q) { return !q->QT || (q->QT == q->Q && q->sQT == q->sQ); }
 // Default path, d >= 32: whether the T equal factors are composed by squaring (squaring_kernel) or one after the other
@@ -332,7 +335,8 @@ ttc_status_t ttc_lqr_solve(const ttc_lqr_problem_t* problem, const ttc_lqr_solut
   } else if (ttc::use_squaring(problem)) {
     ttc::DoublingArgs da;
     da.s = a;
-    da.s.growth_limit = ttc::SQUARING_LIMIT;
+    da.s.growth_limit = bf16 ? ttc::SQUARING_LIMIT_BF16 : ttc::SQUARING_LIMIT_F32;
+    da.qt_limit = bf16 ? ttc::SQUARING_QT_LIMIT_BF16 : ttc::SQUARING_QT_LIMIT_F32;
     da.m = ttc::qt_is_q(problem) ? problem->T : problem->T - 1;
     da.p_from_qt = ttc::qt_is_q(problem) ? 0 : 1;
     // one workspace slot per workgroup, of which there are as many as solve_kernel's grid

@@ -38,6 +38,7 @@ struct DoublingArgs {
   SolveArgs s;  // problem, outputs, workspace (ngroups unused)
   int m;        // number of one-step maps composed before the last step (T, or T-1 when Q_T is given)
   int p_from_qt;  // 1: the backward recursion starts at Q_T; 0: it starts at 0 (Q_T is Q = f(0))
+  float qt_limit = 0.f;  // squaring_kernel: the guard's limit where Q_T is first used (s.growth_limit: in the first squaring)
 };
 
 // workspace slots of a workgroup, d*d floats each

@@ -3,13 +3,22 @@
 //
 // The sequential product costs four products per factor and a pivoted solve per group of three or so, whatever T; a
 // squaring costs eight products and one solve and doubles the number of factors, and on ordinary problems it is several
-// times more accurate (no A^{-1}, no accumulated pair).  Its weak side is accuracy when control is cheap or the open loop
-// grows: I + G_e H_e is then large and the composition loses digits in proportion.  So the kernel watches
-// max |I + G_e H_e| (and |I + P G_e|) and gives up a problem that passes the limit.  Measured over R, Q scaled by 1e-2..1e2
-// and rho(A) in 0.5..1.2 at d = 32, 64, 128: ordinary problems stay below 7, with errors of 1e-6..5e-6; ratios of the
-// scales of 1e2 give 110 and more and errors of 2e-5..1e-4; between, at 16, errors are still below 1e-5.
+// times more accurate (no A^{-1}, no accumulated pair).  Its weak side is accuracy when control is cheap: I + G_e H_e is
+// large from the first squaring on, and the composition loses digits in proportion.  The kernel watches
+// mu = max |I + G_e H_e| (and max |I + P G_e|) and gives up a problem that passes the limits below.
 //
-// A problem given up is marked in its u_0 and solved by solve_handed_kernel, launched behind this one: one over the limit by
+// Measured (float32, d = 32, 64, 128, T = 8..64; errors against float64, product: the grouped product's):
+//   ordinary problems, rho(A) 0.5..1.2          mu below 7                 1e-6..4e-6    (product 5e-6..1e-5)
+//   R scaled by 0.1 / 0.03 / 0.01               mu 15 / 40 / 120           1e-5 / 2e-5 / 7e-5, in the first squaring already
+//   rho(A) = 1.2, 1.3, R scaled by 1..100       mu 3..200, growing late    3e-6..8e-6    (product 2e-6..1e-5)
+//   Q_T = 10 Q .. 1000 Q                        max |I + Q_T G| 15..2000   2e-6..6e-6    (product 2e-6..1e-5)
+// So a large mu means lost digits in the first squaring, and there alone: p.growth_limit is the limit there, 16 for float32
+// inputs (errors of 1e-5, as the product's) and 64 for bfloat16 ones, whose product in groups of five is at 1e-3 by then.
+// Growth that comes later is that of an unstable open loop, whose pair (G_e, H_e) outgrows what the feedback needs
+// (LATE_LIMIT); a squaring that would run into it is not done, the power reached is applied as often as there are factors
+// of it left.  A terminal cost of its own meets its own limit (da.qt_limit) once, when it is first used.
+//
+// A problem given up is marked in its u_0 and solved by solve_handed_kernel, launched behind this one: one over a limit by
 // the recursion of Prop. 3.1 in its printed form, and by the sequential product if R + B^T P B is not positive definite there
 // (a stage cost that is not semidefinite, which squaring loses all digits on); one with a small pivot, a singular A or an R
 // that is not positive definite by the product at once, whose reports it thereby gets.
@@ -36,17 +45,20 @@ __device__ __forceinline__ void add_aop_lds(const float* Wh, float (&rows)[Cfg<D
     for (int k = 0; k < C::KS; ++k) rows[rb][k] += t[rb][k];
 }
 
-// Both I + G_e H_e and I + P G_e have the eigenvalues of I plus a positive semidefinite matrix, so elimination in order
-// meets no small pivot on the problems the guard lets through (CPU, float64: pivots of 1.1 and more, random semidefinite
-// pairs and the benchmark's): the solve is solve_cols, without a pivot search.  A pivot below PIVOT_MIN (a stage cost that is
-// not semidefinite, say) gives the problem up.  A is tried the same way; a pivot below PIVOT_MIN_A leaves the verdict to the
-// pivoted factorisation.
-static constexpr float PIVOT_MIN = 0.25f, PIVOT_MIN_A = 0.015625f;
+// Both I + G_e H_e and I + P G_e have the eigenvalues of I plus a positive semidefinite matrix.  They are not symmetric, but up
+// to mu of about 30 elimination in order meets no small pivot (CPU, float64, random semidefinite pairs and the benchmark's:
+// pivots of 1.1 and more; at 40 some problems in a hundred, at 120 all of them meet negative ones): the solve is solve_cols,
+// without a pivot search.  Above IN_ORDER_MAX it is the pivoted lds_solve; a pivot below PIVOT_MIN (a stage cost that is not
+// semidefinite, say) gives the problem up.  A is tried in order too; a pivot below PIVOT_MIN_A leaves the verdict to the pivoted
+// factorisation.
+static constexpr float PIVOT_MIN = 0.25f, PIVOT_MIN_A = 0.015625f, IN_ORDER_MAX = 24.f;
+// The guard's limit after the first squaring, and the mu at which the coming square of e is expected and not formed.
+static constexpr float LATE_LIMIT = 64.f, GROWTH_STOP = 16.f;
 
 // One row block per wavefront at d = 128 (build.py: with two, 448 of the 512 registers hold matrices and the solves spill:
 // 31.9 against 4.5 ms for 2048 problems, T = 16), two at d = 64 (2.31 against 2.84 ms for 8192 problems, T = 16).
 // The recursion and the solves of the problems given up are in a kernel of their own: inlined here they spilled 345 vector and
-// 107 scalar registers at d = 128 (now 271 and 78), and with R^{-1} B^T kept for a last step without R + B^T P B as well.
+// 107 scalar registers at d = 128 (271 and 78 without), and with R^{-1} B^T kept for a last step without R + B^T P B as well.
 // The thread index is formed anew in the loop: shared with the set-up, its address arithmetic lives across the solves
 // (4.15 against 4.52 ms below).
 // Measured, solve_kernel / with the cold paths inlined / now: d = 128, T = 16, 2048 problems 7.01 / 4.27 / 4.15 ms, T = 64
@@ -73,6 +85,7 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D <= 64 ? 2 : 1)) squaring_kern
     const TIn* x0p = reinterpret_cast<const TIn*>(p.x0) + prob * p.sx0;
     const TIn* QTp = da.p_from_qt ? reinterpret_cast<const TIn*>(p.QT) + prob * p.sQT : Qp;
     uint32_t give_up = 0;   // whom the problem is handed to
+    bool pivoted = false;   // the dense solves search pivots, from the first large mu on
     float rA[C::RB][C::KS], rG[C::RB][C::KS], rH[C::RB][C::KS];
     floatx4 acc[C::RB][C::NT];
 
@@ -133,7 +146,7 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D <= 64 ? 2 : 1)) squaring_kern
     symmetrise_half<D>(WR, tid);
     __syncthreads();
     load_aop_lds<D>(WR, rH, w, i, g);
-    bool have_p = da.p_from_qt != 0;
+    bool have_p = da.p_from_qt != 0, at_QT = have_p;  // at_QT: P is still Q_T
     if (have_p) {
       __syncthreads();
       load_half<D, TIn, false>(WR, QTp, tid);
@@ -146,6 +159,16 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D <= 64 ? 2 : 1)) squaring_kern
     }
     __syncthreads();
 
+    // the dense solve of the pair, whose left half's largest entry is mu.  False: a pivot below PIVOT_MIN, or none at all
+    auto dense = [&](float mu) {
+      pivoted = pivoted || mu > IN_ORDER_MAX;
+      if (!pivoted) {
+        if (solve_pair_in_order<D>(W, PIVOT_MIN, tid)) give_up = HANDED_TO_PRODUCT;
+      } else {
+        if (lds_solve<D>(W, S, tid)) give_up = HANDED_TO_PRODUCT;
+      }
+      return give_up == 0;
+    };
     // [I + P G | P A] with P's rows in c, G and A as the halves hold them, then the solve: the right half becomes
     // (I + P G)^{-1} P A.  False: over the limit, or no solution
     auto mobius = [&](const float(&c)[C::RB][C::KS]) {
@@ -153,18 +176,19 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D <= 64 ? 2 : 1)) squaring_kern
       gemm_acc<D>(acc, c, WL, i, g);
       publish_max();
       __syncthreads();
-      if (!(measure() <= p.growth_limit)) {
+      const float mu = measure();
+      if (!(mu <= (at_QT ? da.qt_limit : LATE_LIMIT))) {
         give_up = HANDED_TO_RECURSION;
         return false;
       }
+      at_QT = false;
       store_rows<D>(WL, acc, w, i, g);
       zero_acc<D>(acc);
       gemm_acc<D>(acc, c, WR, i, g);
       __syncthreads();
       store_rows<D>(WR, acc, w, i, g);
       __syncthreads();
-      if (solve_pair_in_order<D>(W, PIVOT_MIN, tid)) give_up = HANDED_TO_PRODUCT;
-      return give_up == 0;
+      return dense(mu);
     };
     // rows[rb][k] <- rH + A_e^T (the matrix in the right half), through the left half (rows may be rH itself)
     auto apply_AT = [&](float (&rows)[C::RB][C::KS]) {
@@ -187,9 +211,11 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D <= 64 ? 2 : 1)) squaring_kern
 
     // ---- P_1 by binary powering of the one-step map (see ttc_doubling.hpp)
     bool p_is_H = false;  // P_1 = H_e: the last bit met no P
+    float mu_prev = 0.f;  // max |I + G_e H_e| of the squaring before, 0 before the first
+    bool stay = false;    // e is not squared any further, but applied once for each factor of it that is left
     for (int m = da.m; m && !give_up;) {
       const int tid = threadIdx.x + opaque_zero(), lane = tid & 63, w = tid >> 6, i = lane & 15, g = lane >> 4;
-      if (m & 1) {
+      if ((m & 1) || stay) {
         if (!have_p) {
           have_p = true;
           if (m == 1) p_is_H = true;  // f_e(0) = H_e, and e is not touched again
@@ -205,6 +231,10 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D <= 64 ? 2 : 1)) squaring_kern
           store_aop_ws<D>(wsP, c, tid);
         }
       }
+      if (stay) {
+        --m;
+        continue;
+      }
       m >>= 1;
       if (!m) break;
       // e <- e o e
@@ -215,18 +245,24 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D <= 64 ? 2 : 1)) squaring_kern
       publish_max();
       store_rows<D>(WL, acc, w, i, g);
       __syncthreads();
-      if (!(measure() <= p.growth_limit)) {
+      const float mu = measure();
+      if (!(mu <= (mu_prev == 0.f ? p.growth_limit : LATE_LIMIT))) {
         give_up = HANDED_TO_RECURSION;
         break;
       }
       const bool only_H = m == 1 && !have_p;  // the last squaring, and P is still 0: A and G of the square are not needed
+      // growth of an unstable open loop: mu - 1 has grown by r, and the square of e will make it grow by r^2 at least
+      const float up = mu - 1.f, up_prev = mu_prev - 1.f;
+      if (!only_H && mu_prev != 0.f && up > 1.f && up > 2.f * up_prev && up * up * up > GROWTH_STOP * up_prev * up_prev) {
+        stay = true;
+        m *= 2;
+        continue;
+      }
+      mu_prev = mu;
       if (only_H) store_aop_lds<D>(WR, rA, w, i, g);
       else set_half_identity<D>(WR, tid);
       __syncthreads();
-      if (solve_pair_in_order<D>(W, PIVOT_MIN, tid)) {  // right half: M = (I + G H)^{-1}, or M A
-        give_up = HANDED_TO_PRODUCT;
-        break;
-      }
+      if (!dense(mu)) break;  // right half: M = (I + G H)^{-1}, or M A
       if (only_H) {
         zero_acc<D>(acc);
         gemm_acc<D>(acc, rH, WR, i, g);  // V = H M A

@@ -247,3 +247,33 @@ def test_problems_handed_on_stay_by_themselves(d, n):
         for k in SOLVE_KEYS + ("info",):
             got, want = (res[k].nan_to_num(nan=1e30), out[k].nan_to_num(nan=1e30)) if k != "info" else (res[k], out[k])
             assert torch.equal(got, want), k
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,n", [(32, 12), (64, 10), (128, 5)])
+@pytest.mark.parametrize("dtype,T,qt,r,rho", [
+    ("f32", 16, 30, 1.0, None), ("f32", 31, 30, 1.0, None), ("f32", 32, None, 1e2, 1.2), ("f32", 64, None, 1.0, 1.2),
+    ("bf16", 31, 10, 1.0, None), ("bf16", 32, 30, 1.0, None), ("bf16", 31, 100, 1.0, None), ("bf16", 32, 1000, 1.0, None),
+    ("bf16", 12, None, 1 / 30, None), ("bf16", 32, None, 1 / 30, None), ("bf16", 64, None, 1.0, 1.2)])
+def test_what_the_product_kept_stays_with_squaring(d, n, dtype, T, qt, r, rho):
+    """A large terminal cost, an unstable open loop over a long horizon and, with bfloat16 inputs, a ratio of the scales of 30
+    make max |I + G H| large without costing the digits that cheap control costs: the grouped product kept these problems,
+    and the recursion that a single limit sent them to is up to twice as slow.  They are not what the recursion gives bit
+    for bit (a few at the edge of a limit may be), and within 2e-5; with bfloat16 inputs and cheap control within 1e-4, a
+    tenth of the product's own error on them."""
+    b = synth.make_batch(n, d, d, T, seed=d + T, device=DEV, dtype=dtype, r_scale=r)
+    if rho:
+        b.A.mul_(rho / 1.1)
+    QT = None if qt is None else (qt * b.Q).contiguous()
+    out = solve(b, QT=QT)
+    assert not out["info"].any()
+    err = problem_errors(out, recursion64(b, None if QT is None else QT.double().cpu().numpy()))
+    steps = [m[:, None].expand(-1, T, -1, -1).contiguous() for m in (b.A, b.B, b.Q, b.R)]
+    if QT is not None:
+        steps[2][:, T - 1] = QT
+    tv = binding.ttc_lqr_solve_tv(*steps, b.x0)
+    torch.cuda.synchronize()
+    same = (out["P0"] == tv["P0"]).flatten(1).all(1)
+    print(d, dtype, T, qt, r, rho, "%.1e" % err.max(), int(same.sum()))
+    assert same.sum() <= n // 4
+    assert err.max() <= (1e-4 if r < 1 else 2e-5)
