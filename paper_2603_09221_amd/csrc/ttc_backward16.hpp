@@ -1,7 +1,7 @@
 // The backward pass of the layer (ttc_backward.hpp has the method) at d = 16: a workgroup of one wavefront per problem,
 // register to register.  A call at the sizes of the paper's benchmark is bound by the latency of its three serial sweeps
 // over the horizon, so a step does as little as possible in series: the recursion is riccati_step16 (ttc_tv.hpp); a
-// closed-loop step is two dependent products of four matrix instructions for the primal and the dual trajectory together
+// closed-loop step is two dependent products of four matrix instructions (in two halves, dot16) for the primal and the dual trajectory together
 // (a state is a 16 x 16 operand with the primal in column 0 and the dual in column 1); a co-state step is one, beside which
 // the four gradients of the step before, rank-2 outer products, are one matrix instruction each.  The matrices of a step
 // are requested one step ahead.  Measured, kernel time at T = 64, against backward_kernel at d = 16
@@ -11,6 +11,19 @@
 #include "ttc_tv.hpp"
 
 namespace ttc {
+
+// L R in two halves of the contraction that are added at the end: a sum of sixteen terms one after the other, on top of
+// another such sum, carries more rounding than the tree a matrix-vector product by lanes adds up (states, controls and
+// co-states are such products all through the horizon).
+__device__ __forceinline__ floatx4 dot16(const floatx4& a, const floatx4& b) {
+  floatx4 e = floatx4{0.f, 0.f, 0.f, 0.f}, o = e;
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    e = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t], b[t], e, 0, 0, 0);
+    o = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t + 2], b[t + 2], o, 0, 0, 0);
+  }
+  return e + o;
+}
 
 template <typename TIn>
 __global__ void __launch_bounds__(64, 4) backward16_kernel(const BackwardArgs ba) {
@@ -105,23 +118,18 @@ __global__ void __launch_bounds__(64, 4) backward16_kernel(const BackwardArgs ba
     {
       floatx4 An = load_accT16<TIn>(Ap, i, g), Bn = load_accT16<TIn>(Bp, i, g), Kn = floatx4{0.f, 0.f, 0.f, 0.f};
       for (int s = 0; s < T; ++s) {
-        floatx4 Ac[1] = {An}, Bc[1] = {Bn}, Kc[1] = {Kn}, Xn[1];
+        const floatx4 Ac = An, Bc = Bn, Kc = Kn;
         const int sn = s + 1 < T ? s + 1 : s;
         An = load_accT16<TIn>(Ap + (long long)sn * ba.tA, i, g);
         Bn = load_accT16<TIn>(Bp + (long long)sn * ba.tB, i, g);
         if (T > 1) Kn = *reinterpret_cast<const floatx4*>(wsK + (long)(sn - 1) * DD + (unsigned)(i * D + 4 * g));  // K_{s+1}
-        if (s >= 1) {
-          zero16<1>(U);
-          mul16<1>(U, Kc, X);
-        }
-        zero16<1>(Xn);
-        mul16<1>(Xn, Ac, X);
+        if (s >= 1) U[0] = dot16(Kc, X[0]);
+        const floatx4 Ax = dot16(Ac, X[0]);
         if (i < 2) {
           *reinterpret_cast<floatx4*>(traj + 64L * s + 16 * i + 4 * g) = X[0];
           *reinterpret_cast<floatx4*>(traj + 64L * s + 32 + 16 * i + 4 * g) = U[0];
         }
-        mul16<1>(Xn, Bc, U);
-        X[0] = Xn[0];
+        X[0] = Ax + dot16(Bc, U[0]);
       }
       if (i < 2) *reinterpret_cast<floatx4*>(traj + 64L * T + 16 * i + 4 * g) = X[0];
     }
@@ -132,8 +140,7 @@ __global__ void __launch_bounds__(64, 4) backward16_kernel(const BackwardArgs ba
     floatx4 L[1], sA = floatx4{0.f, 0.f, 0.f, 0.f}, sB = sA, sQ = sA, sR = sA, sQT = sA;
     {
       floatx4 Qs[1] = {0.5f * (load_acc16<TIn>(QTp, i, g) + load_accT16<TIn>(QTp, i, g))};
-      zero16<1>(L);
-      mul16<1>(L, Qs, X);  // lam_T = Q_T x_T
+      L[0] = dot16(Qs[0], X[0]);  // lam_T = Q_T x_T
     }
     const bool two = g < 2;
     auto vec = [&](int s, int off, int k) { return traj[64L * s + (unsigned)(off + 16 * k + i)]; };
@@ -155,21 +162,26 @@ __global__ void __launch_bounds__(64, 4) backward16_kernel(const BackwardArgs ba
       if (i < 2) *reinterpret_cast<floatx4*>(&s_lam[i][4 * g]) = L[0];  // lam_{s+1}
       wave_lds_sync();
       const float lam = two ? s_lam[g & 1][i] : 0.f;
-      floatx4 Ac[1] = {An}, Qs[1] = {0.5f * (Qn0 + Qn1)}, Xc[1] = {Xs}, Ln[1];
+      const floatx4 Ac = An, Qs = 0.5f * (Qn0 + Qn1), Xc = Xs;
       // an outer product has two terms: groups 2 and 3 are zero
       const float xo = two ? x_own : 0.f, xx = two ? x_other : 0.f, uo = two ? u_own : 0.f, ux = two ? u_other : 0.f;
       const int sn = s >= 1 ? s - 1 : 0;
       An = load_acc16<TIn>(Ap + (long long)sn * ba.tA, i, g);
       fetch(sn);
-      zero16<1>(Ln);
-      if (s >= 1) mul16<1>(Ln, Qs, Xc);
-      mul16<1>(Ln, Ac, L);  // + A_s^T lam_{s+1}
-      if (!ba.sum_steps) sA = sB = sQ = sR = floatx4{0.f, 0.f, 0.f, 0.f};
-      sA = __builtin_amdgcn_mfma_f32_16x16x4f32(xx, lam, sA, 0, 0, 0);  // transposed: xt lam^T + x lamt^T
-      sB = __builtin_amdgcn_mfma_f32_16x16x4f32(ux, lam, sB, 0, 0, 0);
-      sR = __builtin_amdgcn_mfma_f32_16x16x4f32(0.5f * ux, uo, sR, 0, 0, 0);
-      if (ba.gQT && s == T - 1) sQT = __builtin_amdgcn_mfma_f32_16x16x4f32(0.5f * xt_other, xt_own, sQT, 0, 0, 0);
-      else sQ = __builtin_amdgcn_mfma_f32_16x16x4f32(0.5f * xt_other, xt_own, sQ, 0, 0, 0);
+      floatx4 Ln = dot16(Ac, L[0]);  // A_s^T lam_{s+1}
+      if (s >= 1) Ln += dot16(Qs, Xc);
+      // a step's gradients are formed on their own and then added to the sum
+      const floatx4 none = floatx4{0.f, 0.f, 0.f, 0.f};
+      const floatx4 dA = __builtin_amdgcn_mfma_f32_16x16x4f32(xx, lam, none, 0, 0, 0);  // transposed: xt lam^T + x lamt^T
+      const floatx4 dB = __builtin_amdgcn_mfma_f32_16x16x4f32(ux, lam, none, 0, 0, 0);
+      const floatx4 dR = __builtin_amdgcn_mfma_f32_16x16x4f32(0.5f * ux, uo, none, 0, 0, 0);
+      const floatx4 dQ = __builtin_amdgcn_mfma_f32_16x16x4f32(0.5f * xt_other, xt_own, none, 0, 0, 0);
+      if (!ba.sum_steps) sA = sB = sQ = sR = none;
+      sA += dA;
+      sB += dB;
+      sR += dR;
+      if (ba.gQT && s == T - 1) sQT += dQ;
+      else sQ += dQ;
       if (!ba.sum_steps) {
         const long long o = (prob * T + s) * DD + i * D + 4 * g;
         const floatx4 nan4 = floatx4{nanv, nanv, nanv, nanv};
@@ -180,7 +192,7 @@ __global__ void __launch_bounds__(64, 4) backward16_kernel(const BackwardArgs ba
       }
       xt_own = xo;
       xt_other = xx;
-      L[0] = Ln[0];
+      L[0] = Ln;
       wave_lds_sync();
     }
     if (ba.sum_steps) {

@@ -106,3 +106,27 @@ def test_breakdown_and_argument_errors():
         binding.ttc_lqr_backward_tv(b.A, b.B, b.Q, b.R, b.x0, g, workspace=torch.empty(16, dtype=torch.uint8, device=DEV))
     e = binding.ttc_lqr_backward_tv(b.A[:0], b.B[:0], b.Q[:0], b.R[:0], b.x0[:0], g[:0])
     assert e["gx0"].shape == (0, d)
+
+
+# Errors (1e-7, 2-norm over all problems) of kernels that add up every product of a sweep as a tree over the lanes, on the
+# inputs of the test below.  The inputs are fixed, so is the order of every sum: the errors are the same in every run.
+TREE_SUMS = {(16, 8, 512): (5.42, 4.47, 5.57, 5.17, 4.08), (16, 24, 256): (9.1, 7.32, 7.66, 6.07, 5.64)}
+
+
+@pytest.mark.parametrize("d,T,n", sorted(TREE_SUMS))
+def test_gradients_lose_no_more_to_rounding_than_tree_sums_do(d, T, n):
+    """Norm of the error against float64, per gradient; their mean may not pass the figures above by half a per cent (chains
+    of products in place of trees, or an unrefined inverse in the first step, add two per cent and more)."""
+    num, den = np.zeros(5), np.zeros(5)
+    for seed in (1, 2):
+        b = synth.make_batch(n, d, d, T, seed=seed, device=DEV)
+        g = torch.randn((n, d), generator=torch.Generator().manual_seed(seed)).to(DEV)
+        out = binding.ttc_lqr_backward(b.A, b.B, b.Q, b.R, None, b.x0, T, g)
+        A, B, Q, R, x0 = b.numpy64()
+        ref = go.lqr_gradients(A, B, Q, R, None, x0, T, g.cpu().double().numpy())
+        for i, k in enumerate(("gA", "gB", "gQ", "gR", "gx0")):
+            num[i] += ((out[k].double().cpu().numpy() - ref[k]) ** 2).sum()
+            den[i] += (ref[k] ** 2).sum()
+    ratio = 1e7 * np.sqrt(num / den) / np.array(TREE_SUMS[d, T, n])
+    print(d, T, ratio)
+    assert ratio.mean() <= 1.005
