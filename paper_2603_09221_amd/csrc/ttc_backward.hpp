@@ -56,15 +56,19 @@ __device__ __forceinline__ void matvecT2(MatLoad1&& elem, const float* xa, const
                                          float& yb) {
   constexpr int TPR = Cfg<D>::NTHR / D;
   const int j = tid % D, part = tid / D;
-  float sa = 0.f, sb = 0.f;
-#pragma unroll 8
-  for (int r = part * (D / TPR); r < (part + 1) * (D / TPR); ++r) {
-    const float mv = elem(r, j);
-    sa += mv * xa[r];
-    sb += mv * xb[r];
+  // four sums side by side: one after the other, D / TPR terms round as often (the co-states are such sums at every step)
+  float sa[4] = {0.f, 0.f, 0.f, 0.f}, sb[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 2
+  for (int r = part * (D / TPR); r < (part + 1) * (D / TPR); r += 4) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float mv = elem(r + e, j);
+      sa[e] += mv * xa[r + e];
+      sb[e] += mv * xb[r + e];
+    }
   }
-  red[part * D + j] = sa;
-  red[(TPR + part) * D + j] = sb;
+  red[part * D + j] = (sa[0] + sa[1]) + (sa[2] + sa[3]);
+  red[(TPR + part) * D + j] = (sb[0] + sb[1]) + (sb[2] + sb[3]);
   __syncthreads();
   float a = 0.f, b = 0.f;
 #pragma unroll
@@ -198,7 +202,7 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, TTC_COLS_WAVES(D)) backward_kern
 #pragma unroll
         for (int r = 0; r < C::NT; ++r) f[r][0] = *reinterpret_cast<const floatx4*>((i ? v_ut : v_u) + 16 * r + 4 * g);
       }
-      const int flag = solve_cols<D, 1>(WR, s0, f, w, lane);
+      const int flag = solve_cols<D, 1, true>(WR, s0, f, w, lane);
       if (flag && !info) info = T;
       if (w == 0 && i < 2) {
 #pragma unroll

@@ -124,17 +124,17 @@ __device__ __forceinline__ void gemm_cols(floatx4 (&acc)[D / 16][CT], const floa
 // per block, no right operand through LDS, and a serial chain of some 1500 cycles per 16 columns (the pivoted panels of
 // lds_solve: about 5000).
 // With d <= 32 the explicit inverse alone loses up to a factor of three where control is cheap (the block is most of the
-// matrix); there one step of refinement, U += s[p][p]^{-1} (s[p][c] - s[p][p] U), restores a factor-and-solve's accuracy;
-// from d = 64 on it makes no difference (measured against float64, cost ratios 1 to 1e4).
+// matrix); there one step of refinement, U += s[p][p]^{-1} (s[p][c] - s[p][p] U), restores a factor-and-solve's accuracy
+// (REFINE).  From d = 64 on the recursion does not show it (measured against float64, cost ratios 1 to 1e4), but a single
+// solve does: the backward pass asks for it in its first step's, where it costs nothing beside the steps.
 // Returns, uniformly, whether a pivot was not above piv_min and finite.  Wp must be free to every wavefront on entry; its last
 // reads may still be under way in other wavefronts on return.
-template <int D, int FT>
+template <int D, int FT, bool REFINE = (D <= 32)>
 __device__ __forceinline__ int solve_cols(float* Wp, Cols<D>& s, floatx4 (&f)[D / 16][FT > 0 ? FT : 1], int w, int lane,
                                           float piv_min = 0.f) {
   using C = Cfg<D>;
   constexpr int NT = C::NT, CT = C::RB;
-  constexpr bool REFINE = D <= 32;
-  static_assert(!REFINE || C::NW == 1, "the refinement's operand stays in the wavefront that published the block");
+  constexpr bool LOCAL = C::NW == 1;  // one wavefront: the refinement's operand stays in it
   const int i = lane & 15, g = lane >> 4;
   w = uniform(w);
   int bad = 0;
@@ -142,12 +142,15 @@ __device__ __forceinline__ int solve_cols(float* Wp, Cols<D>& s, floatx4 (&f)[D 
   auto publish = [&](auto P) {  // by the wavefront that owns column tile p
     constexpr int p = decltype(P)::value, k = p % CT;
     float* const o = Wp + 4 * g * C::PITCH + 16 * (p & 1) + i;
-    if constexpr (REFINE) {  // through the tile the inverse goes to below (a wavefront's LDS operations run in order)
+    if constexpr (REFINE && LOCAL) {  // through the tile the inverse goes to below (a wavefront's LDS operations run in order)
 #pragma unroll
       for (int v = 0; v < 4; ++v) o[(16 * p + v) * C::PITCH] = -s[p][k][v];
       wave_lds_sync();
       d_neg = *reinterpret_cast<const floatx4*>(Wp + (16 * p + i) * C::PITCH + 16 * (p & 1) + 4 * g);
       wave_lds_sync();
+    } else if constexpr (REFINE) {  // to the columns behind both buffers' inverses
+#pragma unroll
+      for (int v = 0; v < 4; ++v) o[32 + v * C::PITCH] = -s[p][k][v];
     }
     floatx4 inv = s[p][k];
     bad |= invert_spread16(inv, lane, piv_min);
@@ -184,6 +187,7 @@ __device__ __forceinline__ int solve_cols(float* Wp, Cols<D>& s, floatx4 (&f)[D 
     floatx4 x[NT];
 #pragma unroll
     for (int r = 0; r < NT; ++r) x[r] = *reinterpret_cast<const floatx4*>(Wp + (16 * r + i) * C::PITCH + 16 * (p & 1) + 4 * g);
+    if constexpr (REFINE && !LOCAL) d_neg = *reinterpret_cast<const floatx4*>(Wp + i * C::PITCH + 32 + 16 * (p & 1) + 4 * g);
     auto rest = [&](auto SKIP) {
       static_for<0, CT>([&](auto K) {
         constexpr int k = decltype(K)::value;
@@ -196,7 +200,7 @@ __device__ __forceinline__ int solve_cols(float* Wp, Cols<D>& s, floatx4 (&f)[D 
       constexpr int kn = (p + 1) % CT;
       if (w == (p + 1) / CT) {
         column(P, x, s, IntC<kn>{});
-        if constexpr (REFINE) {  // the others still need this block's operands
+        if constexpr (REFINE && LOCAL) {  // the others still need this block's operands
           rest(IntC<kn>{});
           publish(IntC<p + 1>{});
         } else {

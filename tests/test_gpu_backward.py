@@ -110,7 +110,8 @@ def test_breakdown_and_argument_errors():
 
 # Errors (1e-7, 2-norm over all problems) of kernels that add up every product of a sweep as a tree over the lanes, on the
 # inputs of the test below.  The inputs are fixed, so is the order of every sum: the errors are the same in every run.
-TREE_SUMS = {(16, 8, 512): (5.42, 4.47, 5.57, 5.17, 4.08), (16, 24, 256): (9.1, 7.32, 7.66, 6.07, 5.64)}
+TREE_SUMS = {(16, 8, 512): (5.42, 4.47, 5.57, 5.17, 4.08), (16, 24, 256): (9.1, 7.32, 7.66, 6.07, 5.64),
+             (64, 8, 192): (9.08, 7.74, 8.67, 9.29, 6.95), (128, 8, 48): (12.8, 11.0, 12.1, 13.3, 9.94)}
 
 
 @pytest.mark.parametrize("d,T,n", sorted(TREE_SUMS))
