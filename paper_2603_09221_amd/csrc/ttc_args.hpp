@@ -31,7 +31,7 @@ struct RolloutArgs {
   long long sA, sB, sQ, sR, sQT, sx0;
   float *U, *X, *cost;
   int* info;
-  float* ws;  // gridDim.x slots of (T+3) d*d floats: G, R^{-1} B^T, A^T (register layout), K_0 .. K_{T-1}
+  float* ws;  // gridDim.x slots of (T+3) d*d floats: three for the sweep (register layout), K_0 .. K_{T-1}
 };
 
 struct DoublingArgs {

@@ -62,6 +62,24 @@ __device__ __forceinline__ void add_sym_cols(const TIn* M, Cols<D>& m, int w, in
 #pragma unroll
     for (int k = 0; k < Cfg<D>::RB; ++k) m[r][k] += 0.5f * (t[r][k] + ld4<TIn>(M, o + (unsigned)(16 * k * D + 16 * r)));
 }
+// A matrix by columns to memory and back as it stands in the registers, 16 bytes a lane: of a matrix that every step reads
+// (time-invariant parameters), its symmetric part takes a fifth of the reads this way.
+template <int D>
+__device__ __forceinline__ void keep_cols(float* M, const Cols<D>& m, int tid) {
+#pragma unroll
+  for (int r = 0; r < D / 16; ++r)
+#pragma unroll
+    for (int k = 0; k < Cfg<D>::RB; ++k)
+      reinterpret_cast<floatx4*>(M)[(r * Cfg<D>::RB + k) * Cfg<D>::NTHR + tid] = m[r][k];
+}
+template <int D>
+__device__ __forceinline__ void add_kept_cols(const float* M, Cols<D>& m, int tid) {
+#pragma unroll
+  for (int r = 0; r < D / 16; ++r)
+#pragma unroll
+    for (int k = 0; k < Cfg<D>::RB; ++k)
+      m[r][k] += reinterpret_cast<const floatx4*>(M)[(r * Cfg<D>::RB + k) * Cfg<D>::NTHR + tid];
+}
 // the transpose (times SIGN) to LDS, row-major: a lane's four values are 16 bytes of one row
 template <int D, int SIGN = 1>
 __device__ __forceinline__ void store_cols_T(float* L, const Cols<D>& m, int w, int i, int g) {
@@ -262,9 +280,10 @@ __device__ __forceinline__ int solve_pair_in_order(float* W, float piv_min, int 
 // (symmetric, visible) and the left half is free; on exit, by columns, wk = S^{-1} B^T P A = -K_s, S = R + B^T P B, and
 // pn = A^T P A - (B^T P A)^T wk, which is P_s up to the stage cost.  Six products and one unpivoted solve (S is positive
 // definite).  Returns the solve's breakdown flag.  Other wavefronts may still be reading the left half on return.
-template <int D, typename TIn>
-__device__ __forceinline__ int riccati_step(float* W, const TIn* As, const TIn* Bs, const TIn* Rs, Cols<D>& wk, Cols<D>& pn,
-                                            int tid) {
+// add_R(s, w, i, g) adds the symmetric part of R to s.
+template <int D, typename TIn, typename AddR>
+__device__ __forceinline__ int riccati_step_with(float* W, const TIn* As, const TIn* Bs, AddR&& add_R, Cols<D>& wk, Cols<D>& pn,
+                                                 int tid) {
   using C = Cfg<D>;
   tid += opaque_zero();
   const int lane = tid & 63, w = uniform(tid >> 6), i = lane & 15, g = lane >> 4;
@@ -277,7 +296,7 @@ __device__ __forceinline__ int riccati_step(float* W, const TIn* As, const TIn* 
     store_cols_T<D>(WL, b, w, i, g);  // B^T
     load_cols<D, TIn>(As, a, w, i, g);
     zero_cols<D>(s);
-    add_sym_cols<D, TIn>(Rs, s, w, i, g);  // R is read as its symmetric part
+    add_R(s, w, i, g);
     lds_barrier();
     zero_cols<D>(pb);
     gemm_cols<D>(pb, WR, b, i, g);  // P B
@@ -302,16 +321,28 @@ __device__ __forceinline__ int riccati_step(float* W, const TIn* As, const TIn* 
   return flag;
 }
 
-// P_s = pn + the symmetric part of the stage cost Qs goes to the right half, exactly symmetric.  Contains the barriers it
-// needs.
 template <int D, typename TIn>
-__device__ __forceinline__ void next_value_matrix(float* W, const TIn* Qs, Cols<D>& pn, int tid) {
+__device__ __forceinline__ int riccati_step(float* W, const TIn* As, const TIn* Bs, const TIn* Rs, Cols<D>& wk, Cols<D>& pn,
+                                            int tid) {
+  return riccati_step_with<D, TIn>(
+      W, As, Bs, [&](Cols<D>& s, int w, int i, int g) { add_sym_cols<D, TIn>(Rs, s, w, i, g); }, wk, pn, tid);
+}
+
+// P_s = pn + the symmetric part of the stage cost goes to the right half, exactly symmetric; add_Q(pn, w, i, g) adds it.
+// Contains the barriers it needs.
+template <int D, typename AddQ>
+__device__ __forceinline__ void next_value_matrix_with(float* W, AddQ&& add_Q, Cols<D>& pn, int tid) {
   const int lane = tid & 63, w = uniform(tid >> 6), i = lane & 15, g = lane >> 4;
-  add_sym_cols<D, TIn>(Qs, pn, w, i, g);
+  add_Q(pn, w, i, g);
   store_cols_T<D>(W + D, pn, w, i, g);  // (the solve ended with a barrier: the right half is free)
   lds_barrier();
   symmetrise_half<D>(W + D, tid);
   lds_barrier();
+}
+template <int D, typename TIn>
+__device__ __forceinline__ void next_value_matrix(float* W, const TIn* Qs, Cols<D>& pn, int tid) {
+  next_value_matrix_with<D>(
+      W, [&](Cols<D>& m, int w, int i, int g) { add_sym_cols<D, TIn>(Qs, m, w, i, g); }, pn, tid);
 }
 
 }  // namespace ttc

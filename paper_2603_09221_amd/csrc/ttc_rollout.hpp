@@ -140,8 +140,11 @@ __device__ __forceinline__ int rollout_pivoted_sweep(float* W, SolveScratch<D>& 
 // Roll-out kernel (Alg. 1 with r = 0).  Backward sweep: the recursion of Prop. 3.1 as ttc_lqr_solve_tv runs it, with the
 // same matrices in every step, the gains to the workspace; forward sweep: u_t = K_t x_t, x_{t+1} = A x_t + B u_t and the
 // cost, A and B read from LDS.  R is factored once for its report.
+// Every step needs R and Q as their symmetric parts: these are formed once and kept as the registers hold them (read anew in
+// every step, two elements apart for bfloat16, they made it slower than the pivoted sweep's at d = 128: 24 steps of 256
+// problems 1.98 -> 2.10 ms, with the kept ones 2.01).
 // Against the pivoted sweep for every problem and all five matrices of a forward step from memory: d = 64, T = 8, 4096
-// problems 1.94 -> 1.38 ms; d = 32, 8192 problems 0.79 -> 0.48 ms; d = 128, 1024 problems 3.01 -> 2.75 ms.
+// problems 1.94 -> 1.38 ms; d = 32, 8192 problems 0.80 -> 0.47 ms; d = 128, 1024 problems 3.01 -> 2.74 ms.
 template <int D, typename TIn>
 __global__ void __launch_bounds__(Cfg<D>::NTHR, TTC_COLS_WAVES(D)) rollout_kernel(const RolloutArgs p) {
   using C = Cfg<D>;
@@ -153,7 +156,8 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, TTC_COLS_WAVES(D)) rollout_kerne
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   float* const WL = W;
   float* const WR = W + D;
-  float* const wsC = p.ws + (long)blockIdx.x * (p.T + 3) * D * D;  // G, X, A^T in register layout
+  // symmetric parts of R and Q, in register layout (the pivoted sweep: G, X, A^T)
+  float* const wsC = p.ws + (long)blockIdx.x * (p.T + 3) * D * D;
   float* const wsK = wsC + 3 * D * D;                              // K_0 .. K_{T-1}, row-major
 
   for (long long prob = blockIdx.x; prob < p.n; prob += gridDim.x) {
@@ -171,6 +175,7 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, TTC_COLS_WAVES(D)) rollout_kerne
         floatx4 none[C::NT][1];  // no right-hand sides
         zero_cols<D>(r);
         add_sym_cols<D, TIn>(Rp, r, w, i, g);
+        keep_cols<D>(wsC, r, tb);
         info = solve_cols<D, 0>(WR, r, none, w, lane);
       }
       __syncthreads();
@@ -179,12 +184,22 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, TTC_COLS_WAVES(D)) rollout_kerne
         __syncthreads();
         symmetrise_half<D>(WR, tb);
         __syncthreads();
+        {
+          Cols<D> q;
+          zero_cols<D>(q);
+          add_sym_cols<D, TIn>(Qp, q, w, i, g);
+          keep_cols<D>(wsC + D * D, q, tb);
+        }
         int t = p.T - 1;
         for (; t >= 0; --t) {
           Cols<D> wk, pn;
-          if (riccati_step<D, TIn>(W, Ap, Bp, Rp, wk, pn, tb)) break;
+          const int tk = tb + opaque_zero();
+          if (riccati_step_with<D, TIn>(
+                  W, Ap, Bp, [&](Cols<D>& s, int, int, int) { add_kept_cols<D>(wsC, s, tk); }, wk, pn, tb))
+            break;
           store_cols<D, -1>(wsK + (long)t * D * D, D, wk, w, i, g);  // K_t
-          if (t >= 1) next_value_matrix<D, TIn>(W, Qp, pn, tb);
+          if (t >= 1)
+            next_value_matrix_with<D>(W, [&](Cols<D>& m, int, int, int) { add_kept_cols<D>(wsC + D * D, m, tk); }, pn, tb);
         }
         if (t >= 0) {
           __syncthreads();
