@@ -9,7 +9,10 @@ Without --force only objects older than a source file are rebuilt.
 from __future__ import annotations
 
 import argparse
+import glob
 import os
+import re
+import shutil
 import subprocess
 import sys
 from concurrent.futures import ThreadPoolExecutor
@@ -70,6 +73,57 @@ def _run(cmd):
         print(err, file=sys.stderr)
 
 
+def misplaced_vector_moves(asm: str) -> list:
+    """(kernel, line number, instruction) of vector spills, reloads and copies that stand between the label a wavefront
+    with no active lane jumps to (s_cbranch_execz) and the instruction there that restores EXEC.
+
+    The compiler this was built with places them so now and then, when it spills scalar registers at the same join: a
+    wavefront that skipped the branch then runs them with EXEC = 0 and keeps a stale register or scratch slot (a wrong
+    info, or a wild address and a memory fault).  What provokes it is a branch taken by masking lanes off, on a condition
+    that is the same for a whole wavefront, under high register pressure; the cure is to make that branch scalar (see
+    uniform() in ttc_device.hpp)."""
+    skipped_to = set(re.findall(r"^\s+s_cbranch_execz\s+(\S+)", asm, re.M))
+    kernel, pending, found = None, None, []
+    for n, line in enumerate(asm.split("\n"), 1):
+        label = re.match(r"^([\w.$]+):", line)
+        if label:
+            if label.group(1).startswith(".LBB"):
+                pending = [] if label.group(1) in skipped_to else None
+            elif not label.group(1).startswith("."):
+                kernel, pending = label.group(1), None
+        elif pending is None:
+            continue
+        elif re.match(r"\s+s_(or|mov)_b64 exec,", line):
+            found += pending
+            pending = None
+        elif re.match(r"\s+(scratch_|buffer_|v_accvgpr_|v_mov_b)", line):
+            pending.append((kernel, n, line.strip()))
+        elif re.match(r"\s+s_(cbranch|branch|endpgm|barrier|\w+ exec|\w*saveexec)", line) or \
+                not re.match(r"\s*(;|s_|v_readlane|v_writelane|$)", line):
+            pending = None  # the join's own code has begun
+    return found
+
+
+def _compile(job):
+    """Compile one object in a folder of its own, where the compiler leaves its assembly, and look through that."""
+    cmd, obj = job
+    folder = obj[:-2]
+    shutil.rmtree(folder, ignore_errors=True)
+    os.makedirs(folder)
+    out = os.path.join(folder, os.path.basename(obj))
+    _run(cmd + ["-save-temps=obj", "-o", out])
+    listings = glob.glob(os.path.join(folder, "*gfx950.s"))
+    if len(listings) != 1:
+        raise RuntimeError("%s: %d device listings" % (out, len(listings)))
+    with open(listings[0]) as f:
+        found = misplaced_vector_moves(f.read())
+    if found:
+        raise RuntimeError("vector instructions ahead of an EXEC restore (%s):\n%s"
+                           % (" ".join(cmd), "\n".join("%s line %d: %s" % x for x in found)))
+    os.replace(out, obj)
+    shutil.rmtree(folder)
+
+
 def _newest_source():
     t = 0.0
     for folder in (CSRC, INCLUDE):
@@ -92,12 +146,12 @@ def build(force: bool = True, jobs: int | None = None, extra_flags=()) -> str:
             objs.append(obj)
             if force or not os.path.exists(obj) or os.path.getmtime(obj) < newest:
                 cmd = [hipcc] + HIPCC_FLAGS + list(extra_flags) + UNIT_FLAGS.get((src, d), []) + \
-                      (["-DTTC_D=%d" % d] if d else []) + ["-c", os.path.join(CSRC, src), "-o", obj]
-                work.append(cmd)
+                      (["-DTTC_D=%d" % d] if d else []) + ["-c", os.path.join(CSRC, src)]
+                work.append((cmd, obj))
     # the largest state sizes take longest: start them first
-    work.sort(key=lambda c: -max([int(a[8:]) for a in c if a.startswith("-DTTC_D=")] or [0]))
+    work.sort(key=lambda c: -max([int(a[8:]) for a in c[0] if a.startswith("-DTTC_D=")] or [0]))
     with ThreadPoolExecutor(max_workers=jobs) as ex:
-        list(ex.map(_run, work))
+        list(ex.map(_compile, work))
     if work or not os.path.exists(OUT):
         _run([hipcc, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", OUT] + objs)
     return OUT

@@ -1,0 +1,40 @@
+"""The build looks through the device listings for vector moves that a wavefront without active lanes would lose.  Small
+listings, written by hand, with the move on either side of the restore."""
+import pytest
+
+from paper_2603_09221_amd import build
+
+BODY = """
+a_kernel:                               ; @a_kernel
+; %%bb.0:
+	v_cmp_gt_u32_e32 vcc, 64, v0
+	s_and_saveexec_b64 s[4:5], vcc
+	s_cbranch_execz .LBB0_2
+; %%bb.1:
+	v_add_f32_e32 v1, v1, v2
+.LBB0_2:                                ; %%if.end
+	%s
+	v_readlane_b32 s6, v40, 3
+	%s
+	s_or_b64 exec, exec, s[4:5]
+	%s
+	v_mul_f32_e32 v1, v1, v3
+	s_endpgm
+"""
+NOTHING = "s_nop 0"
+
+
+@pytest.mark.parametrize("move", ["scratch_store_dword off, v7, off offset:128 ; 4-byte Folded Spill",
+                                  "scratch_load_dwordx2 v[6:7], off, off offset:4", "v_accvgpr_write_b32 a3, v7",
+                                  "v_mov_b32_e32 v9, v7"])
+def test_a_move_ahead_of_the_restore_is_found(move):
+    for text in (BODY % (move, NOTHING, NOTHING), BODY % (NOTHING, move, NOTHING)):
+        assert [(k, x) for k, _, x in build.misplaced_vector_moves(text)] == [("a_kernel", move)]
+    assert not build.misplaced_vector_moves(BODY % (NOTHING, NOTHING, move))
+
+
+def test_joins_that_nobody_skips_to_and_other_code_are_left_alone():
+    move = "scratch_store_dword off, v7, off offset:128"
+    assert not build.misplaced_vector_moves((BODY % (move, NOTHING, NOTHING)).replace("s_cbranch_execz", "s_cbranch_scc0"))
+    assert not build.misplaced_vector_moves(BODY % (move, "v_add_f32_e32 v4, v4, v4", NOTHING))
+    assert not build.misplaced_vector_moves(BODY % (move, "s_and_b64 exec, exec, s[8:9]", NOTHING))
