@@ -113,22 +113,25 @@ def alg_flops_doubling(d, T):
     return (f + 8 + 8.0 / 3) * d ** 3
 
 
-def default_squares(d, T, bf16):
-    """Whether the default path of ttc_lqr_solve (Q_T = Q, rebase_every = 0) composes the equal factors by squaring: the
-    library's own rule (use_squaring in csrc/ttc_api.hip)."""
-    if d < 32 or T < 2:
-        return False
-    applications = bin(T).count("1") - 1
-    cost = 100 * (T.bit_length() - 1) + 70 * applications + (35 if applications else 0) + 10
-    return 100 * cost <= 98 * (37 if bf16 else 40) * T
+def default_squares(d, T, bf16, own_QT=False):
+    """Whether the default path of ttc_lqr_solve composes the equal factors by squaring: the library's answer."""
+    from paper_2603_09221_amd import binding
+    return binding.ttc_lqr_solve_squares(binding.Problem(
+        n=1, d=d, m=d, T=T, in_dtype=binding.TTC_BF16 if bf16 else binding.TTC_F32, Q=256, QT=512 if own_QT else None))
+
+
+def alg_flops_squaring(d, T):
+    """Algorithmic flops of one problem on the default path where it squares: the schedule of alg_flops_doubling, whose last
+    step is the printed one (six products and the solve with the positive definite R + B^T P B), and A factored for its
+    report (2/3 d^3)."""
+    return alg_flops_doubling(d, T) + (2.0 / 3 - (8 + 8.0 / 3) + 6 * 2 + 1.0 / 3 + 2) * d ** 3
 
 
 def alg_flops_default(d, T, groups, bf16, rebase_every=0):
-    """Algorithmic flops of one problem on the default path: the sequential product, or the squaring schedule, which then
-    also factors A (2/3 d^3)."""
+    """Algorithmic flops of one problem on the default path: the sequential product, or the squaring schedule."""
     if rebase_every or not default_squares(d, T, bf16):
         return alg_flops(d, T, groups)
-    return alg_flops_doubling(d, T) + 2.0 / 3 * d ** 3
+    return alg_flops_squaring(d, T)
 
 
 def alg_flops_tv(d, T):

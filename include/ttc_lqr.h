@@ -13,7 +13,8 @@
  * Because cond(Y1) grows geometrically with the number of accumulated factors, the T factors are
  * applied in groups and the pair is re-based to [I P] after each group: rebase_every = k asks for
  * ceil(T/k) groups of nearly equal length (the paper's algorithm is one group, rebase_every >= T).
- * At d >= 32, from horizons on at which it is cheaper (all T from 16 on, some from 8 on), the T equal factors are instead
+ * At d >= 32, from horizons on at which it is cheaper, the T equal factors are instead (Q_T = Q: float32 inputs T = 8 and
+ * from 12 on, bfloat16 T = 12, 14 and from 16 on; a Q_T of its own: 13 and from 15 on, bfloat16 from 17 on)
  * composed by squaring (the algebra described at TTC_FLAG_DOUBLING; rebase_every must be 0): more accurate on
  * ordinary problems, and watched by a guard of its own on max |I + G_e H_e|.  What it cannot do is solved by a second launch
  * behind it: by the recursion as below, or (stage costs that are not semidefinite, breakdowns) by the product.
@@ -120,6 +121,11 @@ size_t ttc_lqr_workspace_bytes(const ttc_lqr_problem_t *problem, int for_rollout
  * aligned, used as scratch for the duration of the launch.  Asynchronous on `hip_stream`. */
 ttc_status_t ttc_lqr_solve(const ttc_lqr_problem_t *problem, const ttc_lqr_solution_t *solution,
                            void *workspace, size_t workspace_bytes, void *hip_stream);
+
+/* 1 if ttc_lqr_solve would compose this problem's factors by squaring (see the file header; TTC_FLAG_DOUBLING not
+ * meant), 0 if not or if the problem is not supported.  Looks at d, m, T, in_dtype, flags, rebase_every and at whether
+ * Q_T is Q; needs no device. */
+int ttc_lqr_solve_squares(const ttc_lqr_problem_t *problem);
 
 /* ttc_lqr_solve for callers that cannot allocate device memory or pass a workspace: code running under HIP
  * graph capture, tight serving loops, harnesses that forbid allocation.  Same inputs, outputs, conventions and

@@ -20,7 +20,7 @@ TTC_FLAG_STAGE_COST_AT_X0 = 1
 TTC_FLAG_PURE_SYMPLECTIC = 2
 TTC_FLAG_DOUBLING = 4
 
-EXPORTS = ("ttc_lqr_workspace_bytes", "ttc_lqr_solve", "ttc_lqr_solve_noalloc", "ttc_lqr_noalloc_scratch_bytes",
+EXPORTS = ("ttc_lqr_workspace_bytes", "ttc_lqr_solve", "ttc_lqr_solve_squares", "ttc_lqr_solve_noalloc", "ttc_lqr_noalloc_scratch_bytes",
            "ttc_lqr_rollout", "ttc_lqr_solve_tv", "ttc_lqr_rollout_tv",
            "ttc_lqr_tv_rollout_workspace_bytes", "ttc_lqr_solve_cxt", "ttc_lqr_rollout_cxt",
            "ttc_lqr_cxt_rollout_workspace_bytes", "ttc_lqr_solve_tv_scan",
@@ -101,6 +101,8 @@ def load():
     lib.ttc_lqr_workspace_bytes.argtypes = [ctypes.POINTER(Problem), c_int]
     lib.ttc_lqr_solve.restype = c_int
     lib.ttc_lqr_solve.argtypes = [ctypes.POINTER(Problem), ctypes.POINTER(Solution), c_void_p, c_size_t, c_void_p]
+    lib.ttc_lqr_solve_squares.restype = c_int
+    lib.ttc_lqr_solve_squares.argtypes = [ctypes.POINTER(Problem)]
     lib.ttc_lqr_solve_noalloc.restype = c_int
     lib.ttc_lqr_solve_noalloc.argtypes = [ctypes.POINTER(Problem), ctypes.POINTER(Solution), c_void_p]
     lib.ttc_lqr_noalloc_scratch_bytes.restype = c_size_t
@@ -209,6 +211,11 @@ def make_problem(A, B, Q, R, QT, x0, T, flags=0, rebase_every=0, n=None) -> Prob
 
 def ttc_lqr_workspace_bytes(problem: Problem, for_rollout: bool = False) -> int:
     return load().ttc_lqr_workspace_bytes(ctypes.byref(problem), 1 if for_rollout else 0)
+
+
+def ttc_lqr_solve_squares(problem: Problem) -> bool:
+    """Whether ttc_lqr_solve composes this problem's factors by squaring."""
+    return bool(load().ttc_lqr_solve_squares(ctypes.byref(problem)))
 
 
 def _stream_ptr(stream):

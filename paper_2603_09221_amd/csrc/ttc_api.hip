@@ -267,6 +267,10 @@ size_t ttc_lqr_workspace_bytes(const ttc_lqr_problem_t* problem, int for_rollout
   return slots * per * (for_rollout ? (size_t)problem->T + 3 : solve_slots);
 }
 
+int ttc_lqr_solve_squares(const ttc_lqr_problem_t* problem) {
+  return problem && problem->T >= 1 && ttc::shape_supported(problem) && ttc::use_squaring(problem) ? 1 : 0;
+}
+
 ttc_status_t ttc_lqr_solve(const ttc_lqr_problem_t* problem, const ttc_lqr_solution_t* solution,
                            void* workspace, size_t workspace_bytes, void* hip_stream) {
   const ttc_status_t st = ttc::validate(problem);

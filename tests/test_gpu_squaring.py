@@ -18,15 +18,54 @@ def solve(b, QT=None, **kw):
     return out
 
 
+def squared(T, bf16, own_QT, d=64, **kw):
+    p = binding.Problem(n=1, d=d, m=d, T=T, in_dtype=binding.TTC_BF16 if bf16 else binding.TTC_F32, Q=256,
+                        QT=512 if own_QT else None)
+    for k, v in kw.items():
+        setattr(p, k, v)
+    return binding.ttc_lqr_solve_squares(p)
+
+
 def test_the_rule_takes_long_horizons_and_leaves_short_ones():
-    """Float32: every horizon from 12 on and T = 8; never below 8, where the sequential
-    product is cheaper; never at d = 16, which has its own kernel."""
+    """The library's rule, asked through its query, which bench.py prices the default path with: the horizons up to 40 it
+    takes, for either input type, with Q_T = Q (absent, or the very same array) and with a Q_T of its own; every later one;
+    none at d = 16, which has its own kernel, none where the caller asks for the product or for the flagged path."""
     for d in (32, 64, 128):
-        for bf16 in (False, True):
-            assert not any(bench.default_squares(d, T, bf16) for T in range(1, 8))
-            assert all(bench.default_squares(d, T, bf16) for T in range(16, 300))
-        assert bench.default_squares(d, 8, False) and not bench.default_squares(d, 9, False)
-    assert not any(bench.default_squares(16, T, False) for T in range(1, 100))
+        takes = lambda bf16, own: {T for T in range(1, 41) if squared(T, bf16, own, d=d)}
+        assert takes(False, False) == {8} | set(range(12, 41))
+        assert takes(True, False) == {12, 14} | set(range(16, 41))
+        assert takes(False, True) == {13} | set(range(15, 41))
+        assert takes(True, True) == set(range(17, 41))
+        for T in (41, 64, 127, 1023, 1024, 1000000):
+            assert all(squared(T, b, o, d=d) for b in (False, True) for o in (False, True))
+        assert squared(8, False, True, d=d, QT=256) and not squared(8, False, True, d=d, QT=256, sQT=4)
+        for kw in (dict(rebase_every=3), dict(flags=binding.TTC_FLAG_PURE_SYMPLECTIC), dict(flags=binding.TTC_FLAG_DOUBLING)):
+            assert not squared(64, False, False, d=d, **kw)
+        assert bench.default_squares(d, 8, False) and not bench.default_squares(d, 8, False, own_QT=True)
+    assert not any(squared(T, False, False, d=16) for T in range(1, 100))
+    assert not squared(64, False, False, d=48) and not squared(0, False, False)
+    assert bench.alg_flops_default(64, 8, 3, False) != bench.alg_flops(64, 8, 3)
+    assert bench.alg_flops_default(64, 9, 3, False) == bench.alg_flops(64, 9, 3)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,own_QT", [("f32", False), ("f32", True), ("bf16", False), ("bf16", True)])
+def test_the_rule_is_what_runs(dtype, own_QT):
+    """Where the rule does not square, the result is bit for bit that of the product in its default grouping, asked for by
+    rebase_every; where it does, it is not.  Horizons on both sides of every edge that a rebase_every can ask for."""
+    d, seen = 64, set()
+    for T in range(7, 20):
+        groups = bench.default_groups(T, dtype)
+        ask = [k for k in range(1, T + 1) if -(-T // k) == groups]
+        if not ask:
+            continue
+        b = synth.make_batch(5, d, d, T, seed=T, device=DEV, dtype=dtype)
+        QT = (1.5 * b.Q).contiguous() if own_QT else None
+        out, seq = solve(b, QT=QT), solve(b, QT=QT, rebase_every=ask[0])
+        same = all(torch.equal(out[k], seq[k]) for k in SOLVE_KEYS)
+        assert same != squared(T, dtype == "bf16", own_QT, d=d), T
+        seen.add(same)
+    assert seen == {False, True}
 
 
 @pytest.mark.gpu
