@@ -143,9 +143,11 @@ static bool qt_is_q(const ttc_lqr_problem_t* q) { return !q->QT || (q->QT == q->
 // (solve_kernel).  Costs in hundredths of a squaring, fitted to both kernels at d = 32, 64, 128 and T = 8..64: a squaring
 // 100, an application of a power to P 70, A and G of the last square 35 (not needed when P is still 0), 10 more for the
 // set-up (A is factored for its report); a factor of the sequential product 40, with bfloat16 inputs (longer groups) 37.
-// Measured, sequential / squaring, ms: d = 64, 8192 problems, T = 8 2.14 / 1.88, T = 9 2.26 / 2.34, 12 2.84 / 2.32, 15
-// 3.41 / 2.88, 16 4.44 / 2.31, 64 15.9 / 3.17; d = 128, 2048 problems, T = 8 3.70 / 3.69, 9 3.95 / 4.61, 12 4.95 / 4.61,
-// 16 7.01 / 4.52 (with its own Q_T 7.01 / 6.40), 32 11.8 / 5.35; bfloat16 inputs T = 13 4.91 / 5.22, 16 5.92 / 4.52.
+// Measured, sequential / squaring, ms: d = 64, 8192 problems, T = 8 2.14 / 1.65, 12 2.85 / 2.05, 15 3.42 / 2.50, 16 4.30 / 2.02,
+// 64 15.4 / 2.78; d = 128, 2048 problems, T = 8 3.70 / 3.33, 12 4.95 / 4.19, 15 5.96 / 5.27, 16 6.99 / 4.12, 32 11.8 / 4.93;
+// bfloat16 inputs T = 12 4.66 / 4.15, 16 5.92 / 4.10; left to the product: T = 9, an application of a power besides the squarings
+// of T = 8 (an earlier build 2.26 / 2.34 and 3.95 / 4.61).  The number of problems does not move the line: one problem alone
+// d = 64, T = 8 169 / 136 us, d = 128, T = 12 628 / 510 us, with bfloat16 inputs 594 / 511 us.
 static bool use_squaring(const ttc_lqr_problem_t* q) {
   if (q->d < 32 || (q->flags & (TTC_FLAG_DOUBLING | TTC_FLAG_PURE_SYMPLECTIC)) || q->rebase_every != 0) return false;
   const bool from_zero = qt_is_q(q);

@@ -1,11 +1,11 @@
 // The backward pass of the layer (ttc_backward.hpp has the method) at d = 16: a workgroup of one wavefront per problem,
 // register to register.  A call at the sizes of the paper's benchmark is bound by the latency of its three serial sweeps
 // over the horizon, so a step does as little as possible in series: the recursion is riccati_step16 (ttc_tv.hpp); a
-// closed-loop step is two dependent products of four matrix instructions (in two halves, dot16) for the primal and the dual trajectory together
-// (a state is a 16 x 16 operand with the primal in column 0 and the dual in column 1); a co-state step is one, beside which
-// the four gradients of the step before, rank-2 outer products, are one matrix instruction each.  The matrices of a step
-// are requested one step ahead.  Measured, kernel time at T = 64, against backward_kernel at d = 16
-// (operands through LDS, a workgroup barrier per exchange): 16 problems 417 -> 168 us, 1024: 647 -> 271 us, 2048: 857 -> 430
+// closed-loop step is two dependent products of four matrix instructions, in two halves (dot16), for the primal and the
+// dual trajectory together (a state is a 16 x 16 operand with the primal in column 0 and the dual in column 1); a co-state
+// step is one, beside which the four gradients of the step before, rank-2 outer products, are one matrix instruction each.
+// The matrices of a step are requested one step ahead.  Measured, kernel time at T = 64, against backward_kernel at d = 16
+// (operands through LDS, a workgroup barrier per exchange): 16 problems 417 -> 173 us, 1024: 647 -> 280 us, 2048: 857 -> 440
 // us; at 1024 problems and up it is the traffic, some 14 KB per problem and step, that counts (3.5 TB/s).
 #pragma once
 #include "ttc_tv.hpp"

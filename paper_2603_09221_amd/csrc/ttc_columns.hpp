@@ -8,7 +8,7 @@
 //
 // Measured against steps with matrices by rows and the panel-wise lds_solve, T = 8, float32: ttc_lqr_solve_tv d = 64, 4096
 // problems 1.84 -> 1.29 ms (six products and the solve at 98 TFLOP/s of the 152 the matrix cores reach in float32), d = 32,
-// 8192 problems 0.59 -> 0.44 ms, d = 128, 1024 problems 2.99 -> 2.54 ms; ttc_lqr_backward d = 64, 8192 problems 4.15 -> 2.94
+// 8192 problems 0.59 -> 0.44 ms, d = 128, 1024 problems 2.99 -> 2.54 ms; ttc_lqr_backward d = 64, 8192 problems 4.15 -> 2.90
 // ms.  What is left is the inverse's serial chain, hidden as far as three workgroups a compute unit allow.
 #pragma once
 #include "ttc_common.hpp"

@@ -62,8 +62,8 @@ static constexpr float LATE_LIMIT = 64.f, GROWTH_STOP = 16.f;
 // The thread index is formed anew in the loop: shared with the set-up, its address arithmetic lives across the solves
 // (4.15 against 4.52 ms below).
 // Measured, solve_kernel / with the cold paths inlined / now: d = 128, T = 16, 2048 problems 7.01 / 4.27 / 4.15 ms, T = 64
-// 35 / 5.88 / 5.74; T = 32, bfloat16 inputs 11.8 / 5.35; d = 64, 8192 problems, T = 8 2.14 / 1.70 / 1.65, T = 64
-// 15.9 / 2.87 / 2.81; d = 32, T = 16, 16384 problems 1.7 / 0.73 / 0.71.
+// 35 / 5.88 / 5.74; T = 32, bfloat16 inputs 10.7 / 5.0 / 4.9; d = 64, 8192 problems, T = 8 2.14 / 1.70 / 1.65, T = 64
+// 15.4 / 2.87 / 2.78; d = 32, T = 16, 16384 problems 1.6 / 0.73 / 0.69.
 template <int D, typename TIn>
 __global__ void __launch_bounds__(Cfg<D>::NTHR, (D <= 64 ? 2 : 1)) squaring_kernel(const DoublingArgs da) {
   using C = Cfg<D>;
