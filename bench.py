@@ -793,8 +793,10 @@ def main():
                    "outputs": "gA,gB,gQ,gR,gx0" if path == "bwd" else "U,X,cost" if path == "rollout" else "P0,K0,u0,value"},
         "roofline": {"bound": "mfma", "achieved": achieved, "peak": PEAK_FP32_MFMA_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / PEAK_FP32_MFMA_TFLOPS,
-                     "traffic": measured_traffic(args.config, path, n),
-                     "kernel": kernel_name, "launches_per_step": nchunks,
+                     # (a row belongs to the default algorithm of its workload, not to the groups rebase_every asks for)
+                     "traffic": measured_traffic(args.config, path, n) if not (path == "symplectic" and k) else None,
+                     # squaring: a second kernel takes the problems the first gives up
+                     "kernel": kernel_name, "launches_per_step": nchunks * (2 if squares else 1),
                      "kernel_ms": avg_kernel_s * 1e3, **spread(kernel_ms),
                      "alg_flops_per_problem": flops_pp,
                      "nominal_TFLOPs_N_T_d3": n * T * d ** 3 / avg_kernel_s / 1e12,
