@@ -49,11 +49,10 @@ UNITS = [("ttc_api.hip", None),
 # batch (two blocks spill, as they do in the time-heterogeneous kernel); flagged doubling d = 128, T = 16 501k problems/s
 # against 488k.
 _ONE_ROW_BLOCK = "-DTTC_ROW_BLOCKS(D)=((D)==%d?1:((D)>=32?2:1))"
-# The backward kernel is held to two wavefronts a SIMD, not three: its sweeps over the steps read a matrix per product
-# straight from memory, and with 168 registers those reads wait for one another (time-heterogeneous, T = 8, 8192 problems, d = 64:
-# float32 4.31 -> 3.62 ms, bfloat16 4.53 -> 3.38; 64 problems 0.229 -> 0.187; time-invariant 2.97 -> 2.90).
-_TWO_WAVES = "-DTTC_COLS_WAVES(D)=2"
-UNIT_FLAGS = {("k_backward.hip", 64): [_ONE_ROW_BLOCK % 64, _TWO_WAVES],
+# The backward kernel at d = 64 takes 188 registers by itself; held to the 168 of three wavefronts a SIMD it spills 20 of them and
+# is still the faster (T = 8, 8192 problems, time-invariant 2.26 ms against 2.88).
+_THREE_WAVES = "-DTTC_COLS_WAVES(D)=3"
+UNIT_FLAGS = {("k_backward.hip", 64): [_ONE_ROW_BLOCK % 64, _THREE_WAVES],
               ("k_tv.hip", 64): [_ONE_ROW_BLOCK % 64],
               ("k_tv.hip", 128): [_ONE_ROW_BLOCK % 128],
               ("k_doubling.hip", 128): [_ONE_ROW_BLOCK % 128],

@@ -26,27 +26,20 @@
 
 namespace ttc {
 
+template <int D>
+__device__ __forceinline__ void dot2(const RowShare<D>& m, const float* xa, const float* xb, int tid, float& ya, float& yb) {
+  ya = m.dot(xa, tid);
+  yb = m.dot(xb, tid);
+}
 // Two matrix-vector products at once (the primal and the dual trajectory always need the same matrix): for the
 // row r = tid / TPR of a row-major d x d matrix, ya = sum_c M[r][c] xa[c] and yb likewise; the TPR threads of a
 // row each take a share of the columns and all of them get the sums.  MatLoad(r, c4) returns M[r][c4 .. c4+3].
 template <int D, typename MatLoad>
 __device__ __forceinline__ void matvec2(MatLoad&& row4, const float* xa, const float* xb, int tid, float& ya, float& yb) {
-  constexpr int TPR = Cfg<D>::NTHR / D;  // 2 or 4
-  const int r = tid / TPR, part = tid % TPR;
-  float sa = 0.f, sb = 0.f;
-#pragma unroll
-  for (int c4 = part * (D / TPR); c4 < (part + 1) * (D / TPR); c4 += 4) {
-    const floatx4 mv = row4(r, c4);
-    sa += mv[0] * xa[c4] + mv[1] * xa[c4 + 1] + mv[2] * xa[c4 + 2] + mv[3] * xa[c4 + 3];
-    sb += mv[0] * xb[c4] + mv[1] * xb[c4 + 1] + mv[2] * xb[c4 + 2] + mv[3] * xb[c4 + 3];
-  }
-#pragma unroll
-  for (int m = 1; m < TPR; m <<= 1) {
-    sa += __shfl_xor(sa, m, 64);
-    sb += __shfl_xor(sb, m, 64);
-  }
-  ya = sa;
-  yb = sb;
+  RowShare<D> m;
+  m.load(row4, tid);
+  TTC_SCHED_BARRIER();
+  dot2<D>(m, xa, xb, tid, ya, yb);
 }
 // The transposed products ya[j] = sum_r M[r][j] xa[r], yb likewise: thread (part, j) sums its share of the rows
 // (consecutive threads read consecutive columns), the parts are added through LDS (red: 2 x TPR x D floats).
@@ -58,25 +51,30 @@ __device__ __forceinline__ void matvecT2(MatLoad1&& elem, const float* xa, const
   const int j = tid % D, part = tid / D;
   // four sums side by side: one after the other, D / TPR terms round as often (the co-states are such sums at every step)
   float sa[4] = {0.f, 0.f, 0.f, 0.f}, sb[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 2
-  for (int r = part * (D / TPR); r < (part + 1) * (D / TPR); r += 4) {
+  float m[D / TPR];
+#pragma unroll
+  for (int r = 0; r < D / TPR; ++r) m[r] = elem(part * (D / TPR) + r, j);
+  TTC_SCHED_BARRIER();  // all reads are under way
+#pragma unroll
+  for (int r = 0; r < D / TPR; r += 4) {
+    const floatx4 va = *reinterpret_cast<const floatx4*>(xa + part * (D / TPR) + r);
+    const floatx4 vb = *reinterpret_cast<const floatx4*>(xb + part * (D / TPR) + r);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const float mv = elem(r + e, j);
-      sa[e] += mv * xa[r + e];
-      sb[e] += mv * xb[r + e];
+      sa[e] += m[r + e] * va[e];
+      sb[e] += m[r + e] * vb[e];
     }
   }
   red[part * D + j] = (sa[0] + sa[1]) + (sa[2] + sa[3]);
   red[(TPR + part) * D + j] = (sb[0] + sb[1]) + (sb[2] + sb[3]);
-  __syncthreads();
+  lds_barrier();
   float a = 0.f, b = 0.f;
 #pragma unroll
   for (int q = 0; q < TPR; ++q) {
     a += red[q * D + j];
     b += red[(TPR + q) * D + j];
   }
-  __syncthreads();
+  lds_barrier();
   ya = a;
   yb = b;
 }
@@ -100,7 +98,7 @@ template <int D, typename TIn>
 __global__ void __launch_bounds__(Cfg<D>::NTHR, TTC_COLS_WAVES(D)) backward_kernel(const BackwardArgs ba) {
   using C = Cfg<D>;
   constexpr int TPR = C::NTHR / D;
-  __shared__ __attribute__((aligned(16))) float W[D * C::PITCH];
+  __shared__ __attribute__((aligned(16))) float W[C::PAIR];
   __shared__ float s_red[2 * TPR * D];
   __shared__ __attribute__((aligned(16))) float s_v[8][D];  // working vectors
   const RolloutArgs& p = ba.r;
@@ -224,41 +222,42 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, TTC_COLS_WAVES(D)) backward_kern
     }
 
     // ---- both closed loops forward (Alg. 1): states and controls of every step to the workspace
+    // (barriers inside these loops order LDS only: a full one would wait for the reads and stores in flight)
+    // The gain of a step is read one step ahead.  Every thread writes the entries of its row, all of a row the same: without a
+    // branch around the stores the wait for the gain leaves them in flight.
+    RowShare<D> Kr;
+    Kr.load([](int, int) { return floatx4{0.f, 0.f, 0.f, 0.f}; }, tid);
     for (int s = 0; s < T; ++s) {
-      const TIn* As = Ap + (long long)s * ba.tA;
-      const TIn* Bs = Bp + (long long)s * ba.tB;
-      if (s >= 1) {
-        const float* Ks = wsK + (long)(s - 1) * D * D;
-        float u, ut;
-        matvec2<D>([Ks](int r, int c4) { return *reinterpret_cast<const floatx4*>(Ks + (long)r * D + c4); }, v_x, v_xt,
-                   tid, u, ut);
-        if (lead) {
-          v_u[row] = u;
-          v_ut[row] = ut;
-        }
-        __syncthreads();
-      }
-      float ax, axt, bu, but;
+      RowShare<D> Ar, Br;
       if (resident) {
-        matvec2<D>(lds4(WL), v_x, v_xt, tid, ax, axt);
-        matvec2<D>(lds4(WR), v_u, v_ut, tid, bu, but);
+        Ar.load(lds4(WL), tid);
       } else {
-        matvec2<D>(glob4(As), v_x, v_xt, tid, ax, axt);
-        matvec2<D>(glob4(Bs), v_u, v_ut, tid, bu, but);
+        Ar.load(glob4(Ap + (long long)s * ba.tA), tid);
+        Br.load(glob4(Bp + (long long)s * ba.tB), tid);
       }
-      if (tid < D) {
-        tU[(long)s * D + tid] = v_u[tid];
-        tUt[(long)s * D + tid] = v_ut[tid];
+      float ax, axt, bu, but, u, ut;
+      dot2<D>(Kr, v_x, v_xt, tid, u, ut);
+      if (s == 0) {
+        u = v_u[row];
+        ut = v_ut[row];
       }
-      __syncthreads();  // every thread has read the old states
-      if (lead) {
-        v_x[row] = ax + bu;
-        v_xt[row] = axt + but;
-        tX[(long)(s + 1) * D + row] = ax + bu;
-        tXt[(long)(s + 1) * D + row] = axt + but;
-      }
-      __syncthreads();
+      v_u[row] = u;
+      v_ut[row] = ut;
+      if (s + 1 < T) Kr.load(rows_of<D, float>(wsK + (long)s * D * D), tid);
+      TTC_SCHED_BARRIER();
+      dot2<D>(Ar, v_x, v_xt, tid, ax, axt);
+      if (resident) Br.load(lds4(WR), tid);
+      lds_barrier();  // the controls are complete, and every thread has read the old states
+      dot2<D>(Br, v_u, v_ut, tid, bu, but);
+      v_x[row] = ax + bu;
+      v_xt[row] = axt + but;
+      tU[(long)s * D + row] = u;
+      tUt[(long)s * D + row] = ut;
+      tX[(long)(s + 1) * D + row] = ax + bu;
+      tXt[(long)(s + 1) * D + row] = axt + but;
+      lds_barrier();
     }
+    __syncthreads();  // the trajectories are in memory
 
     // ---- co-states backward (Alg. 2), for both trajectories; dl/dx_0 = lamt_0.  A cost matrix is read as its
     // symmetric part: half of Q x + Q^T x from memory, or the symmetrised copy when it stays in LDS.
@@ -270,13 +269,13 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, TTC_COLS_WAVES(D)) backward_kern
         v_y[row] = r1;
         v_z[row] = r2;
       }
-      __syncthreads();
+      lds_barrier();
       qa = qb = 0.f;
       if (tid < D) {
         qa = 0.5f * (v_y[tid] + c1);
         qb = 0.5f * (v_z[tid] + c2);
       }
-      __syncthreads();
+      lds_barrier();
     };
     {
       float qa, qb;
@@ -287,13 +286,13 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, TTC_COLS_WAVES(D)) backward_kern
         tL[(long)T * D + tid] = qa;
         tLt[(long)T * D + tid] = qb;
       }
-      __syncthreads();
+      lds_barrier();
     }
     if (resident && T >= 2) {  // the stage cost Q, symmetrised, takes B's place
       load_half<D, TIn, false>(WR, Qp, tid);
-      __syncthreads();
+      lds_barrier();
       symmetrise_half<D>(WR, tid);
-      __syncthreads();
+      lds_barrier();
     }
     for (int t = T - 1; t >= 0; --t) {
       // lam_t = Q[t-1] x_t + A_t^T lam_{t+1} (no state cost for t = 0)
@@ -306,7 +305,7 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, TTC_COLS_WAVES(D)) backward_kern
           v_x[tid] = tX[(long)t * D + tid];
           v_xt[tid] = tXt[(long)t * D + tid];
         }
-        __syncthreads();
+        lds_barrier();
         float qa, qb;
         if (resident) {
           float r1, r2;
@@ -315,7 +314,7 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, TTC_COLS_WAVES(D)) backward_kern
             v_y[row] = r1;
             v_z[row] = r2;
           }
-          __syncthreads();
+          lds_barrier();
           qa = tid < D ? v_y[tid] : 0.f;
           qb = tid < D ? v_z[tid] : 0.f;
         } else {
@@ -324,14 +323,14 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, TTC_COLS_WAVES(D)) backward_kern
         al += qa;
         alt += qb;
       }
-      __syncthreads();
+      lds_barrier();
       if (tid < D) {
         v_l[tid] = al;
         v_lt[tid] = alt;
         tL[(long)t * D + tid] = al;
         tLt[(long)t * D + tid] = alt;
       }
-      __syncthreads();
+      lds_barrier();
     }
     if (tid < D) ba.gx0[prob * D + tid] = info ? nanv : v_lt[tid];
     if (tid == 0 && p.info) p.info[prob] = info;

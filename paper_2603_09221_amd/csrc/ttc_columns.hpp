@@ -6,13 +6,19 @@
 // register, and LDS holds left operands only, each read 16 bytes a lane for 4 RB matrix instructions.  (Owning rows
 // instead, every product passes through LDS and every wavefront reads every right operand.)
 //
-// Measured against steps with matrices by rows and the panel-wise lds_solve, T = 8, float32: ttc_lqr_solve_tv d = 64, 4096
-// problems 1.84 -> 1.29 ms (six products and the solve at 98 TFLOP/s of the 152 the matrix cores reach in float32), d = 32,
-// 8192 problems 0.59 -> 0.44 ms, d = 128, 1024 problems 2.99 -> 2.54 ms; ttc_lqr_backward d = 64, 8192 problems 4.15 -> 2.90
-// ms.  What is left is the inverse's serial chain, hidden as far as three workgroups a compute unit allow.
+// The products of d >= 32 run on the float16 matrix cores from split operands (ttc_split.hpp): the registers a split leaves are a
+// right operand and, stored as they are, the left operand of the transpose.  Taking the diagonal's signs E out of A (P A = P E +
+// P (A - E), A^T Y = E Y + (A - E)^T Y) costs one addition in the accumulator and leaves the product with what is small where the
+// dynamics are near the identity; gradients of 8 steps at d = 64 are off by 0.7 times what float32 products gave (24 steps: 0.6).
+//
+// Measured, T = 8, float32, float32 products -> split: roll-out d = 64, 4096 problems 1.36 -> 0.99 ms, d = 32, 8192 problems 0.54 ->
+// 0.45, d = 128, 1024 problems 2.77 -> 2.08; backward pass d = 64, 8192 problems 2.91 -> 2.26; ttc_lqr_solve_tv d = 64, 1024
+// problems 0.36 -> 0.29.  At d = 64 a step of one problem alone takes 24 thousand cycles (28), of which the dense solve is 13:
+// what is left is its serial chain, hidden as far as three workgroups a compute unit allow.
 #pragma once
 #include "ttc_common.hpp"
 #include "ttc_small.hpp"
+#include "ttc_split.hpp"
 
 namespace ttc {
 
@@ -39,6 +45,22 @@ __device__ __forceinline__ void zero_cols(floatx4 (&m)[D / 16][CT]) {
   for (int r = 0; r < D / 16; ++r)
 #pragma unroll
     for (int k = 0; k < CT; ++k) m[r][k] = floatx4{0.f, 0.f, 0.f, 0.f};
+}
+// Of a row-major matrix in memory, the signs (1 or -1) of the diagonal entries of a lane's columns; m -= diag(e).
+template <int D, typename TIn>
+__device__ __forceinline__ void load_diagonal_signs(const TIn* M, float (&e)[Cfg<D>::RB], int w, int i) {
+#pragma unroll
+  for (int k = 0; k < Cfg<D>::RB; ++k)
+    e[k] = __builtin_copysignf(1.f, ld1<TIn>(M, (long)(16 * (Cfg<D>::RB * w + k) + i) * (D + 1)));
+}
+template <int D>
+__device__ __forceinline__ void subtract_diagonal(Cols<D>& m, const float (&e)[Cfg<D>::RB], int w, int i, int g) {
+#pragma unroll
+  for (int r = 0; r < D / 16; ++r)
+#pragma unroll
+    for (int k = 0; k < Cfg<D>::RB; ++k)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) m[r][k][v] -= (r == Cfg<D>::RB * w + k && 4 * g + v == i) ? e[k] : 0.f;
 }
 // from a row-major matrix in memory: a row of 16 lanes reads 16 consecutive elements
 template <int D, typename TIn>
@@ -289,9 +311,8 @@ __device__ __forceinline__ int riccati_step_with(float* W, const TIn* As, const 
   const int lane = tid & 63, w = uniform(tid >> 6), i = lane & 15, g = lane >> 4;
   float* const WL = W;
   float* const WR = W + D;
-  Cols<D> s, a;
-  {
-    Cols<D> b, pb;
+  if constexpr (D == 16) {  // one tile: half of a float16 instruction's depth would be empty
+    Cols<D> s, a, b, pb, pa;
     load_cols<D, TIn>(Bs, b, w, i, g);
     store_cols_T<D>(WL, b, w, i, g);  // B^T
     load_cols<D, TIn>(As, a, w, i, g);
@@ -301,9 +322,6 @@ __device__ __forceinline__ int riccati_step_with(float* W, const TIn* As, const 
     zero_cols<D>(pb);
     gemm_cols<D>(pb, WR, b, i, g);  // P B
     gemm_cols<D>(s, WL, pb, i, g);  // S = R + B^T P B
-  }
-  {
-    Cols<D> pa;
     zero_cols<D>(pa);
     gemm_cols<D>(pa, WR, a, i, g);  // P A
     zero_cols<D>(wk);
@@ -314,11 +332,82 @@ __device__ __forceinline__ int riccati_step_with(float* W, const TIn* As, const 
     lds_barrier();
     zero_cols<D>(pn);
     gemm_cols<D>(pn, WR, pa, i, g);  // A^T P A
+    lds_barrier();
+    const int flag = solve_cols<D, C::RB>(WR, s, wk, w, lane);  // W = S^{-1} F
+    gemm_cols<D>(pn, WL, wk, i, g);                                 // - F^T W
+    return flag;
+  } else {
+    using Split = SplitCols<D, C::RB>;
+    constexpr int L = 0, R = 1;  // the halves
+    float* const signs = W + D * C::PITCH;
+    float e[C::RB];
+    Cols<D> s;
+    {
+      Split a;
+      {
+        Split b;
+        Cols<D> t;
+        {
+          Cols<D> bc;
+          Split p;
+          load_cols<D, TIn>(Bs, bc, w, i, g);
+          load_cols<D, TIn>(As, t, w, i, g);
+          load_diagonal_signs<D, TIn>(As, e, w, i);
+          zero_cols<D>(s);
+          add_R(s, w, i, g);
+          TTC_SCHED_BARRIER();  // the step's reads are all under way
+          // P is symmetric: a lane's four entries of a column are four consecutive ones of its row
+#pragma unroll
+          for (int r = 0; r < C::NT; ++r)
+#pragma unroll
+            for (int k = 0; k < C::RB; ++k)
+              pn[r][k] = *reinterpret_cast<const floatx4*>(WR + (16 * (C::RB * w + k) + i) * C::PITCH + 16 * r + 4 * g);
+          split_cols<D, C::RB>(pn, p);
+          lds_barrier();  // every wavefront has read its columns of P
+          store_split_T<D>(W, R, p, w, i, g);  // P
+          split_cols<D, C::RB>(bc, b);
+          store_split_T<D>(W, L, b, w, i, g);  // B^T
+        }
+        subtract_diagonal<D>(t, e, w, i, g);
+        if (g == 0)
+#pragma unroll
+          for (int k = 0; k < C::RB; ++k) signs[16 * (C::RB * w + k) + i] = e[k];
+        lds_barrier();
+        Cols<D> pb;
+        gemm_split<D, C::RB>(pb, W, R, b, i, g);  // P B
+        split_cols<D, C::RB>(pb, b);
+        gemm_split<D, C::RB, true>(s, W, L, b, i, g);  // S = R + B^T P B
+        split_cols<D, C::RB>(t, a);
+      }
+      Split pa;
+#pragma unroll
+      for (int r = 0; r < C::NT; ++r)
+#pragma unroll
+        for (int k = 0; k < C::RB; ++k) pn[r][k] = pn[r][k] * e[k];
+      gemm_split<D, C::RB, true>(pn, W, R, a, i, g);  // P A = P E + P (A - E)
+      split_cols<D, C::RB>(pn, pa);
+      gemm_split<D, C::RB>(wk, W, L, pa, i, g);  // F = B^T P A
+      Split f;
+      split_cols<D, C::RB>(wk, f);
+      lds_barrier();                           // P and B^T are no longer read
+      store_split_T<D>(W, R, a, w, i, g);  // (A - E)^T
+      store_split_T<D>(W, L, f, w, i, g);  // F^T
+      lds_barrier();
+#pragma unroll
+      for (int r = 0; r < C::NT; ++r) {
+        const floatx4 er = *reinterpret_cast<const floatx4*>(signs + 16 * r + 4 * g);
+#pragma unroll
+        for (int k = 0; k < C::RB; ++k) pn[r][k] = pn[r][k] * er;
+      }
+      gemm_split<D, C::RB, true>(pn, W, R, pa, i, g);  // A^T P A = E P A + (A - E)^T P A
+    }
+    lds_barrier();
+    const int flag = solve_cols<D, C::RB>(WR, s, wk, w, lane);  // W = S^{-1} F
+    Split x;
+    split_cols<D, C::RB>(wk, x);
+    gemm_split<D, C::RB, true, -1>(pn, W, L, x, i, g);  // - F^T W
+    return flag;
   }
-  lds_barrier();
-  const int flag = solve_cols<D, C::RB>(WR, s, wk, w, lane);  // W = S^{-1} F
-  gemm_cols<D>(pn, WL, wk, i, g);                                 // - F^T W
-  return flag;
 }
 
 template <int D, typename TIn>

@@ -73,6 +73,7 @@ struct Cfg {
   static constexpr int VEC = NT >= 4 ? 4 : NT;  // consecutive floats per B-operand LDS read
   static constexpr int NH = NT / VEC;           // B-operand reads per k-step
   static constexpr int PITCH = 2 * D + 4;       // floats per LDS row of the d x 2d pair (+4: bank skew)
+  static constexpr int PAIR = D * PITCH + (D >= 32 ? D + 16 : 0);  // floats of the pair, and the notes of split products behind it
 };
 
 // ----------------------------------------------------------------------------------------------

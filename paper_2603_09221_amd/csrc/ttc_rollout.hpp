@@ -7,37 +7,62 @@ namespace ttc {
 
 // ------------------------------------------------------------------------------------------------
 
-// y[r] = sum_c M[r][c] x[c] for the row r = tid / TPR of a row-major global d x d matrix; the TPR
-// threads of a row (adjacent lanes) each take a share of the columns; all of them get the sum.
+// Matrix-vector products y = M x of a row-major d x d matrix, NTHR / d threads (adjacent lanes) to a row r = tid / TPR, each with
+// its share of the columns.  A share is read into registers in one go, before anything waits for it: left to the scheduler, which
+// saves registers where another part of the kernel needs many, the reads come one after the other, each with its latency (the
+// loops of a time-heterogeneous backward pass 1.7 to 2.5 times as long, measured).
+template <int D>
+struct RowShare {
+  static constexpr int TPR = Cfg<D>::NTHR / D;  // 2 or 4
+  floatx4 v[D / TPR / 4];
+  template <typename MatLoad4>  // (row, column) -> four consecutive entries
+  __device__ __forceinline__ void load(MatLoad4&& row4, int tid) {
+    const int r = tid / TPR, c0 = (tid % TPR) * (D / TPR);
+#pragma unroll
+    for (int c = 0; c < D / TPR / 4; ++c) v[c] = row4(r, c0 + 4 * c);
+  }
+  __device__ __forceinline__ float dot(const float* xs, int tid) const {
+    const int c0 = (tid % TPR) * (D / TPR);
+    float s = 0.f;
+#pragma unroll
+    for (int c = 0; c < D / TPR / 4; ++c) {
+      const floatx4 x = *reinterpret_cast<const floatx4*>(xs + c0 + 4 * c);
+      s += v[c][0] * x[0] + v[c][1] * x[1] + v[c][2] * x[2] + v[c][3] * x[3];
+    }
+    return share_sum(s);
+  }
+  // the sum over the row's threads, in all of them
+  static __device__ __forceinline__ float share_sum(float s) {
+    if constexpr (TPR >= 2)
+      s += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(s), 0xB1, 0xF, 0xF, false));  // quad_perm [1,0,3,2]
+    if constexpr (TPR >= 4)
+      s += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(s), 0x4E, 0xF, 0xF, false));  // quad_perm [2,3,0,1]
+    static_assert(TPR <= 4, "a row's threads are within a quad");
+    return s;
+  }
+};
+template <int D, typename TM>
+__device__ __forceinline__ auto rows_of(const TM* M) {
+  return [M](int r, int c4) { return ld4<TM>(M, (long)r * D + c4); };
+}
+template <int D>
+__device__ __forceinline__ auto rows_in_lds(const float* M) {
+  return [M](int r, int c4) { return *reinterpret_cast<const floatx4*>(M + r * Cfg<D>::PITCH + c4); };
+}
+
 template <int D, typename TM>
 __device__ __forceinline__ float matvec_row(const TM* M, const float* xs, int tid) {
-  constexpr int TPR = Cfg<D>::NTHR / D;  // 2 or 4
-  const int r = tid / TPR, part = tid % TPR;
-  float s = 0.f;
-#pragma unroll
-  for (int c4 = part * (D / TPR); c4 < (part + 1) * (D / TPR); c4 += 4) {
-    const floatx4 mv = ld4<TM>(M, (long)r * D + c4);
-    s += mv[0] * xs[c4] + mv[1] * xs[c4 + 1] + mv[2] * xs[c4 + 2] + mv[3] * xs[c4 + 3];
-  }
-#pragma unroll
-  for (int m = 1; m < TPR; m <<= 1) s += __shfl_xor(s, m, 64);
-  return s;
+  RowShare<D> m;
+  m.load(rows_of<D, TM>(M), tid);
+  return m.dot(xs, tid);
 }
 
 // The same with M in LDS (row pitch PITCH).
 template <int D>
 __device__ __forceinline__ float matvec_row_lds(const float* M, const float* xs, int tid) {
-  constexpr int TPR = Cfg<D>::NTHR / D;
-  const int r = tid / TPR, part = tid % TPR;
-  float s = 0.f;
-#pragma unroll
-  for (int c4 = part * (D / TPR); c4 < (part + 1) * (D / TPR); c4 += 4) {
-    const floatx4 mv = *reinterpret_cast<const floatx4*>(M + r * Cfg<D>::PITCH + c4);
-    s += mv[0] * xs[c4] + mv[1] * xs[c4 + 1] + mv[2] * xs[c4 + 2] + mv[3] * xs[c4 + 3];
-  }
-#pragma unroll
-  for (int m = 1; m < TPR; m <<= 1) s += __shfl_xor(s, m, 64);
-  return s;
+  RowShare<D> m;
+  m.load(rows_in_lds<D>(M), tid);
+  return m.dot(xs, tid);
 }
 
 // Backward sweep of rollout_kernel for a problem whose R + B^T P B is not positive definite everywhere (a stage cost that is
@@ -148,10 +173,10 @@ __device__ __forceinline__ int rollout_pivoted_sweep(float* W, SolveScratch<D>& 
 template <int D, typename TIn>
 __global__ void __launch_bounds__(Cfg<D>::NTHR, TTC_COLS_WAVES(D)) rollout_kernel(const RolloutArgs p) {
   using C = Cfg<D>;
-  __shared__ __attribute__((aligned(16))) float W[D * C::PITCH];
+  __shared__ __attribute__((aligned(16))) float W[C::PAIR];
   __shared__ __attribute__((aligned(16))) SolveScratch<D> S;
   __shared__ float s_red[C::NW];
-  __shared__ float s_x[D], s_u[D], s_xn[D];
+  __shared__ __attribute__((aligned(16))) float s_x[D], s_u[D], s_xn[D];
 
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   float* const WL = W;
@@ -212,35 +237,43 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, TTC_COLS_WAVES(D)) rollout_kerne
     load_half<D, TIn, false>(WR, Bp, tid);
     __syncthreads();  // gains visible to the whole workgroup
 
-    // ---- forward sweep
+    // ---- forward sweep; R and Q stay in registers, the next gain is on its way
     const int r = tid / (C::NTHR / D), part = tid % (C::NTHR / D);
+    RowShare<D> Rr, Qr, Kr;
+    Kr.load(rows_of<D, float>(wsK), tid);
+    Rr.load(rows_of<D, TIn>(Rp), tid);
+    Qr.load(rows_of<D, TIn>(p.T == 1 && !(p.flags & TTC_FLAG_STAGE_COST_AT_X0) ? QTp : Qp), tid);
     if (tid < D) s_x[tid] = ld1<TIn>(x0p, tid);
     __syncthreads();
     float cpart = 0.f;
     if (p.flags & TTC_FLAG_STAGE_COST_AT_X0) {
-      const float qx = matvec_row<D, TIn>(Qp, s_x, tid);
+      const float qx = Qr.dot(s_x, tid);
       if (part == 0) cpart += s_x[r] * qx;
+      if (p.T == 1) Qr.load(rows_of<D, TIn>(QTp), tid);
     }
     if (p.X && tid < D) p.X[prob * (long)(p.T + 1) * D + tid] = s_x[tid];
     for (int t = 0; t < p.T; ++t) {
-      const float u = matvec_row<D, float>(wsK + (long)t * D * D, s_x, tid);
+      const float u = Kr.dot(s_x, tid);
+      if (t + 1 < p.T) Kr.load(rows_of<D, float>(wsK + (long)(t + 1) * D * D), tid);
+      const float ax = matvec_row_lds<D>(WL, s_x, tid);
       if (part == 0) s_u[r] = u;
-      __syncthreads();
-      const float ru = matvec_row<D, TIn>(Rp, s_u, tid);
-      const float xn = matvec_row_lds<D>(WL, s_x, tid) + matvec_row_lds<D>(WR, s_u, tid);
+      lds_barrier();
+      const float ru = Rr.dot(s_u, tid);
+      const float xn = ax + matvec_row_lds<D>(WR, s_u, tid);
       if (part == 0) {
-        cpart += s_u[r] * ru;
+        cpart += u * ru;
         s_xn[r] = xn;
         p.U[(prob * p.T + t) * (long)D + r] = info ? __builtin_nanf("") : u;
-      }
-      __syncthreads();
-      const float qx = matvec_row<D, TIn>(t == p.T - 1 ? QTp : Qp, s_xn, tid);
-      if (part == 0) {
-        cpart += s_xn[r] * qx;
-        s_x[r] = xn;
         if (p.X) p.X[(prob * (p.T + 1) + t + 1) * (long)D + r] = info ? __builtin_nanf("") : xn;
       }
-      __syncthreads();
+      lds_barrier();
+      const float qx = Qr.dot(s_xn, tid);
+      if (t == p.T - 2 && QTp != Qp) Qr.load(rows_of<D, TIn>(QTp), tid);
+      if (part == 0) {
+        cpart += xn * qx;
+        s_x[r] = xn;
+      }
+      lds_barrier();
     }
     cpart = sum64(cpart);
     if (lane == 0) s_red[w] = cpart;

@@ -67,7 +67,7 @@ static constexpr float LATE_LIMIT = 64.f, GROWTH_STOP = 16.f;
 template <int D, typename TIn>
 __global__ void __launch_bounds__(Cfg<D>::NTHR, (D <= 64 ? 2 : 1)) squaring_kernel(const DoublingArgs da) {
   using C = Cfg<D>;
-  __shared__ __attribute__((aligned(16))) float W[D * C::PITCH];
+  __shared__ __attribute__((aligned(16))) float W[C::PAIR];
   __shared__ __attribute__((aligned(16))) SolveScratch<D> S;
   __shared__ float s_red[C::NW];
   __shared__ float s_max[C::NW];  // per wavefront: max |I + G H| of the solve being set up

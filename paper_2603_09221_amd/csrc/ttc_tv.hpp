@@ -98,7 +98,7 @@ __device__ __forceinline__ int riccati_problem(float* W, float* s_red, const Sol
 template <int D, typename TIn>
 __global__ void __launch_bounds__(Cfg<D>::NTHR, TTC_COLS_WAVES(D)) solve_tv_kernel(const TvArgs ta) {
   using C = Cfg<D>;
-  __shared__ __attribute__((aligned(16))) float W[D * C::PITCH];
+  __shared__ __attribute__((aligned(16))) float W[C::PAIR];
   __shared__ float s_red[C::NW];
   const SolveArgs& p = ta.s;
 
@@ -120,9 +120,9 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, TTC_COLS_WAVES(D)) solve_tv_kern
 template <int D, typename TIn>
 __global__ void __launch_bounds__(Cfg<D>::NTHR, TTC_COLS_WAVES(D)) rollout_tv_kernel(const TvRolloutArgs ta) {
   using C = Cfg<D>;
-  __shared__ __attribute__((aligned(16))) float W[D * C::PITCH];
+  __shared__ __attribute__((aligned(16))) float W[C::PAIR];
   __shared__ float s_red[C::NW];
-  __shared__ float s_x[D], s_u[D], s_xn[D];
+  __shared__ __attribute__((aligned(16))) float s_x[D], s_u[D], s_xn[D];
   const RolloutArgs& p = ta.r;
   float* const WR = W + D;
   float* const wsK = p.ws + (long)blockIdx.x * p.T * D * D;  // K_0 .. K_{T-1}, row-major
@@ -160,25 +160,32 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, TTC_COLS_WAVES(D)) rollout_tv_ke
     float cpart = 0.f;
     if (p.X && tid < D) p.X[prob * (long)(p.T + 1) * D + tid] = s_x[tid];
     for (int t = 0; t < p.T; ++t) {
-      const float u = matvec_row<D, float>(wsK + (long)t * D * D, s_x, tid);
+      RowShare<D> Kr, Ar, Br, Rr, Qr;  // the step's five reads side by side
+      Kr.load(rows_of<D, float>(wsK + (long)t * D * D), tid);
+      Ar.load(rows_of<D, TIn>(Ap + (long long)t * ta.tA), tid);
+      Br.load(rows_of<D, TIn>(Bp + (long long)t * ta.tB), tid);
+      Rr.load(rows_of<D, TIn>(Rp + (long long)t * ta.tR), tid);
+      Qr.load(rows_of<D, TIn>(Qp + (long long)t * ta.tQ), tid);
+      TTC_SCHED_BARRIER();
+      const float u = Kr.dot(s_x, tid);
+      const float ax = Ar.dot(s_x, tid);
       if (part == 0) s_u[r] = u;
-      __syncthreads();
-      const float ru = matvec_row<D, TIn>(Rp + (long long)t * ta.tR, s_u, tid);
-      const float xn = matvec_row<D, TIn>(Ap + (long long)t * ta.tA, s_x, tid) +
-                       matvec_row<D, TIn>(Bp + (long long)t * ta.tB, s_u, tid);
+      lds_barrier();
+      const float ru = Rr.dot(s_u, tid);
+      const float xn = ax + Br.dot(s_u, tid);
       if (part == 0) {
-        cpart += s_u[r] * ru;
+        cpart += u * ru;
         s_xn[r] = xn;
         p.U[(prob * p.T + t) * (long)D + r] = info ? __builtin_nanf("") : u;
-      }
-      __syncthreads();
-      const float qx = matvec_row<D, TIn>(Qp + (long long)t * ta.tQ, s_xn, tid);
-      if (part == 0) {
-        cpart += s_xn[r] * qx;
-        s_x[r] = xn;
         if (p.X) p.X[(prob * (p.T + 1) + t + 1) * (long)D + r] = info ? __builtin_nanf("") : xn;
       }
-      __syncthreads();
+      lds_barrier();
+      const float qx = Qr.dot(s_xn, tid);
+      if (part == 0) {
+        cpart += xn * qx;
+        s_x[r] = xn;
+      }
+      lds_barrier();
     }
     cpart = sum64(cpart);
     if (lane == 0) s_red[w] = cpart;
