@@ -58,6 +58,7 @@ UNIT_FLAGS = {("k_backward.hip", 64): [_ONE_ROW_BLOCK % 64, _THREE_WAVES],
               ("k_doubling.hip", 128): [_ONE_ROW_BLOCK % 128],
               ("k_rollout.hip", 64): [_ONE_ROW_BLOCK % 64],
               ("k_rollout.hip", 128): [_ONE_ROW_BLOCK % 128],
+              ("k_squaring.hip", 64): [_ONE_ROW_BLOCK % 64],
               ("k_squaring.hip", 128): [_ONE_ROW_BLOCK % 128]}
 
 _NOISE = "is not a recognized feature for this target"

@@ -73,6 +73,24 @@ __device__ __forceinline__ void load_cols(const TIn* M, Cols<D>& m, int w, int i
 #pragma unroll
       for (int k = 0; k < Cfg<D>::RB; ++k) m[r][k][v] = ld1<TIn>(M, o + (unsigned)((16 * r + v) * D + 16 * k));
 }
+// its transpose (a lane's four entries are consecutive elements)
+template <int D, typename TIn>
+__device__ __forceinline__ void load_cols_T(const TIn* M, Cols<D>& m, int w, int i, int g) {
+  const unsigned o = (unsigned)((16 * Cfg<D>::RB * w + i) * D + 4 * g);
+#pragma unroll
+  for (int r = 0; r < D / 16; ++r)
+#pragma unroll
+    for (int k = 0; k < Cfg<D>::RB; ++k) m[r][k] = ld4<TIn>(M, o + (unsigned)(16 * k * D + 16 * r));
+}
+template <int D>
+__device__ __forceinline__ void eye_cols(Cols<D>& m, int w, int i, int g) {
+#pragma unroll
+  for (int r = 0; r < D / 16; ++r)
+#pragma unroll
+    for (int k = 0; k < Cfg<D>::RB; ++k)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) m[r][k][v] = (r == Cfg<D>::RB * w + k && 4 * g + v == i) ? 1.f : 0.f;
+}
 // m += the symmetric part of such a matrix (the transposed entries of a lane are four consecutive elements)
 template <int D, typename TIn>
 __device__ __forceinline__ void add_sym_cols(const TIn* M, Cols<D>& m, int w, int i, int g) {
@@ -122,6 +140,26 @@ __device__ __forceinline__ void store_cols(float* L, int pitch, const Cols<D>& m
     for (int v = 0; v < 4; ++v)
 #pragma unroll
       for (int k = 0; k < Cfg<D>::RB; ++k) o[(16 * r + v) * pitch + 16 * k] = SIGN > 0 ? m[r][k][v] : -m[r][k][v];
+}
+
+// from LDS (row pitch PITCH), the matrix itself and its transpose
+template <int D>
+__device__ __forceinline__ void read_cols(const float* L, Cols<D>& m, int w, int i, int g) {
+  const float* const o = L + 4 * g * Cfg<D>::PITCH + 16 * Cfg<D>::RB * w + i;
+#pragma unroll
+  for (int r = 0; r < D / 16; ++r)
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+      for (int k = 0; k < Cfg<D>::RB; ++k) m[r][k][v] = o[(16 * r + v) * Cfg<D>::PITCH + 16 * k];
+}
+template <int D>
+__device__ __forceinline__ void read_cols_T(const float* L, Cols<D>& m, int w, int i, int g) {
+  const float* const o = L + (16 * Cfg<D>::RB * w + i) * Cfg<D>::PITCH + 4 * g;
+#pragma unroll
+  for (int r = 0; r < D / 16; ++r)
+#pragma unroll
+    for (int k = 0; k < Cfg<D>::RB; ++k) m[r][k] = *reinterpret_cast<const floatx4*>(o + 16 * k * Cfg<D>::PITCH + 16 * r);
 }
 
 // acc += L R: L row-major in LDS, R by columns.  The left operand of the next four k-steps is read while the current ones
@@ -270,32 +308,88 @@ __device__ __forceinline__ int solve_cols(float* Wp, Cols<D>& s, floatx4 (&f)[D 
   }
 }
 
-// The same on the pair in LDS, [M | RHS] (visible): the right half becomes M^{-1} RHS, the left half is left as it was.
-// RHS = false only reports the pivots (the right half is overwritten all the same).
-template <int D, bool RHS = true>
-__device__ __forceinline__ int solve_pair_in_order(float* W, float piv_min, int tid) {
+// s <- s^{-1} by the same elimination in place: the column of a pivot block becomes that of the inverse as soon as it has been
+// used, so that no right-hand sides are carried (two thirds of the work of solving for the identity, and its registers).
+// With d <= 32, where a block's explicit inverse is not accurate enough, the identity is solved for.
+template <int D>
+__device__ __forceinline__ int invert_cols(float* Wp, Cols<D>& s, int w, int lane, float piv_min) {
   using C = Cfg<D>;
-  tid += opaque_zero();
-  const int lane = tid & 63, w = uniform(tid >> 6), i = lane & 15, g = lane >> 4;
-  float* const WR = W + D;
-  Cols<D> m;
-  floatx4 f[C::NT][RHS ? C::RB : 1];
-  auto read = [&](const float* L, auto& c) {
-    const float* const o = L + 4 * g * C::PITCH + 16 * C::RB * w + i;
+  constexpr int NT = C::NT, CT = C::RB;
+  const int i = lane & 15, g = lane >> 4;
+  w = uniform(w);
+  if constexpr (D <= 32) {
+    Cols<D> f;
+    eye_cols<D>(f, w, i, g);
+    const int flag = solve_cols<D, CT>(Wp, s, f, w, lane, piv_min);
 #pragma unroll
-    for (int r = 0; r < C::NT; ++r)
+    for (int r = 0; r < NT; ++r)
 #pragma unroll
-      for (int v = 0; v < 4; ++v)
+      for (int k = 0; k < CT; ++k) s[r][k] = f[r][k];
+    return flag;
+  }
+  int bad = 0;
+  auto publish = [&](auto P) {  // by the wavefront that owns column tile p
+    constexpr int p = decltype(P)::value, k = p % CT;
+    float* const o = Wp + 4 * g * C::PITCH + 16 * (p & 1) + i;
 #pragma unroll
-        for (int k = 0; k < C::RB; ++k) c[r][k][v] = o[(16 * r + v) * C::PITCH + 16 * k];
+    for (int r = 0; r < NT; ++r)
+      if (r != p)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) o[(16 * r + v) * C::PITCH] = -s[r][k][v];
+    bad |= invert_spread16(s[p][k], lane, piv_min);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) o[(16 * p + v) * C::PITCH] = s[p][k][v];
   };
-  read(W, m);
-  if constexpr (RHS) read(WR, f);
+  auto column = [&](auto P, const floatx4 (&x)[NT], auto K) {
+    constexpr int p = decltype(P)::value, k = decltype(K)::value;
+    floatx4 u = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < 4; ++t) u = __builtin_amdgcn_mfma_f32_16x16x4f32(x[p][t], s[p][k][t], u, 0, 0, 0);
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int r = 0; r < NT; ++r)
+        if (r != p) s[r][k] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[r][t], u[t], s[r][k], 0, 0, 0);
+    s[p][k] = u;
+  };
+  if (w == 0) publish(IntC<0>{});
+  static_for<0, NT>([&](auto P) {
+    constexpr int p = decltype(P)::value;
+    lds_barrier();  // block p is published; block p - 1 (the other buffer) was read before
+    floatx4 x[NT];
+#pragma unroll
+    for (int r = 0; r < NT; ++r) x[r] = *reinterpret_cast<const floatx4*>(Wp + (16 * r + i) * C::PITCH + 16 * (p & 1) + 4 * g);
+    if constexpr (p + 1 < NT) {
+      if (w == (p + 1) / CT) {
+        column(P, x, IntC<(p + 1) % CT>{});
+        publish(IntC<p + 1>{});
+      }
+    }
+    static_for<0, CT>([&](auto K) {
+      constexpr int k = decltype(K)::value;
+      if (CT * w + k == p) {  // the pivot block's own column: its inverse stands in s[p][k], the rest is -s[r][p] of that
+        const floatx4 inv = s[p][k];
+#pragma unroll
+        for (int r = 0; r < NT; ++r)
+          if (r != p) s[r][k] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+          for (int r = 0; r < NT; ++r)
+            if (r != p) s[r][k] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[r][t], inv[t], s[r][k], 0, 0, 0);
+      } else if (CT * w + k != p + 1) {
+        column(P, x, K);
+      }
+    });
+  });
+  const int any = __any(bad) ? 1 : 0;
+  int* const flags = reinterpret_cast<int*>(Wp + D);
+  if (lane == 0) flags[w * C::PITCH] = any;
   lds_barrier();
-  const int flag = solve_cols<D, RHS ? C::RB : 0>(WR, m, f, w, lane, piv_min);
-  if constexpr (RHS) store_cols<D>(WR, C::PITCH, f, w, i, g);
-  lds_barrier();
-  return flag;
+  int all = 0;
+#pragma unroll
+  for (int ww = 0; ww < C::NW; ++ww) all |= flags[ww * C::PITCH];
+  return uniform(all);
 }
 
 // One backward step of Prop. 3.1 with the matrices of one step.  On entry the right half of the pair holds P_{s+1}

@@ -23,31 +23,22 @@
 // (a stage cost that is not semidefinite, which squaring loses all digits on); one with a small pivot, a singular A or an R
 // that is not positive definite by the product at once, whose reports it thereby gets.
 //
-// Where things live.  A_e, G_e and H_e are row blocks in registers (the A operand of a product), across the dense solves, as
-// solve_kernel's constants are; LDS holds the pair a product or solve works on; the one workspace slot of the workgroup
-// holds P while the bits of T still have squarings between them (never for T a power of two).  The last step is the printed
-// one (riccati_step), which needs nothing but P_1 and the problem's own matrices.
+// Where things live.  Everything is held by columns (ttc_columns.hpp), products run on split operands (ttc_split.hpp): G_e and H_e
+// in float32 registers, A_e and its transpose as split registers, which are right operands as they stand and, stored, the left
+// operands of each other.  I + G_e H_e is formed transposed, H_e on the left, so that the columns of its inverse are the rows of M
+// as a left operand; eight products and one inverse a squaring, each product's result split where it is the next one's operand.
+// The one workspace slot of the workgroup holds P while the bits of T still have squarings between them (never for T a power of
+// two).  The last step is the printed one (riccati_step), which needs nothing but P_1 and the problem's own matrices.
 #pragma once
 #include "ttc_doubling.hpp"
 #include "ttc_tv.hpp"
 
 namespace ttc {
 
-// rows[rb][k] += the wavefront's rows of the matrix in the LDS half Wh
-template <int D>
-__device__ __forceinline__ void add_aop_lds(const float* Wh, float (&rows)[Cfg<D>::RB][Cfg<D>::KS], int w, int i, int g) {
-  using C = Cfg<D>;
-  float t[C::RB][C::KS];
-  load_aop_lds<D>(Wh, t, w, i, g);
-#pragma unroll
-  for (int rb = 0; rb < C::RB; ++rb)
-#pragma unroll
-    for (int k = 0; k < C::KS; ++k) rows[rb][k] += t[rb][k];
-}
 
 // Both I + G_e H_e and I + P G_e have the eigenvalues of I plus a positive semidefinite matrix.  They are not symmetric, but up
 // to mu of about 30 elimination in order meets no small pivot (CPU, float64, random semidefinite pairs and the benchmark's:
-// pivots of 1.1 and more; at 40 some problems in a hundred, at 120 all of them meet negative ones): the solve is solve_cols,
+// pivots of 1.1 and more; at 40 some problems in a hundred, at 120 all of them meet negative ones): the solve is by columns,
 // without a pivot search.  Above IN_ORDER_MAX it is the pivoted lds_solve; a pivot below PIVOT_MIN (a stage cost that is not
 // semidefinite, say) gives the problem up.  A is tried in order too; a pivot below PIVOT_MIN_A leaves the verdict to the pivoted
 // factorisation.
@@ -55,29 +46,29 @@ static constexpr float PIVOT_MIN = 0.25f, PIVOT_MIN_A = 0.015625f, IN_ORDER_MAX 
 // The guard's limit after the first squaring, and the mu at which the coming square of e is expected and not formed.
 static constexpr float LATE_LIMIT = 64.f, GROWTH_STOP = 16.f;
 
-// One row block per wavefront at d = 128 (build.py: with two, 448 of the 512 registers hold matrices and the solves spill:
-// 31.9 against 4.5 ms for 2048 problems, T = 16), two at d = 64 (2.31 against 2.84 ms for 8192 problems, T = 16).
-// The recursion and the solves of the problems given up are in a kernel of their own: inlined here they spilled 345 vector and
-// 107 scalar registers at d = 128 (271 and 78 without), and with R^{-1} B^T kept for a last step without R + B^T P B as well.
-// The thread index is formed anew in the loop: shared with the set-up, its address arithmetic lives across the solves
-// (4.15 against 4.52 ms below).
-// Measured, solve_kernel / with the cold paths inlined / now: d = 128, T = 16, 2048 problems 7.01 / 4.27 / 4.15 ms, T = 64
-// 35 / 5.88 / 5.74; T = 32, bfloat16 inputs 10.7 / 5.0 / 4.9; d = 64, 8192 problems, T = 8 2.14 / 1.70 / 1.65, T = 64
-// 15.4 / 2.87 / 2.78; d = 32, T = 16, 16384 problems 1.6 / 0.73 / 0.69.
+// One column tile per wavefront at d >= 64 (build.py): two at d = 128 leave one wavefront a SIMD (T = 16, 8192 problems 14.9 against
+// 11.6 ms), at d = 64 two wavefronts (T = 8, 16384 problems 2.73 against 2.57 ms with one tile and three wavefronts).  The registers
+// do not hold all of it (99 spilled at d = 64, 380 at d = 128, around the inverse), which costs less than another wavefront would.
+// The recursion and the solves of the problems given up are in a kernel of their own: inlined here they spilled many more.
+// Measured, products in float32 with row blocks in registers -> this, float32: d = 64, T = 8, 16384 problems 3.20 -> 2.55 ms, T = 64,
+// 4099 problems 1.49 -> 1.01; d = 128, T = 16, 8192 problems 16.4 -> 11.6; bfloat16 inputs, T = 32, 4096 problems 9.77 -> 6.60.
+// Errors against float64: 0.65e-6 (0.87 before), 0.57e-6 (0.77), 1.3e-6 (1.9), 1.6e-6 (2.4).
 template <int D, typename TIn>
-__global__ void __launch_bounds__(Cfg<D>::NTHR, (D <= 64 ? 2 : 1)) squaring_kernel(const DoublingArgs da) {
+__global__ void __launch_bounds__(Cfg<D>::NTHR, (D) == 64 ? 3 : 2) squaring_kernel(const DoublingArgs da) {
   using C = Cfg<D>;
+  using Split = SplitCols<D, C::RB>;
+  constexpr int L = 0, R = 1;  // the halves of the pair
   __shared__ __attribute__((aligned(16))) float W[C::PAIR];
   __shared__ __attribute__((aligned(16))) SolveScratch<D> S;
   __shared__ float s_red[C::NW];
-  __shared__ float s_max[C::NW];  // per wavefront: max |I + G H| of the solve being set up
+  __shared__ float s_max[C::NW];  // per wavefront: max |I + G H| of the matrix being inverted
   const SolveArgs& p = da.s;
   float* const WL = W;
   float* const WR = W + D;
-  float* const wsP = p.ws + (long)blockIdx.x * D * D;  // P, rows in register layout
+  float* const wsP = p.ws + (long)blockIdx.x * D * D;  // P, as the registers hold it
 
   for (long long prob = blockIdx.x; prob < p.n; prob += gridDim.x) {
-    const int tid = threadIdx.x + opaque_zero(), lane = tid & 63, w = tid >> 6, i = lane & 15, g = lane >> 4;
+    const int tid = threadIdx.x + opaque_zero(), lane = tid & 63, w = uniform(tid >> 6), i = lane & 15, g = lane >> 4;
     const TIn* Ap = reinterpret_cast<const TIn*>(p.A) + prob * p.sA;
     const TIn* Bp = reinterpret_cast<const TIn*>(p.B) + prob * p.sB;
     const TIn* Qp = reinterpret_cast<const TIn*>(p.Q) + prob * p.sQ;
@@ -85,24 +76,8 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D <= 64 ? 2 : 1)) squaring_kern
     const TIn* x0p = reinterpret_cast<const TIn*>(p.x0) + prob * p.sx0;
     const TIn* QTp = da.p_from_qt ? reinterpret_cast<const TIn*>(p.QT) + prob * p.sQT : Qp;
     uint32_t give_up = 0;   // whom the problem is handed to
-    bool pivoted = false;   // the dense solves search pivots, from the first large mu on
-    float rA[C::RB][C::KS], rG[C::RB][C::KS], rH[C::RB][C::KS];
-    floatx4 acc[C::RB][C::NT];
+    bool pivoted = false;   // the inverses search pivots, from the first large mu on
 
-    // the wavefront's max |acc| for the guard; read by everyone after the next barrier
-    auto publish_max = [&] {
-      const float m = wave_absmax<D>(acc);
-      if (lane == 0) s_max[w] = m;
-    };
-    auto measure = [&] {  // its maximum over the workgroup (NaN on top)
-      uint32_t m = 0;
-#pragma unroll
-      for (int ww = 0; ww < C::NW; ++ww) {
-        const uint32_t b = __float_as_uint(s_max[ww]);
-        m = b > m ? b : m;
-      }
-      return __uint_as_float(uniform(m));
-    };
     // (the word's writer is the thread that writes the first of u_0 in emit_gain)
     auto hand_over = [&](uint32_t how) {
       if (threadIdx.x == 0) reinterpret_cast<uint32_t*>(p.u0)[prob * D] = how;
@@ -110,227 +85,250 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D <= 64 ? 2 : 1)) squaring_kern
     };
 
     // ---- a singular A is reported, although nothing here divides by A
-    load_half<D, TIn, false>(WL, Ap, tid);
-    __syncthreads();
-    if (solve_pair_in_order<D, false>(W, PIVOT_MIN_A, tid) && lds_factor<D>(W, S, tid)) {
-      hand_over(HANDED_TO_PRODUCT);
-      continue;
-    }
-    // ---- set-up: G = B R^{-1} B^T, A, H = Q; P = Q_T when it is a matrix of its own
-    load_half<D, TIn, false>(WL, Rp, tid);
-    load_half<D, TIn, false>(WR, Bp, tid);
-    __syncthreads();
-    symmetrise_half<D>(WL, tid);
-    transpose_half<D>(WR, w, i, g);
-    __syncthreads();
-    if (solve_pair_in_order<D>(W, 0.f, tid)) {  // R is not positive definite
-      hand_over(HANDED_TO_PRODUCT);
-      continue;
-    }
+    Split a, at;  // A_e and its transpose
     {
-      float c[C::RB][C::KS];
-      load_aop_global<D, TIn>(Bp, c, w, i, g);
-      zero_acc<D>(acc);
-      gemm_acc<D>(acc, c, WR, i, g);
-      store_rows<D>(WL, acc, w, i, g);
-      __syncthreads();
-      symmetrise_half<D>(WL, tid);  // G is symmetric up to rounding; make it exactly so
-      __syncthreads();
-    }
-    load_aop_lds<D>(WL, rG, w, i, g);
-    __syncthreads();
-    load_half<D, TIn, false>(WL, Ap, tid);
-    load_half<D, TIn, false>(WR, Qp, tid);
-    __syncthreads();
-    load_aop_lds<D>(WL, rA, w, i, g);
-    symmetrise_half<D>(WR, tid);
-    __syncthreads();
-    load_aop_lds<D>(WR, rH, w, i, g);
-    bool have_p = da.p_from_qt != 0, at_QT = have_p;  // at_QT: P is still Q_T
-    if (have_p) {
-      __syncthreads();
-      load_half<D, TIn, false>(WR, QTp, tid);
-      __syncthreads();
-      symmetrise_half<D>(WR, tid);
-      __syncthreads();
-      float c[C::RB][C::KS];
-      load_aop_lds<D>(WR, c, w, i, g);
-      store_aop_ws<D>(wsP, c, tid);
-    }
-    __syncthreads();
-
-    // the dense solve of the pair, whose left half's largest entry is mu.  False: a pivot below PIVOT_MIN, or none at all
-    auto dense = [&](float mu) {
-      pivoted = pivoted || mu > IN_ORDER_MAX;
-      if (!pivoted) {
-        if (solve_pair_in_order<D>(W, PIVOT_MIN, tid)) give_up = HANDED_TO_PRODUCT;
-      } else {
-        if (lds_solve<D>(W, S, tid)) give_up = HANDED_TO_PRODUCT;
-      }
-      return give_up == 0;
-    };
-    // [I + P G | P A] with P's rows in c, G and A as the halves hold them, then the solve: the right half becomes
-    // (I + P G)^{-1} P A.  False: over the limit, or no solution
-    auto mobius = [&](const float(&c)[C::RB][C::KS]) {
-      eye_acc<D>(acc, w, i, g);
-      gemm_acc<D>(acc, c, WL, i, g);
-      publish_max();
-      __syncthreads();
-      const float mu = measure();
-      if (!(mu <= (at_QT ? da.qt_limit : LATE_LIMIT))) {
-        give_up = HANDED_TO_RECURSION;
-        return false;
-      }
-      at_QT = false;
-      store_rows<D>(WL, acc, w, i, g);
-      zero_acc<D>(acc);
-      gemm_acc<D>(acc, c, WR, i, g);
-      __syncthreads();
-      store_rows<D>(WR, acc, w, i, g);
-      __syncthreads();
-      return dense(mu);
-    };
-    // rows[rb][k] <- rH + A_e^T (the matrix in the right half), through the left half (rows may be rH itself)
-    auto apply_AT = [&](float (&rows)[C::RB][C::KS]) {
-      float c[C::RB][C::KS];
-      store_aop_lds<D>(WL, rA, w, i, g);
-      __syncthreads();
-      load_aopT_lds<D>(WL, c, w, i, g);
-      zero_acc<D>(acc);
-      gemm_acc<D>(acc, c, WR, i, g);
-      __syncthreads();
-      store_rows<D>(WL, acc, w, i, g);
-      __syncthreads();
-      load_aop_lds<D>(WL, c, w, i, g);
-#pragma unroll
-      for (int rb = 0; rb < C::RB; ++rb)
-#pragma unroll
-        for (int k = 0; k < C::KS; ++k) rows[rb][k] = rH[rb][k] + c[rb][k];
-      __syncthreads();
-    };
-
-    // ---- P_1 by binary powering of the one-step map (see ttc_doubling.hpp)
-    bool p_is_H = false;  // P_1 = H_e: the last bit met no P
-    float mu_prev = 0.f;  // max |I + G_e H_e| of the squaring before, 0 before the first
-    bool stay = false;    // e is not squared any further, but applied once for each factor of it that is left
-    for (int m = da.m; m && !give_up;) {
-      const int tid = threadIdx.x + opaque_zero(), lane = tid & 63, w = tid >> 6, i = lane & 15, g = lane >> 4;
-      if ((m & 1) || stay) {
-        if (!have_p) {
-          have_p = true;
-          if (m == 1) p_is_H = true;  // f_e(0) = H_e, and e is not touched again
-          else store_aop_ws<D>(wsP, rH, tid);
-        } else {
-          float c[C::RB][C::KS];
-          load_aop_ws<D>(wsP, c, tid, opaque_zero());
-          store_aop_lds<D>(WL, rG, w, i, g);
-          store_aop_lds<D>(WR, rA, w, i, g);
-          __syncthreads();
-          if (!mobius(c)) break;
-          apply_AT(c);  // P <- H_e + A_e^T (I + P G_e)^{-1} P A_e
-          store_aop_ws<D>(wsP, c, tid);
+      Cols<D> m;
+      load_cols<D, TIn>(Ap, m, w, i, g);
+      split_cols<D, C::RB>(m, a);
+      floatx4 none[C::NT][1];  // no right-hand sides
+      if (solve_cols<D, 0>(WR, m, none, w, lane, PIVOT_MIN_A)) {
+        load_half<D, TIn, false>(WL, Ap, tid);
+        __syncthreads();
+        if (lds_factor<D>(W, S, tid)) {
+          hand_over(HANDED_TO_PRODUCT);
+          continue;
         }
+        __syncthreads();
       }
-      if (stay) {
-        --m;
+    }
+    // ---- set-up: G = B R^{-1} B^T, H = Q; P = Q_T when it is a matrix of its own
+    Cols<D> G, H;
+    {
+      Cols<D> r, bt;
+      Split t;
+      load_cols_T<D, TIn>(Bp, bt, w, i, g);
+      zero_cols<D>(r);
+      add_sym_cols<D, TIn>(Rp, r, w, i, g);
+      split_cols<D, C::RB>(bt, t);
+      store_split_T<D>(W, L, t, w, i, g);  // B
+      if (solve_cols<D, C::RB>(WR, r, bt, w, lane)) {  // R is not positive definite
+        hand_over(HANDED_TO_PRODUCT);
         continue;
       }
-      m >>= 1;
-      if (!m) break;
-      // e <- e o e
-      store_aop_lds<D>(WR, rH, w, i, g);
-      __syncthreads();
-      eye_acc<D>(acc, w, i, g);
-      gemm_acc<D>(acc, rG, WR, i, g);  // I + G H
-      publish_max();
-      store_rows<D>(WL, acc, w, i, g);
-      __syncthreads();
-      const float mu = measure();
-      if (!(mu <= (mu_prev == 0.f ? p.growth_limit : LATE_LIMIT))) {
+      split_cols<D, C::RB>(bt, t);
+      gemm_split<D, C::RB>(G, W, L, t, i, g);
+      // G is symmetric up to rounding; make it exactly so
+      store_cols_T<D>(WR, G, w, i, g);
+      load_cols_T<D, TIn>(Ap, bt, w, i, g);
+      split_cols<D, C::RB>(bt, at);
+      zero_cols<D>(H);
+      add_sym_cols<D, TIn>(Qp, H, w, i, g);
+      lds_barrier();
+      read_cols<D>(WR, r, w, i, g);
+#pragma unroll
+      for (int x = 0; x < C::NT; ++x)
+#pragma unroll
+        for (int k = 0; k < C::RB; ++k) G[x][k] = 0.5f * (G[x][k] + r[x][k]);
+    }
+    bool have_p = da.p_from_qt != 0, at_QT = have_p;  // at_QT: P is still Q_T
+    if (have_p) {
+      Cols<D> t;
+      zero_cols<D>(t);
+      add_sym_cols<D, TIn>(QTp, t, w, i, g);
+      keep_cols<D>(wsP, t, tid);
+    }
+    lds_barrier();
+
+    // ---- P_1 by binary powering of the one-step map (see ttc_doubling.hpp).  A turn of the loop either applies e to P or squares
+    // it: both begin with the inverse of a matrix I + (symmetric)(symmetric), formed transposed, so that its columns are the rows
+    // of the inverse wanted as a left operand.
+    bool p_is_H = false;   // P_1 = H_e: the last bit met no P
+    bool bit_done = false; // P has had the current bit of m
+    float mu_prev = 0.f;   // max |I + G_e H_e| of the squaring before, 0 before the first
+    bool stay = false;     // e is not squared any further, but applied once for each factor of it that is left
+    for (int m = da.m; m;) {
+      const int tid = threadIdx.x + opaque_zero(), lane = tid & 63, w = uniform(tid >> 6), i = lane & 15, g = lane >> 4;
+      bool apply = false;
+      if (!bit_done && ((m & 1) || stay)) {
+        apply = have_p;
+        if (!have_p) {  // f_e(0) = H_e
+          have_p = true;
+          if (m == 1) {  // and e is not touched again
+            p_is_H = true;
+            break;
+          }
+          keep_cols<D>(wsP, H, tid);
+        }
+      }
+      if (!apply) {
+        bit_done = false;
+        if (stay) {
+          --m;
+          continue;
+        }
+        m >>= 1;
+        if (!m) break;
+      }
+      Cols<D> s;
+      {
+        Split l, r;
+        if (apply) {
+          zero_cols<D>(s);
+          add_kept_cols<D>(wsP, s, tid);
+          split_cols<D, C::RB>(s, r);
+          split_cols<D, C::RB>(G, l);
+        } else {
+          split_cols<D, C::RB>(H, l);
+          split_cols<D, C::RB>(G, r);
+        }
+        store_split_T<D>(W, L, l, w, i, g);
+        eye_cols<D>(s, w, i, g);
+        lds_barrier();
+        gemm_split<D, C::RB, true>(s, W, L, r, i, g);  // (I + P G)^T, or (I + G H)^T
+      }
+      {
+        float big = 0.f;
+#pragma unroll
+        for (int r = 0; r < C::NT; ++r)
+#pragma unroll
+          for (int k = 0; k < C::RB; ++k)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {  // as bits: NaN on top
+              const float x = __builtin_fabsf(s[r][k][v]);
+              big = __float_as_uint(x) > __float_as_uint(big) ? x : big;
+            }
+        big = wave_max_nonneg(big);
+        if (lane == 0) s_max[w] = big;
+      }
+      lds_barrier();
+      uint32_t mu_bits = 0;
+#pragma unroll
+      for (int ww = 0; ww < C::NW; ++ww) {
+        const uint32_t b = __float_as_uint(s_max[ww]);
+        mu_bits = b > mu_bits ? b : mu_bits;
+      }
+      const float mu = __uint_as_float(uniform(mu_bits));
+      const bool only_H = !apply && m == 1 && !have_p;  // the last squaring, and P is still 0: A and G of the square are not needed
+      if (!(mu <= (apply ? (at_QT ? da.qt_limit : LATE_LIMIT) : mu_prev == 0.f ? p.growth_limit : LATE_LIMIT))) {
         give_up = HANDED_TO_RECURSION;
         break;
       }
-      const bool only_H = m == 1 && !have_p;  // the last squaring, and P is still 0: A and G of the square are not needed
-      // growth of an unstable open loop: mu - 1 has grown by r, and the square of e will make it grow by r^2 at least
-      const float up = mu - 1.f, up_prev = mu_prev - 1.f;
-      if (!only_H && mu_prev != 0.f && up > 1.f && up > 2.f * up_prev && up * up * up > GROWTH_STOP * up_prev * up_prev) {
-        stay = true;
-        m *= 2;
+      if (apply) {
+        at_QT = false;
+      } else {
+        // growth of an unstable open loop: mu - 1 has grown by r, and the square of e will make it grow by r^2 at least
+        const float up = mu - 1.f, up_prev = mu_prev - 1.f;
+        if (!only_H && mu_prev != 0.f && up > 1.f && up > 2.f * up_prev && up * up * up > GROWTH_STOP * up_prev * up_prev) {
+          stay = true;
+          m *= 2;
+          lds_barrier();  // s_max is written again at once
+          continue;
+        }
+        mu_prev = mu;
+      }
+      pivoted = pivoted || mu > IN_ORDER_MAX;
+      int flag;
+      if (!pivoted) {
+        flag = invert_cols<D>(WR, s, w, lane, PIVOT_MIN);
+      } else {
+        store_cols<D>(WL, C::PITCH, s, w, i, g);
+        set_half_identity<D>(WR, tid);
+        __syncthreads();
+        flag = lds_solve<D>(W, S, tid);
+        read_cols<D>(WR, s, w, i, g);
+        lds_barrier();
+      }
+      if (flag) {  // a pivot below PIVOT_MIN, or none at all
+        give_up = HANDED_TO_PRODUCT;
+        break;
+      }
+      Split t;
+      split_cols<D, C::RB>(s, t);
+      store_split_T<D>(W, R, t, w, i, g);  // M = (I + P G)^{-1}, or (I + G H)^{-1}
+      if (apply) {
+        zero_cols<D>(s);
+        add_kept_cols<D>(wsP, s, tid);
+        split_cols<D, C::RB>(s, t);
+        store_split_T<D>(W, L, t, w, i, g);  // P
+        lds_barrier();
+        gemm_split<D, C::RB>(s, W, L, a, i, g);  // P A
+        split_cols<D, C::RB>(s, t);
+        gemm_split<D, C::RB>(s, W, R, t, i, g);  // V = M P A
+        split_cols<D, C::RB>(s, t);
+        lds_barrier();
+        store_split_T<D>(W, L, a, w, i, g);  // A^T
+        lds_barrier();
+#pragma unroll
+        for (int r = 0; r < C::NT; ++r)
+#pragma unroll
+          for (int k = 0; k < C::RB; ++k) s[r][k] = H[r][k];
+        gemm_split<D, C::RB, true>(s, W, L, t, i, g);  // P <- H_e + A_e^T (I + P G_e)^{-1} P A_e
+        keep_cols<D>(wsP, s, tid);
+        lds_barrier();
+        if (stay) --m;
+        else bit_done = true;
         continue;
       }
-      mu_prev = mu;
-      if (only_H) store_aop_lds<D>(WR, rA, w, i, g);
-      else set_half_identity<D>(WR, tid);
-      __syncthreads();
-      if (!dense(mu)) break;  // right half: M = (I + G H)^{-1}, or M A
+      // e <- e o e
+      bit_done = false;
+      Split ma;
       if (only_H) {
-        zero_acc<D>(acc);
-        gemm_acc<D>(acc, rH, WR, i, g);  // V = H M A
-        __syncthreads();
-        store_rows<D>(WR, acc, w, i, g);
-        apply_AT(rH);  // H' = H + A^T V
+        split_cols<D, C::RB>(H, t);
+        store_split_T<D>(W, L, t, w, i, g);  // H
+        lds_barrier();
+        gemm_split<D, C::RB>(s, W, R, a, i, g);  // M A
+        split_cols<D, C::RB>(s, ma);
+        gemm_split<D, C::RB>(s, W, L, ma, i, g);  // V = H M A
+        split_cols<D, C::RB>(s, t);
+        lds_barrier();
+        store_split_T<D>(W, R, a, w, i, g);  // A^T
+        lds_barrier();
+        gemm_split<D, C::RB, true>(H, W, R, t, i, g);  // H' = H + A^T V
+        lds_barrier();
       } else {
-        const int tid = threadIdx.x + opaque_zero(), lane = tid & 63, w = tid >> 6, i = lane & 15, g = lane >> 4;
-        float rM[C::RB][C::KS];
-        load_aop_lds<D>(WR, rM, w, i, g);
-        store_aop_lds<D>(WL, rA, w, i, g);
-        __syncthreads();
-        zero_acc<D>(acc);
-        gemm_acc<D>(acc, rM, WL, i, g);  // M A
+        store_split_T<D>(W, L, at, w, i, g);  // A
+        lds_barrier();
+        gemm_split<D, C::RB>(s, W, R, a, i, g);  // M A
+        split_cols<D, C::RB>(s, ma);
+        split_cols<D, C::RB>(G, t);
+        gemm_split<D, C::RB>(s, W, R, t, i, g);  // M G, symmetric
+        split_cols<D, C::RB>(s, t);
+        lds_barrier();
+        store_split_T<D>(W, R, t, w, i, g);
+        lds_barrier();
+        gemm_split<D, C::RB>(s, W, R, at, i, g);  // M G A^T
+        split_cols<D, C::RB>(s, t);
+        gemm_split<D, C::RB, true>(G, W, L, t, i, g);  // G' = G + A M G A^T
+        gemm_split<D, C::RB>(s, W, L, ma, i, g);       // A' = A M A
+        split_cols<D, C::RB>(H, t);
+        lds_barrier();
+        store_split_T<D>(W, L, t, w, i, g);  // H
+        store_split_T<D>(W, R, a, w, i, g);  // A^T
+        split_cols<D, C::RB>(s, a);
+        lds_barrier();
         {
-          float rAT[C::RB][C::KS];
-          load_aopT_lds<D>(WL, rAT, w, i, g);
-          __syncthreads();
-          store_rows<D>(WL, acc, w, i, g);
-          __syncthreads();
-          zero_acc<D>(acc);
-          gemm_acc<D>(acc, rH, WL, i, g);  // V = H M A
-          store_rows<D>(WR, acc, w, i, g);
-          __syncthreads();
-          zero_acc<D>(acc);
-          gemm_acc<D>(acc, rAT, WR, i, g);  // A^T V
+          Cols<D> v;
+          gemm_split<D, C::RB>(v, W, L, ma, i, g);  // V = H M A
+          split_cols<D, C::RB>(v, t);
         }
-        __syncthreads();
-        store_rows<D>(WR, acc, w, i, g);
-        __syncthreads();
-        add_aop_lds<D>(WR, rH, w, i, g);  // H' = H + A^T V
-        __syncthreads();
-        store_aop_lds<D>(WR, rG, w, i, g);
-        floatx4 accA[C::RB][C::NT];
-        zero_acc<D>(accA);
-        gemm_acc<D>(accA, rA, WL, i, g);  // A' = A M A
-        __syncthreads();
-        zero_acc<D>(acc);
-        gemm_acc<D>(acc, rA, WR, i, g);  // A G
-        __syncthreads();
-        store_rows_T<D>(WR, acc, w, i, g);  // G A^T
-        __syncthreads();
-        zero_acc<D>(acc);
-        gemm_acc<D>(acc, rM, WR, i, g);  // M G A^T
-        store_rows<D>(WL, acc, w, i, g);
-        __syncthreads();
-        zero_acc<D>(acc);
-        gemm_acc<D>(acc, rA, WL, i, g);  // A M G A^T
-        store_rows<D>(WR, acc, w, i, g);  // (every wavefront is past its reads of G A^T)
-        __syncthreads();
-        store_rows<D>(WL, accA, w, i, g);
-        __syncthreads();
-        load_aop_lds<D>(WL, rA, w, i, g);
-        add_aop_lds<D>(WR, rG, w, i, g);  // G' = G + A M G A^T
-        __syncthreads();
+        gemm_split<D, C::RB, true>(H, W, R, t, i, g);  // H' = H + A^T V
+        lds_barrier();
+        store_cols<D>(WL, C::PITCH, s, w, i, g);
+        lds_barrier();
+        read_cols_T<D>(WL, s, w, i, g);
+        split_cols<D, C::RB>(s, at);
+        lds_barrier();
       }
     }
 
     // ---- last step, with the problem's own matrices: as printed
     if (!give_up) {
-      const int tid = threadIdx.x + opaque_zero(), lane = tid & 63, w = tid >> 6, i = lane & 15, g = lane >> 4;
-      if (p_is_H) {
-        store_aop_lds<D>(WR, rH, w, i, g);
-      } else {
-        float c[C::RB][C::KS];
-        load_aop_ws<D>(wsP, c, tid, opaque_zero());
-        store_aop_lds<D>(WR, c, w, i, g);
+      const int tid = threadIdx.x + opaque_zero(), lane = tid & 63, w = uniform(tid >> 6), i = lane & 15, g = lane >> 4;
+      if (!p_is_H) {
+        zero_cols<D>(H);
+        add_kept_cols<D>(wsP, H, tid);
       }
+      store_cols_T<D>(WR, H, w, i, g);
       __syncthreads();
       symmetrise_half<D>(WR, tid);
       __syncthreads();
