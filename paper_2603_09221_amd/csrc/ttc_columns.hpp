@@ -11,9 +11,9 @@
 // P (A - E), A^T Y = E Y + (A - E)^T Y) costs one addition in the accumulator and leaves the product with what is small where the
 // dynamics are near the identity; gradients of 8 steps at d = 64 are off by 0.7 times what float32 products gave (24 steps: 0.6).
 //
-// Measured, T = 8, float32, float32 products -> split: roll-out d = 64, 4096 problems 1.36 -> 0.99 ms, d = 32, 8192 problems 0.54 ->
-// 0.45, d = 128, 1024 problems 2.77 -> 2.08; backward pass d = 64, 8192 problems 2.91 -> 2.26; ttc_lqr_solve_tv d = 64, 1024
-// problems 0.36 -> 0.29.  At d = 64 a step of one problem alone takes 24 thousand cycles (28), of which the dense solve is 13:
+// Measured, T = 8, float32, float32 products -> split: roll-out d = 64, 4096 problems 1.36 -> 0.95 ms, d = 32, 8192 problems 0.54 ->
+// 0.46, d = 128, 1024 problems 2.77 -> 1.71; backward pass d = 64, 8192 problems 2.91 -> 2.21; ttc_lqr_solve_tv d = 64, 1024
+// problems 0.36 -> 0.28.  At d = 64 a step of one problem alone takes 24 thousand cycles (28), of which the dense solve is 13:
 // what is left is its serial chain, hidden as far as three workgroups a compute unit allow.
 #pragma once
 #include "ttc_common.hpp"
@@ -194,6 +194,17 @@ __device__ __forceinline__ void gemm_cols(floatx4 (&acc)[D / 16][CT], const floa
   });
 }
 
+// f(p) for p = 0, CT, .. below NT: a loop from eight blocks on, their code one after the other below.
+template <int NT, int CT, typename F>
+__device__ __forceinline__ void for_each_block(F&& f) {
+  if constexpr (NT >= 8) {
+#pragma unroll 1
+    for (int p = 0; p < NT; p += CT) f(p);
+  } else {
+    static_for<0, NT / CT>([&](auto X) { f(decltype(X)::value * CT); });
+  }
+}
+
 // Dense solve f <- s^{-1} f, both by columns (f: FT column tiles a wavefront, also none), for a symmetric positive definite s,
 // or any whose elimination in order meets pivots above piv_min only: block Gauss-Jordan with 16 x 16 pivot blocks and no pivot search.  Per block p, the wavefront that owns its columns
 // inverts s[p][p] in registers and publishes that inverse and the rest of the column, negated, as left operands (Wp: the
@@ -207,6 +218,11 @@ __device__ __forceinline__ void gemm_cols(floatx4 (&acc)[D / 16][CT], const floa
 // solve does: the backward pass asks for it in its first step's, where it costs nothing beside the steps.
 // Returns, uniformly, whether a pivot was not above piv_min and finite.  Wp must be free to every wavefront on entry; its last
 // reads may still be under way in other wavefronts on return.
+// Row tiles turn by one place a block, so that the pivot block is tile 0 of its column and block p + r tile r, in registers (a
+// matrix instruction adds tile r into the place of tile r - 1) as in LDS: at d = 128 the loop over the blocks is one.  Unrolled there,
+// a solve is five thousand instructions, and a kernel of several fetches them from memory each time (roll-out d = 128, T = 8, 1024
+// problems 2.08 -> 1.74 ms, backward pass 2.75 -> 2.28, squaring T = 16, 8192 problems 11.6 -> 11.0); at d = 64 the loop is the
+// slower of the two (squaring T = 8, 16384 problems 2.55 -> 2.63 ms).
 template <int D, int FT, bool REFINE = (D <= 32)>
 __device__ __forceinline__ int solve_cols(float* Wp, Cols<D>& s, floatx4 (&f)[D / 16][FT > 0 ? FT : 1], int w, int lane,
                                           float piv_min = 0.f) {
@@ -217,80 +233,77 @@ __device__ __forceinline__ int solve_cols(float* Wp, Cols<D>& s, floatx4 (&f)[D 
   w = uniform(w);
   int bad = 0;
   floatx4 d_neg;  // REFINE: minus the pivot block, as a left operand
-  auto publish = [&](auto P) {  // by the wavefront that owns column tile p
-    constexpr int p = decltype(P)::value, k = p % CT;
-    float* const o = Wp + 4 * g * C::PITCH + 16 * (p & 1) + i;
+  auto publish = [&](auto K, int buf) {  // by the wavefront that owns the column tile
+    constexpr int k = decltype(K)::value;
+    float* const o = Wp + 4 * g * C::PITCH + 16 * buf + i;
     if constexpr (REFINE && LOCAL) {  // through the tile the inverse goes to below (a wavefront's LDS operations run in order)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) o[(16 * p + v) * C::PITCH] = -s[p][k][v];
+      for (int v = 0; v < 4; ++v) o[v * C::PITCH] = -s[0][k][v];
       wave_lds_sync();
-      d_neg = *reinterpret_cast<const floatx4*>(Wp + (16 * p + i) * C::PITCH + 16 * (p & 1) + 4 * g);
+      d_neg = *reinterpret_cast<const floatx4*>(Wp + i * C::PITCH + 16 * buf + 4 * g);
       wave_lds_sync();
     } else if constexpr (REFINE) {  // to the columns behind both buffers' inverses
 #pragma unroll
-      for (int v = 0; v < 4; ++v) o[32 + v * C::PITCH] = -s[p][k][v];
+      for (int v = 0; v < 4; ++v) o[32 + v * C::PITCH] = -s[0][k][v];
     }
-    floatx4 inv = s[p][k];
+    floatx4 inv = s[0][k];
     bad |= invert_spread16(inv, lane, piv_min);
 #pragma unroll
     for (int r = 0; r < NT; ++r) {
-      const floatx4 x = r == p ? inv : -s[r][k];
+      const floatx4 x = r == 0 ? inv : -s[r][k];
 #pragma unroll
       for (int v = 0; v < 4; ++v) o[(16 * r + v) * C::PITCH] = x[v];
     }
   };
-  auto column = [&](auto P, const floatx4 (&x)[NT], auto& m, auto K) {
-    constexpr int p = decltype(P)::value, k = decltype(K)::value;
+  auto column = [&](const floatx4 (&x)[NT], auto& m, auto K) {
+    constexpr int k = decltype(K)::value;
     floatx4 u = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int t = 0; t < 4; ++t) u = __builtin_amdgcn_mfma_f32_16x16x4f32(x[p][t], m[p][k][t], u, 0, 0, 0);
+    for (int t = 0; t < 4; ++t) u = __builtin_amdgcn_mfma_f32_16x16x4f32(x[0][t], m[0][k][t], u, 0, 0, 0);
     if constexpr (REFINE) {
-      floatx4 res = m[p][k];
+      floatx4 res = m[0][k];
 #pragma unroll
       for (int t = 0; t < 4; ++t) res = __builtin_amdgcn_mfma_f32_16x16x4f32(d_neg[t], u[t], res, 0, 0, 0);
 #pragma unroll
-      for (int t = 0; t < 4; ++t) u = __builtin_amdgcn_mfma_f32_16x16x4f32(x[p][t], res[t], u, 0, 0, 0);
+      for (int t = 0; t < 4; ++t) u = __builtin_amdgcn_mfma_f32_16x16x4f32(x[0][t], res[t], u, 0, 0, 0);
     }
 #pragma unroll
     for (int t = 0; t < 4; ++t)
 #pragma unroll
-      for (int r = 0; r < NT; ++r)
-        if (r != p) m[r][k] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[r][t], u[t], m[r][k], 0, 0, 0);
-    m[p][k] = u;
+      for (int r = 1; r < NT; ++r)
+        m[r - 1][k] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[r][t], u[t], t == 0 ? m[r][k] : m[r - 1][k], 0, 0, 0);
+    m[NT - 1][k] = u;
   };
-  if (w == 0) publish(IntC<0>{});
-  static_for<0, NT>([&](auto P) {
-    constexpr int p = decltype(P)::value;
-    lds_barrier();  // block p is published; block p - 1 (the other buffer) was read before
-    floatx4 x[NT];
+  if (w == 0) publish(IntC<0>{}, 0);
+  for_each_block<NT, CT>([&](int p0) {
+    static_for<0, CT>([&](auto KK) {
+      constexpr int kk = decltype(KK)::value, kn = (kk + 1) % CT;  // the pivot block's tile in its wavefront, and the next one's
+      const int p = p0 + kk, buf = p & 1;
+      lds_barrier();  // block p is published; block p - 1 (the other buffer) was read before
+      floatx4 x[NT];
 #pragma unroll
-    for (int r = 0; r < NT; ++r) x[r] = *reinterpret_cast<const floatx4*>(Wp + (16 * r + i) * C::PITCH + 16 * (p & 1) + 4 * g);
-    if constexpr (REFINE && !LOCAL) d_neg = *reinterpret_cast<const floatx4*>(Wp + i * C::PITCH + 32 + 16 * (p & 1) + 4 * g);
-    auto rest = [&](auto SKIP) {
-      static_for<0, CT>([&](auto K) {
-        constexpr int k = decltype(K)::value;
-        if constexpr (k != decltype(SKIP)::value)
-          if (CT * w + k > p) column(P, x, s, K);
-      });
-      if constexpr (FT > 0) static_for<0, FT>([&](auto K) { column(P, x, f, K); });
-    };
-    if constexpr (p + 1 < NT) {
-      constexpr int kn = (p + 1) % CT;
-      if (w == (p + 1) / CT) {
-        column(P, x, s, IntC<kn>{});
-        if constexpr (REFINE && LOCAL) {  // the others still need this block's operands
-          rest(IntC<kn>{});
-          publish(IntC<p + 1>{});
-        } else {
-          publish(IntC<p + 1>{});
-          rest(IntC<kn>{});
-        }
+      for (int r = 0; r < NT; ++r) x[r] = *reinterpret_cast<const floatx4*>(Wp + (16 * r + i) * C::PITCH + 16 * buf + 4 * g);
+      if constexpr (REFINE && !LOCAL) d_neg = *reinterpret_cast<const floatx4*>(Wp + i * C::PITCH + 32 + 16 * buf + 4 * g);
+      const bool next_here = p + 1 < NT && w == (p + 1) / CT;
+      auto rest = [&] {
+        static_for<0, CT>([&](auto K) {
+          constexpr int k = decltype(K)::value;
+          if (CT * w + k > p && !(k == kn && next_here)) column(x, s, K);
+        });
+        if constexpr (FT > 0) static_for<0, FT>([&](auto K) { column(x, f, K); });
+      };
+      if constexpr (REFINE && LOCAL) {  // the others still need this block's operands
+        if (next_here) column(x, s, IntC<kn>{});
+        rest();
+        if (next_here) publish(IntC<kn>{}, buf ^ 1);
       } else {
-        rest(IntC<-1>{});
+        if (next_here) {
+          column(x, s, IntC<kn>{});
+          publish(IntC<kn>{}, buf ^ 1);
+        }
+        rest();
       }
-    } else {
-      rest(IntC<-1>{});
-    }
+    });
   });
   // the wavefronts' flags meet in the skew columns of the pair, which nothing else uses
   const int any = __any(bad) ? 1 : 0;
@@ -328,58 +341,54 @@ __device__ __forceinline__ int invert_cols(float* Wp, Cols<D>& s, int w, int lan
     return flag;
   }
   int bad = 0;
-  auto publish = [&](auto P) {  // by the wavefront that owns column tile p
-    constexpr int p = decltype(P)::value, k = p % CT;
-    float* const o = Wp + 4 * g * C::PITCH + 16 * (p & 1) + i;
+  auto publish = [&](auto K, int buf) {  // by the wavefront that owns the column tile
+    constexpr int k = decltype(K)::value;
+    float* const o = Wp + 4 * g * C::PITCH + 16 * buf + i;
 #pragma unroll
-    for (int r = 0; r < NT; ++r)
-      if (r != p)
+    for (int r = 1; r < NT; ++r)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) o[(16 * r + v) * C::PITCH] = -s[r][k][v];
-    bad |= invert_spread16(s[p][k], lane, piv_min);
+      for (int v = 0; v < 4; ++v) o[(16 * r + v) * C::PITCH] = -s[r][k][v];
+    bad |= invert_spread16(s[0][k], lane, piv_min);
 #pragma unroll
-    for (int v = 0; v < 4; ++v) o[(16 * p + v) * C::PITCH] = s[p][k][v];
+    for (int v = 0; v < 4; ++v) o[v * C::PITCH] = s[0][k][v];
   };
-  auto column = [&](auto P, const floatx4 (&x)[NT], auto K) {
-    constexpr int p = decltype(P)::value, k = decltype(K)::value;
-    floatx4 u = floatx4{0.f, 0.f, 0.f, 0.f};
+  // own: the pivot block's column, whose inverse stands in s[0][k]; the rest becomes -s[r][p] times that
+  auto column = [&](const floatx4 (&x)[NT], auto K, bool own) {
+    constexpr int k = decltype(K)::value;
+    floatx4 u = s[0][k];
+    if (!own) {
+      u = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int t = 0; t < 4; ++t) u = __builtin_amdgcn_mfma_f32_16x16x4f32(x[p][t], s[p][k][t], u, 0, 0, 0);
+      for (int t = 0; t < 4; ++t) u = __builtin_amdgcn_mfma_f32_16x16x4f32(x[0][t], s[0][k][t], u, 0, 0, 0);
+    } else {
+#pragma unroll
+      for (int r = 1; r < NT; ++r) s[r][k] = floatx4{0.f, 0.f, 0.f, 0.f};
+    }
 #pragma unroll
     for (int t = 0; t < 4; ++t)
 #pragma unroll
-      for (int r = 0; r < NT; ++r)
-        if (r != p) s[r][k] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[r][t], u[t], s[r][k], 0, 0, 0);
-    s[p][k] = u;
+      for (int r = 1; r < NT; ++r)
+        s[r - 1][k] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[r][t], u[t], t == 0 ? s[r][k] : s[r - 1][k], 0, 0, 0);
+    s[NT - 1][k] = u;
   };
-  if (w == 0) publish(IntC<0>{});
-  static_for<0, NT>([&](auto P) {
-    constexpr int p = decltype(P)::value;
-    lds_barrier();  // block p is published; block p - 1 (the other buffer) was read before
-    floatx4 x[NT];
+  if (w == 0) publish(IntC<0>{}, 0);
+  for_each_block<NT, CT>([&](int p0) {
+    static_for<0, CT>([&](auto KK) {
+      constexpr int kk = decltype(KK)::value, kn = (kk + 1) % CT;
+      const int p = p0 + kk, buf = p & 1;
+      lds_barrier();  // block p is published; block p - 1 (the other buffer) was read before
+      floatx4 x[NT];
 #pragma unroll
-    for (int r = 0; r < NT; ++r) x[r] = *reinterpret_cast<const floatx4*>(Wp + (16 * r + i) * C::PITCH + 16 * (p & 1) + 4 * g);
-    if constexpr (p + 1 < NT) {
-      if (w == (p + 1) / CT) {
-        column(P, x, IntC<(p + 1) % CT>{});
-        publish(IntC<p + 1>{});
+      for (int r = 0; r < NT; ++r) x[r] = *reinterpret_cast<const floatx4*>(Wp + (16 * r + i) * C::PITCH + 16 * buf + 4 * g);
+      const bool next_here = p + 1 < NT && w == (p + 1) / CT;
+      if (next_here) {
+        column(x, IntC<kn>{}, false);
+        publish(IntC<kn>{}, buf ^ 1);
       }
-    }
-    static_for<0, CT>([&](auto K) {
-      constexpr int k = decltype(K)::value;
-      if (CT * w + k == p) {  // the pivot block's own column: its inverse stands in s[p][k], the rest is -s[r][p] of that
-        const floatx4 inv = s[p][k];
-#pragma unroll
-        for (int r = 0; r < NT; ++r)
-          if (r != p) s[r][k] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-          for (int r = 0; r < NT; ++r)
-            if (r != p) s[r][k] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[r][t], inv[t], s[r][k], 0, 0, 0);
-      } else if (CT * w + k != p + 1) {
-        column(P, x, K);
-      }
+      static_for<0, CT>([&](auto K) {
+        constexpr int k = decltype(K)::value;
+        if (!(k == kn && next_here)) column(x, K, CT * w + k == p);
+      });
     });
   });
   const int any = __any(bad) ? 1 : 0;

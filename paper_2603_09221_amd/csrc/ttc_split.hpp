@@ -92,6 +92,20 @@ __device__ __forceinline__ void store_split_T(float* W, int half, const SplitCol
   if (i == 0 && g == 0) split_notes<D>(W, half)[w] = sp.inv;
 }
 
+// and back, by the wavefront that stored it
+template <int D>
+__device__ __forceinline__ void read_split(const float* W, int half, SplitCols<D, Cfg<D>::RB>& sp, int w, int i, int g) {
+  using C = Cfg<D>;
+  const float* const o = W + half * D + (16 * C::RB * w + i) * C::PITCH + 4 * g;
+#pragma unroll
+  for (int k = 0; k < C::RB; ++k)
+#pragma unroll
+    for (int q = 0; q < D / 32; ++q) {
+      sp.h[q][k] = *reinterpret_cast<const halfx8*>(o + 16 * k * C::PITCH + 16 * q);
+      sp.l[q][k] = *reinterpret_cast<const halfx8*>(o + 16 * k * C::PITCH + D / 2 + 16 * q);
+    }
+}
+
 // acc = L b, or acc += SIGN L b (ADD): L a left operand in LDS as store_split_T leaves it, b by columns in split form.  A
 // 16 x 16 tile is formed from zero and then scaled back into acc, under the next tile's matrix instructions.  The left operands
 // of the next two k-steps are in flight while one is used; scheduling barriers keep the compiler from hoisting more.
@@ -108,7 +122,7 @@ __device__ __forceinline__ void gemm_split(floatx4 (&acc)[D / 16][CT], const flo
   for (int s = 1; s <= (NT - 1) / RSEG; ++s) seg[s] = base + opaque_int(16 * s * RSEG * C::PITCH);
   float f[C::NW];
 #pragma unroll
-  for (int ww = 0; ww < C::NW; ++ww) f[ww] = split_notes<D>(W, half)[ww];
+  for (int ww = 0; ww < C::NW; ++ww) f[ww] = __int_as_float(uniform(__float_as_int(split_notes<D>(W, half)[ww])));
   halfx8 h[AHEAD + 1], l[AHEAD + 1];
   auto fetch = [&](auto X) {
     constexpr int x = decltype(X)::value, r = x / NQ, q = x % NQ;

@@ -36,6 +36,28 @@
 namespace ttc {
 
 
+// The pivoted solve and factorisation, which few problems need: at d = 128 as functions of their own, as inlined their registers
+// push the element of the problem into memory on every path (T = 16, 8192 problems 10.96 -> 10.71 ms); at d = 64 the call itself
+// costs more (T = 8, 16384 problems 2.55 -> 3.02 ms).
+template <int D>
+__device__ __attribute__((noinline)) int lds_solve_called(float* W, SolveScratch<D>& S, int tid) {
+  return lds_solve<D>(W, S, tid);
+}
+template <int D>
+__device__ __attribute__((noinline)) int lds_factor_called(float* W, SolveScratch<D>& S, int tid) {
+  return lds_factor<D>(W, S, tid);
+}
+template <int D>
+__device__ __forceinline__ int lds_solve_aside(float* W, SolveScratch<D>& S, int tid) {
+  if constexpr (D == 128) return lds_solve_called<D>(W, S, tid);
+  else return lds_solve<D>(W, S, tid);
+}
+template <int D>
+__device__ __forceinline__ int lds_factor_aside(float* W, SolveScratch<D>& S, int tid) {
+  if constexpr (D == 128) return lds_factor_called<D>(W, S, tid);
+  else return lds_factor<D>(W, S, tid);
+}
+
 // Both I + G_e H_e and I + P G_e have the eigenvalues of I plus a positive semidefinite matrix.  They are not symmetric, but up
 // to mu of about 30 elimination in order meets no small pivot (CPU, float64, random semidefinite pairs and the benchmark's:
 // pivots of 1.1 and more; at 40 some problems in a hundred, at 120 all of them meet negative ones): the solve is by columns,
@@ -47,17 +69,18 @@ static constexpr float PIVOT_MIN = 0.25f, PIVOT_MIN_A = 0.015625f, IN_ORDER_MAX 
 static constexpr float LATE_LIMIT = 64.f, GROWTH_STOP = 16.f;
 
 // One column tile per wavefront at d >= 64 (build.py): two at d = 128 leave one wavefront a SIMD (T = 16, 8192 problems 14.9 against
-// 11.6 ms), at d = 64 two wavefronts (T = 8, 16384 problems 2.73 against 2.57 ms with one tile and three wavefronts).  The registers
-// do not hold all of it (99 spilled at d = 64, 380 at d = 128, around the inverse), which costs less than another wavefront would.
+// 11.6 ms), at d = 64 two wavefronts (T = 8, 16384 problems 2.73 against 2.55 ms with one tile and three wavefronts).  The registers
+// do not hold all of it (96 spilled at d = 64, 330 at d = 128, around the inverse), which costs less than another wavefront would.
 // The recursion and the solves of the problems given up are in a kernel of their own: inlined here they spilled many more.
-// Measured, products in float32 with row blocks in registers -> this, float32: d = 64, T = 8, 16384 problems 3.20 -> 2.55 ms, T = 64,
-// 4099 problems 1.49 -> 1.01; d = 128, T = 16, 8192 problems 16.4 -> 11.6; bfloat16 inputs, T = 32, 4096 problems 9.77 -> 6.60.
+// Measured, products in float32 with row blocks in registers -> this, float32: d = 64, T = 8, 16384 problems 3.21 -> 2.28 ms, T = 64,
+// 4099 problems 1.50 -> 0.91; d = 128, T = 16, 8192 problems 16.3 -> 10.7; bfloat16 inputs, T = 32, 4096 problems 9.77 -> 6.11.
 // Errors against float64: 0.65e-6 (0.87 before), 0.57e-6 (0.77), 1.3e-6 (1.9), 1.6e-6 (2.4).
 template <int D, typename TIn>
 __global__ void __launch_bounds__(Cfg<D>::NTHR, (D) == 64 ? 3 : 2) squaring_kernel(const DoublingArgs da) {
   using C = Cfg<D>;
   using Split = SplitCols<D, C::RB>;
   constexpr int L = 0, R = 1;  // the halves of the pair
+  constexpr bool PARK = D == 128;  // the transpose of A_e waits in LDS while an inverse is formed
   __shared__ __attribute__((aligned(16))) float W[C::PAIR];
   __shared__ __attribute__((aligned(16))) SolveScratch<D> S;
   __shared__ float s_red[C::NW];
@@ -91,10 +114,10 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D) == 64 ? 3 : 2) squaring_kern
       load_cols<D, TIn>(Ap, m, w, i, g);
       split_cols<D, C::RB>(m, a);
       floatx4 none[C::NT][1];  // no right-hand sides
-      if (solve_cols<D, 0>(WR, m, none, w, lane, PIVOT_MIN_A)) {
+      if (__builtin_expect(solve_cols<D, 0>(WR, m, none, w, lane, PIVOT_MIN_A), 0)) {
         load_half<D, TIn, false>(WL, Ap, tid);
         __syncthreads();
-        if (lds_factor<D>(W, S, tid)) {
+        if (lds_factor_aside<D>(W, S, tid)) {
           hand_over(HANDED_TO_PRODUCT);
           continue;
         }
@@ -227,16 +250,24 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D) == 64 ? 3 : 2) squaring_kern
         mu_prev = mu;
       }
       pivoted = pivoted || mu > IN_ORDER_MAX;
+      // The transpose of A_e, the operand that the products behind the inverse need last, waits in LDS as the left operand A_e:
+      // 32 registers at d = 128, where what does not fit goes to memory (16 of its 16-byte pieces a lane cost as much as three products).
+      if constexpr (PARK) store_split_T<D>(W, L, at, w, i, g);
       int flag;
-      if (!pivoted) {
+      if (__builtin_expect(!pivoted, 1)) {
         flag = invert_cols<D>(WR, s, w, lane, PIVOT_MIN);
       } else {
+        if constexpr (PARK) {
+          read_split<D>(W, L, at, w, i, g);
+          lds_barrier();
+        }
         store_cols<D>(WL, C::PITCH, s, w, i, g);
         set_half_identity<D>(WR, tid);
         __syncthreads();
-        flag = lds_solve<D>(W, S, tid);
+        flag = lds_solve_aside<D>(W, S, tid);
         read_cols<D>(WR, s, w, i, g);
         lds_barrier();
+        if constexpr (PARK) store_split_T<D>(W, L, at, w, i, g);
       }
       if (flag) {  // a pivot below PIVOT_MIN, or none at all
         give_up = HANDED_TO_PRODUCT;
@@ -245,11 +276,12 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D) == 64 ? 3 : 2) squaring_kern
       Split t;
       split_cols<D, C::RB>(s, t);
       store_split_T<D>(W, R, t, w, i, g);  // M = (I + P G)^{-1}, or (I + G H)^{-1}
-      if (apply) {
+      if (__builtin_expect(apply, 0)) {
+        if constexpr (PARK) read_split<D>(W, L, at, w, i, g);
         zero_cols<D>(s);
         add_kept_cols<D>(wsP, s, tid);
         split_cols<D, C::RB>(s, t);
-        store_split_T<D>(W, L, t, w, i, g);  // P
+        store_split_T<D>(W, L, t, w, i, g);  // P (the rows just read are this wavefront's own)
         lds_barrier();
         gemm_split<D, C::RB>(s, W, L, a, i, g);  // P A
         split_cols<D, C::RB>(s, t);
@@ -286,7 +318,7 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D) == 64 ? 3 : 2) squaring_kern
         gemm_split<D, C::RB, true>(H, W, R, t, i, g);  // H' = H + A^T V
         lds_barrier();
       } else {
-        store_split_T<D>(W, L, at, w, i, g);  // A
+        if constexpr (!PARK) store_split_T<D>(W, L, at, w, i, g);  // A
         lds_barrier();
         gemm_split<D, C::RB>(s, W, R, a, i, g);  // M A
         split_cols<D, C::RB>(s, ma);
@@ -295,6 +327,7 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D) == 64 ? 3 : 2) squaring_kern
         split_cols<D, C::RB>(s, t);
         lds_barrier();
         store_split_T<D>(W, R, t, w, i, g);
+        if constexpr (PARK) read_split<D>(W, L, at, w, i, g);
         lds_barrier();
         gemm_split<D, C::RB>(s, W, R, at, i, g);  // M G A^T
         split_cols<D, C::RB>(s, t);
