@@ -255,7 +255,7 @@ __device__ __forceinline__ int solve_cols(float* Wp, Cols<D>& s, floatx4 (&f)[D 
       for (int v = 0; v < 4; ++v) o[(16 * r + v) * C::PITCH] = x[v];
     }
   };
-  auto column = [&](const floatx4 (&x)[NT], auto& m, auto K) {
+  auto column = [&](const floatx4 (&x)[NT], auto& m, auto K, int p) {
     constexpr int k = decltype(K)::value;
     floatx4 u = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -267,11 +267,20 @@ __device__ __forceinline__ int solve_cols(float* Wp, Cols<D>& s, floatx4 (&f)[D 
 #pragma unroll
       for (int t = 0; t < 4; ++t) u = __builtin_amdgcn_mfma_f32_16x16x4f32(x[0][t], res[t], u, 0, 0, 0);
     }
+    if constexpr (FT > 0) {
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int r = 1; r < NT; ++r)
+          m[r - 1][k] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[r][t], u[t], t == 0 ? m[r][k] : m[r - 1][k], 0, 0, 0);
+    } else {  // without right-hand sides the rows of blocks already taken are not needed
 #pragma unroll
       for (int r = 1; r < NT; ++r)
-        m[r - 1][k] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[r][t], u[t], t == 0 ? m[r][k] : m[r - 1][k], 0, 0, 0);
+        if (r < NT - p)
+#pragma unroll
+          for (int t = 0; t < 4; ++t)
+            m[r - 1][k] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[r][t], u[t], t == 0 ? m[r][k] : m[r - 1][k], 0, 0, 0);
+    }
     m[NT - 1][k] = u;
   };
   if (w == 0) publish(IntC<0>{}, 0);
@@ -288,17 +297,17 @@ __device__ __forceinline__ int solve_cols(float* Wp, Cols<D>& s, floatx4 (&f)[D 
       auto rest = [&] {
         static_for<0, CT>([&](auto K) {
           constexpr int k = decltype(K)::value;
-          if (CT * w + k > p && !(k == kn && next_here)) column(x, s, K);
+          if (CT * w + k > p && !(k == kn && next_here)) column(x, s, K, p);
         });
-        if constexpr (FT > 0) static_for<0, FT>([&](auto K) { column(x, f, K); });
+        if constexpr (FT > 0) static_for<0, FT>([&](auto K) { column(x, f, K, p); });
       };
       if constexpr (REFINE && LOCAL) {  // the others still need this block's operands
-        if (next_here) column(x, s, IntC<kn>{});
+        if (next_here) column(x, s, IntC<kn>{}, p);
         rest();
         if (next_here) publish(IntC<kn>{}, buf ^ 1);
       } else {
         if (next_here) {
-          column(x, s, IntC<kn>{});
+          column(x, s, IntC<kn>{}, p);
           publish(IntC<kn>{}, buf ^ 1);
         }
         rest();

@@ -58,6 +58,29 @@ __device__ __forceinline__ int lds_factor_aside(float* W, SolveScratch<D>& S, in
   else return lds_factor<D>(W, S, tid);
 }
 
+// f <- s^{-1} f for a symmetric positive definite s, fs being f in split form, through the right half of the pair (s is lost).  At
+// d = 128 by the inverse and a product: right-hand sides carried along double the float32 matrix instructions of an elimination
+// (73 thousand cycles, against 44 for an inverse and 5 for the product); at d = 64 both take 13 thousand.  For R alone: in a step of
+// the recursion, whose value matrix is a difference, an explicit inverse loses too much (cost ratio 1e4: 8e-3 in P_0 for 1e-3).
+// Returns the breakdown flag; the right half is free.
+template <int D>
+__device__ __forceinline__ int invert_or_solve(float* W, Cols<D>& s, Cols<D>& f, const SplitCols<D, Cfg<D>::RB>& fs, int w, int lane,
+                                               int i, int g) {
+  using C = Cfg<D>;
+  if constexpr (D == 128) {
+    const int flag = invert_cols<D>(W + D, s, w, lane, 0.f);
+    SplitCols<D, C::RB> t;
+    split_cols<D, C::RB>(s, t);
+    store_split_T<D>(W, 1, t, w, i, g);
+    lds_barrier();
+    gemm_split<D, C::RB>(f, W, 1, fs, i, g);
+    lds_barrier();
+    return flag;
+  } else {
+    return solve_cols<D, C::RB>(W + D, s, f, w, lane);
+  }
+}
+
 // Both I + G_e H_e and I + P G_e have the eigenvalues of I plus a positive semidefinite matrix.  They are not symmetric, but up
 // to mu of about 30 elimination in order meets no small pivot (CPU, float64, random semidefinite pairs and the benchmark's:
 // pivots of 1.1 and more; at 40 some problems in a hundred, at 120 all of them meet negative ones): the solve is by columns,
@@ -109,6 +132,7 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D) == 64 ? 3 : 2) squaring_kern
 
     // ---- a singular A is reported, although nothing here divides by A
     Split a, at;  // A_e and its transpose
+    Cols<D> G, H;
     {
       Cols<D> m;
       load_cols<D, TIn>(Ap, m, w, i, g);
@@ -125,8 +149,11 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D) == 64 ? 3 : 2) squaring_kern
       }
     }
     // ---- set-up: G = B R^{-1} B^T, H = Q; P = Q_T when it is a matrix of its own
-    Cols<D> G, H;
+    const int thread = tid;
     {
+      // (formed anew at d = 128, or its address arithmetic pushes the element into memory: T = 16, 8192 problems 10.64 -> 9.61 ms)
+      const int tid = D == 128 ? (int)threadIdx.x + opaque_zero() : thread;
+      const int lane = tid & 63, w = uniform(tid >> 6), i = lane & 15, g = lane >> 4;
       Cols<D> r, bt;
       Split t;
       load_cols_T<D, TIn>(Bp, bt, w, i, g);
@@ -134,12 +161,13 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D) == 64 ? 3 : 2) squaring_kern
       add_sym_cols<D, TIn>(Rp, r, w, i, g);
       split_cols<D, C::RB>(bt, t);
       store_split_T<D>(W, L, t, w, i, g);  // B
-      if (solve_cols<D, C::RB>(WR, r, bt, w, lane)) {  // R is not positive definite
+      if (invert_or_solve<D>(W, r, bt, t, w, lane, i, g)) {  // R^{-1} B^T, or R is not positive definite
         hand_over(HANDED_TO_PRODUCT);
         continue;
       }
       split_cols<D, C::RB>(bt, t);
       gemm_split<D, C::RB>(G, W, L, t, i, g);
+      lds_barrier();
       // G is symmetric up to rounding; make it exactly so
       store_cols_T<D>(WR, G, w, i, g);
       load_cols_T<D, TIn>(Ap, bt, w, i, g);
