@@ -23,13 +23,7 @@ hipError_t launch_scan_leaf<TTC_D>(const ScanArgs& a, bool bf16, int ipw, dim3 g
   return hipGetLastError();
 }
 template <>
-hipError_t launch_scan_combine<TTC_D>(const ScanArgs& a, int ipw, dim3 grid, hipStream_t st) {
-#if TTC_D == 16
-  if (ipw == 4) {
-    hipLaunchKernelGGL(scan_combine16_kernel, grid, dim3(64), 0, st, a);
-    return hipGetLastError();
-  }
-#endif
+hipError_t launch_scan_combine<TTC_D>(const ScanArgs& a, dim3 grid, hipStream_t st) {
   hipLaunchKernelGGL((scan_combine_kernel<TTC_D>), grid, dim3(Cfg<TTC_D>::NTHR), 0, st, a);
   return hipGetLastError();
 }

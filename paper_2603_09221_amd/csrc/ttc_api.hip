@@ -233,8 +233,8 @@ static hipError_t run_rollout_tv(const TvRolloutArgs& a, int d, bool bf16, dim3 
 static hipError_t run_scan_leaf(const ScanArgs& a, int d, bool bf16, int ipw, dim3 grid, hipStream_t st) {
   TTC_BY_D(d, launch_scan_leaf<D>(a, bf16, ipw, grid, st))
 }
-static hipError_t run_scan_combine(const ScanArgs& a, int d, int ipw, dim3 grid, hipStream_t st) {
-  TTC_BY_D(d, launch_scan_combine<D>(a, ipw, grid, st))
+static hipError_t run_scan_combine(const ScanArgs& a, int d, dim3 grid, hipStream_t st) {
+  TTC_BY_D(d, launch_scan_combine<D>(a, grid, st))
 }
 static hipError_t run_scan_apply(const ScanArgs& a, int d, int ipw, dim3 grid, hipStream_t st) {
   TTC_BY_D(d, launch_scan_apply<D>(a, ipw, grid, st))
@@ -496,9 +496,9 @@ size_t ttc_lqr_tv_scan_workspace_bytes(const ttc_lqr_tv_problem_t* q) {
   return (size_t)q->n * (size_t)q->T * 3 * (size_t)q->d * (size_t)q->d * sizeof(float);
 }
 
-// Launch shapes of the tree kernels: a round with `items` independent items runs one item per workgroup, except at
-// d = 16 when there are at least fourteen items per compute unit: from there on the kernels that take four items per
-// wavefront are faster (measured on 256 compute units: 16.8 against 17.7 us at 4096 items, 41 against 50 us at 16384;
+// Launch shapes of the tree kernels: a round with `items` independent items runs one item per workgroup, except, at
+// d = 16 when there are at least fourteen items per compute unit, the elements of the steps and the down-sweep: from there
+// on the kernels that take four items per wavefront are faster (the compositions run from register to register and are not) (measured on 256 compute units: 16.8 against 17.7 us at 4096 items, 41 against 50 us at 16384;
 // with 2048 items the one-item kernels finish the round sooner, 13 against 15.5).
 struct ScanPlan {
   long long gb;   // resident workgroups of the one-item kernels
@@ -511,8 +511,9 @@ struct ScanPlan {
       const long long groups = (items + 3) / 4;
       return dim3((unsigned)(groups < gb4 ? groups : gb4));
     }
-    return dim3((unsigned)(items < gb ? items : gb));
+    return grid_one(items);
   }
+  dim3 grid_one(long long items) const { return dim3((unsigned)(items < gb ? items : gb)); }
 };
 static ScanPlan scan_plan(int d, bool bf16) {
   ScanPlan p;
@@ -547,7 +548,7 @@ static hipError_t scan_up_sweep(const ttc_lqr_tv_problem_t* q, ttc::ScanArgs& sa
   for (long long stride = 1; stride < q->T;) {
     sa.stride = (int)stride;
     const long long per = (q->T - stride + 2 * stride - 1) / (2 * stride);
-    e = ttc::run_scan_combine(sa, d, plan.ipw(q->n * per), plan.grid(q->n * per), st);
+    e = ttc::run_scan_combine(sa, d, plan.grid_one(q->n * per), st);
     if (e != hipSuccess) return e;
     stride *= 2;
   }

@@ -83,132 +83,6 @@ __global__ void __launch_bounds__(64, 2) scan_leaf16_kernel(const ScanArgs a) {
   }
 }
 
-// one round of pairwise compositions, four pairs per wavefront
-__global__ void __launch_bounds__(64, 2) scan_combine16_kernel(const ScanArgs a) {
-  constexpr int D = 16, PPW = SCAN16_PPW;
-  using C = Cfg<D>;
-  __shared__ __attribute__((aligned(16))) float Wm[PPW][D * C::PITCH];
-  const SolveArgs& p = a.tv.s;
-  const int st = a.stride;
-  const long long per = (p.T - st + 2LL * st - 1) / (2LL * st);  // pairs per problem in this round
-  const long long items = p.n * per;
-  const long long nquads = (items + PPW - 1) / PPW;
-  for (long long quad = blockIdx.x; quad < nquads; quad += gridDim.x) {
-    const int tid = threadIdx.x + opaque_zero(), lane = tid & 63, i = lane & 15, g = lane >> 4;
-    constexpr int w = 0;
-    float* const Wmine = Wm[g & (PPW - 1)];
-    bool valid[PPW];
-    float* out[PPW];   // A1, G1, H1 in the workspace: rewritten
-    const float* e1[PPW];
-    const float* e2[PPW];
-#pragma unroll
-    for (int q = 0; q < PPW; ++q) {
-      valid[q] = quad * PPW + q < items;
-      const long long item = valid[q] ? quad * PPW + q : items - 1;
-      const long long prob = item / per;
-      const long long j = (item % per) * 2 * st;
-      out[q] = a.ws + (prob * p.T + j) * 3 * D * D;
-      e1[q] = out[q];
-      e2[q] = a.ws + (prob * p.T + j + st) * 3 * D * D;  // A2, G2, H2
-    }
-    floatx4 acc[PPW][C::RB][C::NT], accY[PPW][C::RB][C::NT];
-    float rM[PPW][C::RB][C::KS], rA1T[PPW][C::RB][C::KS], rA2[PPW][C::RB][C::KS];
-    {
-      float rG1[PPW][C::RB][C::KS];
-#pragma unroll
-      for (int q = 0; q < PPW; ++q) {
-        load_half<D, float, false>(Wm[q] + D, e2[q] + 2 * D * D, tid);  // H2
-        load_aop_global<D, float>(e1[q] + D * D, rG1[q], w, i, g);
-        eye_acc<D>(acc[q], w, i, g);
-      }
-      __syncthreads();
-      gemm_acc_quad<PPW>(acc, rG1, Wm, D, i, g);  // I + G1 H2
-#pragma unroll
-      for (int q = 0; q < PPW; ++q) store_rows<D>(Wm[q], acc[q], w, i, g);
-      __syncthreads();
-    }
-#pragma unroll
-    for (int q = 0; q < PPW; ++q) set_half_identity<D>(Wm[q] + D, tid);
-    __syncthreads();
-    const unsigned long long badm = __ballot(solve_rows16<true>(Wmine, lane) != 0);  // right halves: M = (I + G1 H2)^{-1}
-#pragma unroll
-    for (int q = 0; q < PPW; ++q) {
-      load_aop_lds<D>(Wm[q] + D, rM[q], w, i, g);
-      load_half<D, float, false>(Wm[q], e1[q], tid);  // A1
-      zero_acc<D>(acc[q]);
-      zero_acc<D>(accY[q]);
-    }
-    __syncthreads();
-    gemm_acc_quad<PPW>(acc, rM, Wm, 0, i, g);  // X1 = M A1
-#pragma unroll
-    for (int q = 0; q < PPW; ++q) {
-      load_aopT_lds<D>(Wm[q], rA1T[q], w, i, g);
-      load_half<D, float, false>(Wm[q] + D, e1[q] + D * D, tid);  // G1 (M is in registers)
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < PPW; ++q) store_rows<D>(Wm[q], acc[q], w, i, g);  // left halves: X1
-    gemm_acc_quad<PPW>(accY, rM, Wm, D, i, g);                             // Y = M G1
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < PPW; ++q) {
-      load_aop_global<D, float>(e2[q], rA2[q], w, i, g);
-      zero_acc<D>(acc[q]);
-    }
-    gemm_acc_quad<PPW>(acc, rA2, Wm, 0, i, g);  // A = A2 X1
-    {
-      float rH2[PPW][C::RB][C::KS];
-      floatx4 accV[PPW][C::RB][C::NT];
-#pragma unroll
-      for (int q = 0; q < PPW; ++q) {
-        load_aop_global<D, float>(e2[q] + 2 * D * D, rH2[q], w, i, g);
-        zero_acc<D>(accV[q]);
-      }
-      gemm_acc_quad<PPW>(accV, rH2, Wm, 0, i, g);  // V = H2 X1
-#pragma unroll
-      for (int q = 0; q < PPW; ++q) store_rows<D>(Wm[q] + D, accV[q], w, i, g);  // right halves: V (G1 has been used)
-    }
-    __syncthreads();
-    {
-      floatx4 accH[PPW][C::RB][C::NT];
-#pragma unroll
-      for (int q = 0; q < PPW; ++q) load_rows_global<D>(e1[q] + 2 * D * D, accH[q], w, i, g);
-      gemm_acc_quad<PPW>(accH, rA1T, Wm, D, i, g);  // H = H1 + A1^T V
-#pragma unroll
-      for (int q = 0; q < PPW; ++q) {
-        if ((badm >> (16 * q)) & 0xFFFFull) poison<D>(accH[q]);
-        if (valid[q]) {
-          write_rows_global<D>(out[q], acc[q], w, i, g);               // A
-          write_rows_global<D>(out[q] + 2 * D * D, accH[q], w, i, g);  // H
-        }
-        store_rows<D>(Wm[q], accY[q], w, i, g);  // left halves: Y
-        zero_acc<D>(acc[q]);
-      }
-    }
-    __syncthreads();
-    gemm_acc_quad<PPW>(acc, rA2, Wm, 0, i, g);  // Z = A2 Y
-#pragma unroll
-    for (int q = 0; q < PPW; ++q) load_half<D, float, true>(Wm[q] + D, e2[q], tid);  // right halves: A2^T
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < PPW; ++q) store_rows<D>(Wm[q], acc[q], w, i, g);  // left halves: Z
-    __syncthreads();
-    {
-      float rZ[PPW][C::RB][C::KS];
-#pragma unroll
-      for (int q = 0; q < PPW; ++q) {
-        load_aop_lds<D>(Wm[q], rZ[q], w, i, g);
-        load_rows_global<D>(e2[q] + D * D, acc[q], w, i, g);  // G2
-      }
-      gemm_acc_quad<PPW>(acc, rZ, Wm, D, i, g);  // G = G2 + Z A2^T
-#pragma unroll
-      for (int q = 0; q < PPW; ++q)
-        if (valid[q]) write_rows_global<D>(out[q] + D * D, acc[q], w, i, g);
-    }
-    __syncthreads();
-  }
-}
-
 // one level of the down-sweep, four elements per wavefront: P <- H_e + A_e^T (I + P G_e)^{-1} P A_e into the element's H
 __global__ void __launch_bounds__(64, 2) scan_apply16_kernel(const ScanArgs a) {
   constexpr int D = 16, PPW = SCAN16_PPW;
