@@ -24,6 +24,9 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 PEAK_FP32_MFMA_TFLOPS = 157.3   # MI355X dense fp32 matrix peak (256 CUs x 256 flop/clk x 2.4 GHz)
+# Where float32 products run on the float16 matrix cores, three instructions to a product of split operands: a third of the dense
+# float16 peak (2.5 PFLOP/s).  The dense solves between them are float32 instructions still.
+PEAK_SPLIT_PRODUCT_TFLOPS = 2500.0 / 3
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
 
 
@@ -772,6 +775,8 @@ def main():
                 "rollout": alg_flops_rollout(d, T)}.get(path) \
         or alg_flops_default(d, T, groups, cfg["dtype"] == "bf16", k)
     squares = path == "symplectic" and not k and default_squares(d, T, cfg["dtype"] == "bf16")
+    # the kernels whose products are split (squaring, and the Riccati step by columns)
+    peak = PEAK_SPLIT_PRODUCT_TFLOPS if squares or (d >= 32 and path in ("rollout", "bwd")) else PEAK_FP32_MFMA_TFLOPS
     achieved = flops_pp * n / avg_kernel_s / 1e12
     steps_in = T if path == "tv" else 1          # every step has its own matrices on the tv path
     in_bytes = n * (steps_in * (2 * d * d + d * m + m * m) + d) * esize + (n * m * 4 if path == "bwd" else 0)
@@ -791,8 +796,8 @@ def main():
                    "path": path, "rebase_every": None if path != "symplectic" else (k or "default"),
                    "groups": groups if path == "symplectic" and not squares else None, "chunks": nchunks,
                    "outputs": "gA,gB,gQ,gR,gx0" if path == "bwd" else "U,X,cost" if path == "rollout" else "P0,K0,u0,value"},
-        "roofline": {"bound": "mfma", "achieved": achieved, "peak": PEAK_FP32_MFMA_TFLOPS, "unit": "TFLOP/s",
-                     "frac": achieved / PEAK_FP32_MFMA_TFLOPS,
+        "roofline": {"bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak,
+                     "frac_of_fp32_matrix_peak": achieved / PEAK_FP32_MFMA_TFLOPS,
                      # (a row belongs to the default algorithm of its workload, not to the groups rebase_every asks for)
                      "traffic": measured_traffic(args.config, path, n) if not (path == "symplectic" and k) else None,
                      # squaring: a second kernel takes the problems the first gives up

@@ -42,12 +42,11 @@ UNITS = [("ttc_api.hip", None),
          ("k_block.hip", None)]
 
 # Per (source, state size) compile flags: wavefronts of one 16-wide block each (twice as many per problem) instead of
-# two, where measured faster.  The Riccati kernels own matrices by columns: at d = 64 one column tile a wavefront leaves
-# room for three workgroups a compute unit.  The default forward kernel is faster with fewer, fatter wavefronts (its
-# constant operands stay in registers; at d = 64 four problems fit a compute unit).  Measured with one block against two:
-# roll-out d = 128, T = 8, 1024 problems 2.75 ms against 3.04; squaring path d = 128, T = 16 4.5 ms against 31.9 for one
-# batch (two blocks spill, as they do in the time-heterogeneous kernel); flagged doubling d = 128, T = 16 501k problems/s
-# against 488k.
+# two, where measured faster.  The Riccati and squaring kernels own matrices by columns: at d = 64 one column tile a wavefront
+# leaves room for three workgroups a compute unit.  The sequential product is faster with fewer, fatter wavefronts (its constant
+# operands stay in registers; at d = 64 four problems fit a compute unit).  Measured with one block against two: squaring path
+# d = 128, T = 16, 8192 problems 11.6 ms against 14.9, d = 64, T = 8, 16384 problems 2.55 against 2.73; with products in float32,
+# roll-out d = 128, T = 8, 1024 problems 2.75 ms against 3.04; flagged doubling d = 128, T = 16 501k problems/s against 488k.
 _ONE_ROW_BLOCK = "-DTTC_ROW_BLOCKS(D)=((D)==%d?1:((D)>=32?2:1))"
 # The backward kernel at d = 64 takes 188 registers by itself; held to the 168 of three wavefronts a SIMD it spills 20 of them and
 # is still the faster (T = 8, 8192 problems, time-invariant 2.26 ms against 2.88).

@@ -1,10 +1,11 @@
-// The tree over the horizon (ttc_scan.hpp) at d = 16: four elements, compositions or applications per wavefront.
+// The tree over the horizon (ttc_scan.hpp) at d = 16: four elements or applications per wavefront (compositions run one to a
+// wavefront, from register to register: scan_compose16).
 //
-// At d = 16 an element fills a quarter of a wavefront and the dense solve inside a composition is most of its
-// instructions; as in the d = 16 solve kernels (ttc_small.hpp) a workgroup of one wavefront takes four items at a
-// time, forms the products item by item on the matrix cores and runs the four dense solves side by side, lane
-// 16q + r owning row r of item q.  The arithmetic, the workspace layout and the order of the rounds are those of the
-// kernels of ttc_scan.hpp; a ragged last group of four repeats its last item and writes it once.
+// At d = 16 an element fills a quarter of a wavefront and its dense solve is most of its instructions; as in the d = 16
+// solve kernels (ttc_small.hpp) a workgroup of one wavefront takes four items at a time, forms the products item by item
+// on the matrix cores and runs the four dense solves side by side, lane 16q + r owning row r of item q.  The arithmetic,
+// the workspace layout and the order of the rounds are those of the kernels of ttc_scan.hpp; a ragged last group of four
+// repeats its last item and writes it once.
 #pragma once
 #include "ttc_scan.hpp"
 #include "ttc_small.hpp"
