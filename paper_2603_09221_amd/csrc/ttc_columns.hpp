@@ -416,8 +416,8 @@ __device__ __forceinline__ int invert_cols(float* Wp, Cols<D>& s, int w, int lan
 // definite).  Returns the solve's breakdown flag.  Other wavefronts may still be reading the left half on return.
 // add_R(s, w, i, g) adds the symmetric part of R to s.
 template <int D, typename TIn, typename AddR>
-__device__ __forceinline__ int riccati_step_with(float* W, const TIn* As, const TIn* Bs, AddR&& add_R, Cols<D>& wk, Cols<D>& pn,
-                                                 int tid) {
+__device__ __forceinline__ int riccati_step_with(Pair<D>& W, const TIn* As, const TIn* Bs, AddR&& add_R, Cols<D>& wk,
+                                                 Cols<D>& pn, int tid) {
   using C = Cfg<D>;
   tid += opaque_zero();
   const int lane = tid & 63, w = uniform(tid >> 6), i = lane & 15, g = lane >> 4;
@@ -523,7 +523,7 @@ __device__ __forceinline__ int riccati_step_with(float* W, const TIn* As, const 
 }
 
 template <int D, typename TIn>
-__device__ __forceinline__ int riccati_step(float* W, const TIn* As, const TIn* Bs, const TIn* Rs, Cols<D>& wk, Cols<D>& pn,
+__device__ __forceinline__ int riccati_step(Pair<D>& W, const TIn* As, const TIn* Bs, const TIn* Rs, Cols<D>& wk, Cols<D>& pn,
                                             int tid) {
   return riccati_step_with<D, TIn>(
       W, As, Bs, [&](Cols<D>& s, int w, int i, int g) { add_sym_cols<D, TIn>(Rs, s, w, i, g); }, wk, pn, tid);

@@ -42,7 +42,7 @@ __device__ __forceinline__ int first_thread(bool yes, int* s_first) {
 template <int D, typename TIn, bool HANDED = false>
 __device__ __forceinline__ void solve_problems(const SolveArgs& p) {
   using C = Cfg<D>;
-  __shared__ __attribute__((aligned(16))) float W[D * C::PITCH];
+  __shared__ __attribute__((aligned(16))) float W[C::PAIR];
   __shared__ __attribute__((aligned(16))) SolveScratch<D> S;
   __shared__ float s_red[C::NW];
   __shared__ float s_growth[C::NW];  // per wavefront: max |Y1| after the step just taken

@@ -18,6 +18,11 @@ namespace ttc {
 typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
 typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
 
+// The pair in LDS with the notes of split products behind it: a type that carries its size, so that a pair without room for the
+// notes does not compile.
+template <int D>
+using Pair = float[Cfg<D>::PAIR];
+
 // A matrix by columns (ttc_columns.hpp) in split form: m[2q][k] and m[2q + 1][k], a lane's eight values of 32 rows, are one
 // B operand of the matrix core, which visits the contraction index as k = 32 q + 16 (j / 4) + 4 g + j % 4.
 template <int D, int CT>
@@ -69,8 +74,8 @@ __device__ __forceinline__ void split_cols(const floatx4 (&m)[D / 16][CT], Split
 }
 
 // Behind the pair: d floats for the caller, then 1 / s of every wavefront's rows of the left operand in either half.
-template <int D, typename T>
-__device__ __forceinline__ T* split_notes(T* W, int half) {
+template <int D>
+__device__ __forceinline__ float* split_notes(Pair<D>& W, int half) {
   return W + D * Cfg<D>::PITCH + D + 8 * half;
 }
 
@@ -78,7 +83,7 @@ __device__ __forceinline__ T* split_notes(T* W, int half) {
 // column of the matrix, h in the first half of the row's d floats and l in the second, the contraction index in the matrix
 // core's order.  1 / s of the wavefront's rows goes behind the pair.
 template <int D>
-__device__ __forceinline__ void store_split_T(float* W, int half, const SplitCols<D, Cfg<D>::RB>& sp, int w, int i,
+__device__ __forceinline__ void store_split_T(Pair<D>& W, int half, const SplitCols<D, Cfg<D>::RB>& sp, int w, int i,
                                               int g) {
   using C = Cfg<D>;
   float* const o = W + half * D + (16 * C::RB * w + i) * C::PITCH + 4 * g;
@@ -94,7 +99,7 @@ __device__ __forceinline__ void store_split_T(float* W, int half, const SplitCol
 
 // and back, by the wavefront that stored it
 template <int D>
-__device__ __forceinline__ void read_split(const float* W, int half, SplitCols<D, Cfg<D>::RB>& sp, int w, int i, int g) {
+__device__ __forceinline__ void read_split(const Pair<D>& W, int half, SplitCols<D, Cfg<D>::RB>& sp, int w, int i, int g) {
   using C = Cfg<D>;
   const float* const o = W + half * D + (16 * C::RB * w + i) * C::PITCH + 4 * g;
 #pragma unroll
@@ -110,7 +115,7 @@ __device__ __forceinline__ void read_split(const float* W, int half, SplitCols<D
 // 16 x 16 tile is formed from zero and then scaled back into acc, under the next tile's matrix instructions.  The left operands
 // of the next two k-steps are in flight while one is used; scheduling barriers keep the compiler from hoisting more.
 template <int D, int CT, bool ADD = false, int SIGN = 1>
-__device__ __forceinline__ void gemm_split(floatx4 (&acc)[D / 16][CT], const float* W, int half,
+__device__ __forceinline__ void gemm_split(floatx4 (&acc)[D / 16][CT], Pair<D>& W, int half,
                                            const SplitCols<D, CT>& b, int i, int g) {
   using C = Cfg<D>;
   constexpr int NT = C::NT, NQ = D / 32, NX = NT * NQ, AHEAD = NX < 3 ? NX - 1 : 2;

@@ -64,7 +64,7 @@ __device__ __forceinline__ int lds_factor_aside(float* W, SolveScratch<D>& S, in
 // the recursion, whose value matrix is a difference, an explicit inverse loses too much (cost ratio 1e4: 8e-3 in P_0 for 1e-3).
 // Returns the breakdown flag; the right half is free.
 template <int D>
-__device__ __forceinline__ int invert_or_solve(float* W, Cols<D>& s, Cols<D>& f, const SplitCols<D, Cfg<D>::RB>& fs, int w, int lane,
+__device__ __forceinline__ int invert_or_solve(Pair<D>& W, Cols<D>& s, Cols<D>& f, const SplitCols<D, Cfg<D>::RB>& fs, int w, int lane,
                                                int i, int g) {
   using C = Cfg<D>;
   if constexpr (D == 128) {

@@ -68,7 +68,7 @@ __device__ __forceinline__ void emit_step(float* W, float* s_red, const SolveArg
 // index (1 = the step taken first, s = T-1) of the step whose solve broke down; the result is what info becomes.  All
 // threads must call it.
 template <int D, typename TIn>
-__device__ __forceinline__ int riccati_problem(float* W, float* s_red, const SolveArgs& p,
+__device__ __forceinline__ int riccati_problem(Pair<D>& W, float* s_red, const SolveArgs& p,
                                                 long long prob, int T, const TIn* As, const TIn* Bs, const TIn* Qs,
                                                 const TIn* Rs, long long tA, long long tB, long long tQ, long long tR,
                                                 const TIn* PT, const float* PTf, const TIn* Qflag, const TIn* x0p,
