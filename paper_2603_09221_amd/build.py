@@ -52,6 +52,7 @@ _ONE_ROW_BLOCK = "-DTTC_ROW_BLOCKS(D)=((D)==%d?1:((D)>=32?2:1))"
 # is still the faster (T = 8, 8192 problems, time-invariant 2.26 ms against 2.88).
 _THREE_WAVES = "-DTTC_COLS_WAVES(D)=3"
 UNIT_FLAGS = {("k_backward.hip", 64): [_ONE_ROW_BLOCK % 64, _THREE_WAVES],
+              ("k_backward.hip", 128): [_ONE_ROW_BLOCK % 128],
               ("k_tv.hip", 64): [_ONE_ROW_BLOCK % 64],
               ("k_tv.hip", 128): [_ONE_ROW_BLOCK % 128],
               ("k_doubling.hip", 128): [_ONE_ROW_BLOCK % 128],

@@ -46,13 +46,9 @@ __device__ __forceinline__ void zero_cols(floatx4 (&m)[D / 16][CT]) {
 #pragma unroll
     for (int k = 0; k < CT; ++k) m[r][k] = floatx4{0.f, 0.f, 0.f, 0.f};
 }
-// Of a row-major matrix in memory, the signs (1 or -1) of the diagonal entries of a lane's columns; m -= diag(e).
-template <int D, typename TIn>
-__device__ __forceinline__ void load_diagonal_signs(const TIn* M, float (&e)[Cfg<D>::RB], int w, int i) {
-#pragma unroll
-  for (int k = 0; k < Cfg<D>::RB; ++k)
-    e[k] = __builtin_copysignf(1.f, ld1<TIn>(M, (long)(16 * (Cfg<D>::RB * w + k) + i) * (D + 1)));
-}
+// The sign (1 or -1) of an entry on A's diagonal, 0 for one below 1/2 (it would take more out of a small column than there is in it).
+__device__ __forceinline__ float diagonal_sign(float x) { return __builtin_fabsf(x) >= 0.5f ? __builtin_copysignf(1.f, x) : 0.f; }
+// m -= diag(e), e for a lane's columns
 template <int D>
 __device__ __forceinline__ void subtract_diagonal(Cols<D>& m, const float (&e)[Cfg<D>::RB], int w, int i, int g) {
 #pragma unroll
@@ -62,25 +58,142 @@ __device__ __forceinline__ void subtract_diagonal(Cols<D>& m, const float (&e)[C
 #pragma unroll
       for (int v = 0; v < 4; ++v) m[r][k][v] -= (r == Cfg<D>::RB * w + k && 4 * g + v == i) ? e[k] : 0.f;
 }
-// from a row-major matrix in memory: a row of 16 lanes reads 16 consecutive elements
+// the largest of a non-negative value's copies in the four lane groups that hold a column (as bits: NaN on top)
+__device__ __forceinline__ float column_max(float x) {
+  const uint32_t u = __float_as_uint(x);
+  const auto h = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  const uint32_t y = h[0] > h[1] ? h[0] : h[1];
+  const auto q = __builtin_amdgcn_permlane16_swap(y, y, false, false);
+  return __uint_as_float(q[0] > q[1] ? q[0] : q[1]);
+}
+// the largest magnitudes of a lane's columns
+template <int D>
+__device__ __forceinline__ void column_sizes(const Cols<D>& m, float (&x)[Cfg<D>::RB]) {
+#pragma unroll
+  for (int k = 0; k < Cfg<D>::RB; ++k) {
+    float big = 0.f;
+#pragma unroll
+    for (int r = 0; r < D / 16; ++r)
+#pragma unroll
+      for (int v = 0; v < 4; v += 2)
+        big = __builtin_fmaxf(big, __builtin_fmaxf(__builtin_fabsf(m[r][k][v]), __builtin_fabsf(m[r][k][v + 1])));
+    x[k] = column_max(big);
+  }
+}
+// the magnitudes of the diagonal entries of a lane's columns, in all four groups
+template <int D>
+__device__ __forceinline__ void diagonal_sizes(const Cols<D>& m, float (&x)[Cfg<D>::RB], int w, int i, int g) {
+#pragma unroll
+  for (int k = 0; k < Cfg<D>::RB; ++k) {
+    float d = 0.f;
+#pragma unroll
+    for (int r = 0; r < D / 16; ++r)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) d = (r == Cfg<D>::RB * w + k && 4 * g + v == i) ? __builtin_fabsf(m[r][k][v]) : d;
+    x[k] = column_max(d);
+  }
+}
+// the power of two above a magnitude, from 2^-80 to 2^80
+__device__ __forceinline__ float unit_above(float x) {
+  uint32_t u = (__float_as_uint(x) & 0x7F800000u) + (1u << 23);
+  u = u < (47u << 23) ? 47u << 23 : (u > (207u << 23) ? 207u << 23 : u);
+  return __uint_as_float(u);
+}
+// Whether the d values in LDS (as float bits, none negative) span more than a factor of 2^BITS; all wavefronts agree.
+template <int D, int BITS>
+__device__ __forceinline__ bool spread_above(const float* u, int g) {
+  uint32_t lo = ~0u, hi = 0u;
+#pragma unroll
+  for (int r = 0; r < D / 16; ++r) {
+    const floatx4 x = *reinterpret_cast<const floatx4*>(u + 16 * r + 4 * g);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const uint32_t b = __float_as_uint(x[v]);
+      lo = b < lo ? b : lo;
+      hi = b > hi ? b : hi;
+    }
+  }
+  hi = __float_as_uint(column_max(__uint_as_float(hi)));
+  lo = ~__float_as_uint(column_max(__uint_as_float(~lo)));
+  return uniform((int)(hi - lo)) > (BITS << 23);
+}
+// m <- diag(u) m or diag(1 / u) m, u a vector of powers of two in LDS (INVERSE) or of any numbers
+template <int D, bool INVERSE = false>
+__device__ __forceinline__ void scale_rows(Cols<D>& m, const float* u, int g) {
+#pragma unroll
+  for (int r = 0; r < D / 16; ++r) {
+    floatx4 x = *reinterpret_cast<const floatx4*>(u + 16 * r + 4 * g);
+    if (INVERSE)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) x[v] = power_inverse(x[v]);
+#pragma unroll
+    for (int k = 0; k < Cfg<D>::RB; ++k) m[r][k] = m[r][k] * x;
+  }
+}
+// m <- m diag(x)
+template <int D>
+__device__ __forceinline__ void scale_columns(Cols<D>& m, const float (&x)[Cfg<D>::RB]) {
+#pragma unroll
+  for (int r = 0; r < D / 16; ++r)
+#pragma unroll
+    for (int k = 0; k < Cfg<D>::RB; ++k) m[r][k] = m[r][k] * x[k];
+}
+// The power of two whose square is above x >= 0 and at most 4 x (2^80 at most, also for what is not finite).
+__device__ __forceinline__ float unit_of_square(float x) {
+  const uint32_t e = __float_as_uint(x) >> 23;  // 127 + e
+  const uint32_t u = (((e + 127u) >> 1) + 1u) << 23;
+  return __uint_as_float(u < (207u << 23) ? u : 207u << 23);
+}
+// From a row-major matrix in memory, as read: a row of 16 lanes reads 16 consecutive elements; of the transpose a lane's four entries
+// are consecutive.
+template <int D, typename TIn>
+struct ReadCols {
+  decltype(read1((const TIn*)nullptr, 0)) x[D / 16][Cfg<D>::RB][4];
+  __device__ __forceinline__ void read(const TIn* M, int w, int i, int g) {
+    const unsigned o = (unsigned)(4 * g * D + 16 * Cfg<D>::RB * w + i);
+#pragma unroll
+    for (int r = 0; r < D / 16; ++r)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int k = 0; k < Cfg<D>::RB; ++k) x[r][k][v] = read1(M, o + (unsigned)((16 * r + v) * D + 16 * k));
+  }
+  __device__ __forceinline__ void to(Cols<D>& m) const {
+#pragma unroll
+    for (int r = 0; r < D / 16; ++r)
+#pragma unroll
+      for (int k = 0; k < Cfg<D>::RB; ++k)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) m[r][k][v] = widen(x[r][k][v]);
+  }
+};
+template <int D, typename TIn>
+struct ReadColsT {
+  decltype(read4((const TIn*)nullptr, 0)) x[D / 16][Cfg<D>::RB];
+  __device__ __forceinline__ void read(const TIn* M, int w, int i, int g) {
+    const unsigned o = (unsigned)((16 * Cfg<D>::RB * w + i) * D + 4 * g);
+#pragma unroll
+    for (int r = 0; r < D / 16; ++r)
+#pragma unroll
+      for (int k = 0; k < Cfg<D>::RB; ++k) x[r][k] = read4(M, o + (unsigned)(16 * k * D + 16 * r));
+  }
+};
 template <int D, typename TIn>
 __device__ __forceinline__ void load_cols(const TIn* M, Cols<D>& m, int w, int i, int g) {
-  const unsigned o = (unsigned)(4 * g * D + 16 * Cfg<D>::RB * w + i);
-#pragma unroll
-  for (int r = 0; r < D / 16; ++r)
-#pragma unroll
-    for (int v = 0; v < 4; ++v)
-#pragma unroll
-      for (int k = 0; k < Cfg<D>::RB; ++k) m[r][k][v] = ld1<TIn>(M, o + (unsigned)((16 * r + v) * D + 16 * k));
+  ReadCols<D, TIn> t;
+  t.read(M, w, i, g);
+  TTC_SCHED_BARRIER();
+  t.to(m);
 }
-// its transpose (a lane's four entries are consecutive elements)
 template <int D, typename TIn>
 __device__ __forceinline__ void load_cols_T(const TIn* M, Cols<D>& m, int w, int i, int g) {
-  const unsigned o = (unsigned)((16 * Cfg<D>::RB * w + i) * D + 4 * g);
+  ReadColsT<D, TIn> t;
+  t.read(M, w, i, g);
+  TTC_SCHED_BARRIER();
 #pragma unroll
   for (int r = 0; r < D / 16; ++r)
 #pragma unroll
-    for (int k = 0; k < Cfg<D>::RB; ++k) m[r][k] = ld4<TIn>(M, o + (unsigned)(16 * k * D + 16 * r));
+    for (int k = 0; k < Cfg<D>::RB; ++k) m[r][k] = widen(t.x[r][k]);
 }
 template <int D>
 __device__ __forceinline__ void eye_cols(Cols<D>& m, int w, int i, int g) {
@@ -94,13 +207,17 @@ __device__ __forceinline__ void eye_cols(Cols<D>& m, int w, int i, int g) {
 // m += the symmetric part of such a matrix (the transposed entries of a lane are four consecutive elements)
 template <int D, typename TIn>
 __device__ __forceinline__ void add_sym_cols(const TIn* M, Cols<D>& m, int w, int i, int g) {
-  Cols<D> t;
-  load_cols<D, TIn>(M, t, w, i, g);
-  const unsigned o = (unsigned)((16 * Cfg<D>::RB * w + i) * D + 4 * g);
+  ReadCols<D, TIn> t;
+  ReadColsT<D, TIn> tt;
+  t.read(M, w, i, g);
+  tt.read(M, w, i, g);
+  TTC_SCHED_BARRIER();
+  Cols<D> c;
+  t.to(c);
 #pragma unroll
   for (int r = 0; r < D / 16; ++r)
 #pragma unroll
-    for (int k = 0; k < Cfg<D>::RB; ++k) m[r][k] += 0.5f * (t[r][k] + ld4<TIn>(M, o + (unsigned)(16 * k * D + 16 * r)));
+    for (int k = 0; k < Cfg<D>::RB; ++k) m[r][k] += 0.5f * (c[r][k] + widen(tt.x[r][k]));
 }
 // A matrix by columns to memory and back as it stands in the registers, 16 bytes a lane: of a matrix that every step reads
 // (time-invariant parameters), its symmetric part takes a fifth of the reads this way.
@@ -410,20 +527,259 @@ __device__ __forceinline__ int invert_cols(float* Wp, Cols<D>& s, int w, int lan
   return uniform(all);
 }
 
+// Units of the states for the products of a step, as powers of two: the unit D_j of state j is just above max_i |P_ij| / sqrt(P_ii),
+// which is sqrt(P_jj) where P is semidefinite (and no less than half of sqrt(max_i |P_ij|) where P_jj is 0).  Written x' = D x, all
+// entries of P are below 2 whatever the units of the problem, and a product over the states adds terms of like weight.
+template <int D>
+__device__ __forceinline__ void publish_state_units(Pair<D>& W, const Cols<D>& P, int w, int i, int g) {
+  using C = Cfg<D>;
+  float* const aux = control_units<D>(W);
+  float x[C::RB], c[C::RB];
+  diagonal_sizes<D>(P, x, w, i, g);
+  column_sizes<D>(P, c);
+#pragma unroll
+  for (int k = 0; k < C::RB; ++k) {
+    x[k] = unit_of_square(x[k] == 0.f ? c[k] : x[k]);
+    aux[16 * (C::RB * w + k) + i] = power_inverse(x[k]);
+  }
+  lds_barrier();
+#pragma unroll
+  for (int k = 0; k < C::RB; ++k) {
+    float big = __uint_as_float(__float_as_uint(0.5f * x[k]) - 1u);  // (just below, as unit_above goes to the next power)
+#pragma unroll
+    for (int r = 0; r < C::NT; ++r) {
+      const floatx4 y = *reinterpret_cast<const floatx4*>(aux + 16 * r + 4 * g);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) big = __builtin_fmaxf(big, __builtin_fabsf(P[r][k][v]) * y[v]);
+    }
+    state_units<D>(W)[16 * (C::RB * w + k) + i] = unit_above(column_max(big));
+  }
+  lds_barrier();
+}
+// The spread of positive values as a pair of 16-bit numbers of which maxima are taken: the exponent, and 255 less it.
+typedef unsigned short ushortx2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t spread_of(float x) {
+  const uint32_t e = __float_as_uint(x) >> 23;
+  return e | (255u - e) << 16;
+}
+__device__ __forceinline__ uint32_t spread_join(uint32_t a, uint32_t b) {
+  return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(ushortx2, a), __builtin_bit_cast(ushortx2, b)));
+}
+__device__ __forceinline__ uint32_t spread_join16(uint32_t x) {  // over the sixteen lanes of a group
+  x = spread_join(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xF, 0xF, false));   // quad_perm [1,0,3,2]
+  x = spread_join(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xF, 0xF, false));   // quad_perm [2,3,0,1]
+  x = spread_join(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x141, 0xF, 0xF, false));  // row_half_mirror
+  return spread_join(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x140, 0xF, 0xF, false));  // row_mirror
+}
+__device__ __forceinline__ int spread_bits(uint32_t x) { return (int)(x & 0xFFFFu) + (int)(x >> 16) - 255; }  // (-255: all zero)
+// Whether the operands of a step need units of their own: the diagonal of P spans more than a factor of 2^14, or the columns of B or
+// of A (e: the signs taken out of t) more than 2^7; up to there the digits that split operands have beyond float32 do.  One barrier,
+// which all wavefronts reach with P read; it and the judgement cost 2 to 4 % of a step (ttc_lqr_solve_tv, d = 64, T = 8, 8192 problems 1.86
+// -> 1.92 ms).
+template <int D>
+__device__ __forceinline__ bool step_needs_units(Pair<D>& W, const Cols<D>& P, const Cols<D>& B, const Cols<D>& t,
+                                                 const float (&e)[Cfg<D>::RB], int w, int i, int g) {
+  using C = Cfg<D>;
+  uint32_t* const judge = reinterpret_cast<uint32_t*>(column_units<D>(W));
+  float x[3][C::RB];
+  diagonal_sizes<D>(P, x[0], w, i, g);
+  column_sizes<D>(B, x[1]);
+  column_sizes<D>(t, x[2]);
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    uint32_t s = 0;
+#pragma unroll
+    for (int k = 0; k < C::RB; ++k) {
+      if (q == 2) x[q][k] = __builtin_fmaxf(x[q][k], __builtin_fabsf(e[k]));
+      // (a column of zeros has no size; a state without a cost has rows of B and A that must not set the scale)
+      s = spread_join(s, q > 0 && x[q][k] == 0.f ? 0u : spread_of(x[q][k]));
+    }
+    judge[3 * w + q] = spread_join16(s);
+  }
+  lds_barrier();
+  uint32_t s[3] = {0, 0, 0};
+#pragma unroll
+  for (int ww = 0; ww < C::NW; ++ww)
+#pragma unroll
+    for (int q = 0; q < 3; ++q) s[q] = spread_join(s[q], judge[3 * ww + q]);
+  const int p = uniform(spread_bits(s[0])), b = uniform(spread_bits(s[1])), a = uniform(spread_bits(s[2]));
+  return p > 14 || b > 7 || a > 7;
+}
+
+// P, B, R (in s) and A - E (in t) of a step in units of its own, with D E C^{-1} in the place of E.  V and C go behind the pair.
+template <int D>
+__device__ __forceinline__ void step_in_units(Pair<D>& W, Cols<D>& P, Cols<D>& B, Cols<D>& s, Cols<D>& t, float (&e)[Cfg<D>::RB],
+                                              int w, int i, int g) {
+  using C = Cfg<D>;
+  lds_barrier();
+  publish_state_units<D>(W, P, w, i, g);
+  const float* const units = state_units<D>(W);
+  float x[C::RB], y[C::RB], u[C::RB];
+#pragma unroll
+  for (int k = 0; k < C::RB; ++k) {
+    u[k] = units[16 * (C::RB * w + k) + i];
+    x[k] = power_inverse(u[k]);
+  }
+  scale_rows<D, true>(P, units, g);
+  scale_columns<D>(P, x);
+  // V: the largest entry of a column of D B is in [1, 2), and that of R at most 2^80
+  scale_rows<D>(B, units, g);
+  column_sizes<D>(B, x);
+  diagonal_sizes<D>(s, y, w, i, g);
+#pragma unroll
+  for (int k = 0; k < C::RB; ++k) {
+    const float v = __builtin_fmaxf(0.5f * unit_above(x[k]), __builtin_ldexpf(unit_of_square(y[k]), -40));
+    control_units<D>(W)[16 * (C::RB * w + k) + i] = v;
+    x[k] = power_inverse(v);
+  }
+  // C: a column of D A is of the size of the larger of D E and D (A - E)
+  scale_rows<D>(t, units, g);
+  column_sizes<D>(t, y);
+#pragma unroll
+  for (int k = 0; k < C::RB; ++k) {
+    const float big = __builtin_fmaxf(y[k], __builtin_fabsf(e[k]) * u[k]);
+    const float c = big == 0.f ? 1.f : unit_above(big);
+    column_units<D>(W)[16 * (C::RB * w + k) + i] = c;
+    y[k] = power_inverse(c);
+    e[k] *= u[k] * y[k];
+  }
+  scale_columns<D>(t, y);
+  lds_barrier();
+  scale_columns<D>(B, x);
+  scale_columns<D>(s, x);
+  scale_rows<D, true>(s, control_units<D>(W), g);
+}
+
+// The operands of a step at d >= 32, by columns: P (symmetric, from the right half of the pair), B, R (through add_R), E and A - E.
+template <int D, typename TIn, typename AddR>
+__device__ __forceinline__ void step_operands(Pair<D>& W, const TIn* As, const TIn* Bs, AddR&& add_R, Cols<D>& P, Cols<D>& B,
+                                              Cols<D>& s, Cols<D>& t, float (&e)[Cfg<D>::RB], int w, int i, int g) {
+  using C = Cfg<D>;
+  {
+    ReadCols<D, TIn> b, a;
+    decltype(read1(As, 0)) d[C::RB];
+    b.read(Bs, w, i, g);
+    a.read(As, w, i, g);
+#pragma unroll
+    for (int k = 0; k < C::RB; ++k) d[k] = read1(As, (long)(16 * (C::RB * w + k) + i) * (D + 1));
+    zero_cols<D>(s);
+    TTC_SCHED_BARRIER();
+    add_R(s, w, i, g);
+    TTC_SCHED_BARRIER();  // the step's reads are all under way
+    b.to(B);
+    a.to(t);
+#pragma unroll
+    for (int k = 0; k < C::RB; ++k) e[k] = diagonal_sign(widen(d[k]));
+  }
+  // P is symmetric: a lane's four entries of a column are four consecutive ones of its row
+#pragma unroll
+  for (int r = 0; r < C::NT; ++r)
+#pragma unroll
+    for (int k = 0; k < C::RB; ++k)
+      P[r][k] = *reinterpret_cast<const floatx4*>(W + D + (16 * (C::RB * w + k) + i) * C::PITCH + 16 * r + 4 * g);
+  subtract_diagonal<D>(t, e, w, i, g);
+}
+// Its six products and the solve, from these operands (P is replaced, every wavefront has read it).
+template <int D>
+__device__ __forceinline__ int step_products(Pair<D>& W, Cols<D>& pn, const Cols<D>& bc, Cols<D>& s, const Cols<D>& t,
+                                             const float (&e)[Cfg<D>::RB], Cols<D>& wk, int w, int lane, int i, int g) {
+  using C = Cfg<D>;
+  using Split = SplitCols<D, C::RB>;
+  constexpr int L = 0, R = 1;  // the halves
+  float* const signs = diagonal_signs<D>(W);
+  {
+    Split a;
+    {
+      Split b;
+      {
+        Split p;
+        split_cols<D, C::RB>(pn, p);
+        store_split_T<D>(W, R, p, w, i, g);  // P
+        split_cols<D, C::RB>(bc, b);
+        store_split_T<D>(W, L, b, w, i, g);  // B^T
+      }
+      if (g == 0)
+#pragma unroll
+        for (int k = 0; k < C::RB; ++k) signs[16 * (C::RB * w + k) + i] = e[k];
+      lds_barrier();
+      Cols<D> pb;
+      gemm_split<D, C::RB>(pb, W, R, b, i, g);  // P B
+      split_cols<D, C::RB>(pb, b);
+      gemm_split<D, C::RB, true>(s, W, L, b, i, g);  // S = R + B^T P B
+      split_cols<D, C::RB>(t, a);
+    }
+    Split pa;
+    scale_columns<D>(pn, e);
+    gemm_split<D, C::RB, true>(pn, W, R, a, i, g);  // P A = P E + P (A - E)
+    split_cols<D, C::RB>(pn, pa);
+    gemm_split<D, C::RB>(wk, W, L, pa, i, g);  // F = B^T P A
+    Split f;
+    split_cols<D, C::RB>(wk, f);
+    lds_barrier();                           // P and B^T are no longer read
+    store_split_T<D>(W, R, a, w, i, g);  // (A - E)^T
+    store_split_T<D>(W, L, f, w, i, g);  // F^T
+    lds_barrier();
+    scale_rows<D>(pn, signs, g);
+    gemm_split<D, C::RB, true>(pn, W, R, pa, i, g);  // A^T P A = E P A + (A - E)^T P A
+  }
+  lds_barrier();
+  const int flag = solve_cols<D, C::RB>(W + D, s, wk, w, lane);  // W = S^{-1} F
+  Split x;
+  split_cols<D, C::RB>(wk, x);
+  gemm_split<D, C::RB, true, -1>(pn, W, L, x, i, g);  // - F^T W
+  return flag;
+}
+// The same in units of the step's own, powers of two, so that results do not depend on those of the problem: x' = D x before the step's
+// state, u' = V u, x' = C x behind it, and with them D^{-1} P D^{-1}, D B V^{-1}, D A C^{-1}, V^{-1} R V^{-1}.  Split operands keep 40
+// binary digits below the largest entry of a wavefront's columns, float32 ones every digit of every entry: with one state in units of 2^17,
+// d = 64, T = 8, u_0 was off by 3e-3 without; now by what it is in units of one, bit for bit.
+// A function of its own, for the few steps that need it: inlined beside the other it costs both their registers (d = 64, T = 8, 8192
+// problems 1.92 -> 2.01 ms with the scalings behind branches, 2.5 with two copies of the products).
+typedef __attribute__((address_space(3))) float lds_float;
+template <int D, typename TIn>
+__device__ __attribute__((noinline)) int riccati_step_in_units(lds_float* pair, const TIn* As, const TIn* Bs, const TIn* Rs,
+                                                               Cols<D>* wk_out, Cols<D>* pn_out, int tid) {
+  using C = Cfg<D>;
+  Pair<D>& W = *reinterpret_cast<Pair<D>*>((float*)pair);
+  const int lane = tid & 63, w = uniform(tid >> 6), i = lane & 15, g = lane >> 4;
+  Cols<D> wk, pn, bc, s, t;
+  float e[C::RB];
+  step_operands<D, TIn>(
+      W, As, Bs, [&](Cols<D>& m, int w, int i, int g) { add_sym_cols<D, TIn>(Rs, m, w, i, g); }, pn, bc, s, t, e, w, i, g);
+  step_in_units<D>(W, pn, bc, s, t, e, w, i, g);
+  const int flag = step_products<D>(W, pn, bc, s, t, e, wk, w, lane, i, g);
+  const float* const c = column_units<D>(W);
+  float ck[C::RB];
+#pragma unroll
+  for (int k = 0; k < C::RB; ++k) ck[k] = c[16 * (C::RB * w + k) + i];
+  scale_rows<D>(pn, c, g);
+  scale_columns<D>(pn, ck);
+  scale_rows<D, true>(wk, control_units<D>(W), g);
+  scale_columns<D>(wk, ck);
+#pragma unroll
+  for (int r = 0; r < C::NT; ++r)
+#pragma unroll
+    for (int k = 0; k < C::RB; ++k) {
+      (*wk_out)[r][k] = wk[r][k];
+      (*pn_out)[r][k] = pn[r][k];
+    }
+  return flag;
+}
+
 // One backward step of Prop. 3.1 with the matrices of one step.  On entry the right half of the pair holds P_{s+1}
 // (symmetric, visible) and the left half is free; on exit, by columns, wk = S^{-1} B^T P A = -K_s, S = R + B^T P B, and
 // pn = A^T P A - (B^T P A)^T wk, which is P_s up to the stage cost.  Six products and one unpivoted solve (S is positive
 // definite).  Returns the solve's breakdown flag.  Other wavefronts may still be reading the left half on return.
-// add_R(s, w, i, g) adds the symmetric part of R to s.
+// add_R(s, w, i, g) adds the symmetric part of R, the matrix at Rs, to s.
 template <int D, typename TIn, typename AddR>
-__device__ __forceinline__ int riccati_step_with(Pair<D>& W, const TIn* As, const TIn* Bs, AddR&& add_R, Cols<D>& wk,
+__device__ __forceinline__ int riccati_step_with(Pair<D>& W, const TIn* As, const TIn* Bs, const TIn* Rs, AddR&& add_R, Cols<D>& wk,
                                                  Cols<D>& pn, int tid) {
   using C = Cfg<D>;
   tid += opaque_zero();
   const int lane = tid & 63, w = uniform(tid >> 6), i = lane & 15, g = lane >> 4;
-  float* const WL = W;
-  float* const WR = W + D;
   if constexpr (D == 16) {  // one tile: half of a float16 instruction's depth would be empty
+    float* const WL = W;
+    float* const WR = W + D;
     Cols<D> s, a, b, pb, pa;
     load_cols<D, TIn>(Bs, b, w, i, g);
     store_cols_T<D>(WL, b, w, i, g);  // B^T
@@ -449,76 +805,22 @@ __device__ __forceinline__ int riccati_step_with(Pair<D>& W, const TIn* As, cons
     gemm_cols<D>(pn, WL, wk, i, g);                                 // - F^T W
     return flag;
   } else {
-    using Split = SplitCols<D, C::RB>;
-    constexpr int L = 0, R = 1;  // the halves
-    float* const signs = W + D * C::PITCH;
+    Cols<D> bc, s, t;
     float e[C::RB];
-    Cols<D> s;
-    {
-      Split a;
-      {
-        Split b;
-        Cols<D> t;
-        {
-          Cols<D> bc;
-          Split p;
-          load_cols<D, TIn>(Bs, bc, w, i, g);
-          load_cols<D, TIn>(As, t, w, i, g);
-          load_diagonal_signs<D, TIn>(As, e, w, i);
-          zero_cols<D>(s);
-          add_R(s, w, i, g);
-          TTC_SCHED_BARRIER();  // the step's reads are all under way
-          // P is symmetric: a lane's four entries of a column are four consecutive ones of its row
-#pragma unroll
-          for (int r = 0; r < C::NT; ++r)
-#pragma unroll
-            for (int k = 0; k < C::RB; ++k)
-              pn[r][k] = *reinterpret_cast<const floatx4*>(WR + (16 * (C::RB * w + k) + i) * C::PITCH + 16 * r + 4 * g);
-          split_cols<D, C::RB>(pn, p);
-          lds_barrier();  // every wavefront has read its columns of P
-          store_split_T<D>(W, R, p, w, i, g);  // P
-          split_cols<D, C::RB>(bc, b);
-          store_split_T<D>(W, L, b, w, i, g);  // B^T
-        }
-        subtract_diagonal<D>(t, e, w, i, g);
-        if (g == 0)
-#pragma unroll
-          for (int k = 0; k < C::RB; ++k) signs[16 * (C::RB * w + k) + i] = e[k];
-        lds_barrier();
-        Cols<D> pb;
-        gemm_split<D, C::RB>(pb, W, R, b, i, g);  // P B
-        split_cols<D, C::RB>(pb, b);
-        gemm_split<D, C::RB, true>(s, W, L, b, i, g);  // S = R + B^T P B
-        split_cols<D, C::RB>(t, a);
-      }
-      Split pa;
+    step_operands<D, TIn>(W, As, Bs, add_R, pn, bc, s, t, e, w, i, g);
+    if (__builtin_expect(step_needs_units<D>(W, pn, bc, t, e, w, i, g), 0)) {
+      Cols<D> a, b;
+      const int flag = riccati_step_in_units<D, TIn>((lds_float*)(float*)W, As, Bs, Rs, &a, &b, tid);
 #pragma unroll
       for (int r = 0; r < C::NT; ++r)
 #pragma unroll
-        for (int k = 0; k < C::RB; ++k) pn[r][k] = pn[r][k] * e[k];
-      gemm_split<D, C::RB, true>(pn, W, R, a, i, g);  // P A = P E + P (A - E)
-      split_cols<D, C::RB>(pn, pa);
-      gemm_split<D, C::RB>(wk, W, L, pa, i, g);  // F = B^T P A
-      Split f;
-      split_cols<D, C::RB>(wk, f);
-      lds_barrier();                           // P and B^T are no longer read
-      store_split_T<D>(W, R, a, w, i, g);  // (A - E)^T
-      store_split_T<D>(W, L, f, w, i, g);  // F^T
-      lds_barrier();
-#pragma unroll
-      for (int r = 0; r < C::NT; ++r) {
-        const floatx4 er = *reinterpret_cast<const floatx4*>(signs + 16 * r + 4 * g);
-#pragma unroll
-        for (int k = 0; k < C::RB; ++k) pn[r][k] = pn[r][k] * er;
-      }
-      gemm_split<D, C::RB, true>(pn, W, R, pa, i, g);  // A^T P A = E P A + (A - E)^T P A
+        for (int k = 0; k < C::RB; ++k) {
+          wk[r][k] = a[r][k];
+          pn[r][k] = b[r][k];
+        }
+      return flag;
     }
-    lds_barrier();
-    const int flag = solve_cols<D, C::RB>(WR, s, wk, w, lane);  // W = S^{-1} F
-    Split x;
-    split_cols<D, C::RB>(wk, x);
-    gemm_split<D, C::RB, true, -1>(pn, W, L, x, i, g);  // - F^T W
-    return flag;
+    return step_products<D>(W, pn, bc, s, t, e, wk, w, lane, i, g);
   }
 }
 
@@ -526,7 +828,7 @@ template <int D, typename TIn>
 __device__ __forceinline__ int riccati_step(Pair<D>& W, const TIn* As, const TIn* Bs, const TIn* Rs, Cols<D>& wk, Cols<D>& pn,
                                             int tid) {
   return riccati_step_with<D, TIn>(
-      W, As, Bs, [&](Cols<D>& s, int w, int i, int g) { add_sym_cols<D, TIn>(Rs, s, w, i, g); }, wk, pn, tid);
+      W, As, Bs, Rs, [&](Cols<D>& s, int w, int i, int g) { add_sym_cols<D, TIn>(Rs, s, w, i, g); }, wk, pn, tid);
 }
 
 // P_s = pn + the symmetric part of the stage cost goes to the right half, exactly symmetric; add_Q(pn, w, i, g) adds it.

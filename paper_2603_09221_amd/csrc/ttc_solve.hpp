@@ -272,11 +272,11 @@ __device__ __forceinline__ void solve_problems(const SolveArgs& p) {
 }
 
 template <int D, typename TIn>
-__global__ void __launch_bounds__(Cfg<D>::NTHR, (D == 64 ? TTC_D64_WAVES : 1)) solve_kernel(const SolveArgs p) {
+__global__ void __launch_bounds__(Cfg<D>::NTHR, (D == 64 ? TTC_D64_WAVES : D == 32 ? 2 : 1)) solve_kernel(const SolveArgs p) {
   solve_problems<D, TIn>(p);
 }
 template <int D, typename TIn>
-__global__ void __launch_bounds__(Cfg<D>::NTHR, (D == 64 ? TTC_D64_WAVES : 1)) solve_handed_kernel(const SolveArgs p) {
+__global__ void __launch_bounds__(Cfg<D>::NTHR, (D == 64 ? TTC_D64_WAVES : D == 32 ? 2 : 1)) solve_handed_kernel(const SolveArgs p) {
   solve_problems<D, TIn, true>(p);
 }
 

@@ -37,13 +37,15 @@ __device__ __forceinline__ float split_unscale(uint32_t max_bits) {
   e = e < 15 ? 15 : (e > 254 ? 254 : e);
   return __uint_as_float((uint32_t)(e - 14) << 23);
 }
-__device__ __forceinline__ float split_scale(float inv) { return __uint_as_float((254u << 23) - __float_as_uint(inv)); }
 
 __device__ __forceinline__ void split_pair(float x, float y, float s, halfx2& h, halfx2& l) {
   h = __builtin_convertvector(floatx2{x * s, y * s}, halfx2);
   l[0] = (_Float16)__builtin_fmaf(x, s, -(float)h[0]);
   l[1] = (_Float16)__builtin_fmaf(y, s, -(float)h[1]);
 }
+
+// the power of two 1 / x
+__device__ __forceinline__ float power_inverse(float x) { return __uint_as_float((254u << 23) - __float_as_uint(x)); }
 
 template <int D, int CT>
 __device__ __forceinline__ void split_cols(const floatx4 (&m)[D / 16][CT], SplitCols<D, CT>& sp) {
@@ -56,7 +58,7 @@ __device__ __forceinline__ void split_cols(const floatx4 (&m)[D / 16][CT], Split
       for (int v = 0; v < 4; v += 2)
         big = __builtin_fmaxf(big, __builtin_fmaxf(__builtin_fabsf(m[r][k][v]), __builtin_fabsf(m[r][k][v + 1])));
   sp.inv = split_unscale(wave_max_u32(__float_as_uint(big)));
-  const float s = split_scale(sp.inv);
+  const float s = power_inverse(sp.inv);
 #pragma unroll
   for (int q = 0; q < D / 32; ++q)
 #pragma unroll
@@ -73,11 +75,18 @@ __device__ __forceinline__ void split_cols(const floatx4 (&m)[D / 16][CT], Split
       }
 }
 
-// Behind the pair: d floats for the caller, then 1 / s of every wavefront's rows of the left operand in either half.
+// Behind the pair: four times d floats for the caller (units of the states, of the controls and of the columns of A, and the signs of A's
+// diagonal), then 1 / s of every wavefront's rows of the left operand in either half.
 template <int D>
-__device__ __forceinline__ float* split_notes(Pair<D>& W, int half) {
-  return W + D * Cfg<D>::PITCH + D + 8 * half;
-}
+__device__ __forceinline__ float* state_units(Pair<D>& W) { return W + D * Cfg<D>::PITCH; }
+template <int D>
+__device__ __forceinline__ float* control_units(Pair<D>& W) { return W + D * Cfg<D>::PITCH + D; }
+template <int D>
+__device__ __forceinline__ float* column_units(Pair<D>& W) { return W + D * Cfg<D>::PITCH + 2 * D; }
+template <int D>
+__device__ __forceinline__ float* diagonal_signs(Pair<D>& W) { return W + D * Cfg<D>::PITCH + 3 * D; }
+template <int D>
+__device__ __forceinline__ float* split_notes(Pair<D>& W, int half) { return W + D * Cfg<D>::PITCH + 4 * D + 8 * half; }
 
 // The transpose to LDS as a left operand, into the half of the pair that begins at L: row 16 RB w + .. of the transpose is a
 // column of the matrix, h in the first half of the row's d floats and l in the second, the contraction index in the matrix

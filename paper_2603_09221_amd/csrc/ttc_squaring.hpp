@@ -91,6 +91,125 @@ static constexpr float PIVOT_MIN = 0.25f, PIVOT_MIN_A = 0.015625f, IN_ORDER_MAX 
 // The guard's limit after the first squaring, and the mu at which the coming square of e is expected and not formed.
 static constexpr float LATE_LIMIT = 64.f, GROWTH_STOP = 16.f;
 
+// One round of the units below: a lane's s, and all of them in the notes (the last round's and the new ones side by side).  One barrier,
+// the units are to be read behind another one.
+template <int D>
+__device__ __forceinline__ void next_state_units(Pair<D>& W, const Cols<D>& A, float (&s)[Cfg<D>::RB], int w, int i, int g) {
+  using C = Cfg<D>;
+  float* const units = state_units<D>(W);
+#pragma unroll
+  for (int k = 0; k < C::RB; ++k) {
+    float big = 0.f;
+#pragma unroll
+    for (int r = 0; r < C::NT; ++r) {
+      const floatx4 y = *reinterpret_cast<const floatx4*>(units + 16 * r + 4 * g);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const float x = (r == C::RB * w + k && 4 * g + v == i) ? 0.f : __builtin_fabsf(A[r][k][v]) * y[v];
+        big = __builtin_fmaxf(big, x);
+      }
+    }
+    big = column_max(big);
+    s[k] = big == 0.f ? s[k] : __builtin_fmaxf(s[k], unit_above(big));
+    column_units<D>(W)[16 * (C::RB * w + k) + i] = s[k];
+  }
+  lds_barrier();
+#pragma unroll
+  for (int k = 0; k < C::RB; ++k) units[16 * (C::RB * w + k) + i] = s[k];
+}
+// Units of the states and controls of a problem, powers of two in the notes behind the pair: for state k just above the largest of
+// sqrt(Q_kk), sqrt(Q_T,kk) and |A_ik| times that of state i, what it costs by itself and through the states it moves in one step; for
+// control k just above sqrt(R_kk).  Written x' = D x, u' = V u, a problem's matrices do not depend on the units it came in and no entry of
+// A or H is much larger than 1; split operands need that, as they keep 40 binary digits below the largest entry of a wavefront's
+// columns.  A state without a cost of its own takes that of the states it reaches, round after round; one that reaches none has no
+// influence on the others and counts for next to nothing.  Returns whether the units are used; within a factor of 16 they are all 1 and
+// the digits that split operands have beyond float32 do (from 32 on what squaring itself loses shows too: a power's largest entries are
+// then those that the units make large; bfloat16 inputs, T = 16, P_0 1e-5 for 9e-7).  The judgement costs 2 % of a call (d = 64, T = 16,
+// 8192 problems 1.39 -> 1.41 ms); in functions of their own the scalings cost 15 % of every call, by the registers that the paths share,
+// and at d = 128 in float32 they cost less without branches around them (T = 16, 2048 problems 2.51 -> 2.63 ms for 2.74, bfloat16 2.57 ->
+// 2.70 for 2.75).
+template <int D, typename TIn>
+__device__ __forceinline__ bool publish_problem_units(Pair<D>& W, const Cols<D>& A, const TIn* Qp, const TIn* QTp, const TIn* Rp,
+                                                      int w, int i, int g) {
+  using C = Cfg<D>;
+  float* const units = state_units<D>(W);
+  float s[C::RB];
+#pragma unroll
+  for (int k = 0; k < C::RB; ++k) {
+    const int j = 16 * (C::RB * w + k) + i;
+    const long on = (long)j * (D + 1);
+    const auto q = read1(Qp, on), qt = read1(QTp, on), r = read1(Rp, on);
+    const float cost = __builtin_fmaxf(__builtin_fabsf(widen(q)), __builtin_fabsf(widen(qt)));
+    s[k] = cost == 0.f ? 0.f : unit_of_square(cost);
+    units[j] = s[k];
+    control_units<D>(W)[j] = unit_of_square(__builtin_fabsf(widen(r)));
+  }
+  lds_barrier();
+  next_state_units<D>(W, A, s, w, i, g);
+  const bool controls = spread_above<D, 4>(control_units<D>(W), g), states = spread_above<D, 4>(column_units<D>(W), g);
+  float lo = 1.f;  // the smallest unit
+  if (__builtin_expect(states, 0)) {  // (also where a state has none yet)
+    int open = D + 1, before;
+    do {
+      before = open;
+      open = 0;
+      lo = __builtin_inff();
+      for (int r = 0; r < C::NT; ++r) {
+        const floatx4 y = *reinterpret_cast<const floatx4*>(column_units<D>(W) + 16 * r + 4 * g);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          lo = y[v] != 0.f && y[v] < lo ? y[v] : lo;
+          open += __popcll(__ballot(y[v] == 0.f));
+        }
+      }
+      open = uniform(open);
+      lds_barrier();
+      if (open != 0 && open < before) {
+        next_state_units<D>(W, A, s, w, i, g);
+        lds_barrier();
+      }
+    } while (open != 0 && open < before);
+    lo = column_max(lo < __builtin_inff() ? power_inverse(lo) : 0.f);
+    lo = lo == 0.f ? 1.f : power_inverse(lo);  // (no costs at all)
+  }
+  lds_barrier();
+#pragma unroll
+  for (int k = 0; k < C::RB; ++k) {
+    const int j = 16 * (C::RB * w + k) + i;
+    units[j] = !states ? 1.f : s[k] == 0.f ? __builtin_fmaxf(lo * 0x1p-40f, 0x1p-80f) : s[k];
+    control_units<D>(W)[j] = controls ? control_units<D>(W)[j] : 1.f;
+  }
+  lds_barrier();
+  return states || controls;
+}
+// m <- diag(u) m diag(1 / v), u and v in LDS: a map in units of its own
+template <int D>
+__device__ __forceinline__ void map_in_units(Cols<D>& m, const float* u, const float* v, int w, int i, int g) {
+  float x[Cfg<D>::RB];
+#pragma unroll
+  for (int k = 0; k < Cfg<D>::RB; ++k) x[k] = power_inverse(v[16 * (Cfg<D>::RB * w + k) + i]);
+  scale_rows<D>(m, u, g);
+  scale_columns<D>(m, x);
+}
+// the same of its transpose, m = M^T, and back from units: diag(1 / v) m diag(u)
+template <int D>
+__device__ __forceinline__ void map_in_units_T(Cols<D>& m, const float* u, const float* v, int w, int i, int g) {
+  float x[Cfg<D>::RB];
+#pragma unroll
+  for (int k = 0; k < Cfg<D>::RB; ++k) x[k] = u[16 * (Cfg<D>::RB * w + k) + i];
+  scale_rows<D, true>(m, v, g);
+  scale_columns<D>(m, x);
+}
+// diag(1 / u) m diag(1 / u): a cost
+template <int D>
+__device__ __forceinline__ void cost_in_units(Cols<D>& m, const float* u, int w, int i, int g) {
+  float x[Cfg<D>::RB];
+#pragma unroll
+  for (int k = 0; k < Cfg<D>::RB; ++k) x[k] = power_inverse(u[16 * (Cfg<D>::RB * w + k) + i]);
+  scale_rows<D, true>(m, u, g);
+  scale_columns<D>(m, x);
+}
+
 // One column tile per wavefront at d >= 64 (build.py): two at d = 128 leave one wavefront a SIMD (T = 16, 8192 problems 14.9 against
 // 11.6 ms), at d = 64 two wavefronts (T = 8, 16384 problems 2.73 against 2.55 ms with one tile and three wavefronts).  The registers
 // do not hold all of it (96 spilled at d = 64, 330 at d = 128, around the inverse), which costs less than another wavefront would.
@@ -133,9 +252,15 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D) == 64 ? 3 : 2) squaring_kern
     // ---- a singular A is reported, although nothing here divides by A
     Split a, at;  // A_e and its transpose
     Cols<D> G, H;
+    bool own;  // whether the problem is written in units of its own
+    constexpr bool ALWAYS = D == 128 && sizeof(TIn) == 4;  // (multiplied by them in any case, which is exact)
+    const float* const xu = state_units<D>(W);
+    const float* const uu = control_units<D>(W);
     {
       Cols<D> m;
       load_cols<D, TIn>(Ap, m, w, i, g);
+      own = publish_problem_units<D, TIn>(W, m, Qp, QTp, Rp, w, i, g);
+      if (ALWAYS || __builtin_expect(own, 0)) map_in_units<D>(m, xu, xu, w, i, g);
       split_cols<D, C::RB>(m, a);
       floatx4 none[C::NT][1];  // no right-hand sides
       if (__builtin_expect(solve_cols<D, 0>(WR, m, none, w, lane, PIVOT_MIN_A), 0)) {
@@ -159,6 +284,10 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D) == 64 ? 3 : 2) squaring_kern
       load_cols_T<D, TIn>(Bp, bt, w, i, g);
       zero_cols<D>(r);
       add_sym_cols<D, TIn>(Rp, r, w, i, g);
+      if (ALWAYS || __builtin_expect(own, 0)) {
+        cost_in_units<D>(r, uu, w, i, g);
+        map_in_units_T<D>(bt, xu, uu, w, i, g);
+      }
       split_cols<D, C::RB>(bt, t);
       store_split_T<D>(W, L, t, w, i, g);  // B
       if (invert_or_solve<D>(W, r, bt, t, w, lane, i, g)) {  // R^{-1} B^T, or R is not positive definite
@@ -171,9 +300,11 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D) == 64 ? 3 : 2) squaring_kern
       // G is symmetric up to rounding; make it exactly so
       store_cols_T<D>(WR, G, w, i, g);
       load_cols_T<D, TIn>(Ap, bt, w, i, g);
+      if (ALWAYS || __builtin_expect(own, 0)) map_in_units_T<D>(bt, xu, xu, w, i, g);
       split_cols<D, C::RB>(bt, at);
       zero_cols<D>(H);
       add_sym_cols<D, TIn>(Qp, H, w, i, g);
+      if (ALWAYS || __builtin_expect(own, 0)) cost_in_units<D>(H, xu, w, i, g);
       lds_barrier();
       read_cols<D>(WR, r, w, i, g);
 #pragma unroll
@@ -186,6 +317,7 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D) == 64 ? 3 : 2) squaring_kern
       Cols<D> t;
       zero_cols<D>(t);
       add_sym_cols<D, TIn>(QTp, t, w, i, g);
+      if (ALWAYS || __builtin_expect(own, 0)) cost_in_units<D>(t, xu, w, i, g);
       keep_cols<D>(wsP, t, tid);
     }
     lds_barrier();
@@ -393,9 +525,30 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D) == 64 ? 3 : 2) squaring_kern
       __syncthreads();
       symmetrise_half<D>(WR, tid);
       __syncthreads();
-      Cols<D> wk, pn;
-      if (riccati_step<D, TIn>(W, Ap, Bp, Rp, wk, pn, tid)) give_up = HANDED_TO_PRODUCT;
-      else emit_step<D, TIn>(W, s_red, p, prob, wk, pn, Qp, x0p, 0, tid);
+      Cols<D> wk, pn, b, r, t;
+      float e[C::RB];
+      step_operands<D, TIn>(
+          W, Ap, Bp, [&](Cols<D>& m, int w, int i, int g) { add_sym_cols<D, TIn>(Rp, m, w, i, g); }, pn, b, r, t, e, w, i, g);
+      if (ALWAYS || __builtin_expect(own, 0)) {
+        map_in_units<D>(t, xu, xu, w, i, g);  // (A - E: what is on the diagonal stays)
+        map_in_units<D>(b, xu, uu, w, i, g);
+        cost_in_units<D>(r, uu, w, i, g);
+      }
+      if (__builtin_expect(step_needs_units<D>(W, pn, b, t, e, w, i, g), 0)) {  // others than the problem's
+        give_up = HANDED_TO_RECURSION;
+      } else if (step_products<D>(W, pn, b, r, t, e, wk, w, lane, i, g)) {
+        give_up = HANDED_TO_PRODUCT;
+      } else {
+        if (ALWAYS || __builtin_expect(own, 0)) {  // back to the units the problem came in
+          float x[C::RB];
+#pragma unroll
+          for (int k = 0; k < C::RB; ++k) x[k] = xu[16 * (C::RB * w + k) + i];
+          scale_rows<D>(pn, xu, g);
+          scale_columns<D>(pn, x);
+          map_in_units_T<D>(wk, xu, uu, w, i, g);
+        }
+        emit_step<D, TIn>(W, s_red, p, prob, wk, pn, Qp, x0p, 0, tid);
+      }
     }
     if (give_up) hand_over(give_up);
   }
