@@ -26,17 +26,17 @@
 
 namespace ttc {
 
-template <int D>
-__device__ __forceinline__ void dot2(const RowShare<D>& m, const float* xa, const float* xb, int tid, float& ya, float& yb) {
+template <int D, typename V>
+__device__ __forceinline__ void dot2(const RowShare<D, V>& m, const float* xa, const float* xb, int tid, float& ya, float& yb) {
   ya = m.dot(xa, tid);
   yb = m.dot(xb, tid);
 }
 // Two matrix-vector products at once (the primal and the dual trajectory always need the same matrix): for the
 // row r = tid / TPR of a row-major d x d matrix, ya = sum_c M[r][c] xa[c] and yb likewise; the TPR threads of a
-// row each take a share of the columns and all of them get the sums.  MatLoad(r, c4) returns M[r][c4 .. c4+3].
+// row each take a share of the columns and all of them get the sums.  MatLoad(r, c4) returns M[r][c4 .. c4+3], as read.
 template <int D, typename MatLoad>
 __device__ __forceinline__ void matvec2(MatLoad&& row4, const float* xa, const float* xb, int tid, float& ya, float& yb) {
-  RowShare<D> m;
+  RowShare<D, decltype(row4(0, 0))> m;
   m.load(row4, tid);
   TTC_SCHED_BARRIER();
   dot2<D>(m, xa, xb, tid, ya, yb);
@@ -51,7 +51,7 @@ __device__ __forceinline__ void matvecT2(MatLoad1&& elem, const float* xa, const
   const int j = tid % D, part = tid / D;
   // four sums side by side: one after the other, D / TPR terms round as often (the co-states are such sums at every step)
   float sa[4] = {0.f, 0.f, 0.f, 0.f}, sb[4] = {0.f, 0.f, 0.f, 0.f};
-  float m[D / TPR];
+  decltype(elem(0, 0)) m[D / TPR];
 #pragma unroll
   for (int r = 0; r < D / TPR; ++r) m[r] = elem(part * (D / TPR) + r, j);
   TTC_SCHED_BARRIER();  // all reads are under way
@@ -61,8 +61,9 @@ __device__ __forceinline__ void matvecT2(MatLoad1&& elem, const float* xa, const
     const floatx4 vb = *reinterpret_cast<const floatx4*>(xb + part * (D / TPR) + r);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      sa[e] += m[r + e] * va[e];
-      sb[e] += m[r + e] * vb[e];
+      const float x = widen(m[r + e]);
+      sa[e] += x * va[e];
+      sb[e] += x * vb[e];
     }
   }
   red[part * D + j] = (sa[0] + sa[1]) + (sa[2] + sa[3]);
@@ -151,8 +152,8 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, TTC_COLS_WAVES(D)) backward_kern
     float* const v_lt = s_v[5];
     float* const v_y = s_v[6];
     float* const v_z = s_v[7];
-    auto glob4 = [](const TIn* M) { return [M](int r, int c4) { return ld4<TIn>(M, (long)r * D + c4); }; };
-    auto glob1 = [](const TIn* M) { return [M](int r, int j) { return ld1<TIn>(M, (long)r * D + j); }; };
+    auto glob4 = [](const TIn* M) { return [M](int r, int c4) { return read4(M, (long)r * D + c4); }; };
+    auto glob1 = [](const TIn* M) { return [M](int r, int j) { return read1(M, (long)r * D + j); }; };
     auto lds4 = [](const float* Wh) {
       return [Wh](int r, int c4) { return *reinterpret_cast<const floatx4*>(Wh + r * C::PITCH + c4); };
     };
@@ -228,12 +229,13 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, TTC_COLS_WAVES(D)) backward_kern
     RowShare<D> Kr;
     Kr.load([](int, int) { return floatx4{0.f, 0.f, 0.f, 0.f}; }, tid);
     for (int s = 0; s < T; ++s) {
-      RowShare<D> Ar, Br;
-      if (resident) {
-        Ar.load(lds4(WL), tid);
-      } else {
+      RowShareOf<D, TIn> Ar, Br;
+      constexpr bool ONE = sizeof(TIn) == sizeof(float);  // what is read from LDS and from memory has one type, and one product
+      if (!resident) {
         Ar.load(glob4(Ap + (long long)s * ba.tA), tid);
         Br.load(glob4(Bp + (long long)s * ba.tB), tid);
+      } else if constexpr (ONE) {
+        Ar.load(lds4(WL), tid);
       }
       float ax, axt, bu, but, u, ut;
       dot2<D>(Kr, v_x, v_xt, tid, u, ut);
@@ -245,10 +247,13 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, TTC_COLS_WAVES(D)) backward_kern
       v_ut[row] = ut;
       if (s + 1 < T) Kr.load(rows_of<D, float>(wsK + (long)s * D * D), tid);
       TTC_SCHED_BARRIER();
-      dot2<D>(Ar, v_x, v_xt, tid, ax, axt);
-      if (resident) Br.load(lds4(WR), tid);
+      if (!ONE && resident) matvec2<D>(lds4(WL), v_x, v_xt, tid, ax, axt);
+      else dot2<D>(Ar, v_x, v_xt, tid, ax, axt);
+      if constexpr (ONE)
+        if (resident) Br.load(lds4(WR), tid);
       lds_barrier();  // the controls are complete, and every thread has read the old states
-      dot2<D>(Br, v_u, v_ut, tid, bu, but);
+      if (!ONE && resident) matvec2<D>(lds4(WR), v_u, v_ut, tid, bu, but);
+      else dot2<D>(Br, v_u, v_ut, tid, bu, but);
       v_x[row] = ax + bu;
       v_xt[row] = axt + but;
       tU[(long)s * D + row] = u;

@@ -11,10 +11,10 @@ namespace ttc {
 // its share of the columns.  A share is read into registers in one go, before anything waits for it: left to the scheduler, which
 // saves registers where another part of the kernel needs many, the reads come one after the other, each with its latency (the
 // loops of a time-heterogeneous backward pass 1.7 to 2.5 times as long, measured).
-template <int D>
+template <int D, typename V = floatx4>  // V: four entries as read
 struct RowShare {
   static constexpr int TPR = Cfg<D>::NTHR / D;  // 2 or 4
-  floatx4 v[D / TPR / 4];
+  V v[D / TPR / 4];
   template <typename MatLoad4>  // (row, column) -> four consecutive entries
   __device__ __forceinline__ void load(MatLoad4&& row4, int tid) {
     const int r = tid / TPR, c0 = (tid % TPR) * (D / TPR);
@@ -27,7 +27,8 @@ struct RowShare {
 #pragma unroll
     for (int c = 0; c < D / TPR / 4; ++c) {
       const floatx4 x = *reinterpret_cast<const floatx4*>(xs + c0 + 4 * c);
-      s += v[c][0] * x[0] + v[c][1] * x[1] + v[c][2] * x[2] + v[c][3] * x[3];
+      const floatx4 m = widen(v[c]);
+      s += m[0] * x[0] + m[1] * x[1] + m[2] * x[2] + m[3] * x[3];
     }
     return share_sum(s);
   }
@@ -42,22 +43,17 @@ struct RowShare {
   }
 };
 template <int D, typename TM>
+using RowShareOf = RowShare<D, decltype(read4((const TM*)nullptr, 0))>;
+template <int D, typename TM>
 __device__ __forceinline__ auto rows_of(const TM* M) {
-  return [M](int r, int c4) { return ld4<TM>(M, (long)r * D + c4); };
+  return [M](int r, int c4) { return read4(M, (long)r * D + c4); };
 }
 template <int D>
 __device__ __forceinline__ auto rows_in_lds(const float* M) {
   return [M](int r, int c4) { return *reinterpret_cast<const floatx4*>(M + r * Cfg<D>::PITCH + c4); };
 }
 
-template <int D, typename TM>
-__device__ __forceinline__ float matvec_row(const TM* M, const float* xs, int tid) {
-  RowShare<D> m;
-  m.load(rows_of<D, TM>(M), tid);
-  return m.dot(xs, tid);
-}
-
-// The same with M in LDS (row pitch PITCH).
+// The product at once, with M in LDS (row pitch PITCH).
 template <int D>
 __device__ __forceinline__ float matvec_row_lds(const float* M, const float* xs, int tid) {
   RowShare<D> m;
@@ -244,7 +240,8 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, TTC_COLS_WAVES(D)) rollout_kerne
 
     // ---- forward sweep; R and Q stay in registers, the next gain is on its way
     const int r = tid / (C::NTHR / D), part = tid % (C::NTHR / D);
-    RowShare<D> Rr, Qr, Kr;
+    RowShare<D> Kr;
+    RowShareOf<D, TIn> Rr, Qr;
     Kr.load(rows_of<D, float>(wsK), tid);
     Rr.load(rows_of<D, TIn>(Rp), tid);
     Qr.load(rows_of<D, TIn>(p.T == 1 && !(p.flags & TTC_FLAG_STAGE_COST_AT_X0) ? QTp : Qp), tid);

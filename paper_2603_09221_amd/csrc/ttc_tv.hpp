@@ -160,7 +160,8 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, TTC_COLS_WAVES(D)) rollout_tv_ke
     float cpart = 0.f;
     if (p.X && tid < D) p.X[prob * (long)(p.T + 1) * D + tid] = s_x[tid];
     for (int t = 0; t < p.T; ++t) {
-      RowShare<D> Kr, Ar, Br, Rr, Qr;  // the step's five reads side by side
+      RowShare<D> Kr;  // the step's five reads side by side
+      RowShareOf<D, TIn> Ar, Br, Rr, Qr;
       Kr.load(rows_of<D, float>(wsK + (long)t * D * D), tid);
       Ar.load(rows_of<D, TIn>(Ap + (long long)t * ta.tA), tid);
       Br.load(rows_of<D, TIn>(Bp + (long long)t * ta.tB), tid);
