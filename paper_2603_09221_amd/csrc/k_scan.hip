@@ -24,7 +24,11 @@ hipError_t launch_scan_leaf<TTC_D>(const ScanArgs& a, bool bf16, int ipw, dim3 g
 }
 template <>
 hipError_t launch_scan_combine<TTC_D>(const ScanArgs& a, dim3 grid, hipStream_t st) {
+#if TTC_D == 16
+  hipLaunchKernelGGL(scan_combine16_kernel, grid, dim3(64), 0, st, a);
+#else
   hipLaunchKernelGGL((scan_combine_kernel<TTC_D>), grid, dim3(Cfg<TTC_D>::NTHR), 0, st, a);
+#endif
   return hipGetLastError();
 }
 template <>
@@ -45,6 +49,10 @@ hipError_t launch_scan_gather<TTC_D>(const ScanArgs& a, float* P, dim3 grid, hip
 }
 template <>
 int occupancy_scan<TTC_D>() {  // the pairwise compositions (the leaf kernel uses fewer registers)
+#if TTC_D == 16
+  return occupancy_query(scan_combine16_kernel, 64);
+#else
   return occupancy_query(scan_combine_kernel<TTC_D>, Cfg<TTC_D>::NTHR);
+#endif
 }
 }  // namespace ttc

@@ -164,64 +164,7 @@ __device__ __forceinline__ void scan_compose(float* W, SolveScratch<D>& S, float
   }
 }
 
-// The same at d = 16 from register to register, by one wavefront: the accumulator layout of a matrix (lane (i, g) holds M[4g + v][i])
-// is the right operand of a product and the left operand of the transpose's, a row of four entries a lane the left operand of the
-// matrix, and I + G1 H2 is formed transposed so that its inverse comes as a left operand.  No search for pivots: false, with nothing
-// written, where that is not safe (max |I + G1 H2| above 24, a pivot below 1/4, anything not finite; ttc_squaring.hpp has what
-// these limits rest on).  A round with few items is this function's latency, mostly the inverse's; with many it is bound by the
-// inverse's instructions.  16 problems, T = 2048, all rounds: 0.190 -> 0.139 ms a call against compositions that pass through LDS
-// and solve with a search for pivots, four to a wavefront where a round has many (the composition of one item 7.4 -> 4.5 us).
-__device__ __forceinline__ bool scan_compose16(float* e1, const float* e2, int lane) {
-  constexpr int DD = 256;
-  const int i = lane & 15, g = lane >> 4;
-  auto rows = [&](const float* m) { return *reinterpret_cast<const floatx4*>(m + 16 * i + 4 * g); };
-  const floatx4 H2 = rows(e2 + 2 * DD), G1 = rows(e1 + DD), A2 = rows(e2);  // (G and H are symmetric)
-  floatx4 A1;
-#pragma unroll
-  for (int v = 0; v < 4; ++v) A1[v] = e1[64 * g + 16 * v + i];
-  floatx4 H = rows(e1 + 2 * DD), G = rows(e2 + DD);
-  floatx4 x;
-#pragma unroll
-  for (int v = 0; v < 4; ++v) x[v] = 4 * g + v == i ? 1.f : 0.f;
-#define TTC_STEP(c, a, b) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t], b[t], c, 0, 0, 0)
-#pragma unroll
-  for (int t = 0; t < 4; ++t) TTC_STEP(x, H2, G1);  // I + H2 G1 = (I + G1 H2)^T
-  uint32_t big = 0;
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const uint32_t b = __float_as_uint(x[v]) & 0x7FFFFFFFu;
-    big = b > big ? b : big;
-  }
-  const float mu = __uint_as_float(wave_max_u32(big));
-  if (!(mu <= 24.f)) return false;
-  if (__any(invert_spread16(x, lane, 0.25f))) return false;
-  const floatx4 z = floatx4{0.f, 0.f, 0.f, 0.f};
-  floatx4 X1 = z, Y = z, A = z, V = z, Z = z;
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    TTC_STEP(X1, x, A1);  // M A1
-    TTC_STEP(Y, x, G1);   // M G1, symmetric
-  }
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    TTC_STEP(A, A2, X1);  // A2 M A1
-    TTC_STEP(V, H2, X1);  // H2 M A1
-    TTC_STEP(Z, Y, A2);   // M G1 A2^T
-  }
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    TTC_STEP(H, A1, V);  // H1 + A1^T H2 M A1
-    TTC_STEP(G, A2, Z);  // G2 + A2 M G1 A2^T
-  }
-#undef TTC_STEP
-#pragma unroll
-  for (int v = 0; v < 4; ++v) e1[64 * g + 16 * v + i] = A[v];
-  *reinterpret_cast<floatx4*>(e1 + DD + 16 * i + 4 * g) = G;
-  *reinterpret_cast<floatx4*>(e1 + 2 * DD + 16 * i + 4 * g) = H;
-  return true;
-}
-
-// one round of pairwise compositions
+// one round of pairwise compositions (d = 16: ttc_scan16.hpp)
 template <int D>
 __global__ void __launch_bounds__(Cfg<D>::NTHR) scan_combine_kernel(const ScanArgs a) {
   using C = Cfg<D>;
@@ -237,9 +180,6 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR) scan_combine_kernel(const ScanAr
     const long long j = (item % per) * 2 * st;
     float* const e1 = a.ws + (prob * p.T + j) * 3 * D * D;
     const float* const e2 = e1 + (long long)st * 3 * D * D;
-    if constexpr (D == 16) {
-      if (scan_compose16(e1, e2, tid)) continue;
-    }
     scan_compose<D>(W, S, e1, e2, tid);
     __syncthreads();
   }

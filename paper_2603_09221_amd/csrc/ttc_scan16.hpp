@@ -1,5 +1,5 @@
 // The tree over the horizon (ttc_scan.hpp) at d = 16: four elements or applications per wavefront (compositions run one to a
-// wavefront, from register to register: scan_compose16).
+// wavefront, from register to register: Composition16).
 //
 // At d = 16 an element fills a quarter of a wavefront and its dense solve is most of its instructions; as in the d = 16
 // solve kernels (ttc_small.hpp) a workgroup of one wavefront takes four items at a time, forms the products item by item
@@ -81,6 +81,106 @@ __global__ void __launch_bounds__(64, 2) scan_leaf16_kernel(const ScanArgs a) {
       if (bad) write_rows_global<D>(gA[q] + 2 * D * D, acc[q], w, i, g);  // the breakdown reaches P_1 whatever follows
     }
     __syncthreads();
+  }
+}
+
+// A composition (scan_compose has the algebra) from register to register, by one wavefront: the accumulator layout of a matrix (lane (i, g) holds M[4g + v][i])
+// is the right operand of a product and the left operand of the transpose's, a row of four entries a lane the left operand of the
+// matrix, and I + G1 H2 is formed transposed so that its inverse comes as a left operand.
+struct Composition16 {
+  floatx4 H2, G1, A2, A1, H, G, n;  // n: (I + G1 H2)^T
+  __device__ __forceinline__ void load(const float* e1, const float* e2, int lane) {
+    constexpr int DD = 256;
+    const int i = lane & 15, g = lane >> 4;
+    auto rows = [&](const float* m) { return *reinterpret_cast<const floatx4*>(m + 16 * i + 4 * g); };
+    H2 = rows(e2 + 2 * DD);  // (G and H are symmetric)
+    G1 = rows(e1 + DD);
+    A2 = rows(e2);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) A1[v] = e1[64 * g + 16 * v + i];
+    H = rows(e1 + 2 * DD);
+    G = rows(e2 + DD);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) n[v] = 4 * g + v == i ? 1.f : 0.f;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) n = __builtin_amdgcn_mfma_f32_16x16x4f32(H2[t], G1[t], n, 0, 0, 0);  // I + H2 G1 = (I + G1 H2)^T
+  }
+  // x <- the inverse of n, without a search for pivots.  False where that is not safe (max |I + G1 H2| above 24, a pivot below 1/4,
+  // anything not finite; ttc_squaring.hpp has what these limits rest on).
+  __device__ __forceinline__ bool invert_in_order(floatx4& x, int lane) const {
+    uint32_t big = 0;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const uint32_t b = __float_as_uint(n[v]) & 0x7FFFFFFFu;
+      big = b > big ? b : big;
+    }
+    const float mu = __uint_as_float(wave_max_u32(big));
+    if (!(mu <= 24.f)) return false;
+    x = n;
+    return !__any(invert_spread16(x, lane, 0.25f));
+  }
+  // The element, x the inverse of n; into e1.
+  __device__ __forceinline__ void finish(const floatx4& x, float* e1, int lane, bool bad) {
+    constexpr int DD = 256;
+    const int i = lane & 15, g = lane >> 4;
+    const floatx4 z = floatx4{0.f, 0.f, 0.f, 0.f};
+    floatx4 X1 = z, Y = z, A = z, V = z, Z = z;
+#define TTC_STEP(c, a, b) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t], b[t], c, 0, 0, 0)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      TTC_STEP(X1, x, A1);  // M A1
+      TTC_STEP(Y, x, G1);   // M G1, symmetric
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      TTC_STEP(A, A2, X1);  // A2 M A1
+      TTC_STEP(V, H2, X1);  // H2 M A1
+      TTC_STEP(Z, Y, A2);   // M G1 A2^T
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      TTC_STEP(H, A1, V);  // H1 + A1^T H2 M A1
+      TTC_STEP(G, A2, Z);  // G2 + A2 M G1 A2^T
+    }
+#undef TTC_STEP
+    if (bad) H = floatx4{__builtin_nanf(""), __builtin_nanf(""), __builtin_nanf(""), __builtin_nanf("")};
+#pragma unroll
+    for (int v = 0; v < 4; ++v) e1[64 * g + 16 * v + i] = A[v];
+    *reinterpret_cast<floatx4*>(e1 + DD + 16 * i + 4 * g) = G;
+    *reinterpret_cast<floatx4*>(e1 + 2 * DD + 16 * i + 4 * g) = H;
+  }
+};
+
+// One round of pairwise compositions at d = 16, one to a wavefront.  A round with few items is a composition's latency, mostly the
+// inverse's; with many it is bound by the inverse's instructions.  Where elimination in order is not safe (control that costs a hundredth,
+// say) only the inverse passes through LDS, for the pivoted solve; all of such a composition through LDS took 10 % longer than one without the
+// attempt.  T = 2048, all rounds, us a call, 16 problems: 150 in order, 200 pivoted (with four compositions side by side and all of them
+// pivoted and through LDS 197); one problem 68, 90 (97).  1024 problems, T = 64: 235, 301 (284).
+__global__ void __launch_bounds__(64) scan_combine16_kernel(const ScanArgs a) {
+  using C = Cfg<16>;
+  __shared__ __attribute__((aligned(16))) float W[16 * C::PITCH];
+  __shared__ __attribute__((aligned(16))) SolveScratch<16> S;
+  const SolveArgs& p = a.tv.s;
+  const int st = a.stride;
+  const long long per = (p.T - st + 2LL * st - 1) / (2LL * st);  // pairs per problem in this round
+  const long long items = p.n * per;
+  for (long long item = blockIdx.x; item < items; item += gridDim.x) {
+    const int lane = threadIdx.x + opaque_zero(), i = lane & 15, g = lane >> 4;
+    float* const e1 = a.ws + ((item / per) * p.T + (item % per) * 2 * st) * 3 * 256;
+    Composition16 c;
+    floatx4 x;
+    c.load(e1, e1 + (long long)st * 3 * 256, lane);
+    bool bad = false;
+    if (__builtin_expect(!c.invert_in_order(x, lane), 0)) {  // with a search for pivots
+      float* const row = W + i * C::PITCH + 4 * g;
+      *reinterpret_cast<floatx4*>(row) = c.n;  // (a row of I + G1 H2)
+      set_half_identity<16>(W + 16, lane);
+      __syncthreads();
+      bad = lds_solve<16>(W, S, lane) != 0;
+      x = *reinterpret_cast<const floatx4*>(row + 16);
+      __syncthreads();
+    }
+    c.finish(x, e1, lane, bad);
   }
 }
 
