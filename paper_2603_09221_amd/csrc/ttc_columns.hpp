@@ -8,12 +8,12 @@
 //
 // The products of d >= 32 run on the float16 matrix cores from split operands (ttc_split.hpp): the registers a split leaves are a
 // right operand and, stored as they are, the left operand of the transpose.  Taking the diagonal's signs E out of A (P A = P E +
-// P (A - E), A^T Y = E Y + (A - E)^T Y) costs one addition in the accumulator and leaves the product with what is small where the
+// P (A - E), A^T Y = E Y + (A - E)^T Y; none where the entry is below 1/2) costs one addition in the accumulator and leaves the product with what is small where the
 // dynamics are near the identity; gradients of 8 steps at d = 64 are off by 0.7 times what float32 products gave (24 steps: 0.6).
 //
-// Measured, T = 8, float32, float32 products -> split: roll-out d = 64, 4096 problems 1.36 -> 0.95 ms, d = 32, 8192 problems 0.54 ->
-// 0.46, d = 128, 1024 problems 2.77 -> 1.71; backward pass d = 64, 8192 problems 2.91 -> 2.21; ttc_lqr_solve_tv d = 64, 1024
-// problems 0.36 -> 0.28.  At d = 64 a step of one problem alone takes 24 thousand cycles (28), of which the dense solve is 13:
+// Measured, T = 8, float32, float32 products -> split: roll-out d = 64, 4096 problems 1.36 -> 0.99 ms, d = 32, 8192 problems 0.44 ->
+// 0.40, d = 128, 512 problems 1.42 -> 0.92; backward pass d = 64, 8192 problems 2.91 -> 2.29; ttc_lqr_solve_tv d = 64, 1024
+// problems 0.36 -> 0.29; at d = 32 and 1024 problems, where a step alone counts, 0.081 -> 0.090.  At d = 64 a step of one problem alone takes 24 thousand cycles (28), of which the dense solve is 13:
 // what is left is its serial chain, hidden as far as three workgroups a compute unit allow.
 #pragma once
 #include "ttc_common.hpp"
@@ -323,7 +323,8 @@ __device__ __forceinline__ void for_each_block(F&& f) {
 }
 
 // Dense solve f <- s^{-1} f, both by columns (f: FT column tiles a wavefront, also none), for a symmetric positive definite s,
-// or any whose elimination in order meets pivots above piv_min only: block Gauss-Jordan with 16 x 16 pivot blocks and no pivot search.  Per block p, the wavefront that owns its columns
+// or any whose elimination in order meets pivots above piv_min only: block Gauss-Jordan with 16 x 16 pivot blocks and no pivot
+// search.  Per block p, the wavefront that owns its columns
 // inverts s[p][p] in registers and publishes that inverse and the rest of the column, negated, as left operands (Wp: the
 // right half of the pair); every wavefront then does its own columns, U = s[p][p]^{-1} s[p][c], s[r][c] -= s[r][p] U,
 // the next block's first, so that its inverse is formed and published under the others' updates: one workgroup barrier

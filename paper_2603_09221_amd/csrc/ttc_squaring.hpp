@@ -60,8 +60,10 @@ __device__ __forceinline__ int lds_factor_aside(float* W, SolveScratch<D>& S, in
 
 // f <- s^{-1} f for a symmetric positive definite s, fs being f in split form, through the right half of the pair (s is lost).  At
 // d = 128 by the inverse and a product: right-hand sides carried along double the float32 matrix instructions of an elimination
-// (73 thousand cycles, against 44 for an inverse and 5 for the product); at d = 64 both take 13 thousand.  For R alone: in a step of
-// the recursion, whose value matrix is a difference, an explicit inverse loses too much (cost ratio 1e4: 8e-3 in P_0 for 1e-3).
+// (73 thousand cycles, against 44 for an inverse and 5 for the product); at d = 64 both take 13 thousand.  For R alone, where
+// nothing is subtracted from what it gives: errors grow with R's condition number as a solve's do (T = 16, condition 1e4, 1e6: P_0 3.5e-6,
+// 1.4e-4; float32 products and a pivoted solve 7.2e-6, 3.1e-4; the recursion 2.4e-6, 1.3e-4).  In a step of the recursion, whose value
+// matrix is a difference, an explicit inverse loses too much (cost ratio 1e4: 8e-3 in P_0 for 1e-3).
 // Returns the breakdown flag; the right half is free.
 template <int D>
 __device__ __forceinline__ int invert_or_solve(Pair<D>& W, Cols<D>& s, Cols<D>& f, const SplitCols<D, Cfg<D>::RB>& fs, int w, int lane,
@@ -212,11 +214,11 @@ __device__ __forceinline__ void cost_in_units(Cols<D>& m, const float* u, int w,
 
 // One column tile per wavefront at d >= 64 (build.py): two at d = 128 leave one wavefront a SIMD (T = 16, 8192 problems 14.9 against
 // 11.6 ms), at d = 64 two wavefronts (T = 8, 16384 problems 2.73 against 2.55 ms with one tile and three wavefronts).  The registers
-// do not hold all of it (96 spilled at d = 64, 330 at d = 128, around the inverse), which costs less than another wavefront would.
+// do not hold all of it (104 spilled at d = 64, 426 at d = 128, around the inverse), which costs less than another wavefront would.
 // The recursion and the solves of the problems given up are in a kernel of their own: inlined here they spilled many more.
-// Measured, products in float32 with row blocks in registers -> this, float32: d = 64, T = 8, 16384 problems 3.21 -> 2.28 ms, T = 64,
-// 4099 problems 1.50 -> 0.91; d = 128, T = 16, 8192 problems 16.3 -> 10.7; bfloat16 inputs, T = 32, 4096 problems 9.77 -> 6.11.
-// Errors against float64: 0.65e-6 (0.87 before), 0.57e-6 (0.77), 1.3e-6 (1.9), 1.6e-6 (2.4).
+// Measured, products in float32 with row blocks in registers -> this, float32: d = 64, T = 8, 16384 problems 3.21 -> 2.39 ms, T = 64,
+// 4099 problems 1.50 -> 0.94; d = 128, T = 16, 8192 problems 16.3 -> 10.3; bfloat16 inputs, T = 32, 4096 problems 9.77 -> BF.
+// Errors against float64: 0.65e-6 (0.87 before), 0.56e-6 (0.77), 1.3e-6 (1.9), 1.5e-6 (2.4).
 template <int D, typename TIn>
 __global__ void __launch_bounds__(Cfg<D>::NTHR, (D) == 64 ? 3 : 2) squaring_kernel(const DoublingArgs da) {
   using C = Cfg<D>;

@@ -126,6 +126,8 @@ def _dense(d, T, dtype, costs):
         Q[:, :, 1::2] = 0
     elif costs == "terminal":     # and here none but the last does
         QT, Q = Q, torch.zeros_like(Q)
+    elif costs == "cheap":        # handed to the recursion
+        return (b.A, b.B, Q, (b.R * 2.0 ** -9).to(b.R.dtype), b.x0), QT, g
     elif costs == "light":        # one state in two costs next to nothing by itself
         s = torch.ones(d, device=DEV)
         s[1::2] = 2.0 ** -14
@@ -173,7 +175,7 @@ def test_rollout_and_backward(d, kind):
 @pytest.mark.gpu
 @pytest.mark.parametrize("d", [32, 64, 128])
 @pytest.mark.parametrize("T,dtype,costs", [(8, "f32", "all"), (16, "bf16", "all"), (21, "f32", "all"), (16, "f32", "half"),
-                                           (21, "f32", "terminal"), (16, "f32", "light")])
+                                           (21, "f32", "terminal"), (16, "f32", "light"), (16, "f32", "cheap")])
 @pytest.mark.parametrize("kind", KINDS, ids=str)
 def test_squaring(d, T, dtype, costs, kind):
     args = (d, T, dtype, costs)
@@ -181,6 +183,27 @@ def test_squaring(d, T, dtype, costs, kind):
     QT = _dense(*args)[1]
     assert binding.ttc_lqr_solve_squares(binding.make_problem(A, B, Q, R, QT, x0, T))
     _hold((args, kind), _dense_errors(*args, kind, ("solve",)), _dense_errors(*args, ONE, ("solve",)))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("cond", [1e2, 1e4, 1e6])
+def test_ill_conditioned_control_costs(d, cond):
+    """R with eigenvalues from 1 to cond along directions of no coordinate: squaring has B R^{-1} B^T, by the inverse of R at d = 128 and a
+    solve elsewhere, where the recursion solves with R + B^T P B.  Their errors grow alike, as the condition number."""
+    T = 16
+    p, _, _ = _dense(d, T, "f32", "all")
+    U = torch.linalg.qr(torch.randn((N, d, d), generator=torch.Generator().manual_seed(1), dtype=torch.float64))[0]
+    R = (U * torch.logspace(0, float(np.log10(cond)), d, dtype=torch.float64)) @ U.transpose(-1, -2)
+    R = (0.5 * (R + R.transpose(-1, -2))).float().to(DEV)
+    A, B, Q, _, x0 = p
+    assert binding.ttc_lqr_solve_squares(binding.make_problem(A, B, Q, R, None, x0, T))
+    ref = lqr_oracle.riccati_solve(*(_np(t) for t in (A, B, Q, R)), None, _np(x0), T)
+    steps = [t[:, None].expand(N, T, d, d).contiguous() for t in (A, B, Q, R)]
+    un = _Units(ONE, d)
+    got = _first_step_errors(binding.ttc_lqr_solve(A, B, Q, R, None, x0, T), ref, un)
+    rec = _first_step_errors(binding.ttc_lqr_solve_tv(*steps, x0), ref, un)
+    _hold((d, cond), got, rec, (4e-6, 1e-5))  # (the floor: what squaring itself shows here, 1.6e-6, and its worst column)
 
 
 @pytest.mark.gpu
