@@ -775,8 +775,9 @@ def main():
                 "rollout": alg_flops_rollout(d, T)}.get(path) \
         or alg_flops_default(d, T, groups, cfg["dtype"] == "bf16", k)
     squares = path == "symplectic" and not k and default_squares(d, T, cfg["dtype"] == "bf16")
-    # the kernels whose products are split (squaring, and the Riccati step by columns)
-    peak = PEAK_SPLIT_PRODUCT_TFLOPS if squares or (d >= 32 and path in ("rollout", "bwd")) else PEAK_FP32_MFMA_TFLOPS
+    # The kernels whose products are split (squaring, and the Riccati step by columns).  Their flop count holds the dense solves too,
+    # about a fifth, which run at the float32 rate: frac is a lower bound of how busy the float16 pipe would have to be.
+    peak = PEAK_SPLIT_PRODUCT_TFLOPS if squares or (d >= 32 and path in ("rollout", "bwd", "tv")) else PEAK_FP32_MFMA_TFLOPS
     achieved = flops_pp * n / avg_kernel_s / 1e12
     steps_in = T if path == "tv" else 1          # every step has its own matrices on the tv path
     in_bytes = n * (steps_in * (2 * d * d + d * m + m * m) + d) * esize + (n * m * 4 if path == "bwd" else 0)

@@ -22,7 +22,9 @@
  * is about to pass the limit is ended early, and a problem whose pair has passed it is solved instead
  * by the recursion of Prop. 3.1 in its printed form (one positive definite solve per step, as
  * ttc_lqr_solve_tv does), inside the same launch.  The accuracy therefore does not depend on the inputs
- * resembling those the default grouping was measured on; what remains is float32 itself: with state
+ * resembling those the default grouping was measured on, nor on the units that states and controls
+ * come in (at d >= 32 products run in units of the problem's own where those are far apart); what
+ * remains is float32 itself: with state
  * costs some 1e4 times the control costs P0 is a small difference of large terms and every float32
  * evaluation of the recursion loses digits in proportion.
  *
@@ -34,8 +36,9 @@
  *     the HIP stream passed as `hip_stream` (a hipStream_t cast to void*; NULL = default stream).
  *   - Q, R and Q_T are read as their symmetric parts (M + M^T)/2.  R must be positive definite and
  *     A invertible (the paper's parameterisation A = I + ... guarantees it, Sec. 4).
- *   - Inputs may be float32 or bfloat16 (in_dtype); every on-chip quantity and every output is
- *     float32 (App. C "Mixed Precision").
+ *   - Inputs may be float32 or bfloat16 (in_dtype); outputs are float32, and so is every on-chip
+ *     quantity (App. C "Mixed Precision") except operands of products at d >= 32 in the recursion and
+ *     in squaring, which are pairs of float16 terms (23 significant bits; sums are float32).
  *   - Supported shapes: d = m in {16, 32, 64, 128}, T >= 1.  Anything else returns
  *     TTC_ERR_UNSUPPORTED and launches nothing.  Pointers of float32 inputs/outputs must be 16-byte
  *     aligned (8-byte for bfloat16 inputs) and strides multiples of 4 elements, else

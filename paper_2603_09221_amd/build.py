@@ -48,8 +48,9 @@ UNITS = [("ttc_api.hip", None),
 # d = 128, T = 16, 8192 problems 11.6 ms against 14.9, d = 64, T = 8, 16384 problems 2.55 against 2.73; with products in float32,
 # roll-out d = 128, T = 8, 1024 problems 2.75 ms against 3.04; flagged doubling d = 128, T = 16 501k problems/s against 488k.
 _ONE_ROW_BLOCK = "-DTTC_ROW_BLOCKS(D)=((D)==%d?1:((D)>=32?2:1))"
-# The backward kernel at d = 64 takes 188 registers by itself; held to the 168 of three wavefronts a SIMD it spills 20 of them and
-# is still the faster (T = 8, 8192 problems, time-invariant 2.26 ms against 2.88).
+# The backward kernel at d = 64 takes more registers by itself; held to the 168 of three wavefronts a SIMD it spills 14 of them (7 with
+# bfloat16 inputs) and is still the faster (T = 8, 8192 problems, time-invariant 2.26 ms against 2.88).  At d = 128 two column tiles a
+# wavefront leave one wavefront a SIMD, which waits for what it spills (512 problems 1.35 ms against 1.05).
 _THREE_WAVES = "-DTTC_COLS_WAVES(D)=3"
 UNIT_FLAGS = {("k_backward.hip", 64): [_ONE_ROW_BLOCK % 64, _THREE_WAVES],
               ("k_backward.hip", 128): [_ONE_ROW_BLOCK % 128],

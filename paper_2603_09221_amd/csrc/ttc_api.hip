@@ -140,14 +140,15 @@ constexpr float SQUARING_QT_LIMIT_F32 = 64.f, SQUARING_QT_LIMIT_BF16 = 4096.f;
 // Q_T "is Q" when it is absent or the very same array: then P_T = Q = f(0) and a recursion may start at 0
 static bool qt_is_q(const ttc_lqr_problem_t* q) { return !q->QT || (q->QT == q->Q && q->sQT == q->sQ); }
 // Default path, d >= 32: whether the T equal factors are composed by squaring (squaring_kernel) or one after the other
-// (solve_kernel).  Costs in hundredths of a squaring, fitted to both kernels at d = 32, 64, 128 and T = 8..64: a squaring
-// 100, an application of a power to P 70, A and G of the last square 35 (not needed when P is still 0), 10 more for the
-// set-up (A is factored for its report); a factor of the sequential product 40, with bfloat16 inputs (longer groups) 37.
-// Measured, sequential / squaring, ms: d = 64, 8192 problems, T = 8 2.14 / 1.65, 12 2.85 / 2.05, 15 3.42 / 2.50, 16 4.30 / 2.02,
-// 64 15.4 / 2.78; d = 128, 2048 problems, T = 8 3.70 / 3.33, 12 4.95 / 4.19, 15 5.96 / 5.27, 16 6.99 / 4.12, 32 11.8 / 4.93;
-// bfloat16 inputs T = 12 4.66 / 4.15, 16 5.92 / 4.10; left to the product: T = 9, an application of a power besides the squarings
-// of T = 8 (an earlier build 2.26 / 2.34 and 3.95 / 4.61).  The number of problems does not move the line: one problem alone
-// d = 64, T = 8 169 / 136 us, d = 128, T = 12 628 / 510 us, with bfloat16 inputs 594 / 511 us.
+// (solve_kernel).  Costs in hundredths of a squaring: a squaring 100, an application of a power to P 70, A and G of the last square 35
+// (not needed when P is still 0), 10 more for the set-up (A is factored for its report); a factor of the sequential product 40, with
+// bfloat16 inputs (longer groups) 37.  They were fitted when the squaring kernel formed its products in float32; with products of split
+// operands it has become the faster of the two on this side of the line as well, where the product is kept although it takes
+// longer (sequential / squaring, ms: d = 64, 3072 problems, T = 4 0.55 / 0.41, 9 0.88 / 0.58, 11 1.03 / 0.65; d = 128, 512 problems, T = 4
+// 0.64 / 0.48, 9 1.02 / 0.71; bfloat16 inputs d = 64, T = 9 0.79 / 0.58; a Q_T of its own, d = 64, T = 8 0.83 / 0.63, 14 1.25 / 0.72; near
+// equal for T = 2, 3, and for T = 4, 5 with bfloat16 inputs at d = 32).  Beyond the line, the same: d = 64, T = 8 0.83 / 0.49, 12 1.08 / 0.58,
+// 16 1.53 / 0.58; d = 128, T = 8 0.96 / 0.59, 16 1.82 / 0.69; d = 32, 8192 problems, T = 8 0.41 / 0.28, 16 0.76 / 0.33.
+// The number of problems does not matter: one problem alone d = 64, T = 8 166 / 96 us, d = 128, T = 12 626 / 326 us.
 static bool use_squaring(const ttc_lqr_problem_t* q) {
   if (q->d < 32 || (q->flags & (TTC_FLAG_DOUBLING | TTC_FLAG_PURE_SYMPLECTIC)) || q->rebase_every != 0) return false;
   const bool from_zero = qt_is_q(q);
@@ -496,10 +497,10 @@ size_t ttc_lqr_tv_scan_workspace_bytes(const ttc_lqr_tv_problem_t* q) {
   return (size_t)q->n * (size_t)q->T * 3 * (size_t)q->d * (size_t)q->d * sizeof(float);
 }
 
-// Launch shapes of the tree kernels: a round with `items` independent items runs one item per workgroup, except, at
-// d = 16 when there are at least fourteen items per compute unit, the elements of the steps and the down-sweep: from there
-// on the kernels that take four items per wavefront are faster (the compositions run from register to register and are not) (measured on 256 compute units: 16.8 against 17.7 us at 4096 items, 41 against 50 us at 16384;
-// with 2048 items the one-item kernels finish the round sooner, 13 against 15.5).
+// Launch shapes of the tree kernels.  A round with `items` independent items runs one item per workgroup; compositions always do.  At
+// d = 16, from fourteen items per compute unit on, the elements of the steps and the down-sweep take four items per wavefront.  Kernel
+// times on 256 compute units, one item against four, us: down-sweep 8.5 / 9.8 at 2048 items, 14.1 / 10.6 at 4096; elements 10.5 / 14.7 at
+// 2048, 12.8 / 15.2 at 4096, 19.4 / 18.8 at 8192 (their line would be at thirty a compute unit; between, 2 us of a call are lost).
 struct ScanPlan {
   long long gb;   // resident workgroups of the one-item kernels
   long long gb4;  // of the four-item kernels (d = 16)

@@ -1,15 +1,17 @@
 // Float32 products on the float16 matrix cores.
 //
-// v_mfma_f32_16x16x4_f32 takes 32 cycles for 2048 multiply-adds, v_mfma_f32_16x16x32_f16 takes 16 for 8192 (measured 32.0 and
+// v_mfma_f32_16x16x4_f32 takes 32 cycles for 1024 multiply-adds, v_mfma_f32_16x16x32_f16 takes 16 for 8192 (measured 32.0 and
 // 17.0, dependent or not).  A float32 operand is split into two float16 terms, x s = h + l with h = f16(x s) and
 // l = f16(x s - h), and a product is l h' + h l' + h h': 3 instructions of 16 cycles where 8 of 32 stood.  h carries 11
-// significant bits and l, signed, 11 more, so a term is off by 2^-23 of x at most and l l' is left out at 2^-24; against that the
-// matrix core adds 32 products before it rounds, where the float32 instruction rounds after every one.  Measured against float64
+// significant bits and l, signed, 11 more: 23 with the sign of l, of float32's 24, so an operand is off by 2^-23 of x at most, and l l' is
+// left out, 2^-22 of the product at most and 2^-24 as a rule.  Against that the matrix core rounds less often than after every product, as
+// the float32 instruction does.  Measured against float64
 // (rms of the error over the rms of the product, normal operands): K = 32 0.88e-7 (float32 instruction 1.03e-7), K = 64 1.07e-7
 // (1.45e-7), K = 128 1.38e-7 (2.02e-7): the split is the more accurate of the two.
 //
 // s is a power of two, so that scaling is exact: the largest entry of the columns a wavefront owns goes to [2^14, 2^15).  What is
-// 2^15 times smaller than that begins to lose bits of l, which by then are 2^-40 of the largest entry.
+// 2^15 times smaller than that begins to lose bits of l, which by then are 2^-40 of the largest entry: operands have to be written in
+// units in which entries that matter are not much smaller (ttc_columns.hpp and ttc_squaring.hpp see to it).
 #pragma once
 #include "ttc_device.hpp"
 
