@@ -18,6 +18,7 @@
  * composed by squaring (the algebra described at TTC_FLAG_DOUBLING; rebase_every must be 0): more accurate on
  * ordinary problems, and watched by a guard of its own on max |I + G_e H_e|.  What it cannot do is solved by a second launch
  * behind it: by the recursion as below, or (stage costs that are not semidefinite, breakdowns) by the product.
+ * At d = 16 they are composed by squaring at every horizon, in a kernel that does by itself what squaring cannot do.
  * A growth guard watches max |Y1| inside every group (Y1 starts a group as the identity): a group that
  * is about to pass the limit is ended early, and a problem whose pair has passed it is solved instead
  * by the recursion of Prop. 3.1 in its printed form (one positive definite solve per step, as
@@ -125,8 +126,8 @@ size_t ttc_lqr_workspace_bytes(const ttc_lqr_problem_t *problem, int for_rollout
 ttc_status_t ttc_lqr_solve(const ttc_lqr_problem_t *problem, const ttc_lqr_solution_t *solution,
                            void *workspace, size_t workspace_bytes, void *hip_stream);
 
-/* 1 if ttc_lqr_solve would compose this problem's factors by squaring (see the file header; TTC_FLAG_DOUBLING not
- * meant), 0 if not or if the problem is not supported.  Looks at d, m, T, in_dtype, flags, rebase_every and at whether
+/* 1 if ttc_lqr_solve would compose this problem's factors by squaring at d >= 32 (see the file header; TTC_FLAG_DOUBLING not
+ * meant), 0 if not or if the problem is not supported; 0 at d = 16, whose one kernel is not chosen by the horizon.  Looks at d, m, T, in_dtype, flags, rebase_every and at whether
  * Q_T is Q; needs no device. */
 int ttc_lqr_solve_squares(const ttc_lqr_problem_t *problem);
 

@@ -214,7 +214,7 @@ def ttc_lqr_workspace_bytes(problem: Problem, for_rollout: bool = False) -> int:
 
 
 def ttc_lqr_solve_squares(problem: Problem) -> bool:
-    """Whether ttc_lqr_solve composes this problem's factors by squaring."""
+    """Whether ttc_lqr_solve composes this problem's factors by squaring (d >= 32; at d = 16 the query says no, whatever runs)."""
     return bool(load().ttc_lqr_solve_squares(ctypes.byref(problem)))
 
 

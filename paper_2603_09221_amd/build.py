@@ -36,6 +36,7 @@ UNITS = [("ttc_api.hip", None),
          ("k_scan.hip", (16, 32, 64, 128)),
          ("k_backward.hip", (16, 32, 64, 128)),
          ("k_small.hip", None),
+         ("k_squaring16.hip", None),
          ("k_tv_small.hip", None),
          ("k_cxt.hip", None),
          ("k_cxt_bwd.hip", None),

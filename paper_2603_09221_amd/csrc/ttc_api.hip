@@ -62,7 +62,7 @@ static void* scratch_for_current_device() {
 // (registers and LDS decide it); the table is the fallback when no device can be asked.
 enum Kind { KIND_SOLVE = 0, KIND_DOUBLING = 1, KIND_ROLLOUT = 2, KIND_SOLVE_QUAD = 3, KIND_SOLVE_TV = 4, KIND_TV_QUAD = 5,
             KIND_ROLLOUT_TV = 6, KIND_CXT = 7, KIND_SCAN = 8, KIND_BACKWARD = 9, KIND_TV_ONE = 10, KIND_SQUARING = 11,
-            KIND_COUNT = 12 };
+            KIND_SQUARING_QUAD = 12, KIND_SQUARING_ONE = 13, KIND_COUNT = 14 };
 static int dindex(int d) { return d == 16 ? 0 : d == 32 ? 1 : d == 64 ? 2 : 3; }
 template <int D>
 static int occupancy_of(Kind kind, bool bf16) {
@@ -82,6 +82,8 @@ static int occupancy_of(Kind kind, bool bf16) {
     case KIND_SOLVE_QUAD: return occupancy_small(bf16);  // the d = 16 kernels
     case KIND_TV_QUAD: return occupancy_tv_small(bf16, 4);
     case KIND_TV_ONE: return occupancy_tv_small(bf16, 1);
+    case KIND_SQUARING_QUAD: return occupancy_squaring16(bf16, 4);
+    case KIND_SQUARING_ONE: return occupancy_squaring16(bf16, 1);
     case KIND_CXT: return occupancy_cxt(bf16);
     default: return 0;
   }
@@ -104,7 +106,8 @@ static int blocks_per_cu(Kind kind, int d, bool bf16) {
     if (nb <= 0) {
       static const int table[KIND_COUNT][4] = {{20, 8, 2, 1}, {16, 8, 2, 1}, {12, 4, 2, 1}, {8, 8, 2, 1}, {20, 8, 2, 1},
                                                {8, 8, 2, 1},  {12, 4, 2, 1}, {8, 8, 2, 1},  {16, 8, 2, 1},
-                                               {12, 4, 2, 1}, {16, 8, 2, 1}, {16, 8, 2, 1}};
+                                               {12, 4, 2, 1}, {16, 8, 2, 1}, {16, 8, 2, 1},
+                                               {8, 8, 2, 1},  {16, 8, 2, 1}};
       nb = table[kind][dindex(d)];
     }
     c.value = nb > 32 ? 32 : nb;
@@ -124,7 +127,8 @@ constexpr float GROWTH_LIMIT_BF16 = 16384.f;
 
 // d = 16: large batches go four problems to a wavefront (more throughput per instruction issued), small ones
 // one problem to a wavefront (more wavefronts in flight, lower latency).  Crossover measured on MI355X, in
-// problems per compute unit: 12 for the symplectic kernel (T = 8), 12 for the Riccati kernel (T = 64, one / four problems
+// problems per compute unit: 12 for the symplectic kernel (T = 8; by squaring T = 31 41 us at 3071 problems, one to a wavefront, and 41 at
+// 4096, four), 12 for the Riccati kernel (T = 64, one / four problems
 // per wavefront: 2048 problems 209 / 270 us, 3072: 307 / 294, 4096: 405 / 332, 6143: 601 / 529).
 constexpr long long QUAD_MIN_PER_CU_SOLVE = 12;
 constexpr long long QUAD_MIN_PER_CU_TV = 12;
@@ -157,6 +161,12 @@ static bool use_squaring(const ttc_lqr_problem_t* q) {
   const int squarings = 31 - __builtin_clz(m), applications = __builtin_popcount(m) - (from_zero ? 1 : 0);
   const long long cost = 100 * squarings + 70 * applications + (applications ? 35 : 0) + 10;
   return 100 * cost <= 98LL * (q->in_dtype == TTC_BF16 ? 37 : 40) * q->T;
+}
+// d = 16: squaring, whatever the horizon, unless the caller asks for the product, whose kernel is the slower at every one (product /
+// squaring, us a call, float32: 16384 problems T = 1 61 / 42, 3 78 / 58, 8 140 / 69, 16 242 / 80, 33 409 / 105, 262144 problems T = 8 1897 /
+// 1006; 1000 problems T = 19 57 / 26, 31 84 / 26, where a call's host time of 26 is all that is left).
+static bool use_squaring16(const ttc_lqr_problem_t* q) {
+  return q->d == 16 && !(q->flags & (TTC_FLAG_DOUBLING | TTC_FLAG_PURE_SYMPLECTIC)) && q->rebase_every == 0;
 }
 static bool use_quad_kernel_tv(const ttc_lqr_tv_problem_t* q) {
   return q->d == 16 && q->n >= QUAD_MIN_PER_CU_TV * cu_count();
@@ -351,6 +361,13 @@ ttc_status_t ttc_lqr_solve(const ttc_lqr_problem_t* problem, const ttc_lqr_solut
     const long long blocks = gs < gb ? gs : gb;
     e = ttc::run_squaring(da, problem->d, bf16, dim3((unsigned)(problem->n < blocks ? problem->n : blocks)), s);
     if (e == hipSuccess) e = ttc::run_solve_handed(a, problem->d, bf16, grid, s);  // the problems it gave up, usually none
+  } else if (ttc::use_squaring16(problem)) {
+    ttc::DoublingArgs da;
+    da.s = a;
+    da.m = ttc::qt_is_q(problem) ? problem->T : problem->T - 1;
+    da.p_from_qt = ttc::qt_is_q(problem) ? 0 : 1;
+    const long long gs = ttc::grid_blocks(quad ? ttc::KIND_SQUARING_QUAD : ttc::KIND_SQUARING_ONE, 16, bf16);
+    e = ttc::launch_squaring16(da, bf16, quad ? 4 : 1, dim3((unsigned)(items < gs ? items : gs)), s);
   } else if (quad) {
     e = ttc::launch_small(a, bf16, 4, grid, s);
   } else if (small) {  // a batch that does not fill the chip: one problem to a wavefront

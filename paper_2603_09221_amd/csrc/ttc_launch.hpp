@@ -36,6 +36,8 @@ template <int D> int occupancy_backward(bool bf16);
 // d = 16 only; ppw = problems per wavefront (1 or 4)
 hipError_t launch_small(const SolveArgs& a, bool bf16, int ppw, dim3 grid, hipStream_t st);
 int occupancy_small(bool bf16);
+hipError_t launch_squaring16(const DoublingArgs& a, bool bf16, int ppw, dim3 grid, hipStream_t st);
+int occupancy_squaring16(bool bf16, int ppw);
 hipError_t launch_tv_small(const TvArgs& a, bool bf16, int ppw, dim3 grid, hipStream_t st);
 int occupancy_tv_small(bool bf16, int ppw);
 hipError_t launch_cxt(const CxtArgs& a, bool bf16, int ppw, dim3 grid, hipStream_t st);

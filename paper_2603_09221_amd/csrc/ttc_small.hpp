@@ -120,9 +120,9 @@ __device__ __forceinline__ int solve_rows16(float* Wq, int lane) {
 // step is the chain multiplier -> column j + 1 -> its pivot's broadcast -> reciprocal -> next multiplier, some 65 cycles,
 // beside the issue of 15 multiply-adds (4.4 cycles each): column j + 1 is updated first and its pivot's reciprocal is
 // started under the other columns' updates, so that the larger of the two counts and not their sum.
-// Returns, per lane, whether its row's pivot was not positive and finite.
+// Returns, per lane, whether its row's pivot was not above piv_min and finite.
 template <bool NEGATE = false>
-__device__ __forceinline__ int invert_regs16(float (&a)[16]) {
+__device__ __forceinline__ int invert_regs16(float (&a)[16], float piv_min = 0.f) {
   float mypiv = 1.f;
   float pv = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, a[0]), 0x150, 0xF, 0xF, true));
   float rc = __builtin_amdgcn_rcpf(pv);
@@ -172,7 +172,7 @@ __device__ __forceinline__ int invert_regs16(float (&a)[16]) {
   const float s = NEGATE ? -__builtin_amdgcn_rcpf(mypiv) : __builtin_amdgcn_rcpf(mypiv);
 #pragma unroll
   for (int k = 0; k < 16; ++k) a[k] *= s;
-  return !(mypiv > 0.f && mypiv < __builtin_inff());
+  return !(mypiv > piv_min && mypiv < __builtin_inff());
 }
 
 // x of the sixteen lanes of group J (lane / 16), in every group

@@ -310,22 +310,87 @@ __device__ __forceinline__ int riccati_step16(float (*Wm)[16 * Cfg<16>::PITCH], 
   return bad;
 }
 
+// The outputs of the wavefront's problems from the last step taken (W_0 = -K_0 and P_0): only problems with keep[q] are written, NaN
+// where info[q] is not 0, which is reported as info_base + info[q].
+template <typename TIn, int PPW>
+__device__ __forceinline__ void emit_quad16(float (*Wm)[16 * Cfg<16>::PITCH], const SolveArgs& p, const long long (&prob)[PPW],
+                                            const bool (&keep)[PPW], const TIn* const (&Qp)[PPW], floatx4 (&P)[PPW],
+                                            const floatx4 (&Wk)[PPW], const int (&info)[PPW], int info_base, int lane) {
+  constexpr int D = 16;
+  using C = Cfg<D>;
+  const int i = lane & 15, g = lane >> 4, gq = g & (PPW - 1);
+  // No cost on x_0.  Lane (i, g) takes row i of its problem's K_0 and P_0 for u_0 = K_0 x_0 and
+  // value = x_0^T P_0 x_0; the matrices leave as one 16-byte piece per lane and problem
+  long long pg = prob[0];
+  int myinfo = info[0];
+  bool mykeep = keep[0];
+#pragma unroll
+  for (int q = 1; q < PPW; ++q) {
+    pg = gq == q ? prob[q] : pg;
+    myinfo = gq == q ? info[q] : myinfo;
+    mykeep = gq == q ? keep[q] : mykeep;
+  }
+  const float nanv = __builtin_nanf("");
+  const float x0_m = ld1<TIn>(reinterpret_cast<const TIn*>(p.x0), pg * p.sx0 + i);
+#pragma unroll
+  for (int q = 0; q < PPW; ++q) {
+    if (p.flags & TTC_FLAG_STAGE_COST_AT_X0)
+      P[q] += 0.5f * (load_acc16<TIn>(Qp[q], i, g) + load_accT16<TIn>(Qp[q], i, g));
+#pragma unroll
+    for (int v = 0; v < 4; ++v) Wm[q][(4 * g + v) * C::PITCH + i] = -Wk[q][v];          // K_0, row-major
+    *reinterpret_cast<floatx4*>(Wm[q] + D + i * C::PITCH + 4 * g) = P[q];                // P_0
+  }
+  if (g == gq) Wm[gq][i * C::PITCH + 2 * D] = x0_m;  // the first of the four skew columns
+  wave_lds_sync();
+  float u = 0.f, pw = 0.f;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const floatx4 kr = *reinterpret_cast<const floatx4*>(Wm[gq] + i * C::PITCH + 4 * c);
+    const floatx4 pr = *reinterpret_cast<const floatx4*>(Wm[gq] + D + i * C::PITCH + 4 * c);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const float xr = Wm[gq][(4 * c + v) * C::PITCH + 2 * D];
+      u = __builtin_fmaf(kr[v], xr, u);
+      pw = __builtin_fmaf(pr[v], xr, pw);
+    }
+  }
+  const float val = sum16(x0_m * pw);
+  if (mykeep && (PPW == 4 || g == 0)) {
+    p.u0[pg * D + i] = myinfo ? nanv : u;
+    if (i == 0) {
+      if (p.value) p.value[pg] = myinfo ? nanv : val;
+      if (p.info) p.info[pg] = myinfo ? info_base + myinfo : 0;
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < PPW; ++q) {
+    if (!keep[q]) continue;  // uniform over the wavefront
+    const floatx4 nan4 = floatx4{nanv, nanv, nanv, nanv};
+    const float* row = Wm[q] + (lane >> 2) * C::PITCH + 4 * (lane & 3);
+    if (p.K0)
+      *reinterpret_cast<floatx4*>(p.K0 + prob[q] * (long)D * D + 4 * lane) =
+          info[q] ? nan4 : *reinterpret_cast<const floatx4*>(row);
+    if (p.P0)
+      *reinterpret_cast<floatx4*>(p.P0 + prob[q] * (long)D * D + 4 * lane) =
+          info[q] ? nan4 : *reinterpret_cast<const floatx4*>(row + D);
+  }
+  wave_lds_sync();
+}
+
 // The whole backward recursion of the wavefront's PPW problems, from their terminal value matrices (PTp[q], input element
 // type) to the outputs.  Step s of problem q reads A, B, R at Ap[q] + s*tA, ... and the stage cost on the state it starts
 // from at Qp[q] + (s-1)*tQ; zero strides give the time-invariant problem.  Only problems with keep[q] are written;
-// info = info_base + the index (1 = the step taken first) of the step whose solve broke down.  Measured at T = 64, kernel
-// time, against the version that passed every operand through LDS and inverted a row per lane: 16 problems 195 -> 104 us,
-// 1024: 222 -> 127 us, 8192: 1059 -> 546 us.
+// info = info_base + the index (1 = the step taken first) of the step whose solve broke down; returns, uniformly, whether any did.
+// Measured at T = 64, kernel time, against the version that passed every operand through LDS and inverted a row per lane:
+// 16 problems 195 -> 104 us, 1024: 222 -> 127 us, 8192: 1059 -> 546 us.
 template <typename TIn, int PPW>
-__device__ __forceinline__ void riccati_quad(float (*Wm)[16 * Cfg<16>::PITCH], const SolveArgs& p,
+__device__ __forceinline__ bool riccati_quad(float (*Wm)[16 * Cfg<16>::PITCH], const SolveArgs& p,
                                              const long long (&prob)[PPW], const bool (&keep)[PPW], int T,
                                              const TIn* const (&Ap)[PPW], const TIn* const (&Bp)[PPW],
                                              const TIn* const (&Qp)[PPW], const TIn* const (&Rp)[PPW],
                                              const TIn* const (&PTp)[PPW], long long tA, long long tB, long long tQ,
                                              long long tR, int info_base, int tid) {
-  constexpr int D = 16;
-  using C = Cfg<D>;
-  const int lane = tid & 63, i = lane & 15, g = lane >> 4, gq = g & (PPW - 1);
+  const int lane = tid & 63, i = lane & 15, g = lane >> 4;
   int info[PPW] = {};
   int nsolve = 0;
   auto note = [&](int bad) {
@@ -417,62 +482,11 @@ __device__ __forceinline__ void riccati_quad(float (*Wm)[16 * Cfg<16>::PITCH], c
       step(IntC<1>{}, s - 1);
     }
   }
-  // ---- outputs (no cost on x_0): lane (i, g) takes row i of its problem's K_0 and P_0 for u_0 = K_0 x_0 and
-  // value = x_0^T P_0 x_0; the matrices leave as one 16-byte piece per lane and problem
-  long long pg = prob[0];
-  int myinfo = info[0];
-  bool mykeep = keep[0];
+  emit_quad16<TIn, PPW>(Wm, p, prob, keep, Qp, P, Wk, info, info_base, lane);
+  int any = 0;
 #pragma unroll
-  for (int q = 1; q < PPW; ++q) {
-    pg = gq == q ? prob[q] : pg;
-    myinfo = gq == q ? info[q] : myinfo;
-    mykeep = gq == q ? keep[q] : mykeep;
-  }
-  const float nanv = __builtin_nanf("");
-  const float x0_m = ld1<TIn>(reinterpret_cast<const TIn*>(p.x0), pg * p.sx0 + i);
-#pragma unroll
-  for (int q = 0; q < PPW; ++q) {
-    if (p.flags & TTC_FLAG_STAGE_COST_AT_X0)
-      P[q] += 0.5f * (load_acc16<TIn>(Qp[q], i, g) + load_accT16<TIn>(Qp[q], i, g));
-#pragma unroll
-    for (int v = 0; v < 4; ++v) Wm[q][(4 * g + v) * C::PITCH + i] = -Wk[q][v];          // K_0, row-major
-    *reinterpret_cast<floatx4*>(Wm[q] + D + i * C::PITCH + 4 * g) = P[q];                // P_0
-  }
-  if (g == gq) Wm[gq][i * C::PITCH + 2 * D] = x0_m;  // the first of the four skew columns
-  wave_lds_sync();
-  float u = 0.f, pw = 0.f;
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    const floatx4 kr = *reinterpret_cast<const floatx4*>(Wm[gq] + i * C::PITCH + 4 * c);
-    const floatx4 pr = *reinterpret_cast<const floatx4*>(Wm[gq] + D + i * C::PITCH + 4 * c);
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const float xr = Wm[gq][(4 * c + v) * C::PITCH + 2 * D];
-      u = __builtin_fmaf(kr[v], xr, u);
-      pw = __builtin_fmaf(pr[v], xr, pw);
-    }
-  }
-  const float val = sum16(x0_m * pw);
-  if (mykeep && (PPW == 4 || g == 0)) {
-    p.u0[pg * D + i] = myinfo ? nanv : u;
-    if (i == 0) {
-      if (p.value) p.value[pg] = myinfo ? nanv : val;
-      if (p.info) p.info[pg] = myinfo ? info_base + myinfo : 0;
-    }
-  }
-#pragma unroll
-  for (int q = 0; q < PPW; ++q) {
-    if (!keep[q]) continue;  // uniform over the wavefront
-    const floatx4 nan4 = floatx4{nanv, nanv, nanv, nanv};
-    const float* row = Wm[q] + (lane >> 2) * C::PITCH + 4 * (lane & 3);
-    if (p.K0)
-      *reinterpret_cast<floatx4*>(p.K0 + prob[q] * (long)D * D + 4 * lane) =
-          info[q] ? nan4 : *reinterpret_cast<const floatx4*>(row);
-    if (p.P0)
-      *reinterpret_cast<floatx4*>(p.P0 + prob[q] * (long)D * D + 4 * lane) =
-          info[q] ? nan4 : *reinterpret_cast<const floatx4*>(row + D);
-  }
-  wave_lds_sync();
+  for (int q = 0; q < PPW; ++q) any |= info[q];
+  return any != 0;
 }
 
 template <typename TIn, int PPW>
