@@ -329,7 +329,8 @@ __device__ __forceinline__ void for_each_block(F&& f) {
 // right half of the pair); every wavefront then does its own columns, U = s[p][p]^{-1} s[p][c], s[r][c] -= s[r][p] U,
 // the next block's first, so that its inverse is formed and published under the others' updates: one workgroup barrier
 // per block, no right operand through LDS, and a serial chain of some 1500 cycles per 16 columns (the pivoted panels of
-// lds_solve: about 5000).
+// lds_solve: about 5000).  The wavefront on that chain has priority over the others of its SIMD, of this problem and of others (d = 64:
+// squaring T = 8, 16384 problems 2.40 -> 2.31 ms, roll-out T = 8, 4096 problems 0.986 -> 0.959; at d = 128 no difference).
 // With d <= 32 the explicit inverse alone loses up to a factor of three where control is cheap (the block is most of the
 // matrix); there one step of refinement, U += s[p][p]^{-1} (s[p][c] - s[p][p] U), restores a factor-and-solve's accuracy
 // (REFINE).  From d = 64 on the recursion does not show it (measured against float64, cost ratios 1 to 1e4), but a single
@@ -425,8 +426,10 @@ __device__ __forceinline__ int solve_cols(float* Wp, Cols<D>& s, floatx4 (&f)[D 
         if (next_here) publish(IntC<kn>{}, buf ^ 1);
       } else {
         if (next_here) {
+          __builtin_amdgcn_s_setprio(3);  // the others' updates are not waited for by anyone
           column(x, s, IntC<kn>{}, p);
           publish(IntC<kn>{}, buf ^ 1);
+          __builtin_amdgcn_s_setprio(0);
         }
         rest();
       }
@@ -509,8 +512,10 @@ __device__ __forceinline__ int invert_cols(float* Wp, Cols<D>& s, int w, int lan
       for (int r = 0; r < NT; ++r) x[r] = *reinterpret_cast<const floatx4*>(Wp + (16 * r + i) * C::PITCH + 16 * buf + 4 * g);
       const bool next_here = p + 1 < NT && w == (p + 1) / CT;
       if (next_here) {
+        __builtin_amdgcn_s_setprio(3);
         column(x, IntC<kn>{}, false);
         publish(IntC<kn>{}, buf ^ 1);
+        __builtin_amdgcn_s_setprio(0);
       }
       static_for<0, CT>([&](auto K) {
         constexpr int k = decltype(K)::value;
