@@ -74,7 +74,7 @@ __global__ void __launch_bounds__(64, 4) backward16_kernel(const BackwardArgs ba
     auto step = [&](auto U, int s) {
       constexpr int u = decltype(U)::value;
       floatx4 pn[1];
-      const int bad = riccati_step16<1>(Wm, P, A[u], B[u], [&](int) { return 0.5f * (R0[u] + R1[u]); },
+      const int bad = riccati_step16<1, true>(Wm, P, A[u], B[u], [&](int) { return 0.5f * (R0[u] + R1[u]); },
                                         [&] { fetch_abr(u, s - 2); }, W, pn, S, Si, lane);
       if (__any(bad) && !info) info = T - s;
       if (s >= 1) {

@@ -366,7 +366,7 @@ __device__ __forceinline__ int solve_cols(float* Wp, Cols<D>& s, floatx4 (&f)[D 
       for (int v = 0; v < 4; ++v) o[32 + v * C::PITCH] = -s[0][k][v];
     }
     floatx4 inv = s[0][k];
-    bad |= invert_spread16(inv, lane, piv_min);
+    bad |= invert_spread16(inv, Wp + 16 * buf, C::PITCH, lane, piv_min);
 #pragma unroll
     for (int r = 0; r < NT; ++r) {
       const floatx4 x = r == 0 ? inv : -s[r][k];
@@ -478,7 +478,7 @@ __device__ __forceinline__ int invert_cols(float* Wp, Cols<D>& s, int w, int lan
     for (int r = 1; r < NT; ++r)
 #pragma unroll
       for (int v = 0; v < 4; ++v) o[(16 * r + v) * C::PITCH] = -s[r][k][v];
-    bad |= invert_spread16(s[0][k], lane, piv_min);
+    bad |= invert_spread16(s[0][k], Wp + 16 * buf, C::PITCH, lane, piv_min);
 #pragma unroll
     for (int v = 0; v < 4; ++v) o[v * C::PITCH] = s[0][k][v];
   };

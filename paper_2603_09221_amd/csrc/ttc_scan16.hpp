@@ -107,7 +107,8 @@ struct Composition16 {
   }
   // x <- the inverse of n, without a search for pivots.  False where that is not safe (max |I + G1 H2| above 24, a pivot below 1/4,
   // anything not finite; ttc_squaring.hpp has what these limits rest on).
-  __device__ __forceinline__ bool invert_in_order(floatx4& x, int lane) const {
+  // W: 16 x PITCH floats of LDS.
+  __device__ __forceinline__ bool invert_in_order(floatx4& x, float* W, int lane) const {
     uint32_t big = 0;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
@@ -117,7 +118,7 @@ struct Composition16 {
     const float mu = __uint_as_float(wave_max_u32(big));
     if (!(mu <= 24.f)) return false;
     x = n;
-    return !__any(invert_spread16(x, lane, 0.25f));
+    return !invert_spread16(x, W, Cfg<16>::PITCH, lane, 0.25f);
   }
   // The element, x the inverse of n; into e1.
   __device__ __forceinline__ void finish(const floatx4& x, float* e1, int lane, bool bad) {
@@ -171,7 +172,7 @@ __global__ void __launch_bounds__(64) scan_combine16_kernel(const ScanArgs a) {
     floatx4 x;
     c.load(e1, e1 + (long long)st * 3 * 256, lane);
     bool bad = false;
-    if (__builtin_expect(!c.invert_in_order(x, lane), 0)) {  // with a search for pivots
+    if (__builtin_expect(!c.invert_in_order(x, W, lane), 0)) {  // with a search for pivots
       float* const row = W + i * C::PITCH + 4 * g;
       *reinterpret_cast<floatx4*>(row) = c.n;  // (a row of I + G1 H2)
       set_half_identity<16>(W + 16, lane);

@@ -185,12 +185,13 @@ __device__ __forceinline__ float broadcast_group(float x) {
   return __uint_as_float((J & 1) ? q[1] : q[0]);
 }
 
-// The same inverse of one matrix by the whole wavefront: lane (i, g) holds M[i][4g .. 4g+3] (for a symmetric M its
+// The same inverse of one matrix by the whole wavefront, for results that must not depend on how many problems a wavefront has (invert_blocks16,
+// below, is the faster): lane (i, g) holds M[i][4g .. 4g+3] (for a symmetric M its
 // accumulator layout) and ends with the same entries of the inverse, which is its A operand, so that nothing passes
 // through LDS.  Columns are taken four at a time: the four columns of a group are copied to every group first, where they
 // are kept up to date beside the lane's own four; a column then costs seven multiply-adds instead of fifteen.  Every entry
-// sees the operations of invert_regs16 in the same order.  A pivot that is not above piv_min is reported.
-__device__ __forceinline__ int invert_spread16(floatx4& m, int lane, float piv_min = 0.f) {
+// sees the operations of invert_regs16 in the same order.
+__device__ __forceinline__ int invert_columns16(floatx4& m, int lane) {
   const int g = lane >> 4;
   float a[4] = {m[0], m[1], m[2], m[3]};
   float mypiv = 1.f;
@@ -239,7 +240,114 @@ __device__ __forceinline__ int invert_spread16(floatx4& m, int lane, float piv_m
   });
   const float s = __builtin_amdgcn_rcpf(mypiv);
   m = floatx4{a[0] * s, a[1] * s, a[2] * s, a[3] * s};
-  return !(mypiv > piv_min && mypiv < __builtin_inff());
+  return !(mypiv > 0.f && mypiv < __builtin_inff());
+}
+
+// x of the sixteen lanes of group r (lane / 16) in every group, r = 0..3
+__device__ __forceinline__ void groups_of(float x, float (&e)[4]) {
+  const unsigned u = __float_as_uint(x);
+  const auto h = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  const auto lo = __builtin_amdgcn_permlane16_swap(h[0], h[0], false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(h[1], h[1], false, false);
+  e[0] = __uint_as_float(lo[0]);
+  e[1] = __uint_as_float(lo[1]);
+  e[2] = __uint_as_float(hi[0]);
+  e[3] = __uint_as_float(hi[1]);
+}
+// a where the mask is set, b elsewhere
+__device__ __forceinline__ float bits_select(unsigned mask, float a, float b) {
+  return __uint_as_float((mask & __float_as_uint(a)) | (~mask & __float_as_uint(b)));
+}
+__device__ __forceinline__ float bits_negate(float x) { return __uint_as_float(__float_as_uint(x) ^ 0x80000000u); }
+
+// The inverse of one 16 x 16 matrix by the whole wavefront, in order, in place: m in the accumulator layout (lane (i, g) holds
+// M[4g + v][i]) ends as the inverse in the same layout (for a symmetric M its A operand as well).  Block Gauss-Jordan with four pivot rows
+// at a time, rows 4 k + b, k = 0..3: register m[b], which is the panel of these rows as an operand from the right.  The panel is copied to
+// all four lane groups; there row r of it is e[r], of which only the block's own columns count, and y[r], which starts as the rows with the
+// identity in those columns and ends as the rows times the inverse of the block: elimination in order and back substitution, the pivot
+// row's entries broadcast within 16 lanes as the DPP operand of the multiply-add.  The other rows take their update, rank 4, as one matrix
+// instruction, whose operand from the left is minus the block's columns: z = -M^T, kept beside m in the same layout for one more matrix
+// instruction a block.  (Of a symmetric M they are the panel itself, signs turned where a column has been a pivot; taken from there, 60
+// cycles less, solves at d = 64 with R of condition 1e6 came out twice as far off.)
+//
+// What bounds it is the number of instructions a lone wavefront issues (one in five cycles or so) and the chain of sixteen pivots; a
+// column at a time, every lane group updating its four columns and a copy of the pivots' (390 instructions), took 2018 cycles, this
+// (260) 1600; three wavefronts a SIMD slow each other by 6 % only.  Error against float64,
+// well-conditioned matrices: 1.2e-7 (1.3e-7 before).
+// Returns, uniformly, whether a pivot was not above piv_min and finite.
+__device__ __forceinline__ int invert_blocks16(floatx4& m, floatx4 z, int lane, float piv_min) {
+  const int i = lane & 15, g = lane >> 4;
+  unsigned mask = (i & 3) == 0 ? ~0u : 0u;  // the columns of the pivot block, lanes 4 k + b
+  float unit[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) unit[r] = (i >> 2) == r ? 1.f : 0.f;
+  const float own = (i >> 2) == g ? -1.f : 0.f;
+  float kept = 1.f;  // the sixteen pivots: pivot 4 k + b in the lanes 4 b .. 4 b + 3 of group k
+  static_for<0, 4>([&](auto BB) {
+    constexpr int b = decltype(BB)::value;
+    float e[4], y[4], rc;
+    const float a = z[b];  // minus the block's columns
+    groups_of(m[b], e);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) y[r] = bits_select(mask, unit[r], e[r]);
+    float(&E)[4] = e, (&Y)[4] = y;  // (named here, as an asm operand alone does not capture)
+    float& K = kept;
+    // One block, so that the wait states are in our hands: two instructions between a vector write of a register and its DPP read, one
+    // between a reciprocal and its use.  -e[r] as a DPP operand: minus the entry of row r in the pivot's column.
+#define TTC_ALL " row_mask:0xf bank_mask:0xf\n\t"
+#define TTC_RCP(p) "v_rcp_f32_dpp %[rc], %[e" #p "] row_newbcast:%[c" #p "]" TTC_ALL \
+                   "v_mov_b32_dpp %[k], %[e" #p "] row_newbcast:%[c" #p "] row_mask:%[r" #p "] bank_mask:%[bm]\n\t"
+#define TTC_MUL(v, p) "v_mul_f32 %[" #v #p "], %[" #v #p "], %[rc]\n\t"
+#define TTC_SUB(v, r, p) "v_fmac_f32_dpp %[" #v #r "], -%[e" #r "], %[" #v #p "] row_newbcast:%[c" #p "]" TTC_ALL
+#define TTC_ROW(r, m) "v_mov_b32_dpp %[y0], %[y" #r "] quad_perm:[0,1,2,3] row_mask:" #m " bank_mask:0xf\n\t"
+    asm volatile(
+        "s_nop 1\n\t" TTC_RCP(0) TTC_MUL(e, 0) TTC_MUL(y, 0)
+        TTC_SUB(y, 1, 0) TTC_SUB(e, 1, 0) TTC_SUB(y, 2, 0) TTC_SUB(e, 2, 0) TTC_RCP(1) TTC_SUB(y, 3, 0) TTC_SUB(e, 3, 0)
+        TTC_MUL(e, 1) TTC_MUL(y, 1) TTC_SUB(y, 2, 1) TTC_SUB(e, 2, 1) TTC_SUB(y, 3, 1) TTC_SUB(e, 3, 1) TTC_RCP(2)
+        TTC_MUL(e, 2) TTC_MUL(y, 2) TTC_SUB(y, 3, 2) TTC_SUB(e, 3, 2) "s_nop 1\n\t" TTC_RCP(3)
+        TTC_MUL(y, 3) TTC_SUB(y, 2, 3) TTC_SUB(y, 1, 3) TTC_SUB(y, 0, 3) TTC_SUB(y, 1, 2) TTC_SUB(y, 0, 2) TTC_SUB(y, 0, 1)
+        TTC_ROW(1, 0x2) TTC_ROW(2, 0x4) TTC_ROW(3, 0x8) "s_nop 1"
+        : [e0] "+v"(E[0]), [e1] "+v"(E[1]), [e2] "+v"(E[2]), [e3] "+v"(E[3]), [y0] "+v"(Y[0]), [y1] "+v"(Y[1]), [y2] "+v"(Y[2]),
+          [y3] "+v"(Y[3]), [k] "+v"(K), [rc] "=&v"(rc)
+        : [c0] "n"(b), [c1] "n"(4 + b), [c2] "n"(8 + b), [c3] "n"(12 + b), [r0] "n"(1), [r1] "n"(2), [r2] "n"(4), [r3] "n"(8),
+          [bm] "n"(1 << b));
+#undef TTC_ALL
+#undef TTC_RCP
+#undef TTC_MUL
+#undef TTC_SUB
+#undef TTC_ROW
+    const float t = y[0];  // the panel times the inverse of the block, that inverse in the block's columns: row k in group k
+    floatx4 rest;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) rest[v] = bits_select(mask, 0.f, m[v]);
+    m = __builtin_amdgcn_mfma_f32_16x16x4f32(a, t, rest, 0, 0, 0);
+    m[b] = t;
+    if constexpr (b < 3) {
+      const float c = bits_select(mask, own, bits_negate(a));
+#pragma unroll
+      for (int v = 0; v < 4; ++v) rest[v] = v > b ? bits_select(mask, 0.f, z[v]) : z[v];
+      z = __builtin_amdgcn_mfma_f32_16x16x4f32(t, c, rest, 0, 0, 0);
+    }
+    mask = (unsigned)__builtin_amdgcn_update_dpp(0, (int)mask, 0x93, 0xF, 0xF, false);  // quad_perm [3,0,1,2]
+  });
+  return __any(!(kept > piv_min && kept < __builtin_inff())) ? 1 : 0;
+}
+// of a symmetric matrix (symmetric up to rounding; where what follows is refined, as an R of condition 1e6 at d = 64 is 1.6 times as far
+// off as with its own transpose)
+__device__ __forceinline__ int invert_spread16(floatx4& m, int lane, float piv_min = 0.f) {
+  return invert_blocks16(m, -m, lane, piv_min);
+}
+// of any matrix whose elimination in order is safe; T: 16 rows of `pitch` floats (a multiple of four) of LDS that are this wavefront's own,
+// the last read of which it waits for
+__device__ __forceinline__ int invert_spread16(floatx4& m, float* T, int pitch, int lane, float piv_min) {
+  const int i = lane & 15, g = lane >> 4;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) T[(4 * g + v) * pitch + i] = -m[v];
+  wave_lds_sync();
+  const floatx4 z = *reinterpret_cast<const floatx4*>(T + i * pitch + 4 * g);
+  const int bad = invert_blocks16(m, z, lane, piv_min);
+  wave_lds_sync();
+  return bad;
 }
 
 // The same in place in LDS: the left halves of Wm[q] (row r at Wq + r*PITCH), by a workgroup of one wavefront.  The

@@ -57,10 +57,10 @@ __device__ __forceinline__ void quad_of_rows(const float (&a)[16], floatx4 (&x)[
 
 // The inverses of the wavefront's matrices, elimination in order: lane (i, g) holds M[i][4g .. 4g+3] and ends with the same entries of
 // the inverse.  Returns, uniformly, whether a pivot of any of them was not above piv_min and finite.
-template <int PPW>
-__device__ __forceinline__ bool invert16(floatx4 (&x)[PPW], int lane, float piv_min) {
+template <int PPW, bool SYMMETRIC>
+__device__ __forceinline__ bool invert16(floatx4 (&x)[PPW], float (*Wm)[16 * Cfg<16>::PITCH], int lane, float piv_min) {
   if constexpr (PPW == 1) {
-    return __any(invert_spread16(x[0], lane, piv_min));
+    return (SYMMETRIC ? invert_spread16(x[0], lane, piv_min) : invert_spread16(x[0], Wm[0], Cfg<16>::PITCH, lane, piv_min)) != 0;
   } else {
     float a[16];
     rows_of_quad(x, a);
@@ -205,7 +205,7 @@ __device__ __forceinline__ int square_quad16(const DoublingArgs& da, long long q
     }
 #pragma unroll
     for (int q = 0; q < PPW; ++q) x[q] = R[q];
-    if (invert16<PPW>(x, lane, 0.f)) return 2;
+    if (invert16<PPW, true>(x, Wm, lane, 0.f)) return 2;
     if (da.p_from_qt) {  // a terminal cost that will not pass the guard
       float qt = 0.f, qs = 0.f;
 #pragma unroll
@@ -287,7 +287,7 @@ __device__ __forceinline__ int square_quad16(const DoublingArgs& da, long long q
       up_prev = up;
     }
     bool pivoted = mu > SQUARE16_IN_ORDER;
-    if (!pivoted && invert16<PPW>(n, lane, early ? PIVOT16_FIRST : PIVOT16_LATE)) {
+    if (!pivoted && invert16<PPW, false>(n, Wm, lane, early ? PIVOT16_FIRST : PIVOT16_LATE)) {
       if (early) return 2;
       if (negative_diagonal16<PPW>(H, i, g)) return 2;
       form();
@@ -350,7 +350,7 @@ __device__ __forceinline__ int square_quad16(const DoublingArgs& da, long long q
       A[q] = load_acc16<TIn>(Ap[q], i, g);
       B[q] = load_acc16<TIn>(Bp[q], i, g);
     }
-    const int bad = riccati_step16<PPW>(Wm, P, A, B,
+    const int bad = riccati_step16<PPW, true>(Wm, P, A, B,
                                         [&](int q) { return 0.5f * (load_acc16<TIn>(Rp[q], i, g) + load_accT16<TIn>(Rp[q], i, g)); },
                                         [] {}, Wk, pn, S, Si, lane);
     if (__any(bad)) return 2;

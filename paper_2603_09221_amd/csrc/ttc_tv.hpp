@@ -252,7 +252,8 @@ __device__ __forceinline__ void symmetrise16(floatx4 (&P)[PPW], int i, int g) {
 // matrices and Rl(q) returns (the symmetric part of) R, asked for when it is needed; next() is called when A, B and R are
 // no longer needed; on exit Wk = S^{-1} B^T P A = -K_s and
 // pn = A^T P A - (B^T P A)^T Wk.  Wm: 16 x PITCH floats of LDS per problem.  Returns, per lane, a breakdown of the inverse.
-template <int PPW, typename RLoad, typename Next>
+// BLOCKS (one problem to a wavefront): the inverse by blocks of four pivots, the faster; without it by columns, every rounding as with four.
+template <int PPW, bool BLOCKS = false, typename RLoad, typename Next>
 __device__ __forceinline__ int riccati_step16(float (*Wm)[16 * Cfg<16>::PITCH], const floatx4 (&P)[PPW],
                                               const floatx4 (&A)[PPW], const floatx4 (&B)[PPW], RLoad&& Rl, Next&& next,
                                               floatx4 (&Wk)[PPW], floatx4 (&pn)[PPW], floatx4 (&S)[PPW],
@@ -277,7 +278,7 @@ __device__ __forceinline__ int riccati_step16(float (*Wm)[16 * Cfg<16>::PITCH], 
     mul16<PPW>(pn, A, PA);  // A^T P A
     next();
     Si[0] = S[0];
-    bad = invert_spread16(Si[0], lane);
+    bad = BLOCKS ? invert_spread16(Si[0], lane) : invert_columns16(Si[0], lane);
   } else {
 #pragma unroll
     for (int q = 0; q < PPW; ++q) *reinterpret_cast<floatx4*>(Wm[q] + i * C::PITCH + 4 * g) = S[q];  // S^T, row-major
