@@ -93,6 +93,53 @@ static constexpr float PIVOT_MIN = 0.25f, PIVOT_MIN_A = 0.015625f, IN_ORDER_MAX 
 // The guard's limit after the first squaring, and the mu at which the coming square of e is expected and not formed.
 static constexpr float LATE_LIMIT = 64.f, GROWTH_STOP = 16.f;
 
+// Whether A is certainly not singular, without a factorisation, so that none is needed for the report of a singular one: with its columns
+// divided by their diagonal entries it is a matrix of signs and X, ||X||_2 < 1, seen from the Frobenius norm of X, or, which is less by up
+// to the fourth root of d, from that of X^T X (one product, at d = 128, where the layer's A = I + 0.1 N / sqrt(d) needs it).  False also for
+// anything that vanishes, overflows or is not finite on the way.
+template <int D>
+__device__ __forceinline__ bool certainly_regular(Pair<D>& W, float* s_part, Cols<D>& A, int w, int lane, int i, int g) {
+  using C = Cfg<D>;
+  float on[C::RB];
+  diagonal_sizes<D>(A, on, w, i, g);
+  float sq = 0.f;
+#pragma unroll
+  for (int k = 0; k < C::RB; ++k) {
+    on[k] = __builtin_amdgcn_rcpf(on[k]);
+    sq = __builtin_fmaf(0.f, on[k], sq);  // (not a number for a diagonal entry of 0)
+  }
+#pragma unroll
+  for (int r = 0; r < C::NT; ++r)
+#pragma unroll
+    for (int k = 0; k < C::RB; ++k)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const float x = r == C::RB * w + k && 4 * g + v == i ? 0.f : A[r][k][v] * on[k];
+        if constexpr (D == 128) A[r][k][v] = x;
+        else sq = __builtin_fmaf(x, x, sq);
+      }
+  if constexpr (D == 128) {
+    SplitCols<D, C::RB> t;
+    split_cols<D, C::RB>(A, t);
+    store_split_T<D>(W, 0, t, w, i, g);
+    lds_barrier();
+    gemm_split<D, C::RB>(A, W, 0, t, i, g);
+#pragma unroll
+    for (int r = 0; r < C::NT; ++r)
+#pragma unroll
+      for (int k = 0; k < C::RB; ++k)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) sq = __builtin_fmaf(A[r][k][v], A[r][k][v], sq);
+  }
+  sq = sum64(sq);
+  if (lane == 0) s_part[w] = sq;
+  lds_barrier();
+  float all = 0.f;
+#pragma unroll
+  for (int ww = 0; ww < C::NW; ++ww) all += s_part[ww];
+  return uniform(all < 0.9f ? 1 : 0) != 0;
+}
+
 // One round of the units below: a lane's s, and all of them in the notes (the last round's and the new ones side by side).  One barrier,
 // the units are to be read behind another one.
 template <int D>
@@ -251,7 +298,6 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D) == 64 ? 3 : 2) squaring_kern
       __syncthreads();  // every wavefront has left the pair
     };
 
-    // ---- a singular A is reported, although nothing here divides by A
     Split a, at;  // A_e and its transpose
     Cols<D> G, H;
     bool own;  // whether the problem is written in units of its own
@@ -264,16 +310,6 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D) == 64 ? 3 : 2) squaring_kern
       own = publish_problem_units<D, TIn>(W, m, Qp, QTp, Rp, w, i, g);
       if (ALWAYS || __builtin_expect(own, 0)) map_in_units<D>(m, xu, xu, w, i, g);
       split_cols<D, C::RB>(m, a);
-      floatx4 none[C::NT][1];  // no right-hand sides
-      if (__builtin_expect(solve_cols<D, 0>(WR, m, none, w, lane, PIVOT_MIN_A), 0)) {
-        load_half<D, TIn, false>(WL, Ap, tid);
-        __syncthreads();
-        if (lds_factor_aside<D>(W, S, tid)) {
-          hand_over(HANDED_TO_PRODUCT);
-          continue;
-        }
-        __syncthreads();
-      }
     }
     // ---- set-up: G = B R^{-1} B^T, H = Q; P = Q_T when it is a matrix of its own
     const int thread = tid;
@@ -551,6 +587,25 @@ __global__ void __launch_bounds__(Cfg<D>::NTHR, (D) == 64 ? 3 : 2) squaring_kern
         }
         emit_step<D, TIn>(W, s_red, p, prob, wk, pn, Qp, x0p, 0, tid);
       }
+    }
+    // ---- a singular A is reported, although nothing here divides by A: by the sequential product.  Here, where no register of the problem's
+    // is in use any more (ahead of the set-up, inverses got slower by more than the factorisation that this leaves out).
+    if (give_up != HANDED_TO_PRODUCT) {
+      __syncthreads();  // every wavefront has left the pair and s_max
+      const int tid = threadIdx.x + opaque_zero(), lane = tid & 63, w = uniform(tid >> 6), i = lane & 15, g = lane >> 4;
+      Cols<D> m;
+      load_cols<D, TIn>(Ap, m, w, i, g);
+      if (__builtin_expect(!certainly_regular<D>(W, s_max, m, w, lane, i, g), 0)) {
+        lds_barrier();
+        floatx4 none[C::NT][1];  // no right-hand sides
+        load_cols<D, TIn>(Ap, m, w, i, g);
+        if (__builtin_expect(solve_cols<D, 0>(WR, m, none, w, lane, PIVOT_MIN_A), 0)) {
+          load_half<D, TIn, false>(WL, Ap, tid);
+          __syncthreads();
+          if (lds_factor_aside<D>(W, S, tid)) give_up = HANDED_TO_PRODUCT;
+        }
+      }
+      __syncthreads();
     }
     if (give_up) hand_over(give_up);
   }

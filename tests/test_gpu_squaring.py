@@ -316,3 +316,27 @@ def test_what_the_product_kept_stays_with_squaring(d, n, dtype, T, qt, r, rho):
     print(d, dtype, T, qt, r, rho, "%.1e" % err.max(), int(same.sum()))
     assert same.sum() <= n // 4
     assert err.max() <= (1e-4 if r < 1 else 2e-5)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,n", [(32, 9), (64, 9), (128, 5)])
+def test_dynamics_far_from_diagonal_and_scaled(d, n):
+    """Whether A is singular is seen from its distance to a diagonal matrix, or else factored: dense dynamics, a permutation (no diagonal at
+    all), columns in units far apart and a diagonal far from one are solved (2e-5 as above), and reported only where singular."""
+    T = 16
+    b = synth.make_batch(n, d, d, T, seed=3, device=DEV)
+    A = b.A.clone()
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(2)
+    A[0] = torch.randn((d, d), device=DEV, generator=gen) / d ** 0.5
+    A[1] = torch.eye(d, device=DEV).roll(1, 0)
+    A[2] = 0.3 * A[2]
+    A[3] = 0.0
+    A[4, :, 5] = A[4, :, 4]
+    out = solve(synth.LqrBatch(A, b.B, b.Q, b.R, b.x0, T))
+    info = out["info"].cpu().numpy()
+    assert info[3] == 2 and info[0] == info[1] == info[2] == 0 and (info[5:] == 0).all()
+    ref = oracle_solve(synth.LqrBatch(A, b.B, b.Q, b.R, b.x0, T))
+    for p in [q for q in range(n) if q not in (3, 4)]:
+        for k, v in solve_errors({k: out[k][p:p + 1] for k in SOLVE_KEYS}, {k: ref[k][p:p + 1] for k in SOLVE_KEYS}).items():
+            assert v <= 2e-5, (p, k, v)
