@@ -62,7 +62,7 @@ static void* scratch_for_current_device() {
 // (registers and LDS decide it); the table is the fallback when no device can be asked.
 enum Kind { KIND_SOLVE = 0, KIND_DOUBLING = 1, KIND_ROLLOUT = 2, KIND_SOLVE_QUAD = 3, KIND_SOLVE_TV = 4, KIND_TV_QUAD = 5,
             KIND_ROLLOUT_TV = 6, KIND_CXT = 7, KIND_SCAN = 8, KIND_BACKWARD = 9, KIND_TV_ONE = 10, KIND_SQUARING = 11,
-            KIND_SQUARING_QUAD = 12, KIND_SQUARING_ONE = 13, KIND_COUNT = 14 };
+            KIND_SQUARING_QUAD = 12, KIND_SQUARING_ONE = 13, KIND_CXT_THREE = 14, KIND_COUNT = 15 };
 static int dindex(int d) { return d == 16 ? 0 : d == 32 ? 1 : d == 64 ? 2 : 3; }
 template <int D>
 static int occupancy_of(Kind kind, bool bf16) {
@@ -84,7 +84,8 @@ static int occupancy_of(Kind kind, bool bf16) {
     case KIND_TV_ONE: return occupancy_tv_small(bf16, 1);
     case KIND_SQUARING_QUAD: return occupancy_squaring16(bf16, 4);
     case KIND_SQUARING_ONE: return occupancy_squaring16(bf16, 1);
-    case KIND_CXT: return occupancy_cxt(bf16);
+    case KIND_CXT: return occupancy_cxt(bf16, 2);
+    case KIND_CXT_THREE: return occupancy_cxt(bf16, 3);
     default: return 0;
   }
 }
@@ -107,7 +108,7 @@ static int blocks_per_cu(Kind kind, int d, bool bf16) {
       static const int table[KIND_COUNT][4] = {{20, 8, 2, 1}, {16, 8, 2, 1}, {12, 4, 2, 1}, {8, 8, 2, 1}, {20, 8, 2, 1},
                                                {8, 8, 2, 1},  {12, 4, 2, 1}, {8, 8, 2, 1},  {16, 8, 2, 1},
                                                {12, 4, 2, 1}, {16, 8, 2, 1}, {16, 8, 2, 1},
-                                               {8, 8, 2, 1},  {16, 8, 2, 1}};
+                                               {8, 8, 2, 1},  {16, 8, 2, 1}, {12, 8, 2, 1}};
       nb = table[kind][dindex(d)];
     }
     c.value = nb > 32 ? 32 : nb;
@@ -689,12 +690,16 @@ static void fill_cxt_args(ttc::CxtArgs& a, const ttc_lqr_cxt_problem_t* q) {
 }
 
 static hipError_t run_cxt(const ttc::CxtArgs& a, bool bf16, hipStream_t st) {
-  const long long gb = ttc::grid_blocks(ttc::KIND_CXT, 16, bf16);
-  // batches that do not fill the resident wavefronts four problems at a time go one problem to a wavefront
-  const bool single = a.s.n <= gb;
+  // Two wavefronts a SIMD, or three.  A round of three takes 1.4 times as long as one of two (131072 problems, T = 8: 11 rounds of 53 us, 16
+  // of 38; 32768 problems: 3 and 4, 158 us and 148), and what leaves every gain in memory is faster with two (backward pass, 60000 problems,
+  // T = 12: 0.99 ms against 1.01).  Batches that two do not fill four problems at a time go one problem to a wavefront.
+  const long long two = ttc::grid_blocks(ttc::KIND_CXT, 16, bf16), three = ttc::grid_blocks(ttc::KIND_CXT_THREE, 16, bf16);
+  const bool single = a.s.n <= two;
   const long long items = single ? a.s.n : (a.s.n + 3) / 4;
+  const int waves = !single && !a.roll_ws && 7 * ((items + three - 1) / three) < 5 * ((items + two - 1) / two) ? 3 : 2;
+  const long long gb = waves == 3 ? three : two;
   const dim3 grid((unsigned)(items < gb ? items : gb));
-  return ttc::launch_cxt(a, bf16, single ? 1 : 4, grid, st);
+  return ttc::launch_cxt(a, bf16, single ? 1 : 4, waves, grid, st);
 }
 
 ttc_status_t ttc_lqr_solve_cxt(const ttc_lqr_cxt_problem_t* q, const ttc_lqr_solution_t* solution, void* hip_stream) {

@@ -20,25 +20,23 @@
 namespace ttc {
 
 
-#ifndef TTC_CXT_WAVES
-#define TTC_CXT_WAVES 2  // wavefronts per SIMD the register allocation aims at
-#endif
 // The workgroup is one wavefront: its lanes exchange data through LDS with wave_lds_sync(), which leaves the stores
 // of the roll-out's gains in flight (a workgroup barrier would wait for each of them).
 // PPW = problems per wavefront: 4 for batches that fill the chip; 1 for small batches, where a wavefront's
 // latency is what counts: the four rows of 16 lanes then all hold the same problem (they compute, and
 // write, the same values), and every per-problem loop below runs once instead of four times.
-template <typename TIn, int PPW>
-__global__ void __launch_bounds__(64, TTC_CXT_WAVES) solve_cxt_kernel(const CxtArgs ca) {
+// WAVES = wavefronts per SIMD the register allocation aims at: two, or three (46 registers spilled, next to none in a step) for large
+// batches; the launch decides (run_cxt).
+template <typename TIn, int PPW, int WAVES>
+__global__ void __launch_bounds__(64, WAVES) solve_cxt_kernel(const CxtArgs ca) {
   constexpr int D = 16;
   using C = Cfg<D>;
   static_assert(PPW == 1 || PPW == 4, "one problem or four per wavefront");
   __shared__ __attribute__((aligned(16))) float Wm[PPW][D * C::PITCH];
-  // Wm[q]: left half S and then S^{-1} (at the end P_0), right half the value matrix between steps
-  constexpr int PT = D + 4;                                              // row pitch of Vt
-  __shared__ __attribute__((aligned(16))) float Vt[PPW][D * PT];         // V^T; during set-up: s_B, s_Q, s_Qf
-  static_assert(PPW * D * PT >= PPW * 3 * CXT_RMAX, "the coefficients are staged in Vt");
-  float (*const coef)[3][CXT_RMAX] = reinterpret_cast<float (*)[3][CXT_RMAX]>(&Vt[0][0]);
+  // Wm[q]: left half V^T, then S and then S^{-1} (at the end K_0), right half the value matrix between steps (in the last one S_0, at the
+  // end P_0); during set-up the coefficients s_B, s_Q, s_Qf.  Twelve workgroups' worth fit a compute unit: three wavefronts a SIMD.
+  static_assert(D * C::PITCH >= 3 * CXT_RMAX, "the coefficients are staged in Wm");
+  float (*const coef)[3][CXT_RMAX] = reinterpret_cast<float (*)[3][CXT_RMAX]>(&Wm[0][0]);
   __shared__ __attribute__((aligned(16))) float vecs[2][PPW][4][D];      // a_t, gamma_B^t, gamma_Q^(t-1), 1/rinv;
                                                                          // steps alternate between the two copies
   const SolveArgs& p = ca.s;
@@ -186,7 +184,7 @@ __global__ void __launch_bounds__(64, TTC_CXT_WAVES) solve_cxt_kernel(const CxtA
 #pragma unroll
       for (int q = 0; q < PPW; ++q) {
         const float aI = vec[q][0][i];
-        put_acc(Vt[q], PT, accVT[q][0][0]);  // V^T[4g+v][i] = V[i][4g+v]
+        put_acc(Wm[q], C::PITCH, accVT[q][0][0]);  // V^T[4g+v][i] = V[i][4g+v]
 #pragma unroll
         for (int v = 0; v < 4; ++v) cFT[q][0][v] = aI * accVT[q][0][0][v];  // rows of F^T = diag(a) V
       }
@@ -197,7 +195,7 @@ __global__ void __launch_bounds__(64, TTC_CXT_WAVES) solve_cxt_kernel(const CxtA
         floatx4 bV[PPW];
 #pragma unroll
         for (int q = 0; q < PPW; ++q) {
-          bV[q] = get_row(Vt[q], PT);  // V[4g+t][i]
+          bV[q] = get_row(Wm[q], C::PITCH);  // V[4g+t][i]
 #pragma unroll
           for (int v = 0; v < 4; ++v) accS[q][0][0][v] = (4 * g + v == i) ? rI[q] : 0.f;
         }
@@ -209,7 +207,7 @@ __global__ void __launch_bounds__(64, TTC_CXT_WAVES) solve_cxt_kernel(const CxtA
 #pragma unroll
         for (int q = 0; q < PPW; ++q) {
           store_rows<D>(Wm[q], accS[q], w, i, g);
-          if (s == 0 && ca.dual_g) put_acc(Vt[q], PT, accS[q][0][0]);  // S_0 once more below (V^T has been read)
+          if (s == 0 && ca.dual_g) put_acc(Wm[q] + D, C::PITCH, accS[q][0][0]);  // S_0 once more below (P_1 has been read)
         }
       }
       wave_lds_sync();
@@ -218,7 +216,7 @@ __global__ void __launch_bounds__(64, TTC_CXT_WAVES) solve_cxt_kernel(const CxtA
       tm.toc(1);
       if (s == 0 && ca.dual_g) {
         // The dual problem of the backward pass starts from ut_0 = -S_0^{-1} g: y = S_0^{-1} g, refined once with the
-        // residual g - S_0 y.  Lane (i, g) takes row i of its problem's -S_0^{-1} (Wm) and S_0 (Vt).
+        // residual g - S_0 y.  Lane (i, g) takes row i of its problem's -S_0^{-1} (left half) and S_0 (right half).
         float (*dv)[D] = vecs[1][gq];  // the other step's copy is free at s = 0: g, y, residual
         dv[0][i] = g_m;
         wave_lds_sync();
@@ -236,7 +234,7 @@ __global__ void __launch_bounds__(64, TTC_CXT_WAVES) solve_cxt_kernel(const CxtA
         const float y = -row_dot(Wm[gq], C::PITCH, dv[0]);
         dv[1][i] = y;
         wave_lds_sync();
-        dv[2][i] = g_m - row_dot(Vt[gq], PT, dv[1]);
+        dv[2][i] = g_m - row_dot(Wm[gq] + D, C::PITCH, dv[1]);
         wave_lds_sync();
         const float ut0 = -(y - row_dot(Wm[gq], C::PITCH, dv[2]));
         if (quad * PPW + gq < p.n && (PPW == 4 || g == 0)) ca.roll_ws[(pg * slots + p.T + 3) * D * D + i] = ut0;
@@ -282,7 +280,7 @@ __global__ void __launch_bounds__(64, TTC_CXT_WAVES) solve_cxt_kernel(const CxtA
 #pragma unroll
         for (int q = 0; q < PPW; ++q) {
           put_acc(Wm[q] + D, C::PITCH, pn[q][0][0]);  // P_0 (no cost on x_0)
-          put_acc(Vt[q], PT, accW[q][0][0]);          // K_0, row-major
+          put_acc(Wm[q], C::PITCH, accW[q][0][0]);    // K_0, row-major
         }
         vecs[1][gq][0][i] = x0_m;
         wave_lds_sync();
@@ -291,7 +289,7 @@ __global__ void __launch_bounds__(64, TTC_CXT_WAVES) solve_cxt_kernel(const CxtA
           const floatx4 pt = get_row(Wm[q] + D, C::PITCH);
 #pragma unroll
           for (int v = 0; v < 4; ++v) pn[q][0][0][v] = 0.5f * (pn[q][0][0][v] + pt[v]);
-          store_rows<D>(Wm[q], pn[q], w, i, g);  // symmetric P_0
+          store_rows<D>(Wm[q] + D, pn[q], w, i, g);  // symmetric P_0
         }
         wave_lds_sync();
         if (ca.roll_ws) {  // the roll-out wants the gains (written above) and info only
@@ -306,8 +304,8 @@ __global__ void __launch_bounds__(64, TTC_CXT_WAVES) solve_cxt_kernel(const CxtA
           float u = 0.f, pw = 0.f;
 #pragma unroll
           for (int c = 0; c < 4; ++c) {
-            const floatx4 kr = *reinterpret_cast<const floatx4*>(Vt[gq] + i * PT + 4 * c);
-            const floatx4 pr = *reinterpret_cast<const floatx4*>(Wm[gq] + i * C::PITCH + 4 * c);
+            const floatx4 kr = *reinterpret_cast<const floatx4*>(Wm[gq] + i * C::PITCH + 4 * c);
+            const floatx4 pr = *reinterpret_cast<const floatx4*>(Wm[gq] + D + i * C::PITCH + 4 * c);
             const floatx4 xr = *reinterpret_cast<const floatx4*>(xv + 4 * c);
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
@@ -332,10 +330,10 @@ __global__ void __launch_bounds__(64, TTC_CXT_WAVES) solve_cxt_kernel(const CxtA
             const floatx4 nan4 = floatx4{nanv, nanv, nanv, nanv};
             if (p.K0)
               *reinterpret_cast<floatx4*>(p.K0 + prob[q] * (long)D * D + 4 * lane) =
-                  info[q] ? nan4 : *reinterpret_cast<const floatx4*>(Vt[q] + (lane >> 2) * PT + 4 * (lane & 3));
+                  info[q] ? nan4 : *reinterpret_cast<const floatx4*>(Wm[q] + (lane >> 2) * C::PITCH + 4 * (lane & 3));
             if (p.P0)
               *reinterpret_cast<floatx4*>(p.P0 + prob[q] * (long)D * D + 4 * lane) =
-                  info[q] ? nan4 : *reinterpret_cast<const floatx4*>(Wm[q] + (lane >> 2) * C::PITCH + 4 * (lane & 3));
+                  info[q] ? nan4 : *reinterpret_cast<const floatx4*>(Wm[q] + D + (lane >> 2) * C::PITCH + 4 * (lane & 3));
           }
         }
         wave_lds_sync();

@@ -40,8 +40,9 @@ hipError_t launch_squaring16(const DoublingArgs& a, bool bf16, int ppw, dim3 gri
 int occupancy_squaring16(bool bf16, int ppw);
 hipError_t launch_tv_small(const TvArgs& a, bool bf16, int ppw, dim3 grid, hipStream_t st);
 int occupancy_tv_small(bool bf16, int ppw);
-hipError_t launch_cxt(const CxtArgs& a, bool bf16, int ppw, dim3 grid, hipStream_t st);
-int occupancy_cxt(bool bf16);
+// waves = wavefronts per SIMD the kernel's registers are kept to (2 or, four problems to a wavefront, 3)
+hipError_t launch_cxt(const CxtArgs& a, bool bf16, int ppw, int waves, dim3 grid, hipStream_t st);
+int occupancy_cxt(bool bf16, int waves);
 hipError_t launch_rollout_cxt_forward(const CxtRolloutArgs& a, bool bf16, dim3 grid, hipStream_t st);
 
 // backward pass of the structured problems (ttc_cxt_backward.hpp): one wavefront per four problems of the chunk (vec),
