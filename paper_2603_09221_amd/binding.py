@@ -182,31 +182,37 @@ def _stride(t):
     """Elements between consecutive problems of a (n, ...) tensor whose trailing dims are contiguous."""
     if t is None:
         return 0
-    inner = 1
-    for k in range(t.dim() - 1, 0, -1):
-        if t.shape[k] != 1 and t.stride(k) != inner:
-            raise ValueError("per-problem matrices must be contiguous row-major")
-        inner *= t.shape[k]
+    if not t.is_contiguous():
+        inner = 1
+        for k in range(t.dim() - 1, 0, -1):
+            if t.shape[k] != 1 and t.stride(k) != inner:
+                raise ValueError("per-problem matrices must be contiguous row-major")
+            inner *= t.shape[k]
     return t.stride(0)
+
+
+_IN_DTYPES = {torch.float32: TTC_F32, torch.bfloat16: TTC_BF16}
+
+
+def _in_dtype(A, *others):
+    dt = A.dtype
+    for t in others:
+        if t is not None and t.dtype != dt:
+            raise ValueError("all inputs must share one dtype")
+    in_dtype = _IN_DTYPES.get(dt)
+    if in_dtype is None:
+        raise ValueError("inputs must be float32 or bfloat16")
+    return in_dtype
 
 
 def make_problem(A, B, Q, R, QT, x0, T, flags=0, rebase_every=0, n=None) -> Problem:
     """Fill the problem descriptor from tensors A (n,d,d), B (n,d,m), Q (n,d,d), R (n,m,m), QT or None,
     x0 (n,d).  A leading dimension expanded with stride 0 is passed through as a shared matrix."""
-    dt = A.dtype
-    for t in (B, Q, R, x0) + (() if QT is None else (QT,)):
-        if t.dtype != dt:
-            raise ValueError("all inputs must share one dtype")
-    in_dtype = {torch.float32: TTC_F32, torch.bfloat16: TTC_BF16}.get(dt)
-    if in_dtype is None:
-        raise ValueError("inputs must be float32 or bfloat16")
-    p = Problem()
-    p.n = A.shape[0] if n is None else n
-    p.d, p.m, p.T = A.shape[1], B.shape[2], T
-    p.in_dtype, p.flags, p.rebase_every = in_dtype, flags, rebase_every
-    p.A, p.B, p.Q, p.R, p.QT, p.x0 = _ptr(A), _ptr(B), _ptr(Q), _ptr(R), _ptr(QT), _ptr(x0)
-    p.sA, p.sB, p.sQ, p.sR, p.sQT, p.sx0 = (_stride(t) for t in (A, B, Q, R, QT, x0))
-    return p
+    in_dtype = _in_dtype(A, B, Q, R, x0, QT)
+    shape = A.shape
+    return Problem(shape[0] if n is None else n, shape[1], B.shape[2], T, in_dtype, flags, rebase_every,
+                   A.data_ptr(), B.data_ptr(), Q.data_ptr(), R.data_ptr(), _ptr(QT), x0.data_ptr(),
+                   _stride(A), _stride(B), _stride(Q), _stride(R), _stride(QT), _stride(x0))
 
 
 def ttc_lqr_workspace_bytes(problem: Problem, for_rollout: bool = False) -> int:
@@ -218,10 +224,15 @@ def ttc_lqr_solve_squares(problem: Problem) -> bool:
     return bool(load().ttc_lqr_solve_squares(ctypes.byref(problem)))
 
 
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_ptr(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    if _current_raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _current_raw_stream(torch.cuda.current_device())  # (the handle alone; a Stream object costs a microsecond more)
 
 
 def _scratch(nbytes, dev, stream):
@@ -234,6 +245,28 @@ def _scratch(nbytes, dev, stream):
         return torch.empty((max(nbytes, 16),), dtype=torch.uint8, device=dev)
 
 
+def _outputs(out, dev, f32, i32):
+    """`out` (a dict or None) with a new float32, or int32, tensor for every name in f32 and i32 (name: shape) that it lacks."""
+    out = dict(out or {})
+    for name, shape in f32.items():
+        if name not in out:
+            out[name] = torch.empty(shape, dtype=torch.float32, device=dev)
+    for name, shape in i32.items():
+        if name not in out:
+            out[name] = torch.empty(shape, dtype=torch.int32, device=dev)
+    return out
+
+
+def _solve_outputs(out, dev, n, d, m, want_P0, want_K0):
+    shapes = {"P0": (n, d, d)} if want_P0 else {}
+    if want_K0:
+        shapes["K0"] = (n, m, d)
+    shapes["u0"] = (n, m)
+    shapes["value"] = (n,)
+    out = _outputs(out, dev, shapes, {"info": (n,)})
+    return out, Solution(_ptr(out.get("P0")), _ptr(out.get("K0")), _ptr(out["u0"]), _ptr(out["value"]), _ptr(out["info"]))
+
+
 def ttc_lqr_solve(A, B, Q, R, QT, x0, T, *, flags=0, rebase_every=0, want_P0=True, want_K0=True,
                   out=None, workspace=None, stream=None):
     """P0 (n,d,d), K0 (n,m,d), u0 (n,m), value (n), info (n) of n LQR problems; all float32 device tensors.
@@ -241,22 +274,11 @@ def ttc_lqr_solve(A, B, Q, R, QT, x0, T, *, flags=0, rebase_every=0, want_P0=Tru
     `out` may carry preallocated tensors under the same names; `workspace` a uint8 device tensor."""
     lib = load()
     prob = make_problem(A, B, Q, R, QT, x0, T, flags, rebase_every)
-    n, d, m, dev = prob.n, prob.d, prob.m, A.device
-    out = dict(out or {})
-    f32 = dict(dtype=torch.float32, device=dev)
-    if want_P0 and "P0" not in out:
-        out["P0"] = torch.empty((n, d, d), **f32)
-    if want_K0 and "K0" not in out:
-        out["K0"] = torch.empty((n, m, d), **f32)
-    out.setdefault("u0", torch.empty((n, m), **f32))
-    out.setdefault("value", torch.empty((n,), **f32))
-    out.setdefault("info", torch.empty((n,), dtype=torch.int32, device=dev))
-    sol = Solution(_ptr(out.get("P0")), _ptr(out.get("K0")), _ptr(out["u0"]), _ptr(out["value"]), _ptr(out["info"]))
-    need = lib.ttc_lqr_workspace_bytes(ctypes.byref(prob), 0)
+    dev = A.device
+    out, sol = _solve_outputs(out, dev, prob.n, prob.d, prob.m, want_P0, want_K0)
     if workspace is None:
-        workspace = _scratch(need, dev, stream)
-    _check(lib.ttc_lqr_solve(ctypes.byref(prob), ctypes.byref(sol), c_void_p(workspace.data_ptr()),
-                             workspace.numel(), _stream_ptr(stream)))
+        workspace = _scratch(lib.ttc_lqr_workspace_bytes(prob, 0), dev, stream)
+    _check(lib.ttc_lqr_solve(prob, sol, workspace.data_ptr(), workspace.numel(), _stream_ptr(stream)))
     return out
 
 
@@ -292,28 +314,21 @@ def ttc_lqr_rollout(A, B, Q, R, QT, x0, T, *, flags=0, rebase_every=0, workspace
 
 def _tv_strides(t):
     """(problem stride, step stride) in elements of a (n, T, r, c) tensor whose matrices are contiguous row-major."""
-    if t.dim() != 4 or (t.shape[3] != 1 and t.stride(3) != 1) or (t.shape[2] != 1 and t.stride(2) != t.shape[3]):
+    if t.dim() != 4 or (not t.is_contiguous() and
+                        ((t.shape[3] != 1 and t.stride(3) != 1) or (t.shape[2] != 1 and t.stride(2) != t.shape[3]))):
         raise ValueError("expected (n, T, rows, cols) with contiguous row-major matrices")
-    return t.stride(0), t.stride(1)
+    return t.stride()[:2]
 
 
 def make_tv_problem(A, B, Q, R, x0) -> TvProblem:
     """Descriptor of a time-heterogeneous problem from A (n,T,d,d), B (n,T,d,m), Q (n,T,d,d), R (n,T,m,m), x0 (n,d);
     an axis expanded with stride 0 is passed through as shared."""
-    dt = A.dtype
-    for t in (B, Q, R, x0):
-        if t.dtype != dt:
-            raise ValueError("all inputs must share one dtype")
-    in_dtype = {torch.float32: TTC_F32, torch.bfloat16: TTC_BF16}.get(dt)
-    if in_dtype is None:
-        raise ValueError("inputs must be float32 or bfloat16")
-    p = TvProblem()
-    p.n, p.T, p.d, p.m = A.shape[0], A.shape[1], A.shape[2], B.shape[3]
-    p.in_dtype, p.flags = in_dtype, 0
-    p.A, p.B, p.Q, p.R, p.x0 = _ptr(A), _ptr(B), _ptr(Q), _ptr(R), _ptr(x0)
-    (p.sA, p.tA), (p.sB, p.tB), (p.sQ, p.tQ), (p.sR, p.tR) = (_tv_strides(t) for t in (A, B, Q, R))
-    p.sx0 = _stride(x0)
-    return p
+    in_dtype = _in_dtype(A, B, Q, R, x0)
+    (sA, tA), (sB, tB), (sQ, tQ), (sR, tR) = _tv_strides(A), _tv_strides(B), _tv_strides(Q), _tv_strides(R)
+    n, T, d, _ = A.shape
+    return TvProblem(n, d, B.shape[3], T, in_dtype, 0,
+                     A.data_ptr(), B.data_ptr(), Q.data_ptr(), R.data_ptr(), x0.data_ptr(),
+                     sA, sB, sQ, sR, _stride(x0), tA, tB, tQ, tR)
 
 
 def ttc_lqr_solve_tv(A, B, Q, R, x0, *, want_P0=True, want_K0=True, out=None, stream=None):
@@ -321,18 +336,8 @@ def ttc_lqr_solve_tv(A, B, Q, R, x0, *, want_P0=True, want_K0=True, out=None, st
     Q (n,T,d,d) with Q[:, s] the cost on the state step s arrives at (Q[:, T-1] is the terminal cost)."""
     lib = load()
     prob = make_tv_problem(A, B, Q, R, x0)
-    n, d, m, dev = prob.n, prob.d, prob.m, A.device
-    out = dict(out or {})
-    f32 = dict(dtype=torch.float32, device=dev)
-    if want_P0 and "P0" not in out:
-        out["P0"] = torch.empty((n, d, d), **f32)
-    if want_K0 and "K0" not in out:
-        out["K0"] = torch.empty((n, m, d), **f32)
-    out.setdefault("u0", torch.empty((n, m), **f32))
-    out.setdefault("value", torch.empty((n,), **f32))
-    out.setdefault("info", torch.empty((n,), dtype=torch.int32, device=dev))
-    sol = Solution(_ptr(out.get("P0")), _ptr(out.get("K0")), _ptr(out["u0"]), _ptr(out["value"]), _ptr(out["info"]))
-    _check(lib.ttc_lqr_solve_tv(ctypes.byref(prob), ctypes.byref(sol), None, 0, _stream_ptr(stream)))
+    out, sol = _solve_outputs(out, A.device, prob.n, prob.d, prob.m, want_P0, want_K0)
+    _check(lib.ttc_lqr_solve_tv(prob, sol, None, 0, _stream_ptr(stream)))
     return out
 
 
@@ -360,22 +365,11 @@ def ttc_lqr_solve_tv_scan(A, B, Q, R, x0, *, want_P0=True, want_K0=True, out=Non
     """ttc_lqr_solve_tv with the factors composed pairwise over the horizon (small batches, long horizons)."""
     lib = load()
     prob = make_tv_problem(A, B, Q, R, x0)
-    n, d, m, dev = prob.n, prob.d, prob.m, A.device
-    out = dict(out or {})
-    f32 = dict(dtype=torch.float32, device=dev)
-    if want_P0 and "P0" not in out:
-        out["P0"] = torch.empty((n, d, d), **f32)
-    if want_K0 and "K0" not in out:
-        out["K0"] = torch.empty((n, m, d), **f32)
-    out.setdefault("u0", torch.empty((n, m), **f32))
-    out.setdefault("value", torch.empty((n,), **f32))
-    out.setdefault("info", torch.empty((n,), dtype=torch.int32, device=dev))
-    need = lib.ttc_lqr_tv_scan_workspace_bytes(ctypes.byref(prob))
+    dev = A.device
+    out, sol = _solve_outputs(out, dev, prob.n, prob.d, prob.m, want_P0, want_K0)
     if workspace is None:
-        workspace = _scratch(need, dev, stream)
-    sol = Solution(_ptr(out.get("P0")), _ptr(out.get("K0")), _ptr(out["u0"]), _ptr(out["value"]), _ptr(out["info"]))
-    _check(lib.ttc_lqr_solve_tv_scan(ctypes.byref(prob), ctypes.byref(sol), c_void_p(workspace.data_ptr()),
-                                     workspace.numel(), _stream_ptr(stream)))
+        workspace = _scratch(lib.ttc_lqr_tv_scan_workspace_bytes(prob), dev, stream)
+    _check(lib.ttc_lqr_solve_tv_scan(prob, sol, workspace.data_ptr(), workspace.numel(), _stream_ptr(stream)))
     return out
 
 
@@ -407,14 +401,7 @@ def make_cxt_problem(sA, sB, sQ, sQf, rinv, lgA, lgB, lgQ, Bbasis, Qbasis, x0, T
     for k, t in given.items():
         if tuple(t.shape) != shapes[k] or not t.is_contiguous() or t.dtype != sA.dtype:
             raise ValueError(f"{k}: expected a contiguous {shapes[k]} tensor of dtype {sA.dtype}")
-    in_dtype = {torch.float32: TTC_F32, torch.bfloat16: TTC_BF16}.get(sA.dtype)
-    if in_dtype is None:
-        raise ValueError("inputs must be float32 or bfloat16")
-    p = CxtProblem()
-    p.n, p.d, p.r, p.T, p.in_dtype, p.flags = n, d, r, T, in_dtype, 0
-    for k, t in given.items():
-        setattr(p, k, _ptr(t))
-    return p
+    return CxtProblem(n, d, r, T, _in_dtype(sA), 0, *(given[k].data_ptr() for k, _ in CxtProblem._fields_[6:]))
 
 
 def ttc_lqr_solve_cxt(sA, sB, sQ, sQf, rinv, lgA, lgB, lgQ, Bbasis, Qbasis, x0, T, *, want_P0=True, want_K0=True,
@@ -422,18 +409,8 @@ def ttc_lqr_solve_cxt(sA, sB, sQ, sQf, rinv, lgA, lgB, lgQ, Bbasis, Qbasis, x0, 
     """P0, K0, u0, value, info of n structured, contextualised problems (float32 device tensors)."""
     lib = load()
     prob = make_cxt_problem(sA, sB, sQ, sQf, rinv, lgA, lgB, lgQ, Bbasis, Qbasis, x0, T)
-    n, d, dev = prob.n, prob.d, sA.device
-    out = dict(out or {})
-    f32 = dict(dtype=torch.float32, device=dev)
-    if want_P0 and "P0" not in out:
-        out["P0"] = torch.empty((n, d, d), **f32)
-    if want_K0 and "K0" not in out:
-        out["K0"] = torch.empty((n, d, d), **f32)
-    out.setdefault("u0", torch.empty((n, d), **f32))
-    out.setdefault("value", torch.empty((n,), **f32))
-    out.setdefault("info", torch.empty((n,), dtype=torch.int32, device=dev))
-    sol = Solution(_ptr(out.get("P0")), _ptr(out.get("K0")), _ptr(out["u0"]), _ptr(out["value"]), _ptr(out["info"]))
-    _check(lib.ttc_lqr_solve_cxt(ctypes.byref(prob), ctypes.byref(sol), _stream_ptr(stream)))
+    out, sol = _solve_outputs(out, sA.device, prob.n, prob.d, prob.d, want_P0, want_K0)
+    _check(lib.ttc_lqr_solve_cxt(prob, sol, _stream_ptr(stream)))
     return out
 
 
