@@ -777,7 +777,7 @@ ttc_status_t ttc_block_forward(const ttc_block_t* b, const void* x_in, void* x_o
 
   // h_0 = W_in LN(x_in) + b_in
   const bool bf16 = (b->flags & TTC_BLOCK_FLAG_BF16) != 0;
-  ttc::LnStatsArgs s1{x_in, ws + L.stats_in, M, b->C, b->eps};
+  ttc::LnStatsArgs s1{x_in, ws + L.stats_in, M, b->C, b->eps, b->Qc, ws + L.qbasis, r};
   if (ttc::launch_ln_stats(s1, bf16, st) != hipSuccess) return TTC_ERR_DEVICE;
   if (bf16) {
     ttc::GemmLnBf16Args g1{x_in, ws + L.stats_in, b->ln_in_gain, b->ln_in_offset, static_cast<const uint16_t*>(b->W_in),
@@ -788,7 +788,7 @@ ttc_status_t ttc_block_forward(const ttc_block_t* b, const void* x_in, void* x_o
                        static_cast<const float*>(b->W_in), b->b_in, nullptr, h0p, M, HD, b->C};
     if (ttc::launch_gemm_ln(g1, ttc::cu_count(), st) != hipSuccess) return TTC_ERR_DEVICE;
   }
-  // the contextualisation maps and the Q basis
+  // the contextualisation maps
   ttc::CxtMapsArgs c;
   c.H0 = h0p;
   c.W_head = b->W_head; c.b_head = b->b_head; c.W_shared = b->W_shared; c.b_shared = b->b_shared;
@@ -802,7 +802,6 @@ ttc_status_t ttc_block_forward(const ttc_block_t* b, const void* x_in, void* x_o
   c.tokens_per_block = (int)((M + chunks - 1) / chunks);
   chunks = (M + c.tokens_per_block - 1) / c.tokens_per_block;
   if (ttc::launch_cxt_maps(c, (int)(chunks * per_chunk), st) != hipSuccess) return TTC_ERR_DEVICE;
-  if (ttc::launch_qbasis(b->Qc, ws + L.qbasis, r, st) != hipSuccess) return TTC_ERR_DEVICE;
   // o = the heads' first optimal controls
   ttc_lqr_cxt_problem_t q;
   q.n = M * H; q.d = 16; q.r = r; q.T = b->T; q.in_dtype = TTC_F32; q.flags = 0;
@@ -814,15 +813,19 @@ ttc_status_t ttc_block_forward(const ttc_block_t* b, const void* x_in, void* x_o
   a.s.info = info ? info : reinterpret_cast<int32_t*>(ws + L.info);
   if (run_cxt(a, false, st) != hipSuccess) return TTC_ERR_DEVICE;
   // x_out = x_in + W_out LN(o) + b_out
-  ttc::LnStatsArgs s2{op, ws + L.stats_out, M, HD, b->eps};
-  if (ttc::launch_ln_stats(s2, false, st) != hipSuccess) return TTC_ERR_DEVICE;
+  const bool inside = ttc::stats_inside(M, b->C, HD, ttc::cu_count(), bf16);
+  const float* const stats_out = inside ? nullptr : ws + L.stats_out;
+  if (!inside) {
+    ttc::LnStatsArgs s2{op, ws + L.stats_out, M, HD, b->eps};
+    if (ttc::launch_ln_stats(s2, false, st) != hipSuccess) return TTC_ERR_DEVICE;
+  }
   if (bf16) {
-    ttc::GemmLnBf16Args g2{op, ws + L.stats_out, b->ln_out_gain, b->ln_out_offset, static_cast<const uint16_t*>(b->W_out),
-                           b->b_out, static_cast<const uint16_t*>(x_in), x_out, M, b->C, HD};
+    ttc::GemmLnBf16Args g2{op, stats_out, b->ln_out_gain, b->ln_out_offset, static_cast<const uint16_t*>(b->W_out),
+                           b->b_out, static_cast<const uint16_t*>(x_in), x_out, M, b->C, HD, b->eps};
     if (ttc::launch_gemm_ln_bf16(g2, false, true, ttc::cu_count(), st) != hipSuccess) return TTC_ERR_DEVICE;
   } else {
-    ttc::GemmLnArgs g2{op, ws + L.stats_out, b->ln_out_gain, b->ln_out_offset, static_cast<const float*>(b->W_out),
-                       b->b_out, static_cast<const float*>(x_in), static_cast<float*>(x_out), M, b->C, HD};
+    ttc::GemmLnArgs g2{op, stats_out, b->ln_out_gain, b->ln_out_offset, static_cast<const float*>(b->W_out),
+                       b->b_out, static_cast<const float*>(x_in), static_cast<float*>(x_out), M, b->C, HD, b->eps};
     if (ttc::launch_gemm_ln(g2, ttc::cu_count(), st) != hipSuccess) return TTC_ERR_DEVICE;
   }
   return TTC_OK;

@@ -118,11 +118,14 @@ struct LnStatsArgs {
   long long M;
   int L;           // multiple of 4
   float eps;
+  const float* Qc = nullptr;  // r > 0: the same launch forms the basis Q^(i) = Qc^(i) Qc^(i)^T / 4, (r, 16, 16), into Qb
+  float* Qb = nullptr;
+  int r = 0;
 };
 
 struct GemmLnArgs {
   const float* X;       // (M, K) row-major, rows normalised on load with stats, gain, offset
-  const float* stats;   // (M, 2)
+  const float* stats;   // (M, 2); NULL where stats_inside says so: formed in the kernel, with eps
   const float* gain;    // (K)
   const float* offset;  // (K)
   const float* W;       // (N, K) row-major
@@ -131,13 +134,14 @@ struct GemmLnArgs {
   float* Y;             // (M, N)
   long long M;
   int N, K;             // multiples of 4
+  float eps = 0.f;
 };
 
 // the bfloat16 variant of the projections (the block's TTC_BLOCK_FLAG_BF16): X float32 or bfloat16, W bfloat16,
 // Res bfloat16 or NULL, Y float32 or bfloat16 (bfloat16 values are stored as uint16_t)
 struct GemmLnBf16Args {
   const void* X;        // (M, K): element type by the kernel's template argument
-  const float* stats;   // (M, 2)
+  const float* stats;   // (M, 2) or NULL (as above)
   const float* gain;    // (K) float32
   const float* offset;  // (K) float32
   const uint16_t* W;    // (N, K) bfloat16
@@ -146,12 +150,13 @@ struct GemmLnBf16Args {
   void* Y;              // (M, N): element type by the kernel's template argument
   long long M;
   int N, K;             // multiples of 8
+  float eps = 0.f;
 };
 
 // the projections of few tokens or few outputs (element types by the kernel's template arguments)
 struct GemmLnSplitArgs {
   const void* X;        // (M, K)
-  const float* stats;   // (M, 2)
+  const float* stats;   // (M, 2) or NULL (as above)
   const float* gain;    // (K)
   const float* offset;  // (K)
   const void* W;        // (N, K)
@@ -160,6 +165,7 @@ struct GemmLnSplitArgs {
   void* Y;              // (M, N)
   long long M;
   int N, K;             // multiples of 4 (float32 weights) or 8 (bfloat16 weights)
+  float eps;
 };
 
 struct CxtMapsArgs {

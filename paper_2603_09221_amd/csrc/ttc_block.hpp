@@ -1,7 +1,7 @@
 // Kernels of the whole Test-Time Control block around the structured solver (Sec. 4, "Hybrid with Memory Layers",
 // "Multi-Head Structure", "Contextualization", "Parameterization"):
-//     h_0   = W_in LN(x_in) + b_in                     ln_stats_kernel + gemm_ln_kernel
-//     the per-head contextualisation maps s_X(h_0)      cxt_maps_kernel (+ qbasis_kernel: Q^(i) = Qc Qc^T / sqrt(d))
+//     h_0   = W_in LN(x_in) + b_in                     ln_stats_kernel (and Q^(i) = Qc Qc^T / sqrt(d)) + gemm_ln_kernel
+//     the per-head contextualisation maps s_X(h_0)      cxt_maps_kernel
 //     o     = u_1^* of every head's problem             solve_cxt_kernel (ttc_cxt.hpp), fed from the arrays above
 //     x_out = x_in + W_out LN(o) + b_out                ln_stats_kernel + gemm_ln_kernel with the residual
 // The two projections are dense contractions and run on the matrix cores in float32 (v_mfma_f32_16x16x4_f32), the
@@ -15,6 +15,15 @@
 namespace ttc {
 
 typedef float blk_floatx4 __attribute__((ext_vector_type(4)));
+
+// Q = Qc Qc^T / sqrt(16), by a workgroup of 256 threads
+__device__ __forceinline__ void qbasis_form(const float* M, float* Qb) {
+  const int a = threadIdx.x >> 4, b = threadIdx.x & 15;
+  float s = 0.f;
+#pragma unroll
+  for (int k = 0; k < 16; ++k) s = __builtin_fmaf(M[16 * a + k], M[16 * b + k], s);
+  Qb[threadIdx.x] = 0.25f * s;
+}
 
 // mean and reciprocal standard deviation of every row (float32 or bfloat16), one wavefront per row, two passes over
 // the row (the second one reads what the first has just brought into the caches): no cancellation whatever the mean
@@ -40,30 +49,41 @@ __device__ __forceinline__ blk_floatx4 blk_ld4<unsigned short>(const unsigned sh
 }
 
 template <typename TX>
-__global__ void __launch_bounds__(256) ln_stats_kernel(const LnStatsArgs p) {
-  const int lane = threadIdx.x & 63;
-  const long long row = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= p.M) return;
-  const TX* x = reinterpret_cast<const TX*>(p.X) + row * p.L;
+__device__ __forceinline__ void ln_row_stats(const TX* x, int L, float eps, int lane, float& mean, float& rstd) {
   float s = 0.f;
-  for (int k = 4 * lane; k < p.L; k += 256) {
+  for (int k = 4 * lane; k < L; k += 256) {
     const blk_floatx4 v = blk_ld4<TX>(x, k);
     s += (v[0] + v[1]) + (v[2] + v[3]);
   }
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) s += __shfl_xor(s, o, 64);
-  const float mean = s / (float)p.L;
+  mean = s / (float)L;
   float q = 0.f;
-  for (int k = 4 * lane; k < p.L; k += 256) {
+  for (int k = 4 * lane; k < L; k += 256) {
     const blk_floatx4 v = blk_ld4<TX>(x, k);
     const float a = v[0] - mean, b = v[1] - mean, c = v[2] - mean, d = v[3] - mean;
     q += (a * a + b * b) + (c * c + d * d);
   }
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) q += __shfl_xor(q, o, 64);
+  rstd = 1.f / sqrtf(q / (float)L + eps);
+}
+template <typename TX>
+__global__ void __launch_bounds__(256) ln_stats_kernel(const LnStatsArgs p) {
+  const long long rows = (p.M + 3) / 4;  // workgroups; those behind them take a basis matrix each
+  if (blockIdx.x >= rows) {
+    const long long k = blockIdx.x - rows;
+    qbasis_form(p.Qc + k * 256, p.Qb + k * 256);
+    return;
+  }
+  const int lane = threadIdx.x & 63;
+  const long long row = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (row >= p.M) return;
+  float mean, rstd;
+  ln_row_stats<TX>(reinterpret_cast<const TX*>(p.X) + row * p.L, p.L, p.eps, lane, mean, rstd);
   if (lane == 0) {
     p.stats[2 * row] = mean;
-    p.stats[2 * row + 1] = 1.f / sqrtf(q / (float)p.L + p.eps);
+    p.stats[2 * row + 1] = rstd;
   }
 }
 
@@ -363,6 +383,7 @@ struct BlkFrag<unsigned short> {
 template <typename TX, typename TW, typename TY, int NT, int MT, int NWV>
 __global__ void __launch_bounds__(64 * NWV) gemm_ln_split_kernel(const GemmLnSplitArgs p) {
   __shared__ __attribute__((aligned(16))) blk_floatx4 red[NWV > 1 ? NWV * NT * MT * 64 : 1];
+  __shared__ float own[2 * 16 * MT];  // the rows' statistics, where they are formed here
   const TX* const X = reinterpret_cast<const TX*>(p.X);
   const TW* const W = reinterpret_cast<const TW*>(p.W);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, i = lane & 15, g = lane >> 4;
@@ -379,8 +400,27 @@ __global__ void __launch_bounds__(64 * NWV) gemm_ln_split_kernel(const GemmLnSpl
     long long row = m0 + 16 * b + i;
     row = row < p.M ? row : p.M - 1;
     xrow[b] = X + row * p.K;
-    mean[b] = p.stats[2 * row];
-    rstd[b] = p.stats[2 * row + 1];
+    if (p.stats) {
+      mean[b] = p.stats[2 * row];
+      rstd[b] = p.stats[2 * row + 1];
+    }
+  }
+  if (!p.stats) {
+    for (int q = wave; q < 16 * MT; q += NWV) {
+      const long long row = m0 + q < p.M ? m0 + q : p.M - 1;
+      float m, s;
+      ln_row_stats<TX>(X + row * p.K, p.K, p.eps, lane, m, s);
+      if (lane == 0) {
+        own[2 * q] = m;
+        own[2 * q + 1] = s;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int b = 0; b < MT; ++b) {
+      mean[b] = own[2 * (16 * b + i)];
+      rstd[b] = own[2 * (16 * b + i) + 1];
+    }
   }
 #pragma unroll
   for (int a = 0; a < NT; ++a) {
@@ -635,16 +675,6 @@ __global__ void __launch_bounds__(512) cxt_maps16_kernel(const CxtMapsArgs p) {
       dst[((t + u) * p.H + h) * 16 + col] = act ? softplus_f32(z) : z;
     }
   }
-}
-
-// Q^(i) = Qc^(i) Qc^(i)^T / sqrt(16), one workgroup of 256 threads per basis matrix
-__global__ void __launch_bounds__(256) qbasis_kernel(const float* Qc, float* Qb) {
-  const float* M = Qc + (long long)blockIdx.x * 256;
-  const int a = threadIdx.x >> 4, b = threadIdx.x & 15;
-  float s = 0.f;
-#pragma unroll
-  for (int k = 0; k < 16; ++k) s = __builtin_fmaf(M[16 * a + k], M[16 * b + k], s);
-  Qb[(long long)blockIdx.x * 256 + threadIdx.x] = 0.25f * s;
 }
 
 }  // namespace ttc

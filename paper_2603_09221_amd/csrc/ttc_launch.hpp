@@ -52,10 +52,11 @@ hipError_t launch_cxt_basis(const CxtBackwardArgs& a, bool bf16, hipStream_t st)
 hipError_t launch_zero_floats(float* dst, long long n, hipStream_t st);
 // the block around the structured solver (ttc_block.hpp)
 hipError_t launch_ln_stats(const LnStatsArgs& a, bool bf16, hipStream_t st);
+// whether the projection forms the statistics of its rows itself (stats NULL, eps set)
+bool stats_inside(long long M, int N, int K, int cus, bool bf16);
 hipError_t launch_gemm_ln_bf16(const GemmLnBf16Args& a, bool x_bf16, bool out_bf16, int cus, hipStream_t st);
 hipError_t launch_gemm_ln(const GemmLnArgs& a, int cus, hipStream_t st);
 hipError_t launch_cxt_maps(const CxtMapsArgs& a, int blocks, hipStream_t st);
-hipError_t launch_qbasis(const float* Qc, float* Qb, int r, hipStream_t st);
 
 template <typename K>
 inline int occupancy_query(K kernel, int nthr) {
