@@ -1017,8 +1017,9 @@ ttc_status_t ttc_lqr_backward_cxt(const ttc_lqr_cxt_problem_t* q, const float* g
     a.info = gr->info ? gr->info : info_ws - first;  // indexed by the problem's number in the batch
     if (run_cxt(sc, bf16, st) != hipSuccess) return TTC_ERR_DEVICE;
     const long long groups = (a.count + 15) / 16;  // workgroups' worth of problems
-    // slabs of the basis sums: four workgroups per compute unit when the chunk is large, never under the smallest slab
-    const long long slab = (a.count + 4LL * ttc::cu_count() - 1) / (4LL * ttc::cu_count());
+    // slabs of the basis sums: one workgroup per compute unit when the chunk is large (the additions at a slab's end cost more than it gains
+    // from company: 131072 problems, T = 8, 1.47 ms, with two 1.50, with four 1.53), never under the smallest slab
+    const long long slab = (a.count + ttc::cu_count() - 1) / ttc::cu_count();
     a.basis_slab = (int)(slab < ttc::CXT_BASIS_SLAB ? ttc::CXT_BASIS_SLAB : slab > 4096 ? 4096 : slab);
     if (ttc::launch_cxt_backward_vec(a, bf16, dim3((unsigned)(groups < vgrid ? groups : vgrid)), st) != hipSuccess)
       return TTC_ERR_DEVICE;

@@ -331,51 +331,76 @@ __global__ void __launch_bounds__(256, 2) backward_cxt_vec_kernel(const CxtBackw
 }
 
 // gBbasis[k] += sum_p sB[p][k] dBbar[p], gQbasis[k] += sum_p (sQ[p][k] dQbar[p] + sQf[p][k] dQ_T[p]) over a slab of
-// a.basis_slab of the chunk's problems per workgroup; thread e owns entry e of every basis matrix, the sums of a slab are added to the
-// caller's arrays with one atomic addition per entry (the order of the slabs, and with it the last bits, may vary).
+// a.basis_slab of the chunk's problems per workgroup, the sums of a slab added to the caller's arrays with one atomic addition per
+// entry (the order of the slabs, and with it the last bits, may vary).
+// A contraction over the problems, on the matrix cores: sixteen coefficients on the row side, the entries of the kept matrices on the
+// column side, four problems an instruction.  Wavefront w has entries 64 w .. 64 w + 63, column j of its tile t being entry 64 w + 4 j + t, so
+// that a lane reads 16 bytes of a matrix for four instructions; the next STAGES - 1 fours of problems are on their way meanwhile.  What bounds
+// it is the reading, some 3 KB a problem, and the additions at the end, 8192 a slab at r = 16, which want 64 consecutive entries an
+// instruction (every fourth entry a lane: 1.74 ms).  131072 problems, T = 8, r = 16, a call of the backward pass: 1.58 ms
+// with a thread per entry that took the coefficients from lanes (96 instructions a problem), 1.47 with this.
 template <typename TIn>
 __global__ void __launch_bounds__(256) cxt_basis_kernel(const CxtBackwardArgs a) {
-  const int e = threadIdx.x;
+  constexpr int STAGES = 4;
+  __shared__ __attribute__((aligned(16))) float sums_all[4][16 * 68];
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
   const int r = a.c.r;
   const long long q0 = (long long)blockIdx.x * a.basis_slab;
-  long long q1 = q0 + a.basis_slab;
-  q1 = q1 < a.count ? q1 : a.count;
-  for (int k0 = 0; k0 < r; k0 += 16) {  // sixteen basis matrices of each group at a time (registers)
-    float sb[16], sq[16];
+  const int count = (int)(a.count - q0 < a.basis_slab ? a.count - q0 : a.basis_slab);
+  const float* const keep = a.keep + q0 * 768 + 64 * w + 4 * i;
+  for (int k0 = 0; k0 < r; k0 += 16) {
+    const bool live = k0 + i < r;
+    const long long c0 = (a.first + q0) * r + (live ? k0 + i : 0);
+    const TIn* const cB = reinterpret_cast<const TIn*>(a.c.sB) + c0;
+    const TIn* const cQ = reinterpret_cast<const TIn*>(a.c.sQ) + c0;
+    const TIn* const cF = reinterpret_cast<const TIn*>(a.c.sQf) + c0;
+    struct {
+      floatx4 m[3];
+      decltype(read1((const TIn*)nullptr, 0)) c[3];
+    } st[STAGES];
+    auto fetch = [&](auto U, int q) {  // problems past the slab's end: the last one's, with coefficients of zero (below)
+      constexpr int u = decltype(U)::value;
+      const int qq = q + g < count ? q + g : count - 1;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) sb[k] = sq[k] = 0.f;
-    // Lane 16 g + k of every wavefront reads coefficient k0 + k of group g (sB, sQ, sQf) with one load per problem
-    // and the others take it from that lane; the next problem's values are fetched while this one's products are
-    // formed.
-    const int lane = threadIdx.x & 63, grp = lane >> 4, kk = k0 + (lane & 15);
-    const TIn* const cbase = reinterpret_cast<const TIn*>(grp == 0 ? a.c.sB : grp == 1 ? a.c.sQ : a.c.sQf);
-    const bool cread = grp < 3 && kk < r;
-    float nB = 0.f, nQ = 0.f, nF = 0.f, nC = 0.f;
-    if (q0 < q1) {
-      const float* keep = a.keep + q0 * 768;
-      nB = keep[e]; nQ = keep[256 + e]; nF = keep[512 + e];
-      if (cread) nC = ld1<TIn>(cbase, (a.first + q0) * r + kk);
-    }
-    for (long long q = q0; q < q1; ++q) {
-      const float dBbar = nB, dQbar = nQ, dQf = nF, cv = nC;
-      if (q + 1 < q1) {
-        const float* keep = a.keep + (q + 1) * 768;
-        nB = keep[e]; nQ = keep[256 + e]; nF = keep[512 + e];
-        if (cread) nC = ld1<TIn>(cbase, (a.first + q + 1) * r + kk);
-      }
+      for (int x = 0; x < 3; ++x) st[u].m[x] = *reinterpret_cast<const floatx4*>(keep + (long long)qq * 768 + 256 * x);
+      st[u].c[0] = read1(cB, (long)qq * r);
+      st[u].c[1] = read1(cQ, (long)qq * r);
+      st[u].c[2] = read1(cF, (long)qq * r);
+    };
+    floatx4 sb[4], sq[4];
 #pragma unroll
-      for (int k = 0; k < 16; ++k) {  // coefficients past r were read as zero
-        sb[k] = __builtin_fmaf(__builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, cv), k)), dBbar, sb[k]);
-        sq[k] = __builtin_fmaf(__builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, cv), 16 + k)), dQbar, sq[k]);
-        sq[k] = __builtin_fmaf(__builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, cv), 32 + k)), dQf, sq[k]);
-      }
-    }
+    for (int t = 0; t < 4; ++t) sb[t] = sq[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+    static_for<0, STAGES - 1>([&](auto U) { fetch(U, 4 * decltype(U)::value); });
+    for (int q = 0; q < count; q += 4 * STAGES)
+      static_for<0, STAGES>([&](auto U) {
+        constexpr int u = decltype(U)::value;
+        fetch(IntC<(u + STAGES - 1) % STAGES>{}, q + 4 * (u + STAGES - 1));
+        TTC_SCHED_BARRIER();
+        const bool on = live && q + 4 * u + g < count;
+        const float b = on ? widen(st[u].c[0]) : 0.f, c = on ? widen(st[u].c[1]) : 0.f, f = on ? widen(st[u].c[2]) : 0.f;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      if (k0 + k < r) {
-        atomicAdd(a.gBbasis + (long)(k0 + k) * 256 + e, sb[k]);
-        atomicAdd(a.gQbasis + (long)(k0 + k) * 256 + e, sq[k]);
+        for (int t = 0; t < 4; ++t) {
+          sb[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(b, st[u].m[0][t], sb[t], 0, 0, 0);
+          sq[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(c, st[u].m[1][t], sq[t], 0, 0, 0);
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) sq[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(f, st[u].m[2][t], sq[t], 0, 0, 0);
+      });
+    // through LDS, so that a wavefront adds to 64 consecutive entries at a time
+    float* const sums = sums_all[w];
+    for (int half = 0; half < 2; ++half) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        floatx4 x;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) x[t] = half ? sq[t][v] : sb[t][v];
+        *reinterpret_cast<floatx4*>(sums + (4 * g + v) * 68 + 4 * i) = x;
       }
+      wave_lds_sync();
+      float* const out = (half ? a.gQbasis : a.gBbasis) + (long)k0 * 256 + 64 * w + lane;
+      const int rows = r - k0 < 16 ? r - k0 : 16;
+      for (int k = 0; k < rows; ++k) atomicAdd(out + k * 256, sums[k * 68 + lane]);
+      wave_lds_sync();
     }
   }
 }
