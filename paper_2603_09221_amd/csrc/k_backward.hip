@@ -10,13 +10,20 @@
 namespace ttc {
 #if TTC_D == 16
 template <typename TIn>
-static constexpr auto kernel = backward16_kernel<TIn>;
+static constexpr auto kernel = backward16_kernel<TIn, false>;
 #else
 template <typename TIn>
 static constexpr auto kernel = backward_kernel<TTC_D, TIn>;
 #endif
 template <>
 hipError_t launch_backward<TTC_D>(const BackwardArgs& a, bool bf16, dim3 grid, hipStream_t st) {
+#if TTC_D == 16
+  if (a.past_caches) {
+    if (bf16) hipLaunchKernelGGL((backward16_kernel<uint16_t, true>), grid, dim3(64), 0, st, a);
+    else hipLaunchKernelGGL((backward16_kernel<float, true>), grid, dim3(64), 0, st, a);
+    return hipGetLastError();
+  }
+#endif
   if (bf16) hipLaunchKernelGGL(kernel<uint16_t>, grid, dim3(Cfg<TTC_D>::NTHR), 0, st, a);
   else hipLaunchKernelGGL(kernel<float>, grid, dim3(Cfg<TTC_D>::NTHR), 0, st, a);
   return hipGetLastError();

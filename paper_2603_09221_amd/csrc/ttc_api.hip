@@ -146,7 +146,7 @@ constexpr float SQUARING_QT_LIMIT_F32 = 64.f, SQUARING_QT_LIMIT_BF16 = 4096.f;
 static bool qt_is_q(const ttc_lqr_problem_t* q) { return !q->QT || (q->QT == q->Q && q->sQT == q->sQ); }
 // Default path, d >= 32: whether the T equal factors are composed by squaring (squaring_kernel) or one after the other
 // (solve_kernel).  Costs in hundredths of a squaring: a squaring 100, an application of a power to P 70, A and G of the last square 35
-// (not needed when P is still 0), 10 more for the set-up (A is factored for its report); a factor of the sequential product 40, with
+// (not needed when P is still 0), 10 more for the set-up (which then factored A for its report); a factor of the sequential product 40, with
 // bfloat16 inputs (longer groups) 37.  They were fitted when the squaring kernel formed its products in float32; with products of split
 // operands it has become the faster of the two on this side of the line as well, where the product is kept although it takes
 // longer (sequential / squaring, ms: d = 64, 3072 problems, T = 4 0.55 / 0.41, 9 0.88 / 0.58, 11 1.03 / 0.65; d = 128, 512 problems, T = 4
@@ -154,6 +154,7 @@ static bool qt_is_q(const ttc_lqr_problem_t* q) { return !q->QT || (q->QT == q->
 // equal for T = 2, 3, and for T = 4, 5 with bfloat16 inputs at d = 32).  Beyond the line, the same: d = 64, T = 8 0.83 / 0.49, 12 1.08 / 0.58,
 // 16 1.53 / 0.58; d = 128, T = 8 0.96 / 0.59, 16 1.82 / 0.69; d = 32, 8192 problems, T = 8 0.41 / 0.28, 16 0.76 / 0.33.
 // The number of problems does not matter: one problem alone d = 64, T = 8 166 / 96 us, d = 128, T = 12 626 / 326 us.
+// (Squaring has become 4 to 9 % faster since these were taken, the product has not changed.)
 static bool use_squaring(const ttc_lqr_problem_t* q) {
   if (q->d < 32 || (q->flags & (TTC_FLAG_DOUBLING | TTC_FLAG_PURE_SYMPLECTIC)) || q->rebase_every != 0) return false;
   const bool from_zero = qt_is_q(q);
@@ -253,6 +254,16 @@ static hipError_t run_scan_apply(const ScanArgs& a, int d, int ipw, dim3 grid, h
 }
 static hipError_t run_scan_gather(const ScanArgs& a, float* P, int d, dim3 grid, hipStream_t st) {
   TTC_BY_D(d, launch_scan_gather<D>(a, P, grid, st))
+}
+
+// The sweeps of backward16_kernel read the problems' matrices three times, and the 256 MiB cache in front of the memory can hold them
+// between the sweeps if the gradients, written once and not read again, go past it.  Backward pass at d = 16, gradients written as
+// usual / past the caches, us: float32 1024 problems of 16 steps (67 MB) 55.3 / 54.4, 500 of 64 (131 MB) 181 / 178.5, 700 of 64 (184 MB)
+// 217 / 197; bfloat16 1024 of 64 (134 MB) 256 / 206, 1400 of 64 (184 MB) 359 / 337.  Where the matrices do not fit, nothing is kept either
+// way and past the caches is the slower: bfloat16 2048 of 64 (268 MB) 400 / 410, float32 2048 of 64 (537 MB) 418 / 424, 1024 of 256
+// (1.1 GB) 1032 / 1052.
+static bool use_past_caches(long long n, int T, int d, int bytes) {
+  return d == 16 && 4.0 * n * T * d * d * bytes <= 200e6;
 }
 static hipError_t run_backward(const BackwardArgs& a, int d, bool bf16, dim3 grid, hipStream_t st) {
   TTC_BY_D(d, launch_backward<D>(a, bf16, grid, st))
@@ -935,6 +946,7 @@ ttc_status_t ttc_lqr_backward_tv(const ttc_lqr_tv_problem_t* q, const float* gra
   a.gA = gr->gA; a.gB = gr->gB; a.gQ = gr->gQ; a.gR = gr->gR; a.gQT = nullptr; a.gx0 = gr->gx0;
   a.sum_steps = 0;
   const bool bf16 = q->in_dtype == TTC_BF16;
+  a.past_caches = ttc::use_past_caches(q->n, q->T, q->d, bf16 ? 2 : 4);
   const long long gb = ttc::grid_blocks(ttc::KIND_BACKWARD, q->d, bf16);
   const dim3 grid((unsigned)(q->n < gb ? q->n : gb));
   return ttc::run_backward(a, q->d, bf16, grid, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? TTC_OK

@@ -71,6 +71,7 @@ struct BackwardArgs {
   float* gQT;                 // (n, d, d) or NULL: the terminal cost's gradient when it is its own matrix (sum_steps)
   float* gx0;                 // (n, d)
   int sum_steps;              // 1: time-invariant parameters, gradients summed over the steps
+  int past_caches = 0;        // d = 16: 1: the gradients of the steps are written past the caches
 };
 
 constexpr int CXT_RMAX = 64;  // most basis matrices per group

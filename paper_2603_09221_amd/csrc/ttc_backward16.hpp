@@ -25,7 +25,17 @@ __device__ __forceinline__ floatx4 dot16(const floatx4& a, const floatx4& b) {
   return e + o;
 }
 
-template <typename TIn>
+// PAST: the gradients of the steps are written past the caches (use_past_caches, ttc_api.hip).  A template argument: of a
+// branch around the two stores the compiler makes one plain store.
+template <bool PAST>
+__device__ __forceinline__ void store_gradient16(float* p, const floatx4& v) {
+  if constexpr (PAST)
+    __builtin_nontemporal_store(v, reinterpret_cast<floatx4*>(p));
+  else
+    *reinterpret_cast<floatx4*>(p) = v;
+}
+
+template <typename TIn, bool PAST>
 __global__ void __launch_bounds__(64, 4) backward16_kernel(const BackwardArgs ba) {
   constexpr int D = 16, DD = D * D;
   using C = Cfg<D>;
@@ -185,10 +195,10 @@ __global__ void __launch_bounds__(64, 4) backward16_kernel(const BackwardArgs ba
       if (!ba.sum_steps) {
         const long long o = (prob * T + s) * DD + i * D + 4 * g;
         const floatx4 nan4 = floatx4{nanv, nanv, nanv, nanv};
-        *reinterpret_cast<floatx4*>(ba.gA + o) = info ? nan4 : sA;
-        *reinterpret_cast<floatx4*>(ba.gB + o) = info ? nan4 : sB;
-        *reinterpret_cast<floatx4*>(ba.gQ + o) = info ? nan4 : sQ;
-        *reinterpret_cast<floatx4*>(ba.gR + o) = info ? nan4 : sR;
+        store_gradient16<PAST>(ba.gA + o, info ? nan4 : sA);
+        store_gradient16<PAST>(ba.gB + o, info ? nan4 : sB);
+        store_gradient16<PAST>(ba.gQ + o, info ? nan4 : sQ);
+        store_gradient16<PAST>(ba.gR + o, info ? nan4 : sR);
       }
       xt_own = xo;
       xt_other = xx;

@@ -131,3 +131,21 @@ def test_gradients_lose_no_more_to_rounding_than_tree_sums_do(d, T, n):
     ratio = 1e7 * np.sqrt(num / den) / np.array(TREE_SUMS[d, T, n])
     print(d, T, ratio)
     assert ratio.mean() <= 1.005
+
+
+@pytest.mark.parametrize("dtype,n,tol", [("f32", 6103, TOL), ("f32", 6104, TOL), ("bf16", 12207, 2e-3), ("bf16", 12208, 2e-3)])
+def test_gradients_on_either_side_of_the_caches_size(dtype, n, tol):
+    """d = 16, T = 8: up to 200 MB of matrices the steps' gradients are written past the caches, above that they are not; the
+    problems at both ends of the batch against the oracle (tolerances as in the tests above)."""
+    d, T = 16, 8
+    b = synth.make_tv_batch(n, d, d, T, seed=21, device=DEV, dtype=dtype)
+    g = draw_g(n, d, 8)
+    out = binding.ttc_lqr_backward_tv(b.A, b.B, b.Q, b.R, b.x0, g)
+    torch.cuda.synchronize()
+    assert int(out["info"].abs().max()) == 0
+    keys = ("gA", "gB", "gQ", "gR", "gx0")
+    assert all(bool(torch.isfinite(out[k]).all()) for k in keys)
+    pick = torch.cat([torch.arange(24), torch.arange(n - 24, n)]).to(DEV)
+    A, B, Q, R, x0 = (t[pick].float().cpu().double().numpy() for t in (b.A, b.B, b.Q, b.R, b.x0))
+    ref = go.lqr_gradients_tv(A, B, Q, R, x0, g[pick].cpu().double().numpy())
+    check({k: out[k][pick] for k in keys + ("info",)}, ref, keys, tol=tol)
