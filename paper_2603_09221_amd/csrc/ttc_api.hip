@@ -703,11 +703,13 @@ static void fill_cxt_args(ttc::CxtArgs& a, const ttc_lqr_cxt_problem_t* q) {
 static hipError_t run_cxt(const ttc::CxtArgs& a, bool bf16, hipStream_t st) {
   // Two wavefronts a SIMD, or three.  A round of three takes 1.4 times as long as one of two (131072 problems, T = 8: 11 rounds of 53 us, 16
   // of 38; 32768 problems: 3 and 4, 158 us and 148), and what leaves every gain in memory is faster with two (backward pass, 60000 problems,
-  // T = 12: 0.99 ms against 1.01).  Batches that two do not fill four problems at a time go one problem to a wavefront.
+  // T = 12: 0.99 ms against 1.01), as are calls that want the matrices P_0 or K_0 (two / three, u_0 alone, 1048576 problems, T = 8 4.85 /
+  // 4.76 ms, 262144, T = 16 2.24 / 2.16; with both matrices 1048576 problems 4.90 / 5.03, 100000, T = 4 0.278 / 0.319).  Batches that two do not fill four problems at a time go one problem to a wavefront.
   const long long two = ttc::grid_blocks(ttc::KIND_CXT, 16, bf16), three = ttc::grid_blocks(ttc::KIND_CXT_THREE, 16, bf16);
   const bool single = a.s.n <= two;
   const long long items = single ? a.s.n : (a.s.n + 3) / 4;
-  const int waves = !single && !a.roll_ws && 7 * ((items + three - 1) / three) < 5 * ((items + two - 1) / two) ? 3 : 2;
+  const bool stores = a.roll_ws || a.s.P0 || a.s.K0;
+  const int waves = !single && !stores && 7 * ((items + three - 1) / three) < 5 * ((items + two - 1) / two) ? 3 : 2;
   const long long gb = waves == 3 ? three : two;
   const dim3 grid((unsigned)(items < gb ? items : gb));
   return ttc::launch_cxt(a, bf16, single ? 1 : 4, waves, grid, st);

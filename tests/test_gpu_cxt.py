@@ -192,14 +192,18 @@ def test_extreme_modulation_and_weights():
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_two_and_three_wavefronts_a_simd_agree_bit_for_bit(n, dtype):
     """A batch that a round of three wavefronts a SIMD suits better (also with a ragged last four) against the same problems in a batch that
-    takes two: the same operations in the same order."""
+    takes two, and against the call that wants the matrices too, which takes two at any size: the same operations in the same order."""
     b = synth.make_contextual_batch(n, 16, 7, 3, seed=5, device=DEV, dtype=dtype)
     few = 20000
     args = [getattr(b, k) for k in b.PER_PROBLEM]
-    out = binding.ttc_lqr_solve_cxt(*args, b.Bbasis, b.Qbasis, b.x0, b.T)
+    small = dict(want_P0=False, want_K0=False)
+    out = binding.ttc_lqr_solve_cxt(*args, b.Bbasis, b.Qbasis, b.x0, b.T, **small)
+    full = binding.ttc_lqr_solve_cxt(*args, b.Bbasis, b.Qbasis, b.x0, b.T)
     part = lambda lo, hi: binding.ttc_lqr_solve_cxt(*(a[lo:hi].contiguous() for a in args), b.Bbasis, b.Qbasis, b.x0[lo:hi].contiguous(), b.T)
     head, tail = part(0, few), part(n - few, n)
     torch.cuda.synchronize()
     assert int(out["info"].abs().max()) == 0
+    for k in ("u0", "value"):
+        assert torch.equal(out[k], full[k]), k
     for k in ("P0", "K0", "u0", "value"):
-        assert torch.equal(out[k][:few], head[k]) and torch.equal(out[k][n - few:], tail[k]), k
+        assert torch.equal(full[k][:few], head[k]) and torch.equal(full[k][n - few:], tail[k]), k
