@@ -125,14 +125,14 @@ def default_squares(d, T, bf16, own_QT=False):
 
 def alg_flops_squaring(d, T):
     """Algorithmic flops of one problem on the default path where it squares: the schedule of alg_flops_doubling, whose last
-    step is the printed one (six products and the solve with the positive definite R + B^T P B), and A factored for its
-    report (2/3 d^3)."""
-    return alg_flops_doubling(d, T) + (2.0 / 3 - (8 + 8.0 / 3) + 6 * 2 + 1.0 / 3 + 2) * d ** 3
+    step is the printed one (six products and the solve with the positive definite R + B^T P B)."""
+    return alg_flops_doubling(d, T) + (-(8 + 8.0 / 3) + 6 * 2 + 1.0 / 3 + 2) * d ** 3
 
 
 def alg_flops_default(d, T, groups, bf16, rebase_every=0):
-    """Algorithmic flops of one problem on the default path: the sequential product, or the squaring schedule."""
-    if rebase_every or not default_squares(d, T, bf16):
+    """Algorithmic flops of one problem on the default path: the sequential product, or the squaring schedule (at d = 16 at
+    every horizon)."""
+    if rebase_every or not (d == 16 or default_squares(d, T, bf16)):
         return alg_flops(d, T, groups)
     return alg_flops_squaring(d, T)
 
@@ -785,7 +785,7 @@ def main():
     kernel_name = {"doubling": "doubling_kernel<%d>", "tv": "solve_tv_kernel<%d>", "bwd": "backward_kernel<%d>",
                    "rollout": "rollout_kernel<%d>"}.get(
         path, "squaring_kernel<%d>" if squares else "solve_kernel<%d>") % d if d != 16 or path in ("doubling", "bwd", "rollout") else (
-        "solve_tv_small_kernel" if path == "tv" else "solve_small_kernel")
+        "solve_tv_small_kernel" if path == "tv" else "solve_small_kernel" if k else "squaring16_kernel")
     res = {
         "metric": "LQR backward passes/sec (gradients of a loss of u0) at d=%d, T=%d" % (d, T) if path == "bwd" else
                   "LQR rollouts/sec (all controls, states and the cost) at d=%d, T=%d" % (d, T) if path == "rollout" else

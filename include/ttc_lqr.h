@@ -379,7 +379,7 @@ typedef struct {
  * (NULL to skip): h0 (n_tokens, H*16); o (n_tokens, H*16); info (n_tokens*H), as ttc_lqr_solve_cxt reports it for
  * the problem of token t, head h at [t*H + h] (a problem that broke down gives NaN in its token's x_out).
  * workspace: DEVICE, 16-byte aligned, ttc_block_workspace_bytes(block) bytes (TTC_ERR_WORKSPACE otherwise; the size
- * depends on n_tokens, H, r only).  Seven launches on hip_stream; allocates nothing; asynchronous. */
+ * depends on n_tokens, H, r only).  Five or six launches on hip_stream; allocates nothing; asynchronous. */
 size_t ttc_block_workspace_bytes(const ttc_block_t *block);
 ttc_status_t ttc_block_forward(const ttc_block_t *block, const void *x_in, void *x_out, float *h0, float *o,
                                int32_t *info, void *workspace, size_t workspace_bytes, void *hip_stream);

@@ -11,10 +11,11 @@
 // P (A - E), A^T Y = E Y + (A - E)^T Y; none where the entry is below 1/2) costs one addition in the accumulator and leaves the product with what is small where the
 // dynamics are near the identity; gradients of 8 steps at d = 64 are off by 0.7 times what float32 products gave (24 steps: 0.6).
 //
-// Measured, T = 8, float32, float32 products -> split: roll-out d = 64, 4096 problems 1.36 -> 0.99 ms, d = 32, 8192 problems 0.44 ->
-// 0.40, d = 128, 512 problems 1.42 -> 0.92; backward pass d = 64, 8192 problems 2.91 -> 2.29; ttc_lqr_solve_tv d = 64, 1024
-// problems 0.36 -> 0.29; at d = 32 and 1024 problems, where a step alone counts, 0.081 -> 0.090.  At d = 64 a step of one problem alone takes 24 thousand cycles (28), of which the dense solve is 13:
-// what is left is its serial chain, hidden as far as three workgroups a compute unit allow.
+// Measured, T = 8, float32, float32 products -> split -> split, with the inverse of a pivot block by blocks of four pivots and the
+// wavefront on the serial chain at a higher priority: roll-out d = 64, 4096 problems 1.36 -> 0.99 -> 0.94 ms; backward pass d = 64, 8192
+// problems 2.91 -> 2.29 -> 2.20.  Float32 products -> split: roll-out d = 32, 8192 problems 0.44 -> 0.40, d = 128, 512 problems 1.42 ->
+// 0.92; ttc_lqr_solve_tv d = 64, 1024 problems 0.36 -> 0.29; at d = 32 and 1024 problems, where a step alone counts, 0.081 -> 0.090.
+// What is left at d = 64 is the dense solve's serial chain, half of a step, hidden as far as three workgroups a compute unit allow.
 #pragma once
 #include "ttc_common.hpp"
 #include "ttc_small.hpp"

@@ -261,11 +261,13 @@ __device__ __forceinline__ void cost_in_units(Cols<D>& m, const float* u, int w,
 
 // One column tile per wavefront at d >= 64 (build.py): two at d = 128 leave one wavefront a SIMD (T = 16, 8192 problems 14.9 against
 // 11.6 ms), at d = 64 two wavefronts (T = 8, 16384 problems 2.73 against 2.55 ms with one tile and three wavefronts).  The registers
-// do not hold all of it (104 spilled at d = 64, 426 at d = 128, around the inverse), which costs less than another wavefront would.
+// do not hold all of it (100 spilled at d = 64, 470 at d = 128, around the inverse), which costs less than another wavefront would.
 // The recursion and the solves of the problems given up are in a kernel of their own: inlined here they spilled many more.
-// Measured, products in float32 with row blocks in registers -> this, float32: d = 64, T = 8, 16384 problems 3.21 -> 2.39 ms, T = 64,
-// 4099 problems 1.50 -> 0.94; d = 128, T = 16, 8192 problems 16.3 -> 10.3; bfloat16 inputs, T = 32, 4096 problems 9.77 -> 6.24.
-// Errors against float64: 0.65e-6 (0.87 before), 0.56e-6 (0.77), 1.3e-6 (1.9), 1.5e-6 (2.4).
+// Measured, products in float32 with row blocks in registers -> split products -> this, with A proved regular instead of factored, the
+// inverse by blocks and the chain's priority (and at d = 128 the operands' largest entry by the IEEE maximum), ms: d = 64, T = 8, 16384
+// problems 3.21 -> 2.40 -> 2.27, T = 64, 4099 problems 1.50 -> 0.944 -> 0.905; d = 128, T = 16, 8192 problems 16.3 -> 10.3 -> 9.63;
+// bfloat16 inputs, T = 32, 4096 problems 9.77 -> 6.25 -> 5.72.  Errors against float64 with products in float32 -> split: 0.87e-6 ->
+// 0.65e-6, 0.77e-6 -> 0.56e-6, 1.9e-6 -> 1.3e-6, 2.4e-6 -> 1.5e-6; no larger since.
 template <int D, typename TIn>
 __global__ void __launch_bounds__(Cfg<D>::NTHR, (D) == 64 ? 3 : 2) squaring_kernel(const DoublingArgs da) {
   using C = Cfg<D>;
