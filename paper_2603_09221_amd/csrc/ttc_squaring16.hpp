@@ -25,6 +25,13 @@ static constexpr float SQUARE16_FIRST_F32 = 8.f, SQUARE16_FIRST_BF16 = 24.f, SQU
 // Elimination is in order up to this; above it, and where a late one meets a pivot below PIVOT16_LATE (one in two thousand problems at
 // T = 31, rho(A) = 1.1), it searches pivots.  In the first squaring a small pivot means a stage cost that is not semidefinite.
 static constexpr float SQUARE16_IN_ORDER = 24.f, PIVOT16_FIRST = 0.25f, PIVOT16_LATE = 0.0625f;
+// The limit on the diagonal of the inverses of I + G_e H_e and I + P G_e.  Stage costs that are not semidefinite lose digits where an
+// eigenvalue of such a matrix comes near 0, on its way below, and its inverse becomes large; with semidefinite ones it has eigenvalues
+// within (0, 1].  The diagonal, as the other entries depend on the units of the states.  The algorithm in float32 against float64: semidefinite
+// costs (of low rank, in units far apart, unstable, cheap control: 1800 problems) up to 1.47; 14000 problems with eigenvalues of Q below 0,
+// T = 3 to 32, kept under a limit of 2: one off by more than 1e-4 and ten times what the recursion with general solves is (1.1 times that),
+// of 3: six, without a limit 100 times as many (one of two, Q = I with one eigenvalue of -1, T = 4: up to 7.8e-3).
+static constexpr float SQUARE16_INVERSE = 2.f;
 
 // Four registers a lane of four matrices (x[q], lane group g: the entries 4g + v of a row) to a row of sixteen per lane, matrix q in
 // lane group q, and back: registers and lane groups change places, four swaps for each v.
@@ -132,6 +139,22 @@ __device__ __forceinline__ bool negative_diagonal16(const floatx4 (&H)[PPW], int
 #pragma unroll
     for (int v = 0; v < 4; ++v) least = 4 * g + v == i ? __builtin_fminf(least, H[q][v]) : least;
   return __any(least < 0.f);
+}
+
+// Whether a diagonal entry is above the limit in magnitude, or not a number; first of all the entries, which in most problems are below.
+template <int PPW>
+__device__ __forceinline__ bool large_diagonal16(const floatx4 (&M)[PPW], float limit, int i, int g) {
+  float all = 0.f, on = 0.f;
+#pragma unroll
+  for (int q = 0; q < PPW; ++q)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) all = __builtin_elementwise_maximum(all, __builtin_fabsf(M[q][v]));
+  if (!__any(!(all <= limit))) return false;
+#pragma unroll
+  for (int q = 0; q < PPW; ++q)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) on = 4 * g + v == i ? __builtin_elementwise_maximum(on, __builtin_fabsf(M[q][v])) : on;
+  return __any(!(on <= limit));
 }
 
 // What squaring cannot do, by the recursion (recursion) or by the sequential product of solve_small_kernel, which also is for what breaks
@@ -294,6 +317,7 @@ __device__ __forceinline__ int square_quad16(const DoublingArgs& da, long long q
       pivoted = true;
     }
     if (__builtin_expect(pivoted, 0) && invert_pivoted16<PPW>(n, Wm, lane)) return 2;
+    if (large_diagonal16<PPW>(n, SQUARE16_INVERSE, i, g)) return 2;
     zero16<PPW>(x);
     if (apply) {
       mul16<PPW>(x, P, A);

@@ -100,3 +100,53 @@ def test_dense_dynamics(n):
     assert int(out["info"].abs().max()) == 0
     for k, v in solve_errors(out, oracle_solve(b)).items():
         assert v <= 2e-5, (k, v)
+
+
+def recursion64(A, B, Q, R, T):
+    """P_0 and K_0 of the printed recursion in float64 with general solves (R + B^T P B need not be positive definite)."""
+    t = lambda M: M.swapaxes(-1, -2)
+    A, B, Q, R = (M.double().cpu().numpy() for M in (A, B, Q, R))
+    Q, R = 0.5 * (Q + t(Q)), 0.5 * (R + t(R))
+    P = Q
+    for s in range(T - 1, -1, -1):
+        F = t(B) @ P @ A
+        K = -np.linalg.solve(R + t(B) @ P @ B, F)
+        P = (Q if s else 0) + t(A) @ P @ A + t(F) @ K
+        P = 0.5 * (P + t(P))
+    return {"P0": P, "K0": K}
+
+
+def indefinite(kind, n, T):
+    """Stage costs with eigenvalues of about -0.2, or, with B and R near the identity, one of -1 under a positive diagonal."""
+    b = synth.make_batch(n, D, D, T, seed=D + T, device=DEV)
+    eye = torch.eye(D, device=DEV)
+    if kind == "shifted":
+        b.Q.sub_(0.2 * eye)
+        return b
+    gen = torch.Generator().manual_seed(n + T)
+    turn = torch.linalg.qr(torch.randn((n, D, D), generator=gen, dtype=torch.float64))[0]
+    Q = (torch.eye(D, dtype=torch.float64) - 2 * turn[:, :, :1] @ turn[:, :, :1].transpose(1, 2)).float().to(DEV)
+    assert kind == "turned"
+    keep = (Q.diagonal(dim1=1, dim2=2) > 0).all(1)
+    Q[~keep] = eye
+    return synth.LqrBatch(b.A, eye + 0.1 * b.B, Q, eye.repeat(n, 1, 1), b.x0, T)
+
+
+@pytest.mark.parametrize("n", [400, 3300])
+@pytest.mark.parametrize("kind,T", [("shifted", 4), ("shifted", 12), ("shifted", 15), ("shifted", 32), ("turned", 3), ("turned", 4),
+                                    ("turned", 8)])
+def test_a_stage_cost_that_is_not_semidefinite_is_answered_as_by_the_product(n, kind, T):
+    """Squaring loses their digits where I + G H comes near a singular matrix, be it in a late squaring and under a positive diagonal; the
+    sequential product, whose solves are pivoted, answers them.  What it answers is answered, and as well: problems near a singular
+    R + B^T P B lose digits on either path, and there the errors of two float32 evaluations are independent draws, for which 10 is allowed.
+    One problem may be beyond that: of the shifted ones, a float32 recursion with general solves is with 4 to 6 of 400, 14 to 47 of 3300."""
+    b = indefinite(kind, n, T)
+    out, seq = solve(b), solve(b, rebase_every=3)
+    ref = recursion64(b.A, b.B, b.Q, b.R, T)
+    answered = (seq["info"] == 0).cpu().numpy()
+    assert answered.mean() >= 0.5
+    assert not out["info"].cpu().numpy()[answered].any()
+    rel = lambda o, k: np.linalg.norm(o[k].double().cpu().numpy() - ref[k], axis=(1, 2)) / np.linalg.norm(ref[k], axis=(1, 2))
+    err, err_seq = (np.maximum(rel(o, "P0"), rel(o, "K0"))[answered] for o in (out, seq))
+    print(kind, T, "median %.1e %.1e, largest %.1e %.1e" % (np.median(err), np.median(err_seq), err.max(), err_seq.max()))
+    assert (err > np.maximum(1e-4, 10 * err_seq)).sum() <= 1
