@@ -63,6 +63,9 @@ UNIT_FLAGS = {("k_backward.hip", 64): [_ONE_ROW_BLOCK % 64, _THREE_WAVES],
               ("k_squaring.hip", 64): [_ONE_ROW_BLOCK % 64],
               ("k_squaring.hip", 128): [_ONE_ROW_BLOCK % 128]}
 
+# Sources whose functions that are not inlined read and write the problems' matrices (not one by one, as those of the split products)
+NO_FLAT = ("k_squaring16.hip",)
+
 _NOISE = "is not a recognized feature for this target"
 
 
@@ -106,6 +109,20 @@ def misplaced_vector_moves(asm: str) -> list:
     return found
 
 
+def flat_accesses(asm: str) -> list:
+    """(kernel or function, line number, instruction) of flat memory instructions: reads and writes through a pointer of which the
+    compiler could not see whether it is to device memory or to LDS.  The counters of both wait for them; in_memory() and in_lds()
+    in ttc_device.hpp tell a function that is not inlined."""
+    function, found = None, []
+    for n, line in enumerate(asm.split("\n"), 1):
+        label = re.match(r"^([A-Za-z_$][\w$]*):", line)
+        if label:
+            function = label.group(1)
+        elif re.match(r"\s+flat_(load|store|atomic)", line):
+            found.append((function, n, line.strip()))
+    return found
+
+
 def _compile(job):
     """Compile one object in a folder of its own, where the compiler leaves its assembly, and look through that."""
     cmd, obj = job
@@ -118,10 +135,11 @@ def _compile(job):
     if len(listings) != 1:
         raise RuntimeError("%s: %d device listings" % (out, len(listings)))
     with open(listings[0]) as f:
-        found = misplaced_vector_moves(f.read())
-    if found:
-        raise RuntimeError("vector instructions ahead of an EXEC restore (%s):\n%s"
-                           % (" ".join(cmd), "\n".join("%s line %d: %s" % x for x in found)))
+        asm = f.read()
+    for what, found in (("vector instructions ahead of an EXEC restore", misplaced_vector_moves(asm)),
+                        ("flat memory instructions", flat_accesses(asm) if os.path.basename(cmd[-1]) in NO_FLAT else [])):
+        if found:
+            raise RuntimeError("%s (%s):\n%s" % (what, " ".join(cmd), "\n".join("%s line %d: %s" % x for x in found)))
     os.replace(out, obj)
     shutil.rmtree(folder)
 

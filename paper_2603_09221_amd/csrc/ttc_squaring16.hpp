@@ -107,7 +107,7 @@ __device__ __forceinline__ bool near_diagonal16(const floatx4& A, int i, int g) 
 // it.  Returns, uniformly, whether one broke down.
 template <int PPW>
 __device__ __attribute__((noinline)) bool solve_rows16_called(float (*Wm)[16 * Cfg<16>::PITCH], int lane) {
-  return __any(solve_rows16<true>(Wm[(lane >> 4) & (PPW - 1)], lane));
+  return __any(solve_rows16<true>(in_lds(Wm)[(lane >> 4) & (PPW - 1)], lane));
 }
 template <int PPW>
 __device__ __forceinline__ bool invert_pivoted16(floatx4 (&x)[PPW], float (*Wm)[16 * Cfg<16>::PITCH], int lane) {
@@ -160,8 +160,16 @@ __device__ __forceinline__ bool large_diagonal16(const floatx4 (&M)[PPW], float 
 // What squaring cannot do, by the recursion (recursion) or by the sequential product of solve_small_kernel, which also is for what breaks
 // the recursion down; a function of its own, as few problems need it.
 template <typename TIn, int PPW>
-__device__ __attribute__((noinline)) void solve_otherwise16(const SolveArgs& p, long long quad, bool recursion,
-                                                            float (*Wm)[16 * Cfg<16>::PITCH], float* s_red, float (*s_x0)[16]) {
+__device__ __attribute__((noinline)) void solve_otherwise16(const SolveArgs args, long long quad, bool recursion,
+                                                            float (*Wm_)[16 * Cfg<16>::PITCH], float* s_red_, float (*s_x0_)[16]) {
+  SolveArgs p = args;
+  p.A = in_memory(args.A); p.B = in_memory(args.B); p.Q = in_memory(args.Q); p.R = in_memory(args.R); p.QT = in_memory(args.QT);
+  p.x0 = in_memory(args.x0);
+  p.P0 = in_memory(args.P0); p.K0 = in_memory(args.K0); p.u0 = in_memory(args.u0); p.value = in_memory(args.value);
+  p.info = in_memory(args.info);
+  float(*const Wm)[16 * Cfg<16>::PITCH] = in_lds(Wm_);
+  float* const s_red = in_lds(s_red_);
+  float(*const s_x0)[16] = in_lds(s_x0_);
   if (recursion) {
     long long prob[PPW];
     bool valid[PPW];
@@ -398,9 +406,8 @@ __global__ void __launch_bounds__(64, PPW == 4 ? 2 : 3) squaring16_kernel(const 
   for (long long quad = blockIdx.x; quad < nquads; quad += gridDim.x) {
     const int why = uniform(square_quad16<TIn, PPW>(da, quad, Wm));
     if (__builtin_expect(why != 0, 0)) {
-      const SolveArgs p = da.s;  // (a copy: its address is handed on)
       __syncthreads();
-      solve_otherwise16<TIn, PPW>(p, quad, why == 1, Wm, s_red, s_x0);
+      solve_otherwise16<TIn, PPW>(da.s, quad, why == 1, Wm, s_red, s_x0);
       __syncthreads();
     }
   }

@@ -38,3 +38,11 @@ def test_joins_that_nobody_skips_to_and_other_code_are_left_alone():
     assert not build.misplaced_vector_moves((BODY % (move, NOTHING, NOTHING)).replace("s_cbranch_execz", "s_cbranch_scc0"))
     assert not build.misplaced_vector_moves(BODY % (move, "v_add_f32_e32 v4, v4, v4", NOTHING))
     assert not build.misplaced_vector_moves(BODY % (move, "s_and_b64 exec, exec, s[8:9]", NOTHING))
+
+
+def test_flat_accesses_are_found():
+    text = BODY % (NOTHING, "flat_load_dwordx4 v[0:3], v[4:5]", "flat_store_dword v[4:5], v0 offset:16")
+    assert [(k, x.split()[0]) for k, _, x in build.flat_accesses(text)] == [("a_kernel", "flat_load_dwordx4"),
+                                                                          ("a_kernel", "flat_store_dword")]
+    assert not build.flat_accesses(BODY % (NOTHING, "global_load_dwordx4 v[0:3], v[4:5], off", "ds_read_b128 v[0:3], v4"))
+    assert not build.flat_accesses("\t.amdhsa_uses_flat_scratch 0\n\t.max_flat_workgroup_size: 64\n; flat_load_dword v0, v[2:3]\n")
