@@ -66,6 +66,9 @@ UNIT_FLAGS = {("k_backward.hip", 64): [_ONE_ROW_BLOCK % 64, _THREE_WAVES],
 # Sources whose functions that are not inlined read and write the problems' matrices (not one by one, as those of the split products)
 NO_FLAT = ("k_squaring16.hip",)
 
+# Vector registers that a kernel of a unit may spill: these lose time by what is inlined into them (the inverse of a pivot block, the recursion)
+MOST_SPILLED = {("k_solve.hip", 128): 160, ("k_tv.hip", 128): 90}
+
 _NOISE = "is not a recognized feature for this target"
 
 
@@ -123,6 +126,12 @@ def flat_accesses(asm: str) -> list:
     return found
 
 
+def spilled_registers(asm: str) -> list:
+    """(kernel, vector registers spilled) of a listing, from the kernels' metadata at its end."""
+    return [(name, int(count)) for name, count in
+            re.findall(r"^\s+\.name:\s+(_Z\w+)$(?:(?!^\s+\.name:).)*?^\s+\.vgpr_spill_count:\s+(\d+)$", asm, re.M | re.S)]
+
+
 def _compile(job):
     """Compile one object in a folder of its own, where the compiler leaves its assembly, and look through that."""
     cmd, obj = job
@@ -136,8 +145,12 @@ def _compile(job):
         raise RuntimeError("%s: %d device listings" % (out, len(listings)))
     with open(listings[0]) as f:
         asm = f.read()
+    unit = (os.path.basename(cmd[-1]), next((int(a[8:]) for a in cmd if a.startswith("-DTTC_D=")), None))
+    spilled = [x for x in spilled_registers(asm) if x[1] > MOST_SPILLED.get(unit, x[1])]
+    if spilled:
+        raise RuntimeError("more than %d spilled vector registers (%s): %s" % (MOST_SPILLED[unit], " ".join(cmd), spilled))
     for what, found in (("vector instructions ahead of an EXEC restore", misplaced_vector_moves(asm)),
-                        ("flat memory instructions", flat_accesses(asm) if os.path.basename(cmd[-1]) in NO_FLAT else [])):
+                        ("flat memory instructions", flat_accesses(asm) if unit[0] in NO_FLAT else [])):
         if found:
             raise RuntimeError("%s (%s):\n%s" % (what, " ".join(cmd), "\n".join("%s line %d: %s" % x for x in found)))
     os.replace(out, obj)

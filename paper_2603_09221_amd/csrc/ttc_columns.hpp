@@ -349,6 +349,10 @@ __device__ __forceinline__ int solve_cols(float* Wp, Cols<D>& s, floatx4 (&f)[D 
   using C = Cfg<D>;
   constexpr int NT = C::NT, CT = C::RB;
   constexpr bool LOCAL = C::NW == 1;  // one wavefront: the refinement's operand stays in it
+  // The pivot block's inverse by blocks of four pivots, or by columns.  At d = 128 a wavefront holds eight tiles beside it, and -M^T and the panel
+  // of four make registers spill around it that the columns leave alone (solve_tv_kernel 104 / 83, T = 8, 1024 problems 2.05 / 1.90 ms; the
+  // recursion behind squaring, T = 16, 512 problems 2.01 / 1.87; roll-out, 512 problems of 6 steps, 0.694 / 0.706).
+  constexpr bool BLOCKS = D < 128;
   const int i = lane & 15, g = lane >> 4;
   w = uniform(w);
   int bad = 0;
@@ -367,7 +371,8 @@ __device__ __forceinline__ int solve_cols(float* Wp, Cols<D>& s, floatx4 (&f)[D 
       for (int v = 0; v < 4; ++v) o[32 + v * C::PITCH] = -s[0][k][v];
     }
     floatx4 inv = s[0][k];
-    bad |= invert_spread16(inv, Wp + 16 * buf, C::PITCH, lane, piv_min);
+    if constexpr (BLOCKS) bad |= invert_spread16(inv, Wp + 16 * buf, C::PITCH, lane, piv_min);
+    else bad |= invert_columns16(inv, lane, piv_min);
 #pragma unroll
     for (int r = 0; r < NT; ++r) {
       const floatx4 x = r == 0 ? inv : -s[r][k];

@@ -10,6 +10,17 @@
 
 namespace ttc {
 
+// The arguments as a function that is not inlined wants them: scalars, pointers known to be to device memory.
+__device__ __forceinline__ SolveArgs called_args(const SolveArgs& a) {
+  SolveArgs p = a;
+  p.n = uniform64(a.n); p.T = uniform(a.T); p.flags = uniform(a.flags); p.ngroups = uniform(a.ngroups);
+  p.A = in_memory(a.A); p.B = in_memory(a.B); p.Q = in_memory(a.Q); p.R = in_memory(a.R); p.QT = in_memory(a.QT); p.x0 = in_memory(a.x0);
+  p.sA = uniform64(a.sA); p.sB = uniform64(a.sB); p.sQ = uniform64(a.sQ); p.sR = uniform64(a.sR); p.sQT = uniform64(a.sQT); p.sx0 = uniform64(a.sx0);
+  p.P0 = in_memory(a.P0); p.K0 = in_memory(a.K0); p.u0 = in_memory(a.u0); p.value = in_memory(a.value); p.info = in_memory(a.info);
+  p.ws = in_memory(a.ws);
+  return p;
+}
+
 // Development aid: with -DTTC_PHASE_TIMERS, workgroup 0 accumulates s_memtime ticks per phase and adds
 // them to the eight counters of the argument block's debug buffer; otherwise no code.
 #ifdef TTC_PHASE_TIMERS

@@ -60,21 +60,23 @@ __device__ __forceinline__ int opaque_int(int x) {
 
 // A value that is the same in all lanes, as a scalar.  Branches on it become scalar branches; a branch on a lane value is
 // taken by masking lanes off, which matrix-core instructions do not heed.
-// A pointer of a function that is not inlined, as one to device memory or to LDS: there the compiler does not see which, and reads and
-// writes through it are flat instructions, which the counters of both wait for.
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ long long uniform64(long long x) {
+  return (long long)((unsigned long long)(unsigned)uniform((int)(unsigned)x) | (unsigned long long)(unsigned)uniform((int)(x >> 32)) << 32);
+}
+// An argument of a function that is not inlined, as a pointer to device memory, the same in all lanes, or to LDS.  There the compiler does
+// not see which it is, and reads and writes through it are flat instructions, which the counters of both wait for; and it stands in
+// vector registers, as does every address derived from it.
 template <typename T>
 __device__ __forceinline__ T* in_memory(T* p) {
-  auto q = (__attribute__((address_space(1))) T*)p;
-  asm("" : "+v"(q));  // (else the two conversions cancel out)
-  return (T*)q;
+  return (T*)(__attribute__((address_space(1))) T*)uniform64((long long)p);
 }
 template <typename T>
 __device__ __forceinline__ T* in_lds(T* p) {
   auto q = (__attribute__((address_space(3))) T*)p;
-  asm("" : "+v"(q));
+  asm("" : "+v"(q));  // (else the two conversions cancel out)
   return (T*)q;
 }
-__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
 template <int D>
 struct Cfg {

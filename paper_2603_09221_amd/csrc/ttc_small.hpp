@@ -191,7 +191,7 @@ __device__ __forceinline__ float broadcast_group(float x) {
 // through LDS.  Columns are taken four at a time: the four columns of a group are copied to every group first, where they
 // are kept up to date beside the lane's own four; a column then costs seven multiply-adds instead of fifteen.  Every entry
 // sees the operations of invert_regs16 in the same order.
-__device__ __forceinline__ int invert_columns16(floatx4& m, int lane) {
+__device__ __forceinline__ int invert_columns16(floatx4& m, int lane, float piv_min = 0.f) {
   const int g = lane >> 4;
   float a[4] = {m[0], m[1], m[2], m[3]};
   float mypiv = 1.f;
@@ -240,7 +240,7 @@ __device__ __forceinline__ int invert_columns16(floatx4& m, int lane) {
   });
   const float s = __builtin_amdgcn_rcpf(mypiv);
   m = floatx4{a[0] * s, a[1] * s, a[2] * s, a[3] * s};
-  return !(mypiv > 0.f && mypiv < __builtin_inff());
+  return !(mypiv > piv_min && mypiv < __builtin_inff());
 }
 
 // x of the sixteen lanes of group r (lane / 16) in every group, r = 0..3

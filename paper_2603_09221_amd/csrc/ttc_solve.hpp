@@ -22,6 +22,27 @@ __device__ __forceinline__ int first_thread(bool yes, int* s_first) {
   return uniform(first);
 }
 
+// The recursion for one problem of solve_kernel; returns whether a step broke down.
+template <int D, typename TIn>
+__device__ __forceinline__ int recursion_of_problem(Pair<D>& W, float* s_red, const SolveArgs& p, long long prob, int tid) {
+  const TIn* Ap = reinterpret_cast<const TIn*>(p.A) + prob * p.sA;
+  const TIn* Bp = reinterpret_cast<const TIn*>(p.B) + prob * p.sB;
+  const TIn* Qp = reinterpret_cast<const TIn*>(p.Q) + prob * p.sQ;
+  const TIn* Rp = reinterpret_cast<const TIn*>(p.R) + prob * p.sR;
+  const TIn* x0p = reinterpret_cast<const TIn*>(p.x0) + prob * p.sx0;
+  const TIn* QTp = p.QT ? reinterpret_cast<const TIn*>(p.QT) + prob * p.sQT : Qp;
+  return riccati_problem<D, TIn>(W, s_red, p, prob, p.T, Ap, Bp, Qp, Rp, 0, 0, 0, 0, QTp, nullptr, Qp, x0p, 2, tid);
+}
+// As a function of its own in solve_kernel at d = 128: inlined behind the product it costs that registers (131 spilled, 25 without; T = 4, 8192
+// problems 9.68 / 9.56 ms).  Problems of cheap control pay for the call (T = 4, 512 problems 0.770 / 0.788); solve_handed_kernel, which
+// is there for them, has it inlined.
+template <int D, typename TIn>
+__device__ __attribute__((noinline)) int recursion_called(lds_float* pair, lds_float* s_red, const SolveArgs args, long long prob,
+                                                          int tid) {
+  return recursion_of_problem<D, TIn>(*reinterpret_cast<Pair<D>*>(in_lds((float*)pair)), in_lds((float*)s_red), called_args(args),
+                                      uniform64(prob), tid);
+}
+
 // Solve kernel.  Persistent workgroups: workgroup b handles problems b, b + gridDim.x, ...
 //
 // Per problem the work is a sequence of phases, each "build [M | RHS] in LDS, dense solve, consume":
@@ -245,11 +266,11 @@ __device__ __forceinline__ void solve_problems(const SolveArgs& p) {
       // Prop. 3.1 as printed, from P_T: one positive definite solve per step, no A^{-1}, no accumulated factors
       // (what ttc_lqr_solve_tv runs, here with the same matrices in every step).  info: 2 + index of the step.
       __syncthreads();  // every wavefront has left the pair
-      const TIn* Bp = reinterpret_cast<const TIn*>(p.B) + prob * p.sB;
-      const TIn* Rp = reinterpret_cast<const TIn*>(p.R) + prob * p.sR;
-      const TIn* QTp = p.QT ? reinterpret_cast<const TIn*>(p.QT) + prob * p.sQT : Qp;
-      const int broke = riccati_problem<D, TIn>(W, s_red, p, prob, p.T, Ap, Bp, Qp, Rp, 0, 0, 0, 0, QTp, nullptr, Qp, x0p, 2,
-                                                tid + opaque_zero());
+      int broke;
+      if constexpr (D == 128 && !HANDED)
+        broke = recursion_called<D, TIn>((lds_float*)(float*)W, (lds_float*)s_red, p, prob, tid + opaque_zero());
+      else
+        broke = recursion_of_problem<D, TIn>(W, s_red, p, prob, tid + opaque_zero());
       if (HANDED && recursion && broke) {
         retry = true;
         prob -= gridDim.x;

@@ -261,7 +261,8 @@ __device__ __forceinline__ void cost_in_units(Cols<D>& m, const float* u, int w,
 
 // One column tile per wavefront at d >= 64 (build.py): two at d = 128 leave one wavefront a SIMD (T = 16, 8192 problems 14.9 against
 // 11.6 ms), at d = 64 two wavefronts (T = 8, 16384 problems 2.73 against 2.55 ms with one tile and three wavefronts).  The registers
-// do not hold all of it (100 spilled at d = 64, 470 at d = 128, around the inverse), which costs less than another wavefront would.
+// do not hold all of it (float32 / bfloat16 inputs 100 / 114 spilled at d = 64, 444 / 516 at d = 128, around the inverse), which costs less
+// than another wavefront would.
 // The recursion and the solves of the problems given up are in a kernel of their own: inlined here they spilled many more.
 // Measured, products in float32 with row blocks in registers -> split products -> this, with A proved regular instead of factored, the
 // inverse by blocks and the chain's priority (and at d = 128 the operands' largest entry by the IEEE maximum), ms: d = 64, T = 8, 16384

@@ -162,11 +162,8 @@ __device__ __forceinline__ bool large_diagonal16(const floatx4 (&M)[PPW], float 
 template <typename TIn, int PPW>
 __device__ __attribute__((noinline)) void solve_otherwise16(const SolveArgs args, long long quad, bool recursion,
                                                             float (*Wm_)[16 * Cfg<16>::PITCH], float* s_red_, float (*s_x0_)[16]) {
-  SolveArgs p = args;
-  p.A = in_memory(args.A); p.B = in_memory(args.B); p.Q = in_memory(args.Q); p.R = in_memory(args.R); p.QT = in_memory(args.QT);
-  p.x0 = in_memory(args.x0);
-  p.P0 = in_memory(args.P0); p.K0 = in_memory(args.K0); p.u0 = in_memory(args.u0); p.value = in_memory(args.value);
-  p.info = in_memory(args.info);
+  const SolveArgs p = called_args(args);
+  quad = uniform64(quad);
   float(*const Wm)[16 * Cfg<16>::PITCH] = in_lds(Wm_);
   float* const s_red = in_lds(s_red_);
   float(*const s_x0)[16] = in_lds(s_x0_);

@@ -86,7 +86,7 @@ __device__ __forceinline__ int riccati_problem(Pair<D>& W, float* s_red, const S
                                           pn, tid);
     if (flag && !info) info = info_base + T - s;
     if (s >= 1 && !info) {
-      next_value_matrix<D, TIn>(W, Qs + (long long)(s - 1) * tQ, pn, tid);
+      next_value_matrix<D, TIn>(W, Qs + (long long)(s - 1) * tQ, pn, tid + opaque_zero());
     } else {
       emit_step<D, TIn>(W, s_red, p, prob, wk, pn, Qflag, x0p, info, tid);
       break;

@@ -46,3 +46,18 @@ def test_flat_accesses_are_found():
                                                                           ("a_kernel", "flat_store_dword")]
     assert not build.flat_accesses(BODY % (NOTHING, "global_load_dwordx4 v[0:3], v[4:5], off", "ds_read_b128 v[0:3], v4"))
     assert not build.flat_accesses("\t.amdhsa_uses_flat_scratch 0\n\t.max_flat_workgroup_size: 64\n; flat_load_dword v0, v[2:3]\n")
+
+
+def test_spilled_registers_are_counted():
+    """The kernels' metadata as the compiler writes it, the names of arguments before the kernel's own; every unit with a limit is built."""
+    kernel = """  - .args:
+      - .name:           p
+        .size:           8
+    .name:           %s
+    .vgpr_count:     256
+    .vgpr_spill_count: %d
+"""
+    text = "amdhsa.kernels:\n" + kernel % ("_ZN3ttc8a_kernelEv", 104) + kernel % ("_ZN3ttc8b_kernelEv", 0)
+    assert build.spilled_registers(text) == [("_ZN3ttc8a_kernelEv", 104), ("_ZN3ttc8b_kernelEv", 0)]
+    units = {(src, d) for src, sizes in build.UNITS for d in (sizes or (None,))}
+    assert set(build.MOST_SPILLED) <= units
