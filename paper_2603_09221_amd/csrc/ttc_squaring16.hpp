@@ -22,6 +22,11 @@ namespace ttc {
 // recursion); growth that comes later is that of an unstable open loop, and the power reached is then applied as often as needed
 // instead of squared again.
 static constexpr float SQUARE16_FIRST_F32 = 8.f, SQUARE16_FIRST_BF16 = 24.f, SQUARE16_LATE = 256.f, SQUARE16_STOP = 16.f;
+// Where P starts from a terminal cost of its own, P G_e is a product of matrices that know nothing of each other, and elimination in order
+// loses more: pivots are searched from 12 on, or behind one below PIVOT16_FIRST (Q_T = 10 Q, T = 2 6.8e-5 with the limits above, 2.2e-6 so;
+// the sequential product 1.4e-5).  Without a running cost I + G_e H_e is the identity however fast G_e grows: there max |Q_T| max |G_e| is
+// looked at in its place, and from 64 on, as predicted, the power is kept.
+static constexpr float SQUARE16_QT_IN_ORDER = 12.f, SQUARE16_QT_STOP = 64.f;
 // Elimination is in order up to this; above it, and where a late one meets a pivot below PIVOT16_LATE (one in two thousand problems at
 // T = 31, rho(A) = 1.1), it searches pivots.  In the first squaring a small pivot means a stage cost that is not semidefinite.
 static constexpr float SQUARE16_IN_ORDER = 24.f, PIVOT16_FIRST = 0.25f, PIVOT16_LATE = 0.0625f;
@@ -157,6 +162,28 @@ __device__ __forceinline__ bool large_diagonal16(const floatx4 (&M)[PPW], float 
   return __any(!(on <= limit));
 }
 
+template <int PPW>
+__device__ __forceinline__ void identity16(floatx4 (&M)[PPW], int i, int g) {
+#pragma unroll
+  for (int q = 0; q < PPW; ++q)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) M[q][v] = 4 * g + v == i ? 1.f : 0.f;
+}
+
+// The largest magnitude of all entries, NaN on top.
+template <int PPW>
+__device__ __forceinline__ float largest16(const floatx4 (&M)[PPW]) {
+  uint32_t big = 0;
+#pragma unroll
+  for (int q = 0; q < PPW; ++q)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const uint32_t b = __float_as_uint(M[q][v]) & 0x7FFFFFFFu;
+      big = b > big ? b : big;
+    }
+  return __uint_as_float(wave_max_u32(big));
+}
+
 // What squaring cannot do, by the recursion (recursion) or by the sequential product of solve_small_kernel, which also is for what breaks
 // the recursion down; a function of its own, as few problems need it.
 template <typename TIn, int PPW>
@@ -188,7 +215,10 @@ __device__ __attribute__((noinline)) void solve_otherwise16(const SolveArgs args
 }
 
 // The wavefront's problems by squaring; 0, or why it was given up: 1 to the recursion, 2 to the product.
-template <typename TIn, int PPW>
+// OWN_QT: Q_T is a matrix of its own.  A template argument, as the registers of what only such problems need cost the others 3 % (16384
+// problems, T = 8, 68.4 -> 70.1 us); P is read and started under the argument da.p_from_qt all the same, without which the other instance
+// spills 15 registers for 11 (69.8).
+template <typename TIn, int PPW, bool OWN_QT>
 __device__ __forceinline__ int square_quad16(const DoublingArgs& da, long long quad, float (*Wm)[16 * Cfg<16>::PITCH]) {
   using C = Cfg<16>;
   constexpr float FIRST = sizeof(TIn) == 4 ? SQUARE16_FIRST_F32 : SQUARE16_FIRST_BF16;
@@ -234,17 +264,6 @@ __device__ __forceinline__ int square_quad16(const DoublingArgs& da, long long q
 #pragma unroll
     for (int q = 0; q < PPW; ++q) x[q] = R[q];
     if (invert16<PPW, true>(x, Wm, lane, 0.f)) return 2;
-    if (da.p_from_qt) {  // a terminal cost that will not pass the guard
-      float qt = 0.f, qs = 0.f;
-#pragma unroll
-      for (int q = 0; q < PPW; ++q)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          qt = __builtin_fmaxf(qt, __builtin_fabsf(P[q][v]));
-          qs = __builtin_fmaxf(qs, __builtin_fabsf(H[q][v]));
-        }
-      if (wave_max_nonneg(qt) > SQUARE16_LATE * wave_max_nonneg(qs)) return 1;
-    }
     zero16<PPW>(X);
     mul16<PPW>(X, x, BT);  // R^{-1} B^T, refined once
 #pragma unroll
@@ -257,13 +276,23 @@ __device__ __forceinline__ int square_quad16(const DoublingArgs& da, long long q
     zero16<PPW>(G);
     mul16<PPW>(G, BT, X);
     symmetrise16<PPW>(G, i, g);
+    if (OWN_QT && da.m && !(da.m & 1)) {
+      // A terminal cost over its limit with the first G_e already goes at once, not behind the squarings ahead of its application.  (By its
+      // size beside Q's, as before, one beside a small running cost went too, to the recursion: Q = 0, T = 8, 16384 problems 153 us, by
+      // squaring 90; T = 33 520, 134.)
+      identity16<PPW>(n, i, g);
+      mul16<PPW>(n, G, P);
+      if (!(largest16<PPW>(n) <= SQUARE16_LATE)) return 1;
+    }
   }
   // ---- P_1 by binary powering of the one-step map.  A turn either applies e to P or squares it: both begin with the inverse of a
   // matrix I + (symmetric)(symmetric), formed transposed.
   bool have_p = da.p_from_qt != 0;
   bool bit_done = false;  // P has had the current bit of m
   bool stay = false;      // e is not squared any further, but applied once for each factor of it that is left
-  float up_prev = 0.f;    // max |I + G_e H_e| - 1 of the squaring before, 0 before the first
+  float up_prev = 0.f;    // max |I + G_e H_e| - 1 (H = 0: max |Q_T| max |G_e|) of the squaring before, 0 before the first
+  float qt_max = 0.f;     // max |Q_T| if H = 0, or else 0
+  if constexpr (OWN_QT) qt_max = largest16<PPW>(H) == 0.f ? largest16<PPW>(P) : 0.f;
   for (int m = da.m; m;) {
     bool apply = false;
     if (!bit_done && ((m & 1) || stay)) {
@@ -285,37 +314,28 @@ __device__ __forceinline__ int square_quad16(const DoublingArgs& da, long long q
     }
     const bool only_H = !apply && m == 1 && !have_p;  // the last squaring, and P is still 0: A and G of the square are not needed
     auto form = [&] {
-#pragma unroll
-      for (int q = 0; q < PPW; ++q)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) n[q][v] = 4 * g + v == i ? 1.f : 0.f;
+      identity16<PPW>(n, i, g);
       if (apply) mul16<PPW>(n, G, P);  // (I + P G)^T
       else mul16<PPW>(n, H, G);        // (I + G H)^T
     };
     form();
-    uint32_t big = 0;
-#pragma unroll
-    for (int q = 0; q < PPW; ++q)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {  // as bits: NaN on top
-        const uint32_t b = __float_as_uint(n[q][v]) & 0x7FFFFFFFu;
-        big = b > big ? b : big;
-      }
-    const float mu = __uint_as_float(wave_max_u32(big));
-    const float up = mu - 1.f;
+    const float mu = largest16<PPW>(n);
+    const float up = (OWN_QT && qt_max != 0.f && !apply) ? qt_max * largest16<PPW>(G) : mu - 1.f;
     const bool early = !apply && up_prev == 0.f;
+    const bool own = OWN_QT && apply;
     if (!(mu <= (early ? FIRST : SQUARE16_LATE))) return negative_diagonal16<PPW>(H, i, g) ? 2 : 1;
     if (!apply) {
       // mu - 1 has grown by r, and the square of e will make it grow by r^2 at least
-      if (!only_H && up_prev != 0.f && up > 1.f && up > 2.f * up_prev && up * up * up > SQUARE16_STOP * up_prev * up_prev) {
+      const float stop = qt_max != 0.f ? SQUARE16_QT_STOP : SQUARE16_STOP;
+      if (!only_H && up_prev != 0.f && up > 1.f && up > 2.f * up_prev && up * up * up > stop * up_prev * up_prev) {
         stay = true;
         m *= 2;
         continue;
       }
       up_prev = up;
     }
-    bool pivoted = mu > SQUARE16_IN_ORDER;
-    if (!pivoted && invert16<PPW, false>(n, Wm, lane, early ? PIVOT16_FIRST : PIVOT16_LATE)) {
+    bool pivoted = mu > (own ? SQUARE16_QT_IN_ORDER : SQUARE16_IN_ORDER);
+    if (!pivoted && invert16<PPW, false>(n, Wm, lane, early || own ? PIVOT16_FIRST : PIVOT16_LATE)) {
       if (early) return 2;
       if (negative_diagonal16<PPW>(H, i, g)) return 2;
       form();
@@ -391,7 +411,7 @@ __device__ __forceinline__ int square_quad16(const DoublingArgs& da, long long q
   return 0;
 }
 
-template <typename TIn, int PPW>
+template <typename TIn, int PPW, bool OWN_QT>
 __global__ void __launch_bounds__(64, PPW == 4 ? 2 : 3) squaring16_kernel(const DoublingArgs da) {
   constexpr int D = 16;
   using C = Cfg<D>;
@@ -401,7 +421,7 @@ __global__ void __launch_bounds__(64, PPW == 4 ? 2 : 3) squaring16_kernel(const 
   __shared__ __attribute__((aligned(16))) float s_x0[PPW][D];
   const long long nquads = (da.s.n + PPW - 1) / PPW;
   for (long long quad = blockIdx.x; quad < nquads; quad += gridDim.x) {
-    const int why = uniform(square_quad16<TIn, PPW>(da, quad, Wm));
+    const int why = uniform(square_quad16<TIn, PPW, OWN_QT>(da, quad, Wm));
     if (__builtin_expect(why != 0, 0)) {
       __syncthreads();
       solve_otherwise16<TIn, PPW>(da.s, quad, why == 1, Wm, s_red, s_x0);

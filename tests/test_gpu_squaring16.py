@@ -150,3 +150,45 @@ def test_a_stage_cost_that_is_not_semidefinite_is_answered_as_by_the_product(n, 
     err, err_seq = (np.maximum(rel(o, "P0"), rel(o, "K0"))[answered] for o in (out, seq))
     print(kind, T, "median %.1e %.1e, largest %.1e %.1e" % (np.median(err), np.median(err_seq), err.max(), err_seq.max()))
     assert (err > np.maximum(1e-4, 10 * err_seq)).sum() <= 1
+
+
+@pytest.mark.parametrize("n", [9, 3074])
+@pytest.mark.parametrize("T", [4, 8, 17, 33])
+@pytest.mark.parametrize("share", [0.0, 1e-3])
+def test_a_terminal_cost_beside_a_small_running_cost_is_squared(n, T, share):
+    """The guard is on I + P G, which such a terminal cost passes: 2e-5 as on ordinary problems, and not what the recursion gives bit for
+    bit, which takes up to four times as long."""
+    b = synth.make_batch(n, D, D, T, seed=T, device=DEV, rho=0.98)
+    QT, b.Q = b.Q, share * b.Q
+    out = solve(b, QT=QT)
+    assert int(out["info"].abs().max()) == 0
+    for k, v in solve_errors(out, oracle_solve(b, QT=QT)).items():
+        assert v <= 2e-5, (k, v)
+    steps = [m[:, None].expand(-1, T, -1, -1).contiguous() for m in (b.A, b.B, b.Q, b.R)]
+    steps[2][:, T - 1] = QT
+    tv = binding.ttc_lqr_solve_tv(*steps, b.x0)
+    torch.cuda.synchronize()
+    assert not (out["P0"] == tv["P0"]).flatten(1).all(1).any()
+
+
+@pytest.mark.parametrize("n", [40, 3300])
+@pytest.mark.parametrize("T", [2, 8, 9])
+@pytest.mark.parametrize("qt,r", [(3.0, 1.0), (6.0, 1.0), (10.0, 1.0), (0.0, 0.1)])
+def test_a_terminal_cost_is_applied_as_accurately_as_by_the_product(n, T, qt, r):
+    """Q_T = 3 to 10 Q, and Q_T alone with a control a tenth as dear, where elimination of I + Q_T G in order meets small pivots: 2e-5 as on
+    ordinary problems (2e-6..5e-6; without a search for pivots up to 8e-5)."""
+    b = synth.make_batch(n, D, D, T, seed=1, device=DEV, r_scale=r)
+    if qt:
+        QT = (qt * b.Q).contiguous()
+    else:
+        QT, b.Q = b.Q, torch.zeros_like(b.Q)
+    out = solve(b, QT=QT)
+    assert int(out["info"].abs().max()) == 0
+    t = lambda M: M.swapaxes(-1, -2)
+    A, B, Q, R, P = (M.double().cpu().numpy() for M in (b.A, b.B, b.Q, b.R, QT))
+    for s in range(T - 1, -1, -1):
+        F = t(B) @ P @ A
+        K = -np.linalg.solve(R + t(B) @ P @ B, F)
+        P = (Q if s else 0) + t(A) @ P @ A + t(F) @ K
+    rel = lambda x, y: (np.linalg.norm(x.double().cpu().numpy() - y, axis=(1, 2)) / np.linalg.norm(y, axis=(1, 2))).max()
+    assert max(rel(out["P0"], P), rel(out["K0"], K)) <= 2e-5
