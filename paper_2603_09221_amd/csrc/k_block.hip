@@ -27,11 +27,15 @@ static bool split_is_faster(long long M, int N, int K, int cus, bool bf16) {
   const double split = (double)rounds * (bf16 ? 3900. + 8.2 * K : 5300. + 19.5 * K);
   return split <= 0.9 * (bf16 ? 7500. + 40. * K : 8500. + 84.4 * K);
 }
-// Short rows are read so fast that the split kernel forms their statistics itself, in every workgroup that needs them, which costs less
-// than a launch for them while there are few (the block with / without the launch, us a call: K = 256 32 tokens 55.5 / 54.5, 100 66.9 / 65.8,
-// 256 92.2 / 95.9; K = 64 32 tokens 38.7 / 35.2, 256 41.2 / 40.1).
+// Whether the split kernel takes its smallest tile, 16 tokens by 16 outputs, whose sixteen wavefronts share K.
+static bool smallest_tile(long long M, int N, int cus) { return ((N + 15) / 16) * ((M + 31) / 32) < cus; }
+// Short rows are read so fast that the split kernel forms their statistics itself where it takes its smallest tile: a row to each of the
+// workgroup's wavefronts, which costs less than a launch for them.  With larger tiles a wavefront forms those of four or eight rows one after
+// the other, in every workgroup, which costs more.  The block with / without the launch, us a call, K = 256: 1024 outputs, 32 tokens 31.2 /
+// 29.6, 128 37.6 / 38.7; 2048 outputs, 16 tokens 35.9 / 34.5, 32 36.5 / 35.0, 33 37.1 / 38.3; 4096 outputs, 32 tokens 47.5 / 48.8; K = 64,
+// 4096 outputs, 150 tokens 51.6 / 56.3, 1024 outputs, 400 tokens 39.6 / 44.2.
 bool stats_inside(long long M, int N, int K, int cus, bool bf16) {
-  return K <= 512 && M * K <= 128 * 256 && split_is_faster(M, N, K, cus, bf16);
+  return K <= 512 && M * K <= 128 * 256 && smallest_tile(M, N, cus) && split_is_faster(M, N, K, cus, bf16);
 }
 template <typename TX, typename TW, typename TY>
 static hipError_t launch_split(const GemmLnSplitArgs& a, int cus, hipStream_t st) {
@@ -41,7 +45,7 @@ static hipError_t launch_split(const GemmLnSplitArgs& a, int cus, hipStream_t st
     hipLaunchKernelGGL((gemm_ln_split_kernel<TX, TW, TY, 4, 4, 8>), dim3((unsigned)(n64 * m64)), dim3(512), 0, st, a);
   else if (n64 * m32 >= cus)
     hipLaunchKernelGGL((gemm_ln_split_kernel<TX, TW, TY, 4, 2, 8>), dim3((unsigned)(n64 * m32)), dim3(512), 0, st, a);
-  else if (n16 * m32 >= cus)
+  else if (!smallest_tile(a.M, a.N, cus))
     hipLaunchKernelGGL((gemm_ln_split_kernel<TX, TW, TY, 1, 2, 8>), dim3((unsigned)(n16 * m32)), dim3(512), 0, st, a);
   else
     hipLaunchKernelGGL((gemm_ln_split_kernel<TX, TW, TY, 1, 1, 16>), dim3((unsigned)(n16 * m16)), dim3(1024), 0, st, a);

@@ -383,7 +383,8 @@ struct BlkFrag<unsigned short> {
 template <typename TX, typename TW, typename TY, int NT, int MT, int NWV>
 __global__ void __launch_bounds__(64 * NWV) gemm_ln_split_kernel(const GemmLnSplitArgs p) {
   __shared__ __attribute__((aligned(16))) blk_floatx4 red[NWV > 1 ? NWV * NT * MT * 64 : 1];
-  __shared__ float own[2 * 16 * MT];  // the rows' statistics, where they are formed here
+  constexpr bool INSIDE = 16 * MT == NWV;  // the tile whose rows' statistics may be formed here (stats_inside): a wavefront a row
+  __shared__ float own[INSIDE ? 2 * NWV : 1];
   const TX* const X = reinterpret_cast<const TX*>(p.X);
   const TW* const W = reinterpret_cast<const TW*>(p.W);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, i = lane & 15, g = lane >> 4;
@@ -400,27 +401,22 @@ __global__ void __launch_bounds__(64 * NWV) gemm_ln_split_kernel(const GemmLnSpl
     long long row = m0 + 16 * b + i;
     row = row < p.M ? row : p.M - 1;
     xrow[b] = X + row * p.K;
-    if (p.stats) {
+    if (!INSIDE || p.stats) {
       mean[b] = p.stats[2 * row];
       rstd[b] = p.stats[2 * row + 1];
     }
   }
-  if (!p.stats) {
-    for (int q = wave; q < 16 * MT; q += NWV) {
-      const long long row = m0 + q < p.M ? m0 + q : p.M - 1;
-      float m, s;
-      ln_row_stats<TX>(X + row * p.K, p.K, p.eps, lane, m, s);
-      if (lane == 0) {
-        own[2 * q] = m;
-        own[2 * q + 1] = s;
-      }
+  if (INSIDE && !p.stats) {
+    const long long row = m0 + wave < p.M ? m0 + wave : p.M - 1;
+    float m, s;
+    ln_row_stats<TX>(X + row * p.K, p.K, p.eps, lane, m, s);
+    if (lane == 0) {
+      own[2 * wave] = m;
+      own[2 * wave + 1] = s;
     }
     __syncthreads();
-#pragma unroll
-    for (int b = 0; b < MT; ++b) {
-      mean[b] = own[2 * (16 * b + i)];
-      rstd[b] = own[2 * (16 * b + i) + 1];
-    }
+    mean[0] = own[2 * i];
+    rstd[0] = own[2 * i + 1];
   }
 #pragma unroll
   for (int a = 0; a < NT; ++a) {
