@@ -701,15 +701,20 @@ static void fill_cxt_args(ttc::CxtArgs& a, const ttc_lqr_cxt_problem_t* q) {
 }
 
 static hipError_t run_cxt(const ttc::CxtArgs& a, bool bf16, hipStream_t st) {
-  // Two wavefronts a SIMD, or three.  A round of three takes 1.4 times as long as one of two (131072 problems, T = 8: 11 rounds of 53 us, 16
-  // of 38; 32768 problems: 3 and 4, 158 us and 148), and what leaves every gain in memory is faster with two (backward pass, 60000 problems,
-  // T = 12: 0.99 ms against 1.01), as are calls that want the matrices P_0 or K_0 (two / three, u_0 alone, 1048576 problems, T = 8 4.85 /
-  // 4.76 ms, 262144, T = 16 2.24 / 2.16; with both matrices 1048576 problems 4.90 / 5.03, 100000, T = 4 0.278 / 0.319).  Batches that two do not fill four problems at a time go one problem to a wavefront.
+  // Two wavefronts a SIMD, or three, by the rounds that each takes.  A round of three takes 1.4 times as long as one of two (131072 problems,
+  // T = 8: 11 rounds of 53 us, 16 of 38) where there are many; up to five of two the last one, which is seldom full, makes two the faster
+  // (two / three, us: 16725 problems (3 rounds, 2), T = 3 43.8 / 45.9, T = 8 90.8 / 90.2; 35760 (5, 3) T = 3 78.6 / 83.2, T = 8 165.7 / 168.8;
+  // 41000 (6, 4) T = 3 95.0 / 92.8, T = 8 201 / 194), as they are for horizons of one or two, which are mostly set-up (49000, T = 2 85.5 / 87.0,
+  // 73000 126.0 / 128.9).  What leaves every gain in memory is faster with two (backward pass, 60000 problems, T = 12: 0.99 ms against 1.01), as
+  // are calls that want the matrices P_0 or K_0 (u_0 alone, 1048576 problems, T = 8 4.85 / 4.76 ms, 262144, T = 16 2.24 / 2.16; with both matrices
+  // 1048576 problems 4.90 / 5.03, 100000, T = 4 0.278 / 0.319).  Batches that two do not fill four problems at a time go one problem
+  // to a wavefront.
   const long long two = ttc::grid_blocks(ttc::KIND_CXT, 16, bf16), three = ttc::grid_blocks(ttc::KIND_CXT_THREE, 16, bf16);
   const bool single = a.s.n <= two;
   const long long items = single ? a.s.n : (a.s.n + 3) / 4;
   const bool stores = a.roll_ws || a.s.P0 || a.s.K0;
-  const int waves = !single && !stores && 7 * ((items + three - 1) / three) < 5 * ((items + two - 1) / two) ? 3 : 2;
+  const long long rounds2 = (items + two - 1) / two, rounds3 = (items + three - 1) / three;
+  const int waves = !single && !stores && a.s.T >= 3 && rounds2 > 5 && 7 * rounds3 < 5 * rounds2 ? 3 : 2;
   const long long gb = waves == 3 ? three : two;
   const dim3 grid((unsigned)(items < gb ? items : gb));
   return ttc::launch_cxt(a, bf16, single ? 1 : 4, waves, grid, st);
