@@ -323,7 +323,7 @@ def bench_block(args):
         "roofline": {"bound": "mfma", "achieved": achieved, "peak": PEAK_FP32_MFMA_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / PEAK_FP32_MFMA_TFLOPS,
                      "traffic": measured_traffic("ttc_block_c4096%s_T%d" % ("_bf16" if bf16 else "", T), "block", n * H),   # the table's unit is the (token, head) problem
-                     "kernel": "ttc_block_forward (7 launches: ln_stats, gemm_ln, cxt_maps, qbasis, solve_cxt, ln_stats, gemm_ln)",
+                     "kernel": "ttc_block_forward (5 or 6 launches: ln_stats with the basis, gemm_ln, cxt_maps, solve_cxt, ln_stats unless gemm_ln forms the statistics, gemm_ln)",
                      "kernel_ms": kernel_s * 1e3, **spread(kernel_ms),
                      "alg_flops_per_token": flops_pt,
                      "alg_flops_split": {"projections": 4 * C * H * d, "maps": H * 2 * d * (5 * d + 3 * r),

@@ -18,7 +18,10 @@
  * composed by squaring (the algebra described at TTC_FLAG_DOUBLING; rebase_every must be 0): more accurate on
  * ordinary problems, and watched by a guard of its own on max |I + G_e H_e|.  What it cannot do is solved by a second launch
  * behind it: by the recursion as below, or (stage costs that are not semidefinite, breakdowns) by the product.
- * At d = 16 they are composed by squaring at every horizon, in a kernel that does by itself what squaring cannot do.
+ * At d = 16 they are composed by squaring at every horizon, in a kernel that does by itself what squaring cannot do.  There the
+ * last bits of a problem's results depend on the batch: up to a number of problems that the device decides (3071 on an MI355X) each has
+ * a wavefront, from there on four share one, whose inverses round differently and which leave squaring together if one of them
+ * has to.  All of these results are within the path's tolerance; equal calls give equal bits.
  * A growth guard watches max |Y1| inside every group (Y1 starts a group as the identity): a group that
  * is about to pass the limit is ended early, and a problem whose pair has passed it is solved instead
  * by the recursion of Prop. 3.1 in its printed form (one positive definite solve per step, as

@@ -25,7 +25,7 @@ namespace ttc {
 // PPW = problems per wavefront: 4 for batches that fill the chip; 1 for small batches, where a wavefront's
 // latency is what counts: the four rows of 16 lanes then all hold the same problem (they compute, and
 // write, the same values), and every per-problem loop below runs once instead of four times.
-// WAVES = wavefronts per SIMD the register allocation aims at: two, or three (46 registers spilled, next to none in a step) for large
+// WAVES = wavefronts per SIMD the register allocation aims at: two, or three (38 registers spilled, next to none in a step) for large
 // batches; the launch decides (run_cxt).
 template <typename TIn, int PPW, int WAVES>
 __global__ void __launch_bounds__(64, WAVES) solve_cxt_kernel(const CxtArgs ca) {

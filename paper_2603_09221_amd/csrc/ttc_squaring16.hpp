@@ -17,9 +17,10 @@
 namespace ttc {
 
 // The guard, on max |I + G_e H_e| and max |I + P G_e| over the wavefront's problems (ttc_squaring.hpp has what it rests on): what is large
-// in the first squaring is cheap control, which loses digits, and is left to the recursion, which at this size costs no more than the
-// sequential product (float32 from 8 on: ordinary problems stay below 7, T = 8 with R scaled by 0.1 7.6e-6 by squaring, 1.5e-6 by the
-// recursion); growth that comes later is that of an unstable open loop, and the power reached is then applied as often as needed
+// in the first squaring is cheap control, which loses digits, and is left to the recursion (float32 from 8 on: ordinary problems stay below 7,
+// T = 8 with R scaled by 0.1 7.6e-6 by squaring, 1.5e-6 by the recursion), which together with the attempt costs less than the sequential
+// product did, whose guard gives most of these up as well (product / this, us a call: R scaled by 0.1, 16384 problems T = 8 164 / 150, T = 33 526 /
+// 505, 2000 problems 47 / 33 and 143 / 100; by 0.01 the same, 2000 problems 37 / 33 and 107 / 100); growth that comes later is that of an unstable open loop, and the power reached is then applied as often as needed
 // instead of squared again.
 static constexpr float SQUARE16_FIRST_F32 = 8.f, SQUARE16_FIRST_BF16 = 24.f, SQUARE16_LATE = 256.f, SQUARE16_STOP = 16.f;
 // Where P starts from a terminal cost of its own, P G_e is a product of matrices that know nothing of each other, and elimination in order
